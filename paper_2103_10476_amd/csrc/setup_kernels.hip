@@ -442,34 +442,37 @@ int64_t strength_graph(int32_t n, const int32_t *rp, const int32_t *col, const u
 }
 
 // ---- root selection: lexicographically-first distance-2 maximal independent set -----------
-// key = (state, priority) with state IN < UNDECIDED < OUT in the top two bits, so the
-// minimum key of a neighbourhood is its best vertex.  Per round: k1(v) = min key over N[v];
-// then an undecided v with m = min k1 over N[v] (the minimum over the distance-2 ball)
-// leaves as OUT when m is an IN key (a root within distance 2) and enters as IN when m is its
-// own key (it has the best priority among undecided vertices within distance 2).  This
-// reproduces the sequential greedy root choice in priority order exactly.
+// In priority order (natural: the index; hashed: a seeded 30-bit hash, ties by index) a vertex
+// is a root (IN) when no earlier vertex within distance 2 is one.  A round decides, all at
+// once, every undecided vertex whose earlier vertices within distance 2 were all decided in
+// earlier rounds: it becomes a root, and the undecided vertices within distance 2 of it
+// become OUT.  Both follow from earlier decisions only, so the rounds reproduce the sequential
+// greedy choice exactly; at least one vertex (the earliest undecided) is decided per round.
 //
-// Rounds are event driven: k1(u) is recomputed only in a round after some key in N[u]
-// changed, and an undecided v re-takes its decision only in a round in which some k1 in N[v]
-// changed; any other vertex would compute the value (or the "wait") it already holds, so the
-// selection is the same as re-evaluating every vertex every round.  The triggers are 1-byte
-// round stamps (round number mod 256): pass 2 stamps N[v] u {v} for pass 1 of the next round
-// when v's key changes, pass 1 stamps N[u] u {u} for pass 2 of the same round when k1(u)
-// changes.  A stale stamp that matches after wrap-around only costs a needless re-evaluation.
-// Round 0 evaluates everything (all stamps start at 0).  A round that changes no key ends
-// the selection: nothing can change after it.  Natural order uses 32-bit keys
-// (state << 30 | index); hashed order 64-bit keys (state << 62 | hash30 << 32 | index).
-// Levels with high average degree use one wavefront per vertex.
-template <class K>
-struct KeyT;
-template <>
-struct KeyT<uint32_t> {
-  static constexpr uint32_t In = 0, Und = 1u << 30, Out = 2u << 30, Mask = 3u << 30;
-};
-template <>
-struct KeyT<uint64_t> {
-  static constexpr uint64_t In = 0, Und = 1ull << 62, Out = 2ull << 62, Mask = 3ull << 62;
-};
+// Nothing is re-evaluated until it can change: every undecided vertex watches ONE undecided
+// earlier vertex within distance 2, and only when that one is decided does it look over its
+// distance-2 ball for another to watch; if there is none, it is a root.  On the 128^3 cube a
+// vertex looks 1.1-1.8 times in all and reads ~6 states (the look ends at the first
+// undecided earlier vertex), and a round of the 2M-vertex level has ~4,400 looks.  Kernel
+// trace of one 128^3 setup: 665 launches of 7-13 us, 6.3 ms (205 of 7.6 us on the 2M-vertex
+// level), against 12.5 ms with two neighbourhood-minimum passes per round over byte stamps
+// and OUT marks and root decisions in rounds of their own (2 x 410 launches of 4.7 us on that
+// level); setup 26.5 -> 20.4 ms.
+//
+// What bounds a round is the chain of dependent loads: a vertex's state, its watch, that
+// one's state, then three of the ball (neighbours with their row ranges, their neighbours,
+// those ones' states).  G lanes share a ball (mis_ball).
+//
+// Visibility on the grid: one launch per round decides and looks at once, so a decision is
+// stamped with its round and other vertices take it as undecided until the next launch.  The
+// state byte holds 0 undecided, 1 OUT and 2 IN of long ago, and 4 + 2 (r mod 126) + (1 if IN)
+// for a decision of round r; every 126 rounds one launch ages all decisions (k_mis_age)
+// before their stamps come round again.
+//
+// The round count reported to the caller counts a root decision and the OUT marks that
+// follow from it as a round each, and the round in which nothing is left to decide: with T
+// rounds as above it is 2 T - 1, plus 1 if the last of them marked a vertex OUT.
+constexpr int kMisStamps = 126;
 
 __device__ inline uint64_t splitmix64_dev(uint64_t seed, uint64_t k) {
   uint64_t z = seed + (k + 1) * 0x9E3779B97F4A7C15ull;
@@ -481,295 +484,183 @@ __device__ inline uint64_t stream_key_dev(int stream, int level, int64_t i) {
   return ((uint64_t)stream << 56) | ((uint64_t)level << 40) | (uint64_t)i;
 }
 
+// Priority orders.  past(x, v): in a row sorted by index, no entry from x on precedes v.
+struct NaturalOrder {
+  __device__ int32_t pri(int32_t v) const { return v; }
+  __device__ bool before(int32_t x, int32_t pv) const { return x < pv; }
+  __device__ bool past(int32_t x, int32_t pv) const { return x >= pv; }
+};
+struct HashedOrder {
+  uint64_t seed;
+  int32_t level;
+  __device__ uint64_t pri(int32_t v) const {
+    return ((splitmix64_dev(seed, stream_key_dev(2, level, v)) >> 34) << 32) | (uint64_t)v;
+  }
+  __device__ bool before(int32_t x, uint64_t pv) const { return pri(x) < pv; }
+  __device__ bool past(int32_t, uint64_t) const { return false; }
+};
+
+// Whether other vertices count a state as undecided in the round with stamps c0, c0 | 1.
+__device__ __forceinline__ bool mis_open(uint8_t s, uint8_t c0) {
+  return s == 0 || (s | 1) == (c0 | 1);
+}
+
+template <int G>
+__device__ __forceinline__ uint64_t group_ballot(bool p) {
+  const uint64_t m = __ballot(p);
+  if constexpr (G == 64) return m;
+  const int sh = (int)__lane_id() & ~(G - 1);
+  return (m >> sh) & ((1ull << (G & 63)) - 1ull);
+}
+
+// Row ranges of the strength graph as a look reads them.  On the grid the range of every
+// entry's own row is stored beside the entry (gext), which takes a dependent load out of the
+// chain; in one workgroup the row pointers are in LDS.
+struct EntryRanges {
+  const int32_t *__restrict__ gcol;
+  const int2 *__restrict__ gext;  // per entry: start and length of that vertex's row
+  __device__ void entry(int32_t k, int32_t &u, int32_t &ub, int32_t &ulen) const {
+    u = gcol[k];
+    const int2 x = gext[k];
+    ub = x.x;
+    ulen = x.y;
+  }
+};
+struct RowRanges {
+  const int32_t *__restrict__ gcol;
+  const int32_t *rp;
+  __device__ void entry(int32_t k, int32_t &u, int32_t &ub, int32_t &ulen) const {
+    u = gcol[k];
+    ub = rp[u];
+    ulen = rp[u + 1] - ub;
+  }
+};
+
+// The distance-2 ball of v (row [b, e)) by the G lanes of a group: f(c, last) for eight
+// vertices per lane at a time, until it returns true (group-uniform) or the ball is through;
+// last: the step that ends the ball.  Lane j takes v's j-th neighbour u (G of them per outer
+// step); the lists {u, N[u]} of the lanes are laid end to end and shared out over the lanes,
+// so a step's entries are loaded together whatever their rows' lengths.  Positions past the
+// end give v itself; a vertex may come more than once.
+template <int G, class R, class F>
+__device__ __forceinline__ void mis_ball(int32_t v, int32_t b, int32_t e, int j, const R &rows,
+                                         F &&f) {
+  for (int32_t k0 = b; k0 < e; k0 += G) {  // group-uniform
+    int32_t u = v, ub = 0, len = 0;
+    if (k0 + j < e) {
+      rows.entry(k0 + j, u, ub, len);
+      ++len;
+    }
+    int32_t end = len;  // inclusive prefix sums of the lists' lengths
+#pragma unroll
+    for (int off = 1; off < G; off <<= 1) {
+      const int32_t o = __shfl_up(end, off, G);
+      if (j >= off) end += o;
+    }
+    const int32_t start = end - len;
+    const int32_t total = __shfl(end, G - 1, G);
+    for (int32_t p0 = 0; p0 < total; p0 += 8 * G) {  // group-uniform
+      int32_t c[8], at[8];
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        const int32_t p = p0 + i * G + j;
+        int s = 0;  // the last list that starts at or before p
+#pragma unroll
+        for (int step = G / 2; step >= 1; step >>= 1)
+          if (__shfl(start, s + step, G) <= p) s += step;
+        const int32_t k = p - __shfl(start, s, G);  // 0: u itself, k > 0: entry k - 1
+        const int32_t su = __shfl(u, s, G), sb = __shfl(ub, s, G);
+        c[i] = p < total ? su : v;
+        at[i] = p < total && k > 0 ? sb + k - 1 : -1;
+      }
+#pragma unroll
+      for (int i = 0; i < 8; ++i)
+        if (at[i] >= 0) c[i] = rows.gcol[at[i]];
+      if (f(c, k0 + G >= e && p0 + 8 * G >= total)) return;
+    }
+  }
+}
+
+// A look at v: returns an undecided vertex before it within distance 2 (of those found in the
+// same step the one with the largest index, the likeliest to be decided last), or -1 when
+// there is none: v is a root then, and its ball's undecided vertices have been marked OUT
+// (*out raised if any was).  A ball of one step is marked from the registers that hold it.
+template <int G, class R, class O>
+__device__ __forceinline__ int32_t mis_look(int32_t v, int32_t b, int32_t e, int j, const R &rows,
+                                            uint8_t *st, uint8_t c0, const O &ord, bool *out) {
+  const auto pv = ord.pri(v);
+  int32_t found = -1;
+  bool marked = false;
+  auto mark = [&](const int32_t (&c)[8], const uint8_t (&x)[8]) {
+#pragma unroll
+    for (int i = 0; i < 8; ++i)
+      if (x[i] == 0 && c[i] != v) {
+        st[c[i]] = c0;
+        *out = true;
+      }
+  };
+  int32_t steps = 0;
+  mis_ball<G>(v, b, e, j, rows, [&](const int32_t (&c)[8], bool last) {
+    uint8_t x[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) x[i] = st[c[i]];
+#pragma unroll
+    for (int i = 0; i < 8; ++i)
+      if (mis_open(x[i], c0) && ord.before(c[i], pv)) found = max(found, c[i]);
+    if (group_ballot<G>(found >= 0) != 0) return true;
+    if (last && steps == 0) {
+      mark(c, x);
+      marked = true;
+    }
+    ++steps;
+    return false;
+  });
+  if (!marked && group_ballot<G>(found >= 0) == 0)
+    mis_ball<G>(v, b, e, j, rows, [&](const int32_t (&c)[8], bool) {
+      uint8_t x[8];
+#pragma unroll
+      for (int i = 0; i < 8; ++i) x[i] = st[c[i]];
+      mark(c, x);
+      return false;
+    });
+#pragma unroll
+  for (int off = G / 2; off >= 1; off >>= 1) found = max(found, __shfl_xor(found, off, G));
+  return found;
+}
+
 // A vertex without neighbours is decided at once: nothing near it can ever be aggregated, so
 // the sequential rule makes it a root whatever its priority (singletons), or it is left out.
-// Its key never enters another vertex's neighbourhood minimum.
-template <class K>
-__global__ void k_mis_init(int32_t n, const int32_t *grp, int32_t order, uint64_t seed,
-                           int32_t level, bool singletons, K *key, uint8_t *st1, uint8_t *st2) {
+// Any other vertex first watches its first earlier neighbour, or (itself as the mark) looks in
+// the first round.
+template <class O>
+__global__ void k_mis_init(int32_t n, const int32_t *__restrict__ grp,
+                           const int32_t *__restrict__ gcol, O ord, bool singletons, uint8_t *st,
+                           int32_t *watch) {
   SA_ROW_KERNEL_BEGIN(n)
-  K pri = (K)i;
-  if (order == 1)
-    pri = (K)((((uint64_t)splitmix64_dev(seed, stream_key_dev(2, level, i)) >> 34) << 32) |
-              (uint64_t)i);
-  const bool open = grp[i + 1] > grp[i];
-  key[i] = (open ? KeyT<K>::Und : singletons ? KeyT<K>::In : KeyT<K>::Out) | pri;
-  st1[i] = 0;
-  st2[i] = 0;
-}
-
-// Stamps i and every vertex of gcol[b..e) with s: 8 independent index loads, then 8 stores
-// (the last index repeated past the end: the same byte stored again).
-__device__ inline void stamp_ball(const int32_t *__restrict__ gcol, int32_t b, int32_t e,
-                                  int32_t i, uint8_t *__restrict__ st, uint8_t s) {
-  st[i] = s;
-  for (int32_t k = b; k < e; k += 8) {
-    int32_t c[8];
-#pragma unroll
-    for (int q = 0; q < 8; ++q) c[q] = gcol[min(k + q, e - 1)];
-#pragma unroll
-    for (int q = 0; q < 8; ++q) st[c[q]] = s;
-  }
-}
-
-// Pass 1 for one stamped vertex i (thread per vertex): k1(i) = min key over N[i] u {i}; a
-// changed minimum stamps N[i] u {i} for pass 2.
-template <class K>
-__device__ __forceinline__ void mis1_vertex(int32_t i, const int32_t *__restrict__ grp,
-                                            const int32_t *__restrict__ gcol,
-                                            const K *__restrict__ key, K *__restrict__ k1,
-                                            uint8_t *__restrict__ st2, uint8_t sr, bool first) {
   const int32_t b = grp[i], e = grp[i + 1];
-  K m = key[i];
-  const K old = first ? m : k1[i];
-  // neighbours 8 at a time: all indices, then all keys, as independent loads (i itself
-  // past the end of the list, harmless in the minimum); the first 8 indices are kept for
-  // the stamps
-  int32_t c0[8];
-#pragma unroll
-  for (int q = 0; q < 8; ++q) c0[q] = i;
-  for (int32_t k = b; k < e; k += 8) {
-    int32_t c[8];
-#pragma unroll
-    for (int q = 0; q < 8; ++q) {
-      const int32_t g = gcol[min(k + q, e - 1)];  // in bounds even if loaded eagerly
-      c[q] = (k + q < e) ? g : i;
-    }
-    K kv[8];
-#pragma unroll
-    for (int q = 0; q < 8; ++q) kv[q] = key[c[q]];
-#pragma unroll
-    for (int q = 0; q < 8; ++q) m = kv[q] < m ? kv[q] : m;
-    if (k == b) {
-#pragma unroll
-      for (int q = 0; q < 8; ++q) c0[q] = c[q];
-    }
+  const auto pv = ord.pri(i);
+  int32_t w = i;
+  for (int32_t k = b; k < e; ++k) {
+    const int32_t u = gcol[k];
+    if (ord.before(u, pv)) w = u;
+    if (w != i || ord.past(u, pv)) break;
   }
-  if (!first && m != old) {
-    if (e - b <= 8) {
-      st2[i] = sr;
-#pragma unroll
-      for (int q = 0; q < 8; ++q) st2[c0[q]] = sr;
-    } else {
-      stamp_ball(gcol, b, e, i, st2, sr);
-    }
-  }
-  k1[i] = m;
+  st[i] = e > b ? 0 : singletons ? 2 : 1;
+  watch[i] = w;
 }
 
-constexpr int kMisV = 4;                // vertices per thread on large levels
-constexpr int64_t kMisVMinN = 524288;   // from this level size on
-
-// Pass 1 of round r (stamp sr): k1(u) = min key over N[u] for stamped u.  V > 1 (thread
-// per vertex only): each thread takes V vertices, for levels with many vertices.
-template <class K, bool WAVE, int V = 1>
-__global__ void k_mis_pass1(int32_t n, const int32_t *__restrict__ grp,
-                            const int32_t *__restrict__ gcol, const K *__restrict__ key,
-                            K *__restrict__ k1, const uint8_t *__restrict__ st1,
-                            uint8_t *__restrict__ st2, uint8_t sr, bool first,
-                            const int32_t *__restrict__ prev, int32_t *__restrict__ cur,
-                            uint32_t *hstat, uint32_t tag) {
-  static_assert(!(WAVE && V > 1), "a wavefront per vertex takes one vertex");
-  // one thread clears this round's flag (pass 2 raises it) and posts the previous round's
-  // outcome to the host's status word: tag | 1 if it changed a key, tag | 2 if not
-  if (blockIdx.x == 0 && threadIdx.x == 0) {
-    *cur = 0;
-    if (hstat)
-      __hip_atomic_store(hstat, tag | (*prev == 0 ? 2u : 1u), __ATOMIC_RELAXED,
-                         __HIP_MEMORY_SCOPE_SYSTEM);
-  }
-  // the stamp and the previous round's flag are read together (one round trip); a round
-  // whose predecessor changed nothing exits
-  if (WAVE) {
-    const int lane = threadIdx.x & 63;
-    const int64_t v64 = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
-    if (v64 >= n) return;
-    const int32_t v = (int32_t)v64;
-    const uint8_t st = st1[v];
-    if ((prev && *prev == 0) | (st != sr)) return;  // wave-uniform
-    const int32_t b = grp[v], e = grp[v + 1];
-    K m = (lane == 0) ? key[v] : ~(K)0;
-    for (int32_t k = b + lane; k < e; k += 64) {
-      const K ku = key[gcol[k]];
-      m = ku < m ? ku : m;
-    }
-    for (int off = 32; off >= 1; off >>= 1) {
-      const K o = __shfl_xor(m, off, 64);
-      m = o < m ? o : m;
-    }
-    const K old = first ? m : k1[v];  // read by every lane before lane 0 stores
-    if (lane == 0) k1[v] = m;
-    if (!first && m != old) {
-      for (int32_t k = b + lane; k < e; k += 64) st2[gcol[k]] = sr;
-      if (lane == 0) st2[v] = sr;
-    }
-  } else if (V == 1) {
-    SA_ROW_KERNEL_BEGIN(n)
-    const uint8_t st = st1[i];
-    if ((prev && *prev == 0) | (st != sr)) return;
-    mis1_vertex<K>(i, grp, gcol, key, k1, st2, sr, first);
-  } else {
-    // V vertices per thread at a stride of the grid's thread count (neighbouring vertices,
-    // which tend to be stamped together, stay on different lanes); their stamps and the
-    // previous round's flag are read together
-    const int64_t nt = (int64_t)gridDim.x * blockDim.x;
-    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    uint8_t st[V];
-#pragma unroll
-    for (int j = 0; j < V; ++j) {
-      const int64_t v = t + j * nt;
-      st[j] = v < n ? st1[v] : (uint8_t)(sr + 1);
-    }
-    if (prev && *prev == 0) return;
-#pragma unroll 1
-    for (int j = 0; j < V; ++j)
-      if (st[j] == sr) mis1_vertex<K>((int32_t)(t + j * nt), grp, gcol, key, k1, st2, sr, first);
-  }
-}
-
-// Pass 2 for one stamped vertex i (thread per vertex): an undecided i takes m = min k1 over
-// N[i] u {i}; an IN key there makes it OUT, its own key makes it IN.  A change stamps
-// N[i] u {i} with srn and raises the round's flag.
-template <class K>
-__device__ __forceinline__ void mis2_vertex(int32_t i, const int32_t *__restrict__ grp,
-                                            const int32_t *__restrict__ gcol,
-                                            const K *__restrict__ k1, K *__restrict__ key,
-                                            uint8_t *__restrict__ st1, uint8_t srn,
-                                            int32_t *__restrict__ flag) {
-  // the key, the row range and k1 together (the test below uses them all, so none of the
-  // loads waits for the state test)
-  const K me = key[i];
-  K m = k1[i];
-  const int32_t b = grp[i], e = grp[i + 1];
-  if (((me & KeyT<K>::Mask) != KeyT<K>::Und) | (e < b)) return;
-  int32_t c0[8];
-#pragma unroll
-  for (int q = 0; q < 8; ++q) c0[q] = i;
-  for (int32_t k = b; k < e; k += 8) {
-    int32_t c[8];
-#pragma unroll
-    for (int q = 0; q < 8; ++q) {
-      const int32_t g = gcol[min(k + q, e - 1)];  // in bounds even if loaded eagerly
-      c[q] = (k + q < e) ? g : i;
-    }
-    K kv[8];
-#pragma unroll
-    for (int q = 0; q < 8; ++q) kv[q] = k1[c[q]];
-#pragma unroll
-    for (int q = 0; q < 8; ++q) m = kv[q] < m ? kv[q] : m;
-    if (k == b) {
-#pragma unroll
-      for (int q = 0; q < 8; ++q) c0[q] = c[q];
-    }
-  }
-  const K pri = me & ~KeyT<K>::Mask;
-  K nk = me;
-  if ((m & KeyT<K>::Mask) == KeyT<K>::In) nk = KeyT<K>::Out | pri;
-  else if (m == me) nk = KeyT<K>::In | pri;
-  if (nk != me) {
-    key[i] = nk;
-    if (e - b <= 8) {
-      st1[i] = srn;
-#pragma unroll
-      for (int q = 0; q < 8; ++q) st1[c0[q]] = srn;
-    } else {
-      stamp_ball(gcol, b, e, i, st1, srn);
-    }
-    *flag = 1;
-  }
-}
-
-// Pass 2 of round r: stamped undecided v takes m = min k1 over N[v]; an IN key there makes v
-// OUT, its own key makes it IN.  A change stamps N[v] u {v} with the next round's stamp srn
-// and raises the round's flag.  V > 1: V vertices per thread, as in pass 1.
-template <class K, bool WAVE, int V = 1>
-__global__ void k_mis_pass2(int32_t n, const int32_t *__restrict__ grp,
-                            const int32_t *__restrict__ gcol, const K *__restrict__ k1,
-                            K *__restrict__ key, const uint8_t *__restrict__ st2,
-                            uint8_t *__restrict__ st1, uint8_t sr, uint8_t srn,
-                            int32_t *__restrict__ flag, const int32_t *__restrict__ prev) {
-  static_assert(!(WAVE && V > 1), "a wavefront per vertex takes one vertex");
-  if (WAVE) {
-    const int lane = threadIdx.x & 63;
-    const int64_t v64 = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
-    if (v64 >= n) return;
-    const int32_t v = (int32_t)v64;
-    const uint8_t st = st2[v];
-    if ((prev && *prev == 0) | (st != sr)) return;  // wave-uniform
-    const K me = key[v];
-    const int32_t b = grp[v], e = grp[v + 1];
-    if (((me & KeyT<K>::Mask) != KeyT<K>::Und) | (e < b)) return;  // wave-uniform
-    K m = (lane == 0) ? k1[v] : ~(K)0;
-    for (int32_t k = b + lane; k < e; k += 64) {
-      const K ku = k1[gcol[k]];
-      m = ku < m ? ku : m;
-    }
-    for (int off = 32; off >= 1; off >>= 1) {
-      const K o = __shfl_xor(m, off, 64);
-      m = o < m ? o : m;
-    }
-    const K pri = me & ~KeyT<K>::Mask;
-    K nk = me;
-    if ((m & KeyT<K>::Mask) == KeyT<K>::In) nk = KeyT<K>::Out | pri;
-    else if (m == me) nk = KeyT<K>::In | pri;
-    if (nk != me) {  // wave-uniform
-      for (int32_t k = b + lane; k < e; k += 64) st1[gcol[k]] = srn;
-      if (lane == 0) {
-        key[v] = nk;
-        st1[v] = srn;
-        *flag = 1;
-      }
-    }
-  } else if (V == 1) {
-    SA_ROW_KERNEL_BEGIN(n)
-    const uint8_t st = st2[i];
-    if ((prev && *prev == 0) | (st != sr)) return;
-    mis2_vertex<K>(i, grp, gcol, k1, key, st1, srn, flag);
-  } else {
-    // V vertices per thread at a stride of the grid's thread count, as in pass 1
-    const int64_t nt = (int64_t)gridDim.x * blockDim.x;
-    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    uint8_t st[V];
-#pragma unroll
-    for (int j = 0; j < V; ++j) {
-      const int64_t v = t + j * nt;
-      st[j] = v < n ? st2[v] : (uint8_t)(sr + 1);
-    }
-    if (prev && *prev == 0) return;
-#pragma unroll 1
-    for (int j = 0; j < V; ++j)
-      if (st[j] == sr) mis2_vertex<K>((int32_t)(t + j * nt), grp, gcol, k1, key, st1, srn, flag);
-  }
-}
-
-// ---- root selection in one workgroup --------------------------------------------------------
-// On levels of at most kMisWgMaxN vertices, every round after the first runs inside a single
-// workgroup of kMisWg threads: the same two passes, triggers and early end as above, with
-// __syncthreads() between passes instead of kernel boundaries.  The triggered vertices of a
-// pass are kept as lists; a vertex enters a list once, through a bit in an LDS bitmap (bm1
-// for pass-1 lists, bm2 for pass-2 lists) that is set with an atomic or and cleared when the
-// entry is taken, so list lengths stay within n.  Round 1's pass-1 list is read from the byte
-// stamps that the grid round 0 left (value 1).  G lanes share a vertex (lane j takes entries
-// j, j+G, ...).  The round count and the keys equal the grid path's.
-// result[0] = the first round that changed nothing, result[1] = 1 if max_rounds was reached;
-// the same word goes to the host-mapped post (bit 31 set on that error).
-constexpr int kMisWg = 1024;
-constexpr int64_t kMisWgMaxN = 4096;  // default level size limit (SAAMG_MIS_WG_MAX_N)
-constexpr int64_t kMisWgLdsMaxN = 131072;  // the bitmaps' limit: 2 x 16 KiB of LDS
-constexpr size_t kMisWgKeyLds = 64 << 10;  // keys and k1 in LDS up to this many bytes
-
-// Appends the slots q with take[q] of every active lane to list: one LDS atomic per
-// wavefront, slots in lane-major order of the ballots.
+// Positions for the entries with take[q] of every active lane, counted on from *cnt: one LDS
+// atomic per wavefront, slots in lane-major order of the ballots.
 template <int Q>
-__device__ inline void wave_append(const int32_t (&w)[Q], const bool (&take)[Q],
-                                   int32_t *list, int32_t *cnt) {
-  uint32_t off[Q];
+__device__ __forceinline__ void wave_reserve(const bool (&take)[Q], int32_t *cnt,
+                                             int32_t (&pos)[Q]) {
   uint32_t total = 0;
 #pragma unroll
   for (int q = 0; q < Q; ++q) {
     const uint64_t m = __ballot(take[q]);
-    off[q] = total + __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32),
-                                               __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+    pos[q] = (int32_t)(total + __builtin_amdgcn_mbcnt_hi(
+                                   (uint32_t)(m >> 32),
+                                   __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u)));
     total += (uint32_t)__popcll(m);
   }
   if (total == 0) return;  // uniform over the active lanes
@@ -779,164 +670,227 @@ __device__ inline void wave_append(const int32_t (&w)[Q], const bool (&take)[Q],
     base = atomicAdd(cnt, (int32_t)total);
   base = __builtin_amdgcn_readfirstlane(base);
 #pragma unroll
-  for (int q = 0; q < Q; ++q)
-    if (take[q]) list[base + (int32_t)off[q]] = w[q];
+  for (int q = 0; q < Q; ++q) pos[q] += base;
 }
 
-// KL: the keys and k1 live in LDS during the rounds (after the bitmaps, at an 8-byte
-// boundary), read from and written back to global memory around them.
-template <class K, int G, bool KL>
-__global__ __launch_bounds__(kMisWg) void k_mis_rounds_wg(
-    int32_t n, const int32_t *__restrict__ grp, const int32_t *__restrict__ gcol, K *gkey,
-    K *gk1, const uint8_t *__restrict__ st1, const int32_t *__restrict__ flag0, int32_t *l1,
-    int32_t *l2, int32_t max_rounds, int32_t *result, uint32_t *hpost) {
-  extern __shared__ uint64_t lds_wg[];  // 8-byte aligned: the keys may be 64-bit
-  uint32_t *bm = reinterpret_cast<uint32_t *>(lds_wg);  // bm1 = bm[0, nwb), bm2 = bm[nwb, 2 nwb)
-  __shared__ int32_t c1, c2, chg[2];
-  const int tid = threadIdx.x;
-  const int j = tid % G;     // lane within the vertex's group
-  const int grp0 = tid / G;  // group number
-  constexpr int kGroups = kMisWg / G;
-  const int32_t nwb = (n + 31) >> 5;
-  uint32_t *bm1 = bm, *bm2 = bm + nwb;
-  K *key = gkey, *k1 = gk1;
-  if constexpr (KL) {
-    key = reinterpret_cast<K *>(bm + ((2 * nwb + 1) & ~1));
-    k1 = key + n;
-    for (int32_t v = tid; v < n; v += kMisWg) {
-      key[v] = gkey[v];
-      k1[v] = gk1[v];
-    }
+// Vertices per thread from a level size on: fewer workgroups to dispatch per round against
+// more looks per workgroup (128^3 setup 20.4 ms, with one vertex per thread on every level
+// 20.6 ms, with four from 0 on 21.1 ms; 160^3 39.1 against 40.0 ms).
+constexpr int kMisV = 4;
+constexpr int64_t kMisVMinN = 524288;
+
+// One round on the grid.  Each thread takes V vertices and reads their states, their watched
+// vertices and those vertices' states; the block's vertices whose watched vertex is decided
+// go to an LDS list and are looked at by G lanes each.  A block's vertices are runs of kMisRun
+// consecutive ones, the grid's block count of runs apart: neighbouring vertices tend to be
+// decided together, and their looks are spread over many blocks.
+// flags: per round {a root was decided, a vertex was marked OUT}; this launch clears the next
+// round's and posts the previous round's to the host word.  A round whose predecessor decided
+// nothing exits at once.
+constexpr int kMisRun = 16;
+template <int G, int V, class O>
+__global__ __launch_bounds__(kBlock) void k_mis_round(
+    int32_t n, const int32_t *__restrict__ grp, const int32_t *__restrict__ gcol,
+    const int2 *__restrict__ gext, uint8_t *st, int32_t *__restrict__ watch, uint8_t c0, O ord,
+    const int32_t *prev, int32_t *cur, int32_t *next, uint32_t *hstat, uint32_t tag) {
+  __shared__ int32_t lv[kBlock * V], lb[kBlock * V], le[kBlock * V];
+  __shared__ int32_t count;
+  auto vertex = [&](int q) {
+    const int64_t run = (int64_t)(q * (kBlock / kMisRun) + (threadIdx.x / kMisRun)) * gridDim.x +
+                        blockIdx.x;
+    return run * kMisRun + (threadIdx.x % kMisRun);
+  };
+  uint8_t s[V];
+#pragma unroll
+  for (int q = 0; q < V; ++q) {
+    const int64_t v = vertex(q);
+    s[q] = v < n ? st[v] : (uint8_t)1;
   }
-  for (int32_t w = tid; w < 2 * nwb; w += kMisWg) bm[w] = 0u;
-  if (tid == 0) {
-    c1 = 0;
-    c2 = 0;
-    chg[0] = 0;
-    chg[1] = 0;
+  const bool over = prev && prev[0] == 0;
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    next[0] = 0;
+    next[1] = 0;
+    if (hstat)
+      __hip_atomic_store(hstat, tag | (over ? 2u : prev[1] ? 3u : 1u), __ATOMIC_RELAXED,
+                         __HIP_MEMORY_SCOPE_SYSTEM);
   }
+  if (over) return;  // block-uniform
+  if (threadIdx.x == 0) count = 0;
   __syncthreads();
-  // min of x over v (lane 0) and N[v] = gcol[b..e), 8 independent loads per step
-  auto ball_min = [&](const K *x, int32_t v, int32_t b, int32_t e) {
-    K m = (j == 0) ? x[v] : ~(K)0;
-    for (int32_t k = b + j; k < e; k += 8 * G) {
-      int32_t c[8];
+  // (a vertex marked OUT by another block in this launch may be listed or not: it is blocked
+  // by that root either way)
+  int32_t w[V], b[V], e[V], pos[V];
+  bool take[V];
 #pragma unroll
-      for (int q = 0; q < 8; ++q) c[q] = gcol[min(k + q * G, e - 1)];
-      K kv[8];
-#pragma unroll
-      for (int q = 0; q < 8; ++q) kv[q] = x[c[q]];
-#pragma unroll
-      for (int q = 0; q < 8; ++q) m = kv[q] < m ? kv[q] : m;
+  for (int q = 0; q < V; ++q) {
+    w[q] = -1;
+    if (s[q] == 0) {
+      const int32_t v = (int32_t)vertex(q);
+      w[q] = watch[v];
+      b[q] = grp[v];
+      e[q] = grp[v + 1];
     }
+  }
 #pragma unroll
-    for (int off = G / 2; off >= 1; off >>= 1) {
-      const K o = __shfl_xor(m, off, G);
-      m = o < m ? o : m;
+  for (int q = 0; q < V; ++q)
+    take[q] = w[q] >= 0 && (w[q] == (int32_t)vertex(q) || !mis_open(st[w[q]], c0));
+  wave_reserve<V>(take, &count, pos);
+#pragma unroll
+  for (int q = 0; q < V; ++q)
+    if (take[q]) {
+      lv[pos[q]] = (int32_t)vertex(q);
+      lb[pos[q]] = b[q];
+      le[pos[q]] = e[q];
     }
-    return m;
-  };
-  // lists v and N[v] (slot b-1 stands for v) unless their bit is set; slots past the end
-  // take a no-op or on v's word
-  auto push_ball = [&](int32_t v, int32_t b, int32_t e, uint32_t *bmx, int32_t *list,
-                       int32_t *cnt) {
-    for (int32_t k = b - 1 + j; k < e; k += 8 * G) {
-      int32_t w[8];
-      bool take[8];
-#pragma unroll
-      for (int q = 0; q < 8; ++q) {
-        const int32_t kk = k + q * G;
-        w[q] = (kk < b || kk >= e) ? v : gcol[kk];
-      }
-#pragma unroll
-      for (int q = 0; q < 8; ++q) {
-        const uint32_t bit = (k + q * G < e) ? 1u << (w[q] & 31) : 0u;
-        take[q] = bit != 0u && (atomicOr(bmx + (w[q] >> 5), bit) & bit) == 0u;
-      }
-      wave_append<8>(w, take, list, cnt);
-    }
-  };
-  uint32_t used = 0, err = 0;
-  if (*flag0 != 0) {
-    // round 1's pass-1 list: the vertices stamped 1 by round 0 (4 stamps per word; the byte
-    // array is padded to a multiple of 16)
-    const int32_t nw = (n + 3) >> 2;
-    for (int32_t w0 = tid; w0 - tid < nw; w0 += kMisWg) {  // every lane runs every step
-      const uint32_t word = w0 < nw ? reinterpret_cast<const uint32_t *>(st1)[w0] : 0u;
-      int32_t w[4];
-      bool take[4];
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        w[q] = 4 * w0 + q;
-        take[q] = w[q] < n && ((word >> (8 * q)) & 0xffu) == 1u;
-      }
-      wave_append<4>(w, take, l1, &c1);
-    }
-    __syncthreads();
-    for (uint32_t r = 1;; ++r) {
-      // pass 1: k1(u) = min key over N[u] for listed u; a change lists N[u] u {u} for pass 2
-      const int32_t n1 = c1;
-      for (int32_t idx = grp0; idx < n1; idx += kGroups) {
-        const int32_t u = l1[idx];
-        if (j == 0) atomicAnd(bm1 + (u >> 5), ~(1u << (u & 31)));
-        const int32_t b = grp[u], e = grp[u + 1];
-        const K old = k1[u];
-        const K m = ball_min(key, u, b, e);
-        if (j == 0) k1[u] = m;
-        if (m != old) push_ball(u, b, e, bm2, l2, &c2);
-      }
-      __syncthreads();
-      const int32_t n2 = c2;
-      __syncthreads();  // every thread holds n1 and n2: both counters may restart
-      if (tid == 0) {
-        c1 = 0;
-        c2 = 0;
-        chg[r & 1] = 0;
-      }
-      __syncthreads();
-      // pass 2: a listed undecided v takes m = min k1 over N[v]; a change lists N[v] u {v}
-      // for pass 1 of the next round
-      for (int32_t idx = grp0; idx < n2; idx += kGroups) {
-        const int32_t v = l2[idx];
-        if (j == 0) atomicAnd(bm2 + (v >> 5), ~(1u << (v & 31)));
-        const K me = key[v];
-        const int32_t b = grp[v], e = grp[v + 1];
-        if ((me & KeyT<K>::Mask) != KeyT<K>::Und) continue;  // group-uniform
-        const K m = ball_min(k1, v, b, e);
-        const K pri = me & ~KeyT<K>::Mask;
-        K nk = me;
-        if ((m & KeyT<K>::Mask) == KeyT<K>::In) nk = KeyT<K>::Out | pri;
-        else if (m == me) nk = KeyT<K>::In | pri;
-        if (nk != me) {  // group-uniform
-          if (j == 0) {
-            key[v] = nk;
-            chg[r & 1] = 1;
-          }
-          push_ball(v, b, e, bm1, l1, &c1);
+  __syncthreads();
+  const int32_t m = count;
+  const EntryRanges rows{gcol, gext};
+  auto looks = [&](auto gc) {
+    constexpr int L = decltype(gc)::value;
+    const int j = threadIdx.x % L;
+    for (int32_t i = threadIdx.x / L; i < m; i += kBlock / L) {
+      const int32_t v = lv[i];
+      bool out = false;
+      const int32_t f = mis_look<L>(v, lb[i], le[i], j, rows, st, c0, ord, &out);
+      if (j == 0) {
+        if (f >= 0) {
+          watch[v] = f;
+        } else {
+          st[v] = c0 | 1;
+          cur[0] = 1;
         }
       }
-      __syncthreads();
-      if (chg[r & 1] == 0) {  // workgroup-uniform
-        used = r;
-        break;
-      }
-      if ((int64_t)r >= (int64_t)max_rounds) {
-        used = r;
-        err = 1;
-        break;
-      }
+      if (out) cur[1] = 1;
     }
+  };
+  // up to 4 looks have a wavefront each (fewer steps through a ball)
+  if (G == 32 && m <= kBlock / 64) looks(std::integral_constant<int, 64>{});
+  else looks(std::integral_constant<int, G>{});
+}
+
+// Decisions of earlier rounds lose their stamps (four states per thread).
+__global__ void k_mis_age(int32_t nw, uint32_t *st) {
+  SA_ROW_KERNEL_BEGIN(nw)
+  const uint32_t w = st[i];
+  uint32_t o = 0;
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const uint32_t x = (w >> (8 * q)) & 0xffu;
+    o |= (x >= 4u ? 1u + (x & 1u) : x) << (8 * q);
   }
-  if constexpr (KL) {  // the keys back to global memory (k1 is not read after the rounds)
-    __syncthreads();
-    for (int32_t v = tid; v < n; v += kMisWg) gkey[v] = key[v];
+  st[i] = o;
+}
+
+// ---- root selection in one workgroup --------------------------------------------------------
+// On levels of at most kMisWgMaxN vertices all rounds run inside a single workgroup of kMisWg
+// threads, with __syncthreads() in place of kernel boundaries; the states, watched vertices and
+// row pointers are in LDS, only the neighbour lists are read from memory.  The same polls,
+// looks and stamps as on the grid; a round's looks get a wavefront each while they are few,
+// else 16 lanes.  result[0] = the reported round count (bit 31: max_rounds reached); the same
+// word goes to the host-mapped post.
+constexpr int kMisWg = 1024;
+constexpr int64_t kMisWgMaxN = 4096;  // default level size limit (SAAMG_MIS_WG_MAX_N)
+// (64^2 grid and 128^3 cube: within 1% of the grid's rounds at this size, with no launches)
+constexpr int kMisWgV = 5;            // vertices per thread: levels up to 5120 vertices fit LDS
+constexpr int64_t kMisWgLdsMaxN = kMisWgV * kMisWg;
+
+template <class O>
+__global__ __launch_bounds__(kMisWg) void k_mis_wg(int32_t n, const int32_t *__restrict__ grp,
+                                                   const int32_t *__restrict__ gcol,
+                                                   const int32_t *__restrict__ gwatch,
+                                                   uint8_t *gst, O ord, int32_t max_rounds,
+                                                   int32_t *result, uint32_t *hpost) {
+  __shared__ int32_t rp[kMisWgLdsMaxN + 1], watch[kMisWgLdsMaxN];
+  __shared__ uint8_t st[kMisWgLdsMaxN];
+  __shared__ uint16_t list[kMisWgLdsMaxN];
+  __shared__ int32_t count[2], root[2], mark[2];
+  const int tid = threadIdx.x;
+  for (int32_t i = tid; i < n; i += kMisWg) {
+    rp[i] = grp[i];
+    watch[i] = gwatch[i];
+    st[i] = gst[i];
   }
   if (tid == 0) {
-    result[0] = (int32_t)used;
-    result[1] = (int32_t)err;
-    if (hpost)
-      __hip_atomic_store(hpost, used | (err << 31), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    rp[n] = grp[n];
+    count[0] = count[1] = root[0] = root[1] = mark[0] = mark[1] = 0;
   }
+  __syncthreads();
+  const RowRanges rows{gcol, rp};
+  int32_t T = 0;  // rounds that decided something
+  bool out_last = false, err = false;
+  for (int32_t r = 0;; ++r) {  // workgroup-uniform
+    const uint8_t c0 = (uint8_t)(4 + 2 * (r % kMisStamps));
+    const int h = r & 1;  // this round's counters; the other round's are cleared in this one
+    if (r > 0 && r % kMisStamps == 0) {
+      for (int32_t i = tid; i < n; i += kMisWg)
+        if (st[i] >= 4) st[i] = 1 + (st[i] & 1);
+      __syncthreads();
+    }
+    bool take[kMisWgV];
+    int32_t pos[kMisWgV];
+#pragma unroll
+    for (int q = 0; q < kMisWgV; ++q) {
+      const int32_t v = q * kMisWg + tid;
+      take[q] = false;
+      if (v < n && st[v] == 0) {
+        const int32_t w = watch[v];
+        take[q] = w == v || !mis_open(st[w], c0);
+      }
+    }
+    wave_reserve<kMisWgV>(take, &count[h], pos);
+#pragma unroll
+    for (int q = 0; q < kMisWgV; ++q)
+      if (take[q]) list[pos[q]] = (uint16_t)(q * kMisWg + tid);
+    __syncthreads();
+    const int32_t m = count[h];
+    if (tid == 0) count[h ^ 1] = root[h ^ 1] = mark[h ^ 1] = 0;
+    auto looks = [&](auto gc) {
+      constexpr int G = decltype(gc)::value;
+      const int j = tid % G;
+      for (int32_t i = tid / G; i < m; i += kMisWg / G) {
+        const int32_t v = list[i];
+        bool out = false;
+        const int32_t f = mis_look<G>(v, rp[v], rp[v + 1], j, rows, st, c0, ord, &out);
+        if (j == 0) {
+          if (f >= 0) {
+            watch[v] = f;
+          } else {
+            st[v] = c0 | 1;
+            root[h] = 1;
+          }
+        }
+        if (out) mark[h] = 1;
+      }
+    };
+    if (m <= 2 * (kMisWg / 64)) looks(std::integral_constant<int, 64>{});
+    else looks(std::integral_constant<int, 16>{});
+    __syncthreads();
+    if (root[h] == 0) break;
+    ++T;
+    out_last = mark[h] != 0;
+    if (r >= max_rounds) {
+      err = true;
+      break;
+    }
+  }
+  for (int32_t i = tid; i < n; i += kMisWg) gst[i] = st[i];
+  if (tid == 0) {
+    const uint32_t used = T > 0 ? 2u * (uint32_t)T - 1u + (out_last ? 1u : 0u) : 0u;
+    const uint32_t word = used | (err ? 1u << 31 : 0u);
+    result[0] = (int32_t)word;
+    if (hpost)
+      __hip_atomic_store(hpost, word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+  }
+}
+
+// Beside each entry of the graph the start and length of that vertex's own row.
+__global__ void k_mis_ranges(int64_t nnz, const int32_t *__restrict__ grp,
+                             const int32_t *__restrict__ gcol, int2 *gext) {
+  const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (k >= nnz) return;
+  const int32_t u = gcol[k];
+  const int32_t b = grp[u];
+  gext[k] = make_int2(b, grp[u + 1] - b);
 }
 
 // Largest row length of a CSR (two-stage maximum, no contended atomics).
@@ -975,25 +929,27 @@ int32_t max_row_length(int32_t n, const int32_t *rp, hipStream_t s) {
   return m;
 }
 
-template <class K>
-__global__ void k_roots(int32_t n, const K *key, int32_t *isr) {
+// IN states: 2, or a stamp with its lowest bit set.
+__device__ __forceinline__ bool mis_in(uint8_t s) { return s == 2 || (s >= 4 && (s & 1) != 0); }
+
+__global__ void k_roots(int32_t n, const uint8_t *st, int32_t *isr) {
   SA_ROW_KERNEL_BEGIN(n)
-  isr[i] = ((key[i] & KeyT<K>::Mask) == KeyT<K>::In) ? 1 : 0;
+  isr[i] = mis_in(st[i]) ? 1 : 0;
 }
-template <class K>
-__global__ void k_agg_phase1(int32_t n, const int32_t *grp, const int32_t *gcol, const K *key,
+__global__ void k_agg_phase1(int32_t n, const int32_t *grp, const int32_t *gcol,
+                             const uint8_t *st,
                              const int32_t *rid, int32_t *agg1, uint8_t *is_root,
                              int32_t *root_vertex) {
   SA_ROW_KERNEL_BEGIN(n)
   int32_t a = -1;
-  const bool root = (key[i] & KeyT<K>::Mask) == KeyT<K>::In;
+  const bool root = mis_in(st[i]);
   if (root) {
     a = rid[i];
     root_vertex[a] = i;
   } else {
     for (int32_t k = grp[i]; k < grp[i + 1]; ++k) {
       const int32_t u = gcol[k];
-      if ((key[u] & KeyT<K>::Mask) == KeyT<K>::In) {
+      if (mis_in(st[u])) {
         a = rid[u];
         break;
       }
@@ -1059,30 +1015,26 @@ __global__ void k_agg_phase2(int32_t n, const int32_t *grp, const int32_t *gcol,
   agg[i] = a;
 }
 
-template <class K>
+template <class O>
 static int32_t aggregate_impl(int32_t n, int64_t nnzG, const int32_t *grp, const int32_t *gcol,
-                              int32_t order, uint64_t seed, int32_t level, bool singletons,
-                              int32_t *agg,
+                              O ord, bool singletons, int32_t *agg,
                               uint8_t *is_root, Arena &ar, int32_t **root_vertex,
                               int32_t *rounds_out, hipStream_t s) {
   Arena tmp;
   tmp.stream = s;
-  K *key = tmp.alloc<K>(n);
-  K *k1 = tmp.alloc<K>(n);
-  uint8_t *st1 = tmp.alloc<uint8_t>((n + 15) & ~15);  // padded for word reads
-  uint8_t *st2 = tmp.alloc<uint8_t>((n + 15) & ~15);
-  // levels up to wg_max_n vertices run the rounds after the first in one workgroup
+  uint8_t *st = tmp.alloc<uint8_t>(((int64_t)n + 15) & ~(int64_t)15);  // padded for word reads
+  int32_t *watch = tmp.alloc<int32_t>(n);
+  // levels up to wg_max_n vertices run every round in one workgroup
   int64_t wg_max_n = kMisWgMaxN;
   if (const char *e = std::getenv("SAAMG_MIS_WG_MAX_N")) wg_max_n = std::atoll(e);
   const bool one_wg = nnzG > 0 && n <= std::min(wg_max_n, kMisWgLdsMaxN);
-  k_mis_init<K><<<grid_for(n), kBlock, 0, s>>>(n, grp, order, seed, level, singletons, key, st1,
-                                               st2);
+  k_mis_init<O><<<grid_for(n), kBlock, 0, s>>>(n, grp, gcol, ord, singletons, st, watch);
   SA_LAUNCH_CHECK();
   // Rounds are launched back to back, at most kAhead past the last round whose outcome the
-  // host has seen.  Pass 1 of round r+1 posts round r's outcome into a pinned status ring
-  // (slot r mod kRing, tagged with r); the first round that changed nothing ends the
+  // host has seen.  The launch of round r+1 posts round r's outcome into a pinned status ring
+  // (slot r mod kRing, tagged with r); the first round that decided nothing ends the
   // selection, and the rounds still queued behind it exit at once.  Device flags live in a
-  // ring of the same size: pass 1 of round r clears slot r, pass 2 raises it.  If a status
+  // ring of the same size: round r clears slot r+1 and raises slot r.  If a status
   // word is not seen within spin_ns (20 ms; the environment variable SAAMG_STATUS_SPIN_NS
   // overrides it, 0 taking the fallback at every wait), the stream is synchronised and the
   // device flags read instead, so the outcome never depends on the host mapping alone.
@@ -1091,89 +1043,82 @@ static int32_t aggregate_impl(int32_t n, int64_t nnzG, const int32_t *grp, const
   if (const char *e = std::getenv("SAAMG_STATUS_SPIN_NS")) spin_ns = std::atoll(e);
   // every round before the last decides at least one vertex, so this bound is never reached
   const int64_t cap = (int64_t)n + 2 + 2 * kAhead;
-  int32_t *flags = tmp.alloc<int32_t>(kRing);
+  int32_t *flags = tmp.alloc<int32_t>(2 * kRing);
+  fill_i32(flags, 0, 2 * kRing, s);
   volatile uint32_t *hs = (volatile uint32_t *)pinned_status(sizeof(uint32_t) * kRing);
   for (int q = 0; q < kRing; ++q) hs[q] = ~0u;
   uint32_t *hs_dev = nullptr;
   SA_HIP(hipHostGetDevicePointer((void **)&hs_dev, (void *)hs, 0));
-  const int32_t maxdeg = max_row_length(n, grp, s);
-  const bool wave = maxdeg > 64 || nnzG > 24 * (int64_t)n;
-  const unsigned g = wave ? grid_for((int64_t)n * 64) : grid_for(n);
-  // large thread-per-vertex levels: kMisV vertices per thread (grid gv), fewer workgroups to
-  // dispatch per pass; SAAMG_MIS_V_MIN_N overrides the level size from which they are used
+  // lanes per look: the longest row's neighbours in one step where 64 lanes hold them.  8 on
+  // every level took the 128^3 setup from 20.7 to 25.3 ms; 64 on every level but those of
+  // rows up to 8 took the 100^3 27-point cube's from 17.8 to 19.2 ms
+  const int32_t maxdeg = one_wg ? 0 : max_row_length(n, grp, s);
+  int2 *gext = nullptr;
+  if (!one_wg && nnzG > 0) {
+    gext = tmp.alloc<int2>(nnzG);
+    k_mis_ranges<<<grid_for(nnzG), kBlock, 0, s>>>(nnzG, grp, gcol, gext);
+    SA_LAUNCH_CHECK();
+  }
+  // large levels: kMisV vertices per thread, fewer workgroups to dispatch per round;
+  // SAAMG_MIS_V_MIN_N overrides the level size from which they are used
   int64_t v_min_n = kMisVMinN;
   if (const char *e = std::getenv("SAAMG_MIS_V_MIN_N")) v_min_n = std::atoll(e);
-  const unsigned gv =
-      (!wave && n >= v_min_n) ? (unsigned)ceil_div(n, (int64_t)kBlock * kMisV) : 0u;
+  const bool many = n >= v_min_n;
+  const unsigned g = grid_for(n, many ? kBlock * kMisV : kBlock);
   auto launch_round = [&](int64_t r) {
-    const uint8_t sr = (uint8_t)(r & 255), srn = (uint8_t)((r + 1) & 255);
+    const uint8_t c0 = (uint8_t)(4 + 2 * (r % kMisStamps));
+    if (r > 0 && r % kMisStamps == 0) {
+      const int32_t nw = (int32_t)ceil_div(n, 4);
+      k_mis_age<<<grid_for(nw), kBlock, 0, s>>>(nw, (uint32_t *)st);
+    }
     const bool first = r == 0;
-    const int32_t *prev = first ? nullptr : flags + ((r - 1) & (kRing - 1));
-    int32_t *cur = flags + (r & (kRing - 1));
+    const int32_t *prev = first ? nullptr : flags + 2 * ((r - 1) & (kRing - 1));
+    int32_t *cur = flags + 2 * (r & (kRing - 1));
+    int32_t *next = flags + 2 * ((r + 1) & (kRing - 1));
     uint32_t *post = first ? nullptr : hs_dev + ((r - 1) & (kRing - 1));
     const uint32_t tag = (uint32_t)(r - 1) << 2;
-    if (wave) {
-      k_mis_pass1<K, true><<<g, kBlock, 0, s>>>(n, grp, gcol, key, k1, st1, st2, sr, first,
-                                                 prev, cur, post, tag);
-      k_mis_pass2<K, true><<<g, kBlock, 0, s>>>(n, grp, gcol, k1, key, st2, st1, sr, srn, cur,
-                                                 prev);
-    } else if (gv > 0) {
-      k_mis_pass1<K, false, kMisV><<<gv, kBlock, 0, s>>>(n, grp, gcol, key, k1, st1, st2, sr,
-                                                         first, prev, cur, post, tag);
-      k_mis_pass2<K, false, kMisV><<<gv, kBlock, 0, s>>>(n, grp, gcol, k1, key, st2, st1, sr,
-                                                         srn, cur, prev);
-    } else {
-      k_mis_pass1<K, false><<<g, kBlock, 0, s>>>(n, grp, gcol, key, k1, st1, st2, sr, first,
-                                                  prev, cur, post, tag);
-      k_mis_pass2<K, false><<<g, kBlock, 0, s>>>(n, grp, gcol, k1, key, st2, st1, sr, srn,
-                                                  cur, prev);
-    }
+    auto go = [&](auto gc, auto vc) {
+      constexpr int G = decltype(gc)::value, V = decltype(vc)::value;
+      k_mis_round<G, V, O><<<g, kBlock, 0, s>>>(n, grp, gcol, gext, st, watch, c0, ord, prev,
+                                                cur, next, post, tag);
+    };
+    using I1 = std::integral_constant<int, 1>;
+    using IV = std::integral_constant<int, kMisV>;
+    auto lanes = [&](auto gc) {
+      if (many) go(gc, IV{});
+      else go(gc, I1{});
+    };
+    if (maxdeg <= 8) lanes(std::integral_constant<int, 8>{});
+    else if (maxdeg <= 32) lanes(std::integral_constant<int, 32>{});
+    else lanes(std::integral_constant<int, 64>{});
     SA_LAUNCH_CHECK();
   };
   int64_t launched = 0, seen = 0;  // rounds launched; rounds whose outcome is known
+  bool out_last = false;           // the last round seen marked a vertex OUT
   int32_t used = 0;
+  auto finish_at = [&](int64_t r) {  // round r decided nothing
+    used = r > 0 ? (int32_t)(2 * r - 1 + (out_last ? 1 : 0)) : 0;
+  };
   bool done = nnzG == 0;
   int32_t *wg_result = nullptr;
   if (one_wg) {
-    // round 0 on the grid (every vertex), the rest in one workgroup
-    wg_result = tmp.alloc<int32_t>(2);
-    int32_t *l12 = tmp.alloc<int32_t>(2 * (int64_t)n);
-    launch_round(0);
-    const int32_t max_rounds = (int32_t)std::min<int64_t>((int64_t)n + 2, INT32_MAX);
-    // rows past 16 entries: 4 lanes per vertex
-    const size_t bits = sizeof(uint32_t) * (size_t)((2 * ((n + 31) / 32) + 1) & ~1);
-    // the keys and k1 go to LDS too while they fit kMisWgKeyLds bytes
-    const size_t keys = 2 * sizeof(K) * (size_t)n;
-    const bool kl = keys <= kMisWgKeyLds;
-    const size_t lds = bits + (kl ? keys : 0);
-    auto go = [&](auto g, auto klc) {
-      constexpr int G = decltype(g)::value;
-      constexpr bool KL = decltype(klc)::value;
-      k_mis_rounds_wg<K, G, KL><<<1, kMisWg, lds, s>>>(n, grp, gcol, key, k1, st1, flags, l12,
-                                                       l12 + n, max_rounds, wg_result, hs_dev);
-    };
-    using G1 = std::integral_constant<int, 1>;
-    using G4 = std::integral_constant<int, 4>;
-    if (maxdeg > 16) {
-      if (kl) go(G4{}, std::true_type{});
-      else go(G4{}, std::false_type{});
-    } else {
-      if (kl) go(G1{}, std::true_type{});
-      else go(G1{}, std::false_type{});
-    }
+    wg_result = tmp.alloc<int32_t>(1);
+    const int32_t max_rounds = n + 2;
+    k_mis_wg<O><<<1, kMisWg, 0, s>>>(n, grp, gcol, watch, st, ord, max_rounds, wg_result, hs_dev);
     SA_LAUNCH_CHECK();
     done = true;
   }
   auto wait_from = std::chrono::steady_clock::now();
   while (!done) {
-    // round `seen`'s status is posted by pass 1 of round seen+1
+    // round `seen`'s status is posted by the launch of round seen+1
     if (launched >= seen + 2) {
       const uint32_t v = hs[seen & (kRing - 1)];
       if ((v & ~3u) == ((uint32_t)seen << 2) && (v & 3u) != 0 && v != ~0u) {
         if ((v & 3u) == 2u) {
-          used = (int32_t)seen;
+          finish_at(seen);
           done = true;
         } else {
+          out_last = (v & 3u) == 3u;
           ++seen;
         }
         wait_from = std::chrono::steady_clock::now();
@@ -1189,20 +1134,24 @@ static int32_t aggregate_impl(int32_t n, int64_t nnzG, const int32_t *grp, const
     if (std::chrono::duration_cast<std::chrono::nanoseconds>(now - wait_from).count() <
         spin_ns)
       continue;
-    // status not seen in time: every launched round's flag is final when the readback's copy
-    // runs (after them on the stream)
-    int32_t hf[kRing];
+    // status not seen in time: every launched round's flags are final when the readback's
+    // copy runs (after them on the stream)
+    int32_t hf[2 * kRing];
     readback(hf, flags, sizeof(hf), s);
-    for (; seen < launched && !done; ++seen)
-      if (hf[seen & (kRing - 1)] == 0) {
-        used = (int32_t)seen;
+    for (; seen < launched && !done; ++seen) {
+      const int32_t *f = hf + 2 * (seen & (kRing - 1));
+      if (f[0] == 0) {
+        finish_at(seen);
         done = true;
+      } else {
+        out_last = f[1] != 0;
       }
+    }
     if (done) break;
     wait_from = std::chrono::steady_clock::now();
   }
   int32_t *isr = tmp.alloc<int32_t>(n + 1);
-  k_roots<K><<<grid_for(n), kBlock, 0, s>>>(n, key, isr);
+  k_roots<<<grid_for(n), kBlock, 0, s>>>(n, st, isr);
   SA_LAUNCH_CHECK();
   int32_t *rid = tmp.alloc<int32_t>(n + 1);
   exclusive_scan_i32(isr, rid, n, s);
@@ -1210,18 +1159,14 @@ static int32_t aggregate_impl(int32_t n, int64_t nnzG, const int32_t *grp, const
   if (one_wg) {
     // the workgroup's outcome, posted to the host-mapped word (read back if it is not seen)
     uint32_t v = hs[0];
-    if (v == ~0u) {
-      int32_t r2[2];
-      readback(r2, wg_result, sizeof(r2), s);
-      v = (uint32_t)r2[0] | ((uint32_t)r2[1] << 31);
-    }
+    if (v == ~0u) v = (uint32_t)read1(wg_result, s);
     if (v >> 31) throw Error(SA_ERR_COARSEN_STALLED, "root selection did not end");
     used = (int32_t)v;
   }
   if (rounds_out) *rounds_out = used;
   int32_t *rv = ar.alloc<int32_t>(nc > 0 ? nc : 1);
   int32_t *agg1 = tmp.alloc<int32_t>(n);
-  k_agg_phase1<K><<<grid_for(n), kBlock, 0, s>>>(n, grp, gcol, key, rid, agg1, is_root, rv);
+  k_agg_phase1<<<grid_for(n), kBlock, 0, s>>>(n, grp, gcol, st, rid, agg1, is_root, rv);
   SA_LAUNCH_CHECK();
   k_agg_phase2<<<grid_for(n), kBlock, 0, s>>>(n, grp, gcol, agg1, agg);
   SA_LAUNCH_CHECK();
@@ -1233,11 +1178,11 @@ int32_t aggregate(int32_t n, int64_t nnzG, const int32_t *grp, const int32_t *gc
                   int32_t order, uint64_t seed, int32_t level, bool singletons, int32_t *agg,
                   uint8_t *is_root, Arena &ar, int32_t **root_vertex, int32_t *rounds,
                   hipStream_t s) {
-  if (order == 0 && n < (1 << 30))
-    return aggregate_impl<uint32_t>(n, nnzG, grp, gcol, order, seed, level, singletons, agg,
-                                    is_root, ar, root_vertex, rounds, s);
-  return aggregate_impl<uint64_t>(n, nnzG, grp, gcol, order, seed, level, singletons, agg,
-                                  is_root, ar, root_vertex, rounds, s);
+  if (order == 0)
+    return aggregate_impl(n, nnzG, grp, gcol, NaturalOrder{}, singletons, agg, is_root, ar,
+                          root_vertex, rounds, s);
+  return aggregate_impl(n, nnzG, grp, gcol, HashedOrder{seed, level}, singletons, agg, is_root,
+                        ar, root_vertex, rounds, s);
 }
 
 // ---- Sprsfy (Sec. 2.5) --------------------------------------------------------------------
