@@ -422,9 +422,10 @@ struct ScalarGather {
   const double *p[kMaxGather];
   int32_t n;
 };
-__global__ void k_gather_scalars(ScalarGather g, double *out) {
+__global__ void k_gather_scalars(ScalarGather g, double *out, int32_t zeros) {
   const int i = threadIdx.x;
   if (i < g.n) out[i] = g.p[i] ? *g.p[i] : 0.0;
+  if (i < zeros) out[g.n + i] = 0.0;
 }
 
 // GPU part of level l's smoother set-up on stream s: the inverse diagonal of A_l and the
@@ -478,8 +479,20 @@ static void finish_setup(sa_hierarchy *h, bool fresh) {
   readback(ew, h->err, sizeof(ew), s);
   if ((ew[0] | ew[1]) & E_DIAG)
     throw Error(SA_ERR_NONPOSITIVE_DIAG, "non-positive diagonal in a level operator");
+  // (and, in a setup, the longest rows of the matrices the solve multiplies with)
   std::vector<double> sc;
-  if (nl > 1) {
+  std::vector<Csr *> mats;
+  if (fresh) {
+    for (int l = 0; l < nl; ++l) {
+      Level &L = h->lv[l];
+      if (l + 1 < nl || l == 0) mats.push_back(&L.A);
+      if (l + 1 < nl) {
+        mats.push_back(&L.P);
+        mats.push_back(&L.R);
+      }
+    }
+  }
+  {
     ScalarGather g{};
     for (int l = 0; l + 1 < nl; ++l) {
       g.p[3 * l] = h->lv[l].sm_lam_d;
@@ -489,11 +502,23 @@ static void finish_setup(sa_hierarchy *h, bool fresh) {
     g.n = 3 * (nl - 1);
     Arena tmp;
     tmp.stream = s;
-    double *d = tmp.alloc<double>(g.n);
-    k_gather_scalars<<<1, 64, 0, s>>>(g, d);
+    const int32_t words = (kMaxRowJobs + 1) / 2;  // the row lengths' room, in doubles
+    double *d = tmp.alloc<double>(g.n + words);
+    k_gather_scalars<<<1, 64, 0, s>>>(g, d, words);
     SA_LAUNCH_CHECK();
-    sc.resize(g.n);
-    readback(sc.data(), d, sizeof(double) * g.n, s);
+    if (fresh) {
+      MaxRowJobs jobs{};
+      for (const Csr *m : mats) {
+        jobs.rp[jobs.count] = m->rp;
+        jobs.n[jobs.count++] = m->n;
+      }
+      max_row_lengths(jobs, (int32_t *)(d + g.n), s);
+    }
+    sc.resize(g.n + words);
+    readback(sc.data(), d, sizeof(double) * sc.size(), s);
+    const int32_t *longest = (const int32_t *)(sc.data() + g.n);
+    for (size_t q = 0; q < mats.size(); ++q)
+      mats[q]->lanes = spmv_lanes(mats[q]->n, mats[q]->nnz, longest[q]);
   }
   for (int l = 0; l + 1 < nl; ++l) {
     Level &L = h->lv[l];
@@ -554,8 +579,9 @@ static void finish_setup(sa_hierarchy *h, bool fresh) {
     // the solve's SpMVs on A: every level but a coarsest one with more than one level (its
     // dense solve takes no SpMV); level 0 also serves the Krylov method
     if (l + 1 < nl || l == 0) {
-      if (fresh) sell_build(L.A, L.Aell, f32 && l + 1 < nl, h->ar, s);
-      else sell_values(L.A, L.Aell, s);
+      if (fresh && sell_build(L.A, L.Aell, f32 && l + 1 < nl, h->ar, s))
+        L.A.lanes = 0;  // the grouped solves' CSR rows keep the sliced rows' order
+      if (!fresh) sell_values(L.A, L.Aell, s);
     }
   }
   if (fresh) {

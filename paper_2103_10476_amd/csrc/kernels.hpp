@@ -5,13 +5,14 @@
 namespace sa {
 
 // ---------------- solve-phase kernels (solve_kernels.hip) ------------------------------
-// y = A x with every row of at most 64 entries summed sequentially in ascending column order
-// from 0 (products staged through LDS).  A longer row is summed the same way when `plain` is
-// set -- the setup's eigenvalue estimates, whose results decide the hierarchy bit for bit --
-// and otherwise, in the solve, as 64 interleaved in-order partial sums added in order, which
-// cuts the row's dependent chain of adds from L to about L/64 + 64 (a rounding-level
-// difference from the sequential sum).  Variants fuse the row-local epilogue used by the
-// smoother, residual and transfer steps.
+// y = A x.  Row blocks: every row of at most 64 entries is summed sequentially in ascending
+// column order from 0 (products staged through LDS).  A longer row is summed the same way when
+// `plain` is set -- the setup's eigenvalue estimates, whose results decide the hierarchy bit
+// for bit -- and otherwise, in the solve, as 64 interleaved in-order partial sums added in
+// order, which cuts the row's dependent chain of adds from L to about L/64 + 64.  Rows by
+// lanes (the solve only): G lanes sum the entries j, j + G, ... each, and their sums are added
+// pairwise.  The orders differ at rounding level.  Variants fuse the row-local epilogue used
+// by the smoother, residual and transfer steps.
 template <class T>
 struct SpmvArgs {
   int32_t n;
@@ -27,6 +28,7 @@ struct SpmvArgs {
   const T *sval = nullptr;
   int32_t nslice = 0;
   bool plain = false;  // long rows in sequential order too (see above)
+  int32_t lanes = 0;   // rows by lanes in the solve (see spmv_lanes); 0: the row blocks
 };
 // Row partition for the SpMV kernels: block b owns the rows whose cost rp[r] + 8 r lies in
 // [2048 b, 2048 (b+1)), i.e. at most 256 rows and (long rows aside) at most 2048 entries;
@@ -34,8 +36,26 @@ struct SpmvArgs {
 void spmv_plan(Csr &A, Arena &ar, hipStream_t s);
 template <class T>
 inline SpmvArgs<T> spmv_args(const Csr &A, const T *val, const T *x) {
-  return SpmvArgs<T>{A.n, A.rp, A.col, val, x, A.bstart, A.nblk};
+  SpmvArgs<T> a{A.n, A.rp, A.col, val, x, A.bstart, A.nblk};
+  a.lanes = A.lanes;
+  return a;
 }
+// Lanes per row for the solve's SpMVs on an n-row matrix whose longest row has maxrow entries,
+// or 0 where the row blocks serve it better (the rule is at the definition).
+int32_t spmv_lanes(int32_t n, int64_t nnz, int32_t maxrow);
+// Workgroups of a solve-phase SpMV on A's CSR arrays.
+inline int32_t spmv_blocks(const Csr &A) {
+  if (A.n <= 0) return 0;
+  return A.lanes > 0 ? (int32_t)ceil_div((int64_t)A.n * A.lanes, kBlock) : A.nblk;
+}
+// Longest rows of several matrices, each maximised into *out (zeroed before).
+constexpr int kMaxRowJobs = 48;
+struct MaxRowJobs {
+  const int32_t *rp[kMaxRowJobs];
+  int32_t n[kMaxRowJobs];
+  int32_t count;
+};
+void max_row_lengths(const MaxRowJobs &jobs, int32_t *out, hipStream_t s);
 // Switches an SpMV to the sliced-ELL copy S with values val (no change when S is not built).
 template <class T>
 inline SpmvArgs<T> with_sell(SpmvArgs<T> a, const Sell &S, const T *val) {

@@ -38,6 +38,7 @@ template <class T, class Epi>
 struct GSpmv {
   const int32_t *bstart, *rp, *col;
   const T *val, *x;
+  int32_t n, lanes;  // rows by lanes when lanes > 0
   Epi epi;
 };
 
@@ -48,7 +49,15 @@ __global__ __launch_bounds__(kBlock) void k_gspmv(const GSpmv<T, Epi> *segs,
   const int32_t g = xcd_block(blockIdx.x, gridDim.x);
   const int32_t s = find_seg(boff, nseg, g);
   const GSpmv<T, Epi> a = segs[s];
-  spmv_block<T, Epi>(g - boff[s], a.bstart, a.rp, a.col, a.val, a.x, a.epi, sh);
+  const int32_t blk = g - boff[s];
+  switch (a.lanes) {  // block-uniform
+    case 0: spmv_block<T, Epi>(blk, a.bstart, a.rp, a.col, a.val, a.x, a.epi, sh); break;
+    case 4: spmv_rows<T, Epi, 4>(blk, a.n, a.rp, a.col, a.val, a.x, a.epi); break;
+    case 8: spmv_rows<T, Epi, 8>(blk, a.n, a.rp, a.col, a.val, a.x, a.epi); break;
+    case 16: spmv_rows<T, Epi, 16>(blk, a.n, a.rp, a.col, a.val, a.x, a.epi); break;
+    case 32: spmv_rows<T, Epi, 32>(blk, a.n, a.rp, a.col, a.val, a.x, a.epi); break;
+    default: spmv_rows<T, Epi, 64>(blk, a.n, a.rp, a.col, a.val, a.x, a.epi); break;
+  }
 }
 
 enum GVecOp : int32_t {
@@ -230,7 +239,7 @@ View<float> view_of(Level &L, float) {
 
 template <class T, class Epi>
 GSpmv<T, Epi> gspmv(const Csr &M, const T *val, const T *x, const Epi &e) {
-  return GSpmv<T, Epi>{M.bstart, M.rp, M.col, val, x, e};
+  return GSpmv<T, Epi>{M.bstart, M.rp, M.col, val, x, M.n, M.lanes, e};
 }
 
 // One grouped SpMV launch over `items` (matrix, values, x, epilogue).
@@ -359,7 +368,7 @@ void rec_smooth(Recorder &rc, const std::vector<Item> &its, bool uzero) {
         sp.push_back(gspmv<T>(*v[k].A, v[k].Aval, u,
                               EpJacobi<T>{u, (const T *)its[k].f, v[k].invD, (T)L.jac_w,
                                           v[k].d1}));
-        nb.push_back(L.A.n > 0 ? L.A.nblk : 0);
+        nb.push_back(spmv_blocks(L.A));
         cp.push_back(gv(f32 ? G_COPY_F : G_COPY_D, L.A.n, v[k].d1, nullptr, its[k].u));
       }
       rec_spmv(rc, sp, nb);
@@ -392,7 +401,7 @@ void rec_smooth(Recorder &rc, const std::vector<Item> &its, bool uzero) {
       sp.push_back(gspmv<T>(*v[k].A, v[k].Aval, (const T *)its[k].u,
                             EpChebStart<T>{(const T *)its[k].f, v[k].invD, (T)L.cheb_theta,
                                            v[k].r, dc[k]}));
-      nb.push_back(L.A.n > 0 ? L.A.nblk : 0);
+      nb.push_back(spmv_blocks(L.A));
       add.push_back(gv(f32 ? G_VEC_ADD_F : G_VEC_ADD_D, L.A.n, dc[k], nullptr, its[k].u));
       rin.push_back(v[k].r);
     }
@@ -409,7 +418,7 @@ void rec_smooth(Recorder &rc, const std::vector<Item> &its, bool uzero) {
                             EpChebStep<T>{dc[k], rin[k], v[k].invD, v[k].r, (T *)its[k].u,
                                           dn[k], (T)L.cheb_c1[m - 1], (T)L.cheb_c2[m - 1],
                                           uzero && m == 1, last}));
-      nb.push_back(L.A.n > 0 ? L.A.nblk : 0);
+      nb.push_back(spmv_blocks(L.A));
       rin[k] = v[k].r;
       std::swap(dc[k], dn[k]);
     }
@@ -461,7 +470,7 @@ void rec_vcycle(Recorder &rc, const std::vector<Item> &its) {
       const Level &L = fine[k].h->lv[fine[k].level];
       sp.push_back(gspmv<T>(*v[k].A, v[k].Aval, (const T *)fine[k].u,
                             EpResid<T>{(const T *)fine[k].f, v[k].r}));
-      nb.push_back(L.A.n > 0 ? L.A.nblk : 0);
+      nb.push_back(spmv_blocks(L.A));
     }
     rec_spmv(rc, sp, nb);
   }
@@ -474,7 +483,7 @@ void rec_vcycle(Recorder &rc, const std::vector<Item> &its) {
       const Level &L = h->lv[fine[k].level];
       View<T> vc = view_of(h->lv[fine[k].level + 1], T());
       sp.push_back(gspmv<T>(L.R, v[k].Rval, v[k].r, EpStore<T>{vc.f}));
-      nb.push_back(L.R.n > 0 ? L.R.nblk : 0);
+      nb.push_back(spmv_blocks(L.R));
       next.push_back({h, fine[k].level + 1, vc.f, vc.u});
     }
     rec_spmv(rc, sp, nb);
@@ -486,7 +495,7 @@ void rec_vcycle(Recorder &rc, const std::vector<Item> &its) {
     for (size_t k = 0; k < fine.size(); ++k) {
       const Level &L = fine[k].h->lv[fine[k].level];
       sp.push_back(gspmv<T>(L.P, v[k].Pval, (const T *)next[k].u, EpAdd<T>{(T *)fine[k].u}));
-      nb.push_back(L.P.n > 0 ? L.P.nblk : 0);
+      nb.push_back(spmv_blocks(L.P));
     }
     rec_spmv(rc, sp, nb);
   }
@@ -706,7 +715,7 @@ void BatchSolver::tick(std::vector<BatchSystem *> &finished) {
     for (BatchSystem *b : first) {
       const Level &L0 = b->h->lv[0];
       sp.push_back(gspmv<double>(L0.A, L0.A.val, b->h->p, EpStore<double>{b->h->q}));
-      nb.push_back(L0.A.n > 0 ? L0.A.nblk : 0);
+      nb.push_back(spmv_blocks(L0.A));
     }
     rec_spmv(rc, sp, nb);
     std::vector<DotJob> dj;

@@ -188,6 +188,62 @@ __device__ __forceinline__ void spmv_block(int32_t b, const int32_t *__restrict_
   }
 }
 
+// Rows by lanes: G lanes of a wavefront share a row; lane j adds the products of the row's
+// entries j, j + G, ... in order from 0, and the lanes' sums are added pairwise (j with j ^ G/2,
+// then j ^ G/4, ...).  A lane's loads are issued U at a time.  No LDS and no barriers: where
+// rows are of similar length, or the matrix is small, a row costs its chain of dependent
+// loads (row range, entries, x) instead of a block's.  100^3 27-point level 0 (26 entries per
+// row, 309 MB): row blocks 93-97 us; 4 lanes 77-82 us; 2 and 8 lanes 102 and 97-114 us.
+// 180,000-row elasticity level 0 (76 per row, 165 MB): 51-58 against 29-33 us with 8 lanes.
+// 1,631 rows of 721: 7.4-9.4 against 4.6-6.4 us with 64.
+template <class T, class Epi, int G>
+__device__ __forceinline__ void spmv_rows(int64_t blk, int32_t n, const int32_t *__restrict__ rp,
+                                          const int32_t *__restrict__ col,
+                                          const T *__restrict__ val, const T *__restrict__ x,
+                                          const Epi &epi) {
+  constexpr int U = G == 4 ? 8 : 4;
+  const int64_t row64 = blk * (kBlock / G) + threadIdx.x / G;
+  if (row64 >= n) return;
+  const int32_t row = (int32_t)row64;
+  const int j = threadIdx.x % G;
+  const int32_t b = rp[row], e = rp[row + 1];
+  typename Epi::Pre pre{};
+  if (j == 0) pre = epi.load(row);
+  T s = T(0);
+  int32_t k = b + j;
+  for (; k + (U - 1) * G < e; k += U * G) {
+    int32_t c[U];
+    T v[U], xv[U];
+#pragma unroll
+    for (int q = 0; q < U; ++q) {
+      c[q] = col[k + q * G];
+      v[q] = val[k + q * G];
+    }
+#pragma unroll
+    for (int q = 0; q < U; ++q) xv[q] = x[c[q]];
+#pragma unroll
+    for (int q = 0; q < U; ++q) s += v[q] * xv[q];
+  }
+  if (k < e) {  // up to U - 1 more, loaded together (the row's last entry past its end)
+    int32_t c[U - 1];
+    T v[U - 1], xv[U - 1];
+#pragma unroll
+    for (int q = 0; q < U - 1; ++q) {
+      const int32_t kk = min(k + q * G, e - 1);
+      c[q] = col[kk];
+      v[q] = val[kk];
+    }
+#pragma unroll
+    for (int q = 0; q < U - 1; ++q) xv[q] = x[c[q]];
+#pragma unroll
+    for (int q = 0; q < U - 1; ++q)
+      if (k + q * G < e) s += v[q] * xv[q];
+  }
+#pragma unroll
+  for (int off = G / 2; off >= 1; off >>= 1) s += __shfl_xor(s, off, G);
+  if (j == 0) epi.store(row, s, pre);
+}
+
 // ---- fused SpMV epilogues: row i receives s = (A x)_i ------------------------------------
 // load(i) reads the row's other inputs (issued before the row's entries are gathered, so
 // their latency overlaps); store(i, s, pre) computes and writes.  Inputs are never vectors

@@ -11,6 +11,8 @@
 // definition, while the global
 // loads stay fully coalesced (HBM-bound: ~12 B/entry for FP64, ~8 B/entry for FP32).
 // Operators with short rows use a sliced-ELL copy instead (k_spmv_sell).
+#include <algorithm>
+
 #include "solve_device.hpp"
 
 namespace sa {
@@ -24,6 +26,67 @@ __global__ __launch_bounds__(kBlock) void k_spmv(const int32_t *__restrict__ bst
   __shared__ SpmvShared<T> sh;
   spmv_block<T, Epi, Split>(xcd_block(blockIdx.x, gridDim.x), bstart, rp, col, val, x, epi,
                             sh);
+}
+
+template <class T, class Epi, int G>
+__global__ __launch_bounds__(kBlock) void k_spmv_rows(int32_t n, const int32_t *__restrict__ rp,
+                                                      const int32_t *__restrict__ col,
+                                                      const T *__restrict__ val,
+                                                      const T *__restrict__ x, Epi epi) {
+  spmv_rows<T, Epi, G>(xcd_block(blockIdx.x, gridDim.x), n, rp, col, val, x, epi);
+}
+
+// Where rows by lanes serve better than the row blocks (solve kernel times by level of the
+// 128^3, 160^3, 96^3 and 47^3 cubes, the 27-point and the elasticity problems, every lane
+// count against the row blocks):
+//  - rows of 24 entries or more on average and none over 4 times that: lanes for 8 to 12
+//    entries each (27 per row: 4 lanes; 62 and 76: 8; 136: 16, 5.6-7.6 us, with 32 6.9-8.8).
+//    Shorter rows leave the lanes' loads too short runs (16 per row: 40-57 us against
+//    30-39), and one long row in a wavefront holds up its neighbours (rows of 30 on average
+//    and thousands at most: 15-27 us against 9-12).
+//  - matrices small enough for every row to have its lanes on the chip at once (n G up to
+//    2^18): lanes for 4 entries of an average row and 16 of the longest as far as that
+//    allows, if no row has more than 32 entries per lane (8 steps of loads).  These cost
+//    their latency: 4-5 us against the row blocks' 6-10.  (Lanes for single entries gain
+//    0.3 us more on a matrix alone and cost the grouped solve of eight systems 5%.)
+int32_t spmv_lanes(int32_t n, int64_t nnz, int32_t maxrow) {
+  if (n <= 0 || nnz <= 0) return 0;
+  const int64_t mean = (nnz + n - 1) / n;
+  int32_t g = 4;
+  while (g < 64 && mean > (g == 4 ? 32 : 12 * g)) g *= 2;
+  if (nnz >= 24 * (int64_t)n && maxrow <= 4 * mean && (int64_t)n * g > (int64_t(1) << 17))
+    return g;
+  if ((int64_t)n * g > (int64_t(1) << 18)) return 0;
+  const int64_t len = std::max<int64_t>(mean, maxrow / 4);
+  while (g < 64 && 4 * g < len && 2 * (int64_t)n * g <= (int64_t(1) << 18)) g *= 2;
+  return maxrow <= 32 * g ? g : 0;
+}
+
+// A block per 2048 rows of one matrix (grid.y: the matrices).
+__global__ __launch_bounds__(kBlock) void k_max_rows(MaxRowJobs jobs, int32_t *out) {
+  __shared__ int32_t sh[kBlock / 64];
+  const int q = blockIdx.y;
+  const int32_t n = jobs.n[q];
+  const int32_t *rp = jobs.rp[q];
+  int32_t m = 0;
+  for (int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x; i < n;
+       i += (int64_t)gridDim.x * kBlock)
+    m = max(m, rp[i + 1] - rp[i]);
+  for (int off = 32; off >= 1; off >>= 1) m = max(m, __shfl_xor(m, off, 64));
+  if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = m;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    for (int w = 1; w < kBlock / 64; ++w) m = max(m, sh[w]);
+    if (m > 0) atomicMax(out + q, m);
+  }
+}
+void max_row_lengths(const MaxRowJobs &jobs, int32_t *out, hipStream_t s) {
+  if (jobs.count <= 0) return;
+  int32_t most = 1;
+  for (int32_t q = 0; q < jobs.count; ++q) most = std::max(most, jobs.n[q]);
+  const unsigned nb = (unsigned)std::min<int64_t>(256, ceil_div(most, 2048));
+  k_max_rows<<<dim3(nb, (unsigned)jobs.count), kBlock, 0, s>>>(jobs, out);
+  SA_LAUNCH_CHECK();
 }
 
 // Sliced-ELL SpMV: one wavefront per 64-row slice, lane l on row 64 s + l.  The k-th entries
@@ -175,11 +238,29 @@ void spmv_plan(Csr &A, Arena &ar, hipStream_t s) {
 }
 
 template <class T, class Epi>
+static void launch_rows(const SpmvArgs<T> &a, const Epi &epi, hipStream_t s) {
+  auto go = [&](auto gc) {
+    constexpr int G = decltype(gc)::value;
+    k_spmv_rows<T, Epi, G><<<(unsigned)ceil_div((int64_t)a.n * G, kBlock), kBlock, 0, s>>>(
+        a.n, a.rp, a.col, a.val, a.x, epi);
+  };
+  switch (a.lanes) {
+    case 4: go(std::integral_constant<int, 4>{}); break;
+    case 8: go(std::integral_constant<int, 8>{}); break;
+    case 16: go(std::integral_constant<int, 16>{}); break;
+    case 32: go(std::integral_constant<int, 32>{}); break;
+    default: go(std::integral_constant<int, 64>{}); break;
+  }
+}
+
+template <class T, class Epi>
 static void launch_spmv(const SpmvArgs<T> &a, const Epi &epi, hipStream_t s) {
   if (a.n <= 0) return;
   if (a.sval)
     k_spmv_sell<T, Epi><<<(unsigned)ceil_div(a.nslice, kBlock / 64), kBlock, 0, s>>>(
         a.n, a.nslice, a.sptr, a.scol, a.sval, a.x, epi);
+  else if (a.lanes > 0 && !a.plain && !HasBlockMax<Epi>::value)
+    launch_rows(a, epi, s);
   else if (a.plain)
     k_spmv<T, Epi, false><<<(unsigned)a.nblk, kBlock, 0, s>>>(a.bstart, a.rp, a.col, a.val, a.x,
                                                               epi);
