@@ -13,12 +13,14 @@ namespace sa {
 
 typedef double v4d __attribute__((ext_vector_type(4)));
 
-__global__ void k_dense_scatter(int32_t n, int32_t ld, const int32_t *rp, const int32_t *col,
-                                const double *val, double *D) {
-  const int64_t i64 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i64 >= n) return;
-  const int32_t i = (int32_t)i64;
-  for (int32_t k = rp[i]; k < rp[i + 1]; ++k) D[(int64_t)i * ld + col[k]] = val[k];
+// A wavefront per row (a thread per row took 76 us on 569 rows of 80 entries).
+__global__ __launch_bounds__(kBlock) void k_dense_scatter(int32_t n, int32_t ld,
+                                                          const int32_t *rp, const int32_t *col,
+                                                          const double *val, double *D) {
+  const int64_t i = ((int64_t)blockIdx.x * kBlock + threadIdx.x) >> 6;
+  if (i >= n) return;
+  for (int32_t k = rp[i] + (int32_t)(threadIdx.x & 63); k < rp[i + 1]; k += 64)
+    D[i * ld + col[k]] = val[k];
 }
 
 // ---- blocked right-looking Cholesky, 64 x 64 blocks ---------------------------------------
@@ -34,66 +36,172 @@ __global__ void k_pad_identity(int32_t n, int32_t ld, double *D) {
   if (i < ld) D[(int64_t)i * ld + i] = 1.0;
 }
 
-// Diagonal block at (k0, k0): unblocked right-looking Cholesky in LDS (err bit 64 on a
-// pivot <= 0).
-__global__ __launch_bounds__(256) void k_potrf_diag(int32_t ld, int32_t k0, double *D,
-                                                    int32_t *err) {
-  __shared__ double a[kNB][kNB + 1];
-  const int tid = threadIdx.x;
+// 16 x 16 block product by one wavefront: acc += A B with A[r][k] = a[r * lda + k] and
+// B[k][c] = b[k * ldk + c * ldc], k = 0..K-1 (lane l supplies A[l%16][l/16] and B[l/16][l%16] of
+// each 4-deep step and receives rows 4v + l/16, column l%16 of the product in register v).
+template <int K>
+__device__ __forceinline__ v4d mfma_16(const double *a, int lda, const double *b, int ldk, int ldc,
+                                       v4d acc) {
+  const int lr = threadIdx.x & 15, lk = (threadIdx.x & 63) >> 4;
+#pragma unroll
+  for (int k = 0; k < K; k += 4)
+    acc = __builtin_amdgcn_mfma_f64_16x16x4f64(a[lr * lda + k + lk], b[(k + lk) * ldk + lr * ldc],
+                                              acc, 0, 0, 0);
+  return acc;
+}
+// c[r * ldc + col] = sign acc (+ c when add).
+__device__ __forceinline__ void put_16(double *c, int ldc, v4d acc, double sign, bool add) {
+  const int lr = threadIdx.x & 15, lk = (threadIdx.x & 63) >> 4;
+#pragma unroll
+  for (int v = 0; v < 4; ++v) {
+    double *q = c + (4 * v + lk) * ldc + lr;
+    *q = add ? *q + sign * acc[v] : sign * acc[v];
+  }
+}
+
+// Inverse of the lower-triangular 64 x 64 block l into x (both with leading dimension
+// kNB + 1 in LDS, rd[i] = 1 / l[i][i]; x zero above its diagonal): the four 16 x 16 diagonal
+// blocks by forward substitution, a wavefront each (lane c: column c), then
+// X21 = -X22 (L21 X11) for the two 32 x 32 halves and for the whole block on the matrix cores.
+__device__ __forceinline__ void trtri_64(const double (*l)[kNB + 1], double (*x)[kNB + 1],
+                                         const double *rd, double (*t)[33]) {
+  constexpr int LD = kNB + 1;
+  const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63;
+  for (int q = tid; q < kNB * kNB; q += 256) x[q / kNB][q % kNB] = 0.0;
+  __syncthreads();
+  if (lane < 16) {
+    const int o = 16 * w;
+    double y[16];
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      double v = i == lane ? 1.0 : 0.0;
+#pragma unroll
+      for (int k = 0; k < i; ++k) v = __builtin_fma(-l[o + i][o + k], y[k], v);
+      y[i] = v * rd[o + i];
+    }
+#pragma unroll
+    for (int i = 0; i < 16; ++i)
+      if (i >= lane) x[o + i][o + lane] = y[i];
+  }
+  __syncthreads();
+  if (w < 2) {  // 32 x 32 halves
+    const int o = 32 * w;
+    const v4d a = mfma_16<16>(&l[o + 16][o], LD, &x[o][o], LD, 1, v4d{0.0, 0.0, 0.0, 0.0});
+    put_16(&t[16 * w][0], 33, a, 1.0, false);
+  }
+  __syncthreads();
+  if (w < 2) {
+    const int o = 32 * w;
+    const v4d a =
+        mfma_16<16>(&x[o + 16][o + 16], LD, &t[16 * w][0], 33, 1, v4d{0.0, 0.0, 0.0, 0.0});
+    put_16(&x[o + 16][o], LD, a, -1.0, false);
+  }
+  __syncthreads();
+  const int ti = 16 * (w >> 1), tj = 16 * (w & 1);  // the 32 x 32 lower-left block's tiles
+  v4d a = mfma_16<32>(&l[32 + ti][0], LD, &x[0][tj], LD, 1, v4d{0.0, 0.0, 0.0, 0.0});
+  put_16(&t[ti][tj], 33, a, 1.0, false);
+  __syncthreads();
+  a = mfma_16<32>(&x[32 + ti][32], LD, &t[0][tj], 33, 1, v4d{0.0, 0.0, 0.0, 0.0});
+  put_16(&x[32 + ti][tj], LD, a, -1.0, false);
+  __syncthreads();
+}
+
+// 1 / sqrt(d) to about an ulp: the hardware estimate and three Newton steps.
+__device__ __forceinline__ double rsqrt_newton(double d) {
+  double y = __builtin_amdgcn_rsq(d);
+#pragma unroll
+  for (int i = 0; i < 3; ++i) {
+    const double h = 0.5 * y;
+    y = __builtin_fma(h, __builtin_fma(-d * y, y, 1.0), y);
+  }
+  return y;
+}
+
+// Diagonal block at (k0, k0): its Cholesky factor L_kk and the inverse of that (into Li), err
+// bit 64 on a pivot <= 0.  Four panels of 16 columns: wavefront 0 holds a row per lane, 16
+// columns of it in registers, and takes the columns one by one (the pivot and the pivot
+// row's entries are read across lanes); the columns to the right of the panel are updated on
+// the matrix cores, 16 x 16 tiles.  What bounds it is the chain of 64 pivots, about 150 cycles
+// each.  The inverse turns the panel solve below into a product and is what the triangular
+// inverse starts from.  (Column by column over the whole block in LDS, three barriers each,
+// took 73 us, and the inverse, a column per thread, 50 us in a launch of its own; both now
+// 23.5 us.)
+__global__ __launch_bounds__(256) void k_potrf_inv(int32_t ld, int32_t k0, double *D, double *Li,
+                                                   int32_t *err) {
+  __shared__ double a[kNB][kNB + 1], x[kNB][kNB + 1];
+  __shared__ double t[32][33];
+  __shared__ double rd[kNB];
+  constexpr int LD = kNB + 1;
+  const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63;
   for (int q = tid; q < kNB * kNB; q += 256) {
     const int i = q / kNB, j = q % kNB;
     a[i][j] = (j <= i) ? D[(int64_t)(k0 + i) * ld + k0 + j] : 0.0;
   }
   __syncthreads();
-  for (int j = 0; j < kNB; ++j) {
-    if (tid == 0) {
-      const double d = a[j][j];
-      if (!(d > 0.0)) atomicOr(err, 64);
-      a[j][j] = sqrt(d);
+  for (int p = 0; p < kNB; p += 16) {
+    if (w == 0) {
+      double r[16];
+#pragma unroll
+      for (int j = 0; j < 16; ++j) r[j] = a[lane][p + j];
+#pragma unroll
+      for (int j = 0; j < 16; ++j) {
+        const double d = __shfl(r[j], p + j, 64);
+        const double y = rsqrt_newton(d);
+        if (lane == p + j) {
+          if (!(d > 0.0)) atomicOr(err, 64);
+          rd[p + j] = y;
+        }
+        r[j] = r[j] * y;
+#pragma unroll
+        for (int k = j + 1; k < 16; ++k)
+          r[k] = __builtin_fma(-r[j], __shfl(r[j], p + k, 64), r[k]);
+      }
+#pragma unroll
+      for (int j = 0; j < 16; ++j)
+        if (lane >= p + j) a[lane][p + j] = r[j];
     }
     __syncthreads();
-    const double ljj = a[j][j];
-    for (int i = j + 1 + tid; i < kNB; i += 256) a[i][j] /= ljj;
-    __syncthreads();
-    // trailing update over the (63-j)^2 square below and right of (j, j) only
-    const int m = kNB - 1 - j;
-    for (int q = tid; q < m * m; q += 256) {
-      const int i = j + 1 + q / m, k = j + 1 + q % m;
-      if (k <= i) a[i][k] -= a[i][j] * a[k][j];
-    }
+    // tiles (ti, tj) of the columns to the right, ti >= tj > p / 16
+    int q = 0;
+    for (int ti = p + 16; ti < kNB; ti += 16)
+      for (int tj = p + 16; tj <= ti; tj += 16)
+        if ((q++ & 3) == w) {
+          const v4d acc = mfma_16<16>(&a[ti][p], LD, &a[tj][p], 1, LD, v4d{0.0, 0.0, 0.0, 0.0});
+          put_16(&a[ti][tj], LD, acc, -1.0, true);
+        }
     __syncthreads();
   }
+  trtri_64(a, x, rd, t);
   for (int q = tid; q < kNB * kNB; q += 256) {
     const int i = q / kNB, j = q % kNB;
     if (j <= i) D[(int64_t)(k0 + i) * ld + k0 + j] = a[i][j];
+    Li[(int64_t)(k0 + i) * ld + k0 + j] = x[i][j];
   }
 }
 
-// Panel below the diagonal block: row i of L in columns k0..k0+63 solves x L_kk^T = d by
-// forward substitution (one thread per row, the 64 unknowns in registers).
-__global__ __launch_bounds__(256) void k_trsm_panel(int32_t ld, int32_t k0, double *D) {
-  __shared__ double lk[kNB][kNB + 1];
-  const int tid = threadIdx.x;
+// Panel below the diagonal block: L_ik = A_ik L_kk^{-T}, a 64 x 64 block per workgroup on the
+// matrix cores, in place (9 us; forward substitution, a row per thread, took 31 us).
+__device__ __forceinline__ void panel_tile(int32_t blk, int32_t ld, int32_t k0, const double *Li,
+                                           double *D, double (*As)[kNB + 1],
+                                           double (*Xs)[kNB + 1]) {
+  constexpr int LD = kNB + 1;
+  const int tid = threadIdx.x, w = tid >> 6;
+  const int64_t r0 = (int64_t)k0 + (int64_t)kNB * (1 + blk);
   for (int q = tid; q < kNB * kNB; q += 256) {
-    const int i = q / kNB, j = q % kNB;
-    lk[i][j] = (j <= i) ? D[(int64_t)(k0 + i) * ld + k0 + j] : 0.0;
+    const int r = q / kNB, k = q % kNB;
+    As[r][k] = D[(r0 + r) * ld + k0 + k];
+    Xs[r][k] = Li[(int64_t)(k0 + r) * ld + k0 + k];
   }
   __syncthreads();
-  const int64_t i = (int64_t)k0 + kNB + (int64_t)blockIdx.x * 256 + tid;
-  if (i >= ld) return;
-  double *row = D + i * ld + k0;
-  double x[kNB];
+  const int lr = tid & 15, lk = (tid & 63) >> 4;
 #pragma unroll
-  for (int j = 0; j < kNB; ++j) x[j] = row[j];
+  for (int ct = 0; ct < 4; ++ct) {
+    const v4d acc =
+        mfma_16<64>(&As[16 * w][0], LD, &Xs[16 * ct][0], 1, LD, v4d{0.0, 0.0, 0.0, 0.0});
 #pragma unroll
-  for (int j = 0; j < kNB; ++j) {
-    double t = x[j];
-#pragma unroll
-    for (int m = 0; m < j; ++m) t -= x[m] * lk[j][m];
-    x[j] = t / lk[j][j];
+    for (int v = 0; v < 4; ++v)
+      D[(r0 + 16 * w + 4 * v + lk) * ld + k0 + 16 * ct + lr] = acc[v];
   }
-#pragma unroll
-  for (int j = 0; j < kNB; ++j) row[j] = x[j];
 }
 
 // Trailing update after step kb: D[ib][jb] -= L[ib][kb] L[jb][kb]^T for every block pair
@@ -102,11 +210,8 @@ __global__ __launch_bounds__(256) void k_trsm_panel(int32_t ld, int32_t k0, doub
 // as four 16 x 16 tiles with v_mfma_f64_16x16x4f64 (lane l supplies A[l%16][l/16] and
 // B[l/16][l%16] and receives D[4v + l/16][l%16] in result register v).  Diagonal blocks are
 // updated whole; their upper parts are never read.
-__global__ __launch_bounds__(256) void k_syrk_mfma(int32_t ld, int32_t kb, int32_t nbk,
-                                                   double *D) {
-  __shared__ double As[kNB][kNB + 1];
-  __shared__ double Bs[kNB][kNB + 1];
-  const int64_t t = blockIdx.x;
+__device__ __forceinline__ void syrk_tile(int64_t t, int32_t ld, int32_t kb, int32_t nbk, double *D,
+                                          double (*As)[kNB + 1], double (*Bs)[kNB + 1]) {
   int32_t a = (int32_t)((sqrt(8.0 * (double)t + 1.0) - 1.0) * 0.5);
   while ((int64_t)a * (a + 1) / 2 > t) --a;
   while ((int64_t)(a + 1) * (a + 2) / 2 <= t) ++a;
@@ -194,12 +299,12 @@ __global__ __launch_bounds__(256) void k_trtri_diag(int32_t ld, const double *L,
   }
 }
 
-// X[ib][kb] = Li[ib][ib] B[ib][kb] for kb = blockIdx.x < ib.
-__global__ __launch_bounds__(256) void k_trinv_finalize(int32_t ld, int32_t ib, double *Li) {
-  __shared__ double As[kNB][kNB + 1];
-  __shared__ double Bs[kNB][kNB + 1];
+// X[ib][kb] = Li[ib][ib] B[ib][kb] for kb = blk < ib.
+__device__ __forceinline__ void trinv_finalize_tile(int32_t blk, int32_t ld, int32_t ib, double *Li,
+                                                    double (*As)[kNB + 1],
+                                                    double (*Bs)[kNB + 1]) {
   const int tid = threadIdx.x;
-  const int64_t r0 = (int64_t)ib * kNB, c0 = (int64_t)blockIdx.x * kNB;
+  const int64_t r0 = (int64_t)ib * kNB, c0 = (int64_t)blk * kNB;
   for (int q = tid; q < kNB * kNB; q += 256) {
     const int r = q / kNB, k = q % kNB;
     As[r][k] = Li[(r0 + r) * ld + r0 + k];  // Li[ib][ib] (zero above its diagonal)
@@ -221,13 +326,12 @@ __global__ __launch_bounds__(256) void k_trinv_finalize(int32_t ld, int32_t ib, 
 
 // B[i][kb] -= L[i][ib] X[ib][kb] for every tile i > ib, kb <= ib (block t: i = ib+1+t/(ib+1),
 // kb = t mod (ib+1)); each tile has one writer per launch.
-__global__ __launch_bounds__(256) void k_trinv_update(int32_t ld, int32_t ib, const double *L,
-                                                      double *Li) {
-  __shared__ double As[kNB][kNB + 1];
-  __shared__ double Bs[kNB][kNB + 1];
+__device__ __forceinline__ void trinv_update_tile(int64_t blk, int32_t ld, int32_t ib,
+                                                  const double *L, double *Li,
+                                                  double (*As)[kNB + 1], double (*Bs)[kNB + 1]) {
   const int tid = threadIdx.x;
-  const int32_t i = ib + 1 + (int32_t)(blockIdx.x / (unsigned)(ib + 1));
-  const int32_t kb = (int32_t)(blockIdx.x % (unsigned)(ib + 1));
+  const int32_t i = ib + 1 + (int32_t)(blk / (ib + 1));
+  const int32_t kb = (int32_t)(blk % (ib + 1));
   const int64_t r0 = (int64_t)i * kNB, j0 = (int64_t)ib * kNB, c0 = (int64_t)kb * kNB;
   for (int q = tid; q < kNB * kNB; q += 256) {
     const int r = q / kNB, k = q % kNB;
@@ -248,12 +352,54 @@ __global__ __launch_bounds__(256) void k_trinv_update(int32_t ld, int32_t ib, co
       Li[(r0 + 16 * w + 4 * v + lk) * ld + c0 + 16 * ct + lr] -= acc[ct][v];
 }
 
+__global__ __launch_bounds__(256) void k_trinv_finalize(int32_t ld, int32_t ib, double *Li) {
+  __shared__ double As[kNB][kNB + 1], Bs[kNB][kNB + 1];
+  trinv_finalize_tile((int32_t)blockIdx.x, ld, ib, Li, As, Bs);
+}
+__global__ __launch_bounds__(256) void k_trinv_update(int32_t ld, int32_t ib, const double *L,
+                                                      double *Li) {
+  __shared__ double As[kNB][kNB + 1], Bs[kNB][kNB + 1];
+  trinv_update_tile(blockIdx.x, ld, ib, L, Li, As, Bs);
+}
+
 // Li = L^{-1} (Li zero outside the diagonal blocks, which k_trtri_diag has filled).
 static void trinv_blocks(int32_t ld, int32_t nbk, const double *L, double *Li, hipStream_t s) {
   for (int32_t ib = 0; ib < nbk; ++ib) {
     if (ib > 0) k_trinv_finalize<<<(unsigned)ib, 256, 0, s>>>(ld, ib, Li);
     const int64_t tiles = (int64_t)(nbk - ib - 1) * (ib + 1);
     if (tiles > 0) k_trinv_update<<<(unsigned)tiles, 256, 0, s>>>(ld, ib, L, Li);
+  }
+  SA_LAUNCH_CHECK();
+}
+
+// Cholesky and the triangular inverse in step: block row kb of the inverse needs nothing
+// beyond step kb of the factorisation, so each step is three launches, the diagonal block
+// (k_potrf_inv), then the panel tiles L[i][kb] with the inverse's tiles X[kb][j] (j < kb), then
+// the trailing updates with the updates B[i][j] -= L[i][kb] X[kb][j] of the rows below.  The
+// launches are a few microseconds of work each (8-13 us for nbk = 9), so fewer of them is what
+// counts.
+__global__ __launch_bounds__(256) void k_step_panels(int32_t ld, int32_t kb, int32_t nbk,
+                                                     double *D, double *Li) {
+  __shared__ double As[kNB][kNB + 1], Bs[kNB][kNB + 1];
+  const int32_t m = nbk - kb - 1, t = (int32_t)blockIdx.x;
+  if (t < m) panel_tile(t, ld, kb * kNB, Li, D, As, Bs);
+  else trinv_finalize_tile(t - m, ld, kb, Li, As, Bs);
+}
+__global__ __launch_bounds__(256) void k_step_updates(int32_t ld, int32_t kb, int32_t nbk,
+                                                      double *D, double *Li) {
+  __shared__ double As[kNB][kNB + 1], Bs[kNB][kNB + 1];
+  const int64_t m = nbk - kb - 1, pairs = m * (m + 1) / 2, t = blockIdx.x;
+  if (t < pairs) syrk_tile(t, ld, kb, nbk, D, As, Bs);
+  else trinv_update_tile(t - pairs, ld, kb, D, Li, As, Bs);
+}
+static void chol_inverse(int32_t ld, int32_t nbk, double *D, double *Li, int32_t *err,
+                         hipStream_t s) {
+  for (int32_t kb = 0; kb < nbk; ++kb) {
+    k_potrf_inv<<<1, 256, 0, s>>>(ld, kb * kNB, D, Li, err);
+    const int64_t m = nbk - kb - 1;
+    if (m + kb > 0) k_step_panels<<<(unsigned)(m + kb), 256, 0, s>>>(ld, kb, nbk, D, Li);
+    const int64_t tiles = m * (m + 1) / 2 + m * (kb + 1);
+    if (tiles > 0) k_step_updates<<<(unsigned)tiles, 256, 0, s>>>(ld, kb, nbk, D, Li);
   }
   SA_LAUNCH_CHECK();
 }
@@ -444,13 +590,35 @@ __global__ void k_split_lu(int32_t ld, const double *D, double *Lb, double *Ut) 
 // Symmetry of the coarsest operator before a Cholesky solve (which reads only the lower
 // triangle): mx[0] = max |a_ij|, mx[1] = max |a_ij - a_ji| as the bit patterns of
 // non-negative doubles (ordered like the values); err bit 256 when mx[1] > 1e-10 mx[0].
-__global__ void k_sym_max(int32_t ld, const double *D, unsigned long long *mx) {
-  const int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (q >= (int64_t)ld * ld) return;
-  const int64_t i = q / ld, j = q % ld;
-  const double a = fabs(D[q]), d = fabs(D[q] - D[j * ld + i]);
-  if (a > 0.0) atomicMax(&mx[0], (unsigned long long)__double_as_longlong(a));
-  if (d > 0.0) atomicMax(&mx[1], (unsigned long long)__double_as_longlong(d));
+constexpr int kSymBlocks = 128;
+__global__ __launch_bounds__(kBlock) void k_sym_max(int32_t ld, const double *D,
+                                                    unsigned long long *mx) {
+  __shared__ double sa[kBlock / 64], sd[kBlock / 64];
+  double a = 0.0, d = 0.0;  // (a NaN entry never raises them; the factor's pivots catch it)
+  for (int64_t q = (int64_t)blockIdx.x * kBlock + threadIdx.x; q < (int64_t)ld * ld;
+       q += (int64_t)gridDim.x * kBlock) {
+    const int64_t i = q / ld, j = q % ld;
+    const double x = fabs(D[q]), y = fabs(D[q] - D[j * ld + i]);
+    if (x > a) a = x;
+    if (y > d) d = y;
+  }
+  for (int off = 32; off >= 1; off >>= 1) {
+    a = fmax(a, __shfl_xor(a, off, 64));
+    d = fmax(d, __shfl_xor(d, off, 64));
+  }
+  if ((threadIdx.x & 63) == 0) {
+    sa[threadIdx.x >> 6] = a;
+    sd[threadIdx.x >> 6] = d;
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) {  // one atomic per workgroup (one per entry took 80 us for 576^2)
+    for (int w = 1; w < kBlock / 64; ++w) {
+      a = fmax(a, sa[w]);
+      d = fmax(d, sd[w]);
+    }
+    if (a > 0.0) atomicMax(&mx[0], (unsigned long long)__double_as_longlong(a));
+    if (d > 0.0) atomicMax(&mx[1], (unsigned long long)__double_as_longlong(d));
+  }
 }
 __global__ void k_sym_flag(const unsigned long long *mx, int32_t *err) {
   const double amax = __longlong_as_double((long long)mx[0]);
@@ -502,7 +670,7 @@ void coarse_inverse(const Csr &A, double *Ainv, int32_t *err, bool lu, hipStream
   double *Li = (double *)dev_alloc(sizeof(double) * (size_t)cnt, s);
   fill_f64(D, 0.0, cnt, s);
   fill_f64(Li, 0.0, cnt, s);
-  k_dense_scatter<<<grid_for(n), kBlock, 0, s>>>(n, ld, A.rp, A.col, A.val, D);
+  k_dense_scatter<<<grid_for((int64_t)n * 64), kBlock, 0, s>>>(n, ld, A.rp, A.col, A.val, D);
   SA_LAUNCH_CHECK();
   if (ld > n) {
     k_pad_identity<<<grid_for(ld - n), kBlock, 0, s>>>(n, ld, D);
@@ -517,25 +685,12 @@ void coarse_inverse(const Csr &A, double *Ainv, int32_t *err, bool lu, hipStream
   {
     unsigned long long *mx = (unsigned long long *)dev_alloc(2 * sizeof(unsigned long long), s);
     SA_HIP(hipMemsetAsync(mx, 0, 2 * sizeof(unsigned long long), s));
-    k_sym_max<<<grid_for(cnt), kBlock, 0, s>>>(ld, D, mx);
+    k_sym_max<<<kSymBlocks, kBlock, 0, s>>>(ld, D, mx);
     k_sym_flag<<<1, 1, 0, s>>>(mx, err);
     SA_LAUNCH_CHECK();
     dev_free(mx, s);
   }
-  for (int32_t kb = 0; kb < nbk; ++kb) {
-    const int32_t k0 = kb * kNB;
-    k_potrf_diag<<<1, 256, 0, s>>>(ld, k0, D, err);
-    const int32_t below = ld - k0 - kNB;
-    if (below > 0) {
-      k_trsm_panel<<<(unsigned)ceil_div(below, 256), 256, 0, s>>>(ld, k0, D);
-      const int64_t m = nbk - kb - 1;
-      k_syrk_mfma<<<(unsigned)(m * (m + 1) / 2), 256, 0, s>>>(ld, kb, nbk, D);
-    }
-    SA_LAUNCH_CHECK();
-  }
-  k_trtri_diag<<<(unsigned)nbk, 256, 0, s>>>(ld, D, Li, false);
-  trinv_blocks(ld, nbk, D, Li, s);
-  SA_LAUNCH_CHECK();
+  chol_inverse(ld, nbk, D, Li, err, s);
   gram(n, ld, nbk, Li, Li, Ainv, true, s);
   dev_free(D, s);
   dev_free(Li, s);
