@@ -77,6 +77,14 @@ static void stream_after(hipStream_t waiter, hipStream_t first) {
   SA_HIP(hipEventDestroy(ev));
 }
 
+// Rows long enough to leave the setup's thread-per-row kernels serial: a wavefront per row
+// instead.  27-point rows stay below (100^3 27-point level 0: lumping 360 us, strength 117,
+// strength graph 152 and P 140; with a wavefront per row 1,069, 324 and 216, and P by a sparse
+// product, 400).
+static bool long_rows(int32_t maxrow, int64_t nnz, int32_t n) {
+  return maxrow > 64 || nnz > 48 * (int64_t)n;
+}
+
 static double safeguard_mult(double sigma) {
   return (sigma == 1.0 / 3.0) ? 2.0 : 4.0 / (3.0 * (1.0 - sigma));
 }
@@ -235,7 +243,7 @@ static bool build_level_system(sa_hierarchy *h, int l) {
   node_graph(L.As, bs, ar, L.Gn, s);
   L.nmask = ar.alloc<uint8_t>(L.Gn.nnz > 0 ? L.Gn.nnz : 1);
   int32_t *scount = tmp.alloc<int32_t>(m + 1);
-  const bool gwave = max_row_length(m, L.Gn.rp, s) > 64 || L.Gn.nnz > 24 * (int64_t)m;
+  const bool gwave = long_rows(max_row_length(m, L.Gn.rp, s), L.Gn.nnz, m);
   if (h->dim > 0) {
     double *w = tmp.alloc<double>(L.Gn.nnz > 0 ? L.Gn.nnz : 1);
     double *Ld = tmp.alloc<double>(m);
@@ -247,7 +255,7 @@ static bool build_level_system(sa_hierarchy *h, int l) {
     block_strength(L.As, bs, L.Gn, o.theta, L.nmask, scount, s);
   }
   L.As.maxrow = L.A.maxrow = max_row_length(n, L.As.rp, s);  // A and As share the pattern
-  L.wave_rows = L.As.maxrow > 64 || L.As.nnz > 24 * (int64_t)n;
+  L.wave_rows = long_rows(L.As.maxrow, L.As.nnz, n);
   L.mask = ar.alloc<uint8_t>(L.As.nnz);
   dof_mask(L.As, bs, L.Gn, L.nmask, L.mask, s);
   int32_t *grp = nullptr, *gcol = nullptr;
@@ -287,9 +295,8 @@ static bool build_level(sa_hierarchy *h, int l) {
   } else {
     find_diag(n, L.As.rp, L.As.col, L.As.val, dval, s);
   }
-  // rows long enough to leave thread-per-row kernels serial: one wavefront per row instead
   L.As.maxrow = L.A.maxrow = max_row_length(n, L.As.rp, s);  // A and As share the pattern
-  L.wave_rows = L.As.maxrow > 64 || L.As.nnz > 24 * (int64_t)n;
+  L.wave_rows = long_rows(L.As.maxrow, L.As.nnz, n);
   L.mask = ar.alloc<uint8_t>(L.As.nnz);
   int32_t *scount = tmp.alloc<int32_t>(n + 1);
   strength(n, L.As.rp, L.As.col, sval, dval, o.theta * o.theta, L.mask, scount, L.wave_rows,

@@ -341,23 +341,49 @@ void aggregate_centroids(int32_t n, const int32_t *agg, int32_t nc, const double
 }
 
 // ---- aggregation graph G = S u S^T ------------------------------------------------------
-__global__ void k_fill_strong(int32_t n, const int32_t *rp, const int32_t *col,
-                              const uint8_t *mask, const int32_t *srp, int32_t *scol,
-                              int32_t *tcnt) {
-  SA_ROW_KERNEL_BEGIN(n)
-  int32_t w = srp[i];
-  for (int32_t k = rp[i]; k < rp[i + 1]; ++k) {
-    const uint8_t m = mask[k];
-    if (m == 1 || m == 2) {
-      scol[w++] = col[k];
-      atomicAdd(&tcnt[col[k]], 1);
+// The strong entries of 256 rows are one contiguous run of scol, in entry order: the block
+// takes its rows' entries 256 at a time and packs the strong ones behind those before.  Each
+// also takes its place in its column's list (trank), so the transpose needs no second count.
+__global__ __launch_bounds__(kBlock) void k_fill_strong(int32_t n, const int32_t *__restrict__ rp,
+                                                        const int32_t *__restrict__ col,
+                                                        const uint8_t *__restrict__ mask,
+                                                        const int32_t *__restrict__ srp,
+                                                        int32_t *__restrict__ scol,
+                                                        int32_t *tcnt,
+                                                        int32_t *__restrict__ trank) {
+  __shared__ int32_t s_n[2][kBlock / 64];
+  const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
+  const int64_t r0 = (int64_t)blockIdx.x * kBlock;
+  const int64_t r1 = min<int64_t>(n, r0 + kBlock);
+  const int32_t e0 = rp[r0], e1 = rp[r1];
+  int32_t w = srp[r0];
+  int h = 0;
+  for (int32_t c = e0; c < e1; c += kBlock, h ^= 1) {
+    const int32_t e = c + t;
+    const uint8_t m = e < e1 ? mask[e] : (uint8_t)0;
+    const bool st = m == 1 || m == 2;
+    const uint64_t bm = __ballot(st);
+    if (lane == 0) s_n[h][wv] = __popcll(bm);
+    __syncthreads();  // (the other half's counts are read before this round's barrier)
+    int32_t before = 0, all = 0;
+#pragma unroll
+    for (int q = 0; q < kBlock / 64; ++q) {
+      before += q < wv ? s_n[h][q] : 0;
+      all += s_n[h][q];
     }
+    if (st) {
+      const int32_t pos = w + before + __popcll(bm & ((1ull << lane) - 1ull));
+      const int32_t j = col[e];
+      scol[pos] = j;
+      trank[pos] = atomicAdd(&tcnt[j], 1);
+    }
+    w += all;
   }
 }
 __global__ __launch_bounds__(kW) void k_fill_strong_w(int32_t n, const int32_t *rp,
                                                       const int32_t *col, const uint8_t *mask,
                                                       const int32_t *srp, int32_t *scol,
-                                                      int32_t *tcnt) {
+                                                      int32_t *tcnt, int32_t *trank) {
   SA_WAVE_ROW_BEGIN(n)
   int32_t w = srp[i];
   for (int32_t c = rp[i]; c < rp[i + 1]; c += kW) {
@@ -371,18 +397,42 @@ __global__ __launch_bounds__(kW) void k_fill_strong_w(int32_t n, const int32_t *
     }
     const unsigned long long bm = __ballot(st);
     if (st) {
-      scol[w + __popcll(bm & ((1ull << lane) - 1ull))] = j;
-      atomicAdd(&tcnt[j], 1);
+      const int32_t pos = w + __popcll(bm & ((1ull << lane) - 1ull));
+      scol[pos] = j;
+      trank[pos] = atomicAdd(&tcnt[j], 1);
     }
     w += __popcll(bm);
   }
 }
-__global__ void k_scatter_t(int32_t n, const int32_t *srp, const int32_t *scol, int32_t *tpos,
-                            int32_t *tcol) {
-  SA_ROW_KERNEL_BEGIN(n)
-  for (int32_t k = srp[i]; k < srp[i + 1]; ++k) {
-    int32_t p = atomicAdd(&tpos[scol[k]], 1);
-    tcol[p] = i;
+// Entry-parallel (256 rows per block, an entry's row by binary search in LDS): every entry's
+// row goes to its place in its column's list, rp[column] + rank.  VAL: the value too.
+template <bool VAL>
+__global__ __launch_bounds__(kBlock) void k_scatter_ranked(int32_t n,
+                                                           const int32_t *__restrict__ rp,
+                                                           const int32_t *__restrict__ col,
+                                                           const double *__restrict__ val,
+                                                           const int32_t *__restrict__ rank,
+                                                           const int32_t *__restrict__ trp,
+                                                           int32_t *__restrict__ tcol,
+                                                           double *__restrict__ tval) {
+  __shared__ int32_t s_rp[kBlock + 1];
+  const int t = threadIdx.x;
+  const int64_t r0 = (int64_t)blockIdx.x * kBlock;
+  const int32_t nr = (int32_t)min<int64_t>(kBlock, (int64_t)n - r0);
+  if (t < nr) s_rp[t] = rp[r0 + t];
+  if (t == 0) s_rp[nr] = rp[r0 + nr];  // nr can be kBlock: no thread t == nr
+  __syncthreads();
+  const int32_t e0 = s_rp[0], e1 = s_rp[nr];
+  for (int32_t e = e0 + t; e < e1; e += kBlock) {
+    int32_t lo = 0, hi = nr - 1;  // the entry's row: the last r with s_rp[r] <= e
+    while (lo < hi) {
+      const int32_t mid = (lo + hi + 1) >> 1;
+      if (s_rp[mid] <= e) lo = mid;
+      else hi = mid - 1;
+    }
+    const int32_t p = trp[col[e]] + rank[e];
+    tcol[p] = (int32_t)r0 + lo;
+    if (VAL) tval[p] = val[e];
   }
 }
 __global__ void k_union(int32_t n, const int32_t *arp, const int32_t *acol, const int32_t *brp,
@@ -416,15 +466,15 @@ int64_t strength_graph(int32_t n, const int32_t *rp, const int32_t *col, const u
   int32_t *scol = tmp.alloc<int32_t>(nnzS);
   int32_t *tcnt = tmp.alloc<int32_t>(n + 1);
   fill_i32(tcnt, 0, n + 1, s);
-  if (wave) k_fill_strong_w<<<(unsigned)n, kW, 0, s>>>(n, rp, col, mask, srp, scol, tcnt);
-  else k_fill_strong<<<grid_for(n), kBlock, 0, s>>>(n, rp, col, mask, srp, scol, tcnt);
+  int32_t *trank = tmp.alloc<int32_t>(nnzS);
+  if (wave) k_fill_strong_w<<<(unsigned)n, kW, 0, s>>>(n, rp, col, mask, srp, scol, tcnt, trank);
+  else k_fill_strong<<<grid_for(n), kBlock, 0, s>>>(n, rp, col, mask, srp, scol, tcnt, trank);
   SA_LAUNCH_CHECK();
   int32_t *trp = tmp.alloc<int32_t>(n + 1);
   exclusive_scan_i32(tcnt, trp, n, s);
-  int32_t *tpos = tmp.alloc<int32_t>(n + 1);
-  SA_HIP(hipMemcpyAsync(tpos, trp, sizeof(int32_t) * (n + 1), hipMemcpyDeviceToDevice, s));
   int32_t *tcol = tmp.alloc<int32_t>(nnzS);
-  k_scatter_t<<<grid_for(n), kBlock, 0, s>>>(n, srp, scol, tpos, tcol);
+  k_scatter_ranked<false><<<grid_for(n), kBlock, 0, s>>>(n, srp, scol, nullptr, trank, trp, tcol,
+                                                         nullptr);
   SA_LAUNCH_CHECK();
   sort_rows(n, trp, tcol, nullptr, s);
   int32_t *gcnt = tmp.alloc<int32_t>(n + 1);
@@ -1845,8 +1895,12 @@ int64_t lump(int32_t n, int64_t nnz_a, const int32_t *rp, const int32_t *col, co
     k_lump_fill<128><<<(unsigned)ceil_div(n, 128), kBlock, 0, s>>>(
         n, rp, col, val, mask, abar.rp, abar.col, abar.val, offlmp, tau, one_norm, mult, invD,
         err);
-  else
+  else if (nnz_a <= 30 * (int64_t)n)
     k_lump_fill<64><<<(unsigned)ceil_div(n, 64), kBlock, 0, s>>>(
+        n, rp, col, val, mask, abar.rp, abar.col, abar.val, offlmp, tau, one_norm, mult, invD,
+        err);
+  else
+    k_lump_fill<32><<<(unsigned)ceil_div(n, 32), kBlock, 0, s>>>(
         n, rp, col, val, mask, abar.rp, abar.col, abar.val, offlmp, tau, one_norm, mult, invD,
         err);
   SA_LAUNCH_CHECK();
@@ -2221,11 +2275,15 @@ void scale_sym(int32_t n, const int32_t *rp, const int32_t *col, const double *v
 
 
 // ---- per-row sort by column --------------------------------------------------------------
-// Rows of up to kSortShort entries: a register sorting network in one thread (the keys of a
-// row are distinct in every caller).  Longer rows: one block per
-// row, bitonic sort in LDS (kSortLds entries) or, beyond that, in a global scratch region
-// sized for the row.  Keys within a row are distinct, so the order is unique.
+// Keys within a row are distinct, so the order is unique.  Up to kSortShort entries: 8 lanes
+// per row hold 4 keys each and count, for each of theirs, the row's smaller keys (its place).
+// Up to kSortMid: a wavefront per row does the same with 4 keys per lane read against the
+// row's keys in LDS.  Longer rows: one block per row, bitonic sort in LDS (kSortLds entries)
+// or, beyond that, in a global scratch region sized for the row.  (A sorting network in one
+// thread's registers for the short rows: 131 us for the 600K rows of the 128^3 cube's first
+// R; a block's bitonic sort for the middle ones: 690 us for 54K rows of about 40, now 57.)
 constexpr int32_t kSortShort = 32;
+constexpr int32_t kSortMid = 256;
 constexpr int32_t kSortLds = 4096;
 
 __device__ inline void wave_append(bool pred, int32_t *counter, int32_t *list, int32_t value) {
@@ -2239,58 +2297,77 @@ __device__ inline void wave_append(bool pred, int32_t *counter, int32_t *list, i
   if (pred) list[base + __popcll(m & ((1ull << lane) - 1ull))] = value;
 }
 
-// Sorts L <= N (key, value) pairs with distinct keys in registers: a bitonic network of width
-// N over the pairs padded with INT_MAX keys, all indices static so nothing leaves registers.
-template <int N>
-__device__ __forceinline__ void sort_regs(int32_t *c, double *v, int32_t L) {
-  int32_t kk[N];
-  double vv[N];
+// nlist[0], nlist[1]: the rows listed for the wavefront and the block sort (mid, longrows).
+__global__ __launch_bounds__(kBlock) void k_sort_short(int32_t n, const int32_t *__restrict__ rp,
+                                                       int32_t *c, double *v, int32_t *nlist,
+                                                       int32_t *mid, int32_t *longrows) {
+  const int64_t i64 = ((int64_t)blockIdx.x * kBlock + threadIdx.x) >> 3;
+  const int j = threadIdx.x & 7;
+  const bool live = i64 < n;
+  const int32_t i = live ? (int32_t)i64 : 0;
+  const int32_t b = live ? rp[i] : 0;
+  const int32_t L = live ? rp[i + 1] - b : 0;
+  wave_append(j == 0 && L > kSortShort && L <= kSortMid, nlist, mid, i);
+  wave_append(j == 0 && L > kSortMid, nlist + 1, longrows, i);
+  if (L <= 1 || L > kSortShort) return;  // uniform over the row's lanes
+  int32_t k[4], place[4] = {0, 0, 0, 0};
+  double x[4];
 #pragma unroll
-  for (int q = 0; q < N; ++q) {
-    kk[q] = q < L ? c[q] : INT_MAX;
-    vv[q] = (v && q < L) ? v[q] : 0.0;
+  for (int q = 0; q < 4; ++q) {
+    const bool in = j + 8 * q < L;
+    k[q] = in ? c[b + j + 8 * q] : INT_MAX;
+    x[q] = v && in ? v[b + j + 8 * q] : 0.0;
   }
 #pragma unroll
-  for (int k = 2; k <= N; k <<= 1)
+  for (int p = 0; p < 4; ++p) {
+    if (8 * p < L) {
 #pragma unroll
-    for (int j = k >> 1; j > 0; j >>= 1)
+      for (int o = 0; o < 8; ++o) {
+        const int32_t other = __shfl(k[p], o, 8);
 #pragma unroll
-      for (int q = 0; q < N; ++q) {
-        const int l = q ^ j;
-        if (l > q) {
-          const bool up = (q & k) == 0;
-          if ((kk[q] > kk[l]) == up) {
-            const int32_t tk = kk[q];
-            kk[q] = kk[l];
-            kk[l] = tk;
-            const double tv = vv[q];
-            vv[q] = vv[l];
-            vv[l] = tv;
-          }
-        }
+        for (int q = 0; q < 4; ++q) place[q] += other < k[q] ? 1 : 0;
       }
+    }
+  }
 #pragma unroll
-  for (int q = 0; q < N; ++q)
-    if (q < L) {
-      c[q] = kk[q];
-      if (v) v[q] = vv[q];
+  for (int q = 0; q < 4; ++q)
+    if (j + 8 * q < L) {
+      c[b + place[q]] = k[q];
+      if (v) v[b + place[q]] = x[q];
     }
 }
 
-__global__ void k_sort_short(int32_t n, const int32_t *rp, int32_t *c, double *v,
-                             int32_t *nlong, int32_t *longrows) {
-  const int64_t i64 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const bool live = i64 < n;
-  const int32_t i = live ? (int32_t)i64 : 0;
-  const int32_t b = live ? rp[i] : 0, e = live ? rp[i + 1] : 0;
-  const bool is_long = live && (e - b > kSortShort);
-  wave_append(is_long, nlong, longrows, i);
-  if (!live || is_long) return;
-  const int32_t L = e - b;
-  if (L <= 1) return;
-  if (L <= 8) sort_regs<8>(c + b, v ? v + b : nullptr, L);
-  else if (L <= 16) sort_regs<16>(c + b, v ? v + b : nullptr, L);
-  else sort_regs<32>(c + b, v ? v + b : nullptr, L);
+__global__ __launch_bounds__(kBlock) void k_sort_mid(const int32_t *rows, int32_t nrows,
+                                                     const int32_t *__restrict__ rp, int32_t *c,
+                                                     double *v) {
+  __shared__ __attribute__((aligned(16))) int32_t s_k[kBlock / 64][kSortMid];
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  const int64_t slot = (int64_t)blockIdx.x * (kBlock / 64) + wv;
+  const int32_t i = slot < nrows ? rows[slot] : -1;
+  const int32_t b = i >= 0 ? rp[i] : 0;
+  const int32_t L = i >= 0 ? rp[i + 1] - b : 0;
+  int32_t k[4], place[4] = {0, 0, 0, 0};
+  double x[4];
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const bool in = lane + 64 * q < L;
+    k[q] = in ? c[b + lane + 64 * q] : INT_MAX;
+    x[q] = v && in ? v[b + lane + 64 * q] : 0.0;
+    s_k[wv][lane + 64 * q] = k[q];
+  }
+  __syncthreads();
+  for (int32_t o = 0; o < L; o += 4) {  // wave-uniform; past the row the keys are INT_MAX
+    const int4 t = *(const int4 *)&s_k[wv][o];
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+      place[q] += (t.x < k[q]) + (t.y < k[q]) + (t.z < k[q]) + (t.w < k[q]);
+  }
+#pragma unroll
+  for (int q = 0; q < 4; ++q)
+    if (lane + 64 * q < L) {
+      c[b + place[q]] = k[q];
+      if (v) v[b + place[q]] = x[q];
+    }
 }
 
 __device__ inline void bitonic_kv_any(int32_t *k, double *v, int32_t L) {
@@ -2366,12 +2443,18 @@ void sort_rows(int32_t n, const int32_t *rp, int32_t *col, double *val, hipStrea
   if (n <= 0) return;
   Arena tmp;
   tmp.stream = s;
-  int32_t *nlong = tmp.alloc<int32_t>(1);
-  int32_t *rows = tmp.alloc<int32_t>(n);
-  fill_i32(nlong, 0, 1, s);
-  k_sort_short<<<grid_for(n), kBlock, 0, s>>>(n, rp, col, val, nlong, rows);
+  int32_t *nlist = tmp.alloc<int32_t>(2);
+  int32_t *mid = tmp.alloc<int32_t>(n), *rows = tmp.alloc<int32_t>(n);
+  fill_i32(nlist, 0, 2, s);
+  k_sort_short<<<grid_for((int64_t)n * 8), kBlock, 0, s>>>(n, rp, col, val, nlist, mid, rows);
   SA_LAUNCH_CHECK();
-  const int32_t nl = read1(nlong, s);
+  int32_t hn[2];
+  readback(hn, nlist, sizeof(hn), s);
+  if (hn[0] > 0) {
+    k_sort_mid<<<(unsigned)ceil_div(hn[0], kBlock / 64), kBlock, 0, s>>>(mid, hn[0], rp, col, val);
+    SA_LAUNCH_CHECK();
+  }
+  const int32_t nl = hn[1];
   if (nl == 0) return;
   int64_t *caps = tmp.alloc<int64_t>(nl + 1);
   int64_t *goff = tmp.alloc<int64_t>(nl + 1);
@@ -2386,25 +2469,22 @@ void sort_rows(int32_t n, const int32_t *rp, int32_t *col, double *val, hipStrea
 }
 
 // ---- transpose with values ---------------------------------------------------------------
-__global__ void k_count_cols(int64_t nnz, const int32_t *col, int32_t *cnt) {
+// Every entry takes its place in its column's list as it is counted (rank), so the scatter
+// needs no atomics of its own.  (3.4M entries: count 114 us, scatter 80; a thread per row of
+// P scattering with an atomic per entry 178 us, and 600 us for 4.8M entries in 26-entry rows.)
+__global__ void k_count_cols(int64_t nnz, const int32_t *col, int32_t *cnt, int32_t *rank) {
   const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (e < nnz) atomicAdd(&cnt[col[e]], 1);
-}
-__global__ void k_scatter_tv(int32_t n, const int32_t *rp, const int32_t *col, const double *val,
-                             int32_t *pos, int32_t *tcol, double *tval) {
-  SA_ROW_KERNEL_BEGIN(n)
-  for (int32_t k = rp[i]; k < rp[i + 1]; ++k) {
-    const int32_t p = atomicAdd(&pos[col[k]], 1);
-    tcol[p] = i;
-    tval[p] = val[k];
-  }
+  if (e < nnz) rank[e] = atomicAdd(&cnt[col[e]], 1);
 }
 void transpose(const Csr &P, Arena &ar, Csr &R, hipStream_t s) {
   const int32_t m = P.ncols;
-  int32_t *cnt = (int32_t *)dev_alloc(sizeof(int32_t) * (m + 1), s);
+  Arena tmp;
+  tmp.stream = s;
+  int32_t *cnt = tmp.alloc<int32_t>(m + 1);
+  int32_t *rank = tmp.alloc<int32_t>(P.nnz);
   fill_i32(cnt, 0, m + 1, s);
   if (P.nnz > 0) {
-    k_count_cols<<<grid_for(P.nnz), kBlock, 0, s>>>(P.nnz, P.col, cnt);
+    k_count_cols<<<grid_for(P.nnz), kBlock, 0, s>>>(P.nnz, P.col, cnt, rank);
     SA_LAUNCH_CHECK();
   }
   R.n = m;
@@ -2412,15 +2492,14 @@ void transpose(const Csr &P, Arena &ar, Csr &R, hipStream_t s) {
   R.nnz = P.nnz;
   R.rp = ar.alloc<int32_t>(m + 1);
   exclusive_scan_i32(cnt, R.rp, m, s);
-  SA_HIP(hipMemcpyAsync(cnt, R.rp, sizeof(int32_t) * (m + 1), hipMemcpyDeviceToDevice, s));
   R.col = ar.alloc<int32_t>(P.nnz);
   R.val = ar.alloc<double>(P.nnz);
   if (P.n > 0) {
-    k_scatter_tv<<<grid_for(P.n), kBlock, 0, s>>>(P.n, P.rp, P.col, P.val, cnt, R.col, R.val);
+    k_scatter_ranked<true><<<grid_for(P.n), kBlock, 0, s>>>(P.n, P.rp, P.col, P.val, rank, R.rp,
+                                                            R.col, R.val);
     SA_LAUNCH_CHECK();
   }
   sort_rows(m, R.rp, R.col, R.val, s);
-  dev_free(cnt, s);
 }
 
 __global__ void k_inv_diag(int32_t n, const double *d, double *inv, int32_t *err) {

@@ -96,29 +96,35 @@ __global__ __launch_bounds__(kBlock) void k_count_products(int32_t m, const int3
   }
 }
 
-// One wavefront per row of X (long rows): xpref by a wavefront prefix sum.
-__global__ __launch_bounds__(64) void k_count_products_w(int32_t m, const int32_t *xrp,
-                                                         const int32_t *xcol,
-                                                         const int32_t *yrp, int64_t *cnt,
-                                                         int32_t *xpref) {
-  const int32_t i = blockIdx.x;
-  if (i >= m) return;
-  const int lane = threadIdx.x;
+// G lanes per row of X (longer rows): xpref by a prefix sum over the lanes.
+template <int G>
+__global__ __launch_bounds__(kBlock) void k_count_products_w(int32_t m,
+                                                             const int32_t *__restrict__ xrp,
+                                                             const int32_t *__restrict__ xcol,
+                                                             const int32_t *__restrict__ yrp,
+                                                             int64_t *__restrict__ cnt,
+                                                             int32_t *__restrict__ xpref) {
+  const int64_t i64 = ((int64_t)blockIdx.x * kBlock + threadIdx.x) / G;
+  if (i64 >= m) return;  // uniform over the row's lanes
+  const int32_t i = (int32_t)i64;
+  const int lane = threadIdx.x % G;
+  const int32_t end = xrp[i + 1];
   int64_t base = 0;
-  for (int32_t c = xrp[i]; c < xrp[i + 1]; c += 64) {
+  for (int32_t c = xrp[i]; c < end; c += G) {
     const int32_t e = c + lane;
     int32_t len = 0;
-    if (e < xrp[i + 1]) {
+    if (e < end) {
       const int32_t k = xcol[e];
       len = yrp[k + 1] - yrp[k];
     }
     int32_t incl = len;
-    for (int off = 1; off < 64; off <<= 1) {
-      const int32_t v = __shfl_up(incl, off, 64);
+#pragma unroll
+    for (int off = 1; off < G; off <<= 1) {
+      const int32_t v = __shfl_up(incl, off, G);
       if (lane >= off) incl += v;
     }
-    if (e < xrp[i + 1]) xpref[e] = (int32_t)(base + incl - len);
-    base += __shfl(incl, 63, 64);
+    if (e < end) xpref[e] = (int32_t)(base + incl - len);
+    base += __shfl(incl, G - 1, G);
   }
   if (lane == 0) cnt[i] = base;
 }
@@ -460,33 +466,42 @@ __device__ __forceinline__ void lds_add(double *acc, uint32_t *bits, int32_t j, 
 // builds); win[slot] = (first column, width), and *maxw the largest width.
 // One wavefront per row (X rows of the long bin reach thousands of entries): lanes take the
 // row's entries, then a shuffle minimum / maximum.
-__global__ void k_row_window(const int32_t *rows, int32_t nrows, const int32_t *xrp,
-                             const int32_t *xcol, const int32_t *yrp, const int32_t *ycol,
-                             int2 *win, int32_t *maxw) {
+__global__ __launch_bounds__(kBlock) void k_row_window(const int32_t *rows, int32_t nrows,
+                                                       const int32_t *xrp, const int32_t *xcol,
+                                                       const int32_t *yrp, const int32_t *ycol,
+                                                       int2 *win, int32_t *maxw) {
+  __shared__ int32_t s_w[kBlock / 64];
   const int64_t slot = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
-  if (slot >= nrows) return;  // wave-uniform
   const int lane = threadIdx.x & 63;
-  const int32_t i = rows[slot];
   int32_t lo = 0x7fffffff, hi = -1;
-  for (int32_t e = xrp[i] + lane; e < xrp[i + 1]; e += 64) {
-    const int32_t k = xcol[e];
-    const int32_t b = yrp[k], en = yrp[k + 1];
-    if (b < en) {
-      lo = min(lo, ycol[b]);
-      hi = max(hi, ycol[en - 1]);
+  if (slot < nrows) {  // wave-uniform
+    const int32_t i = rows[slot];
+    for (int32_t e = xrp[i] + lane; e < xrp[i + 1]; e += 64) {
+      const int32_t k = xcol[e];
+      const int32_t b = yrp[k], en = yrp[k + 1];
+      if (b < en) {
+        lo = min(lo, ycol[b]);
+        hi = max(hi, ycol[en - 1]);
+      }
     }
   }
   for (int off = 32; off >= 1; off >>= 1) {
     lo = min(lo, __shfl_xor(lo, off, 64));
     hi = max(hi, __shfl_xor(hi, off, 64));
   }
+  const int32_t w = hi >= lo ? hi - lo + 1 : 0;
   if (lane == 0) {
-    const int32_t w = hi >= lo ? hi - lo + 1 : 0;
-    win[slot] = make_int2(hi >= lo ? lo : 0, w);
+    if (slot < nrows) win[slot] = make_int2(hi >= lo ? lo : 0, w);
+    s_w[threadIdx.x >> 6] = w;
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    int32_t m = s_w[0];
+    for (int q = 1; q < kBlock / 64; ++q) m = max(m, s_w[q]);
     // only a wider window touches the shared maximum: an atomic per row took 2,020 us for
-    // 176K rows, all on one word (now 118 us)
-    if (w > __hip_atomic_load(maxw, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
-      atomicMax(maxw, w);
+    // 176K rows, all on one word (a wavefront each, reading the word first, 118 us)
+    if (m > __hip_atomic_load(maxw, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
+      atomicMax(maxw, m);
   }
 }
 
@@ -1187,12 +1202,22 @@ void spgemm(const Csr &X, const Csr &Y, Arena &ar, Csr &C, hipStream_t s) {
   // bits)
   int32_t *counters = tmp.alloc<int32_t>(10);
   fill_i32(counters, 0, 8, s);
-  // rows of up to 64 entries: a thread per row, which also bins the row; longer: a
-  // wavefront per row, binned after the scan
-  const bool wave_count =
-      m > 0 && (X.maxrow >= 0 ? X.maxrow : max_row_length(m, X.rp, s)) > 64;
-  if (wave_count)
-    k_count_products_w<<<(unsigned)m, 64, 0, s>>>(m, X.rp, X.col, Y.rp, cnt, xpref);
+  // short rows: a thread per row, which also bins the row; longer: 16, 32 or 64 lanes per
+  // row, binned after the scan (970K rows of 26 entries: 261 us and 48 for the binning,
+  // against 640 with a thread per row, whose Y row lengths are a chain of gathers)
+  const int32_t xmax = m > 0 ? (X.maxrow >= 0 ? X.maxrow : max_row_length(m, X.rp, s)) : 0;
+  const bool wave_count = m > 0 && (xmax > 64 || X.nnz > 8 * (int64_t)m);
+  auto count_rows = [&](auto gc) {
+    constexpr int G = decltype(gc)::value;
+    k_count_products_w<G><<<grid_for((int64_t)m * G), kBlock, 0, s>>>(m, X.rp, X.col, Y.rp, cnt,
+                                                                     xpref);
+  };
+  if (wave_count && xmax > 64)
+    count_rows(std::integral_constant<int, 64>{});
+  else if (wave_count && X.nnz > 20 * (int64_t)m)
+    count_rows(std::integral_constant<int, 32>{});
+  else if (wave_count)
+    count_rows(std::integral_constant<int, 16>{});
   else if (m > 0)
     k_count_products<<<grid_for(m), kBlock, 0, s>>>(m, X.rp, X.col, Y.rp, cnt, xpref, lists,
                                                     counters);
