@@ -230,13 +230,46 @@ void *pinned_status(size_t bytes) { return pinned_buffer(t_status, bytes); }
 // after a system-scope fence, writes the readback's tag; the host polls the tag instead of
 // synchronising the stream (~3 us less per readback, and the stream's earlier work is done by
 // then: the copy runs after it).
-constexpr int32_t kWordsMax = 1024;  // words per small readback; the tag follows them
-__global__ void k_copy_words(uint32_t *dst, const uint32_t *src, int32_t nw, uint32_t *tag,
-                             uint32_t seq) {
-  for (int32_t i = threadIdx.x; i < nw; i += blockDim.x) dst[i] = src[i];
-  __threadfence_system();
-  __syncthreads();
-  if (threadIdx.x == 0) *(volatile uint32_t *)tag = seq;
+__global__ void k_copy_words(HostWords w, const uint32_t *src, int32_t nw) {
+  post_words(w, src, nw);
+}
+
+HostWords host_words() {
+  uint32_t *st = (uint32_t *)pinned_buffer(t_words, 4 * (kWordsMax + 1));
+  uint32_t *dst = nullptr;
+  SA_HIP(hipHostGetDevicePointer((void **)&dst, st, 0));
+  // a nonzero tag of this thread's own; the word is cleared first, so a tag left by an
+  // earlier readback (or an earlier owner of the buffer) is never taken for this one
+  static thread_local uint32_t seq = 0;
+  seq = seq + 1 == 0 ? 1 : seq + 1;
+  *(volatile uint32_t *)(st + kWordsMax) = 0;
+  return HostWords{dst, st, seq};
+}
+
+void host_words_wait(const HostWords &w, void *host, size_t bytes, hipStream_t s) {
+  // wait at most SAAMG_STATUS_SPIN_NS (default 20 ms; 0: synchronise at once), then
+  // synchronise the stream, which also reports an earlier kernel's failure
+  int64_t spin_ns = 20000000;
+  if (const char *e = std::getenv("SAAMG_STATUS_SPIN_NS")) spin_ns = std::atoll(e);
+  volatile uint32_t *tag = w.host + kWordsMax;
+  bool seen = false;
+  if (spin_ns > 0) {
+    const auto t0 = std::chrono::steady_clock::now();
+    for (uint32_t polls = 0;; ++polls) {
+      if (*tag == w.seq) {
+        seen = true;
+        break;
+      }
+      if ((polls & 255u) == 255u &&
+          std::chrono::duration_cast<std::chrono::nanoseconds>(std::chrono::steady_clock::now() -
+                                                               t0)
+                  .count() >= spin_ns)
+        break;
+    }
+  }
+  if (!seen) SA_HIP(hipStreamSynchronize(s));
+  std::atomic_thread_fence(std::memory_order_acquire);
+  std::memcpy(host, w.host, bytes);
 }
 
 void readback(void *host, const void *dev, size_t bytes, hipStream_t s) {
@@ -247,40 +280,10 @@ void readback(void *host, const void *dev, size_t bytes, hipStream_t s) {
     return;
   }
   if (bytes <= 4 * (size_t)kWordsMax && bytes % 4 == 0 && (uintptr_t)dev % 4 == 0) {
-    uint32_t *st = (uint32_t *)pinned_buffer(t_words, 4 * (kWordsMax + 1));
-    uint32_t *dst = nullptr;
-    SA_HIP(hipHostGetDevicePointer((void **)&dst, st, 0));
-    // a nonzero tag of this thread's own; the word is cleared first, so a tag left by an
-    // earlier readback (or an earlier owner of the buffer) is never taken for this one
-    static thread_local uint32_t seq = 0;
-    seq = seq + 1 == 0 ? 1 : seq + 1;
-    volatile uint32_t *tag = st + kWordsMax;
-    *tag = 0;
-    k_copy_words<<<1, kBlock, 0, s>>>(dst, (const uint32_t *)dev, (int32_t)(bytes / 4),
-                                      dst + kWordsMax, seq);
+    const HostWords w = host_words();
+    k_copy_words<<<1, kBlock, 0, s>>>(w, (const uint32_t *)dev, (int32_t)(bytes / 4));
     SA_LAUNCH_CHECK();
-    // wait at most SAAMG_STATUS_SPIN_NS (default 20 ms; 0: synchronise at once), then
-    // synchronise the stream, which also reports an earlier kernel's failure
-    int64_t spin_ns = 20000000;
-    if (const char *e = std::getenv("SAAMG_STATUS_SPIN_NS")) spin_ns = std::atoll(e);
-    bool seen = false;
-    if (spin_ns > 0) {
-      const auto t0 = std::chrono::steady_clock::now();
-      for (uint32_t polls = 0;; ++polls) {
-        if (*tag == seq) {
-          seen = true;
-          break;
-        }
-        if ((polls & 255u) == 255u &&
-            std::chrono::duration_cast<std::chrono::nanoseconds>(
-                std::chrono::steady_clock::now() - t0)
-                    .count() >= spin_ns)
-          break;
-      }
-    }
-    if (!seen) SA_HIP(hipStreamSynchronize(s));
-    std::atomic_thread_fence(std::memory_order_acquire);
-    std::memcpy(host, st, bytes);
+    host_words_wait(w, host, bytes, s);
     return;
   }
   void *st = pinned_staging(bytes);

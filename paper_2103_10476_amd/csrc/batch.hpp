@@ -22,6 +22,9 @@ struct BatchSystem {
   Phase phase = kJoining;
   bool pr = false, fresh = false;
   double g0 = 0.0, thr = 0.0, rr = 0.0;
+  int s_at = 0;                    // which of the hierarchy's two sets of scalars is current
+  const double *rr_part = nullptr;  // this tick's partials of r.r (null: none formed)
+  int32_t rr_m = 0;
   void *user = nullptr;
 };
 

@@ -72,6 +72,23 @@ void meter_end();
 void meter_read(const Meter *m, int64_t *live, int64_t *peak);  // consistent snapshot
 // Blocking device-to-host copy staged through a per-thread pinned buffer.
 void readback(void *host, const void *dev, size_t bytes, hipStream_t s);
+// Small readbacks by the calling thread's coherent words: host_words() clears the tag, a kernel
+// stores up to kWordsMax words through the device mapping and then the tag (post_words, by
+// every thread of one block), host_words_wait polls the tag and copies the words out.
+constexpr int32_t kWordsMax = 1024;  // words per small readback; the tag follows them
+struct HostWords {
+  uint32_t *dev;   // device address of the words
+  uint32_t *host;  // the same words on the host
+  uint32_t seq;    // the tag to write
+};
+HostWords host_words();
+void host_words_wait(const HostWords &w, void *host, size_t bytes, hipStream_t s);
+__device__ __forceinline__ void post_words(const HostWords &w, const uint32_t *src, int32_t nw) {
+  for (int32_t i = threadIdx.x; i < nw; i += blockDim.x) w.dev[i] = src[i];
+  __threadfence_system();
+  __syncthreads();
+  if (threadIdx.x == 0) *(volatile uint32_t *)(w.dev + kWordsMax) = w.seq;
+}
 // A per-thread pinned host buffer of at least `bytes`, separate from the readback staging:
 // kernels write it through its device mapping while the calling thread polls it.
 void *pinned_status(size_t bytes);

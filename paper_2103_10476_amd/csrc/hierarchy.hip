@@ -17,6 +17,7 @@
 #include <mutex>
 
 #include "hierarchy.hpp"
+#include "solve_device.hpp"
 
 namespace sa {
 
@@ -598,10 +599,8 @@ static void finish_setup(sa_hierarchy *h, bool fresh) {
     h->p = h->ar.alloc<double>(n);
     h->q = h->ar.alloc<double>(n);
     h->zold = h->ar.alloc<double>(n);
-    h->w = h->ar.alloc<double>(n);
-    h->tmp64 = h->ar.alloc<double>(std::max<int64_t>(n, kMaxDense));
-    h->dws = h->ar.alloc<double>(dot_ws_size(n));
-    h->S = h->ar.alloc<PcgScalars>(1);
+    h->dws = h->ar.alloc<double>(3 * dot_ws_size(n));  // r.z or p.q; r.(z - zold); r.r
+    h->S = h->ar.alloc<PcgScalars>(2);
   }
   SA_HIP(hipStreamSynchronize(s));
 }
@@ -809,9 +808,12 @@ static LevelView<float> view32(Level &L) {
   return v;
 }
 
+// One smoothing pass.  uzero: u = 0 on entry (not read); first_done: then the first step has
+// been taken by the kernel that formed f.  zout (or null): the result in FP64 too; returns
+// whether it was written.
 template <class T>
-static void smooth(sa_hierarchy *h, int l, Level &L, LevelView<T> &v, const T *f, T *u,
-                   bool uzero) {
+static bool smooth(sa_hierarchy *h, int l, Level &L, LevelView<T> &v, const T *f, T *u,
+                   bool uzero, bool first_done, double *zout) {
   const int es = (int)sizeof(T);
   const hipStream_t s = h->stream;
   const sa_options &o = h->opt;
@@ -821,7 +823,7 @@ static void smooth(sa_hierarchy *h, int l, Level &L, LevelView<T> &v, const T *f
     const T w = (T)L.jac_w;
     int sweep = 0;
     if (uzero) {
-      jacobi_first<T>(n, f, v.invD, w, u, s);
+      if (!first_done) jacobi_first<T>(n, f, v.invD, w, u, s);
       sweep = 1;
     }
     for (; sweep < o.degree; ++sweep) {
@@ -831,13 +833,13 @@ static void smooth(sa_hierarchy *h, int l, Level &L, LevelView<T> &v, const T *f
       prof_end(h, l, 4, es);
       SA_HIP(hipMemcpyAsync(u, v.d1, sizeof(T) * n, hipMemcpyDeviceToDevice, s));
     }
-    return;
+    return false;
   }
   const T theta = (T)L.cheb_theta;
   T *dc = v.d1, *dn = v.d2;
   const T *rin;
   if (uzero) {
-    cheb_first<T>(n, f, v.invD, theta, dc, u, o.degree == 1, s);
+    if (!first_done) cheb_first<T>(n, f, v.invD, theta, dc, u, o.degree == 1, s);
     rin = f;
   } else {
     A.x = u;
@@ -852,69 +854,67 @@ static void smooth(sa_hierarchy *h, int l, Level &L, LevelView<T> &v, const T *f
     const bool last = (m == o.degree - 1);
     prof_begin(h, l);
     spmv_cheb_step<T>(A, rin, v.r, v.invD, (T)L.cheb_c1[m - 1], (T)L.cheb_c2[m - 1], u,
-                      uzero && m == 1, dn, last, s);
+                      uzero && m == 1, dn, last, last ? zout : nullptr, s);
     // x = d, rin, invD, rout, u (read unless from zero), u written, dout unless last
     prof_end(h, l, 5 + ((uzero && m == 1) ? 0 : 1) + (last ? 0 : 1), es);
     rin = v.r;
     std::swap(dc, dn);
   }
+  return o.degree > 1 && zout != nullptr;
 }
 
+// One V-cycle on level l.  first_done: the level's first smoother step has been taken by the
+// kernel that formed f; zout (or null): the result in FP64 too.  Returns whether it was
+// written.
 template <class T>
-static void coarse_apply(sa_hierarchy *h, Level &L, const T *f, T *u);
-template <>
-void coarse_apply<double>(sa_hierarchy *h, Level &L, const double *f, double *u) {
-  gemv_f64(L.A.n, L.Ainv, f, u, h->stream);
-}
-template <>
-void coarse_apply<float>(sa_hierarchy *h, Level &L, const float *f, float *u) {
-  double *f64 = h->tmp64;
-  double *u64 = L.u;
-  cast_f32_to_f64(f, f64, L.A.n, h->stream);
-  gemv_f64(L.A.n, L.Ainv, f64, u64, h->stream);
-  cast_f64_to_f32(u64, u, L.A.n, h->stream);
-}
-
-template <class T>
-static void vcycle(sa_hierarchy *h, int l, const T *f, T *u) {
+static bool vcycle(sa_hierarchy *h, int l, const T *f, T *u, bool first_done = false,
+                   double *zout = nullptr) {
   Level &L = h->lv[l];
   const int nl = (int)h->lv.size();
+  const hipStream_t s = h->stream;
   if (l + 1 == nl) {
-    coarse_apply<T>(h, L, f, u);
-    return;
+    gemv<T>(L.A.n, L.Ainv, f, u, s);
+    return false;
   }
   LevelView<T> v;
   if constexpr (sizeof(T) == 8) v = view64(L);
   else v = view32(L);
+  Level &Lc = h->lv[l + 1];
   LevelView<T> vc;
-  if constexpr (sizeof(T) == 8) vc = view64(h->lv[l + 1]);
-  else vc = view32(h->lv[l + 1]);
-  const hipStream_t s = h->stream;
-  smooth<T>(h, l, L, v, f, u, true);
+  if constexpr (sizeof(T) == 8) vc = view64(Lc);
+  else vc = view32(Lc);
+  smooth<T>(h, l, L, v, f, u, true, first_done, nullptr);
   SpmvArgs<T> A = v.A;
   A.x = u;
   prof_begin(h, l);
   spmv_resid<T>(A, f, v.r, s);
   prof_end(h, l, 3, (int)sizeof(T));
+  // the restriction also takes the next level's first smoother step on what it forms
   SpmvArgs<T> R = v.R;
   R.x = v.r;
-  spmv_store<T>(R, vc.f, s);
-  vcycle<T>(h, l + 1, vc.f, vc.u);
+  const bool coarsest = l + 2 == nl;
+  if (coarsest) spmv_store<T>(R, vc.f, s);
+  else if (h->opt.smoother == SA_JACOBI)
+    spmv_restrict_jacobi<T>(R, vc.f, vc.invD, (T)Lc.jac_w, vc.u, s);
+  else
+    spmv_restrict_cheb<T>(R, vc.f, vc.invD, (T)Lc.cheb_theta, vc.d1, vc.u, h->opt.degree == 1, s);
+  vcycle<T>(h, l + 1, vc.f, vc.u, !coarsest);
   SpmvArgs<T> P = v.P;
   P.x = vc.u;
   spmv_add<T>(P, u, s);
-  smooth<T>(h, l, L, v, f, u, false);
+  return smooth<T>(h, l, L, v, f, u, false, false, zout);
 }
 
-// z = M^{-1} r at the fine level, in the hierarchy's precision.
-static void precondition(sa_hierarchy *h, const double *r, double *z) {
+// z = M^{-1} r at the fine level, in the hierarchy's precision.  first_done: the fine level's
+// first smoother step (and in FP32 the cast of r) has been taken with r.
+static void precondition(sa_hierarchy *h, const double *r, double *z, bool first_done = false) {
   Level &L0 = h->lv[0];
   if (h->opt.precision == SA_FP32_VCYCLE && h->lv.size() > 1) {
-    cast_f64_to_f32(r, L0.ff, h->n, h->stream);
-    vcycle<float>(h, 0, L0.ff, L0.uf);
-    cast_f32_to_f64(L0.uf, z, h->n, h->stream);
+    if (!first_done) cast_f64_to_f32(r, L0.ff, h->n, h->stream);
+    if (!vcycle<float>(h, 0, L0.ff, L0.uf, first_done, z))
+      cast_f32_to_f64(L0.uf, z, h->n, h->stream);
   } else {
-    vcycle<double>(h, 0, r, z);
+    vcycle<double>(h, 0, r, z, first_done);
   }
 }
 
@@ -928,10 +928,13 @@ static sa_status solve_impl(sa_hierarchy *h, const double *b, double *x, sa_loca
                   (o.pcg_beta < 0 && o.precision == SA_FP32_VCYCLE);
   copy_in(h->r, b, sizeof(double) * n, loc, s);
   fill_f64(h->x, 0.0, n, s);
-  PcgScalars *S = h->S;
-  SA_HIP(hipMemsetAsync(S, 0, sizeof(PcgScalars), s));
-  dot_f64(h->r, h->r, n, &S->rr, h->dws, s);
-  const double g0 = read1(&S->rr, s);
+  PcgScalars *S = h->S;  // two sets: see the PCG steps in solve_device.hpp
+  static_assert(sizeof(PcgScalars) % 4 == 0, "scalars cleared as 32-bit words");
+  fill_i32((int32_t *)S, 0, (int64_t)(2 * sizeof(PcgScalars) / 4), s);
+  double *wrr = h->dws + 2 * dot_ws_size(n);
+  PcgScalars hs;
+  pcg_read(&hs, dot_parts(h->r, h->r, n, wrr, s), S, s);
+  const double g0 = hs.rr;
   int32_t its = 0;
   double rr = g0;
   sa_status st = SA_NOT_CONVERGED;
@@ -950,23 +953,37 @@ static sa_status solve_impl(sa_hierarchy *h, const double *b, double *x, sa_loca
     return SA_OK;
   }
   const double thr = (o.rtol * o.rtol) * g0;
-  precondition(h, h->r, h->z);
-  SA_HIP(hipMemcpyAsync(h->p, h->z, sizeof(double) * n, hipMemcpyDeviceToDevice, s));
-  dot_f64(h->r, h->z, n, &S->rho1, h->dws, s);
-  pcg_init_rho(S, s);
+  double *z = h->z, *zold = h->zold;
+  DotParts rz, rw;
+  precondition(h, h->r, z);
+  dot_rz_parts(h->r, z, nullptr, n, h->dws, &rz, &rw, s);
+  pcg_update_p(n, h->p, z, rz, rw, S, S, pr, true, s);
   SpmvArgs<double> A =
       with_sell(spmv_args<double>(h->lv[0].A, h->lv[0].A.val, h->p), h->lv[0].Aell,
                 h->lv[0].Aell.val);
+  // the fine level's first Chebyshev step of the next preconditioner application rides along
+  // with the residual's update
+  const bool first = h->lv.size() > 1 && o.smoother == SA_CHEBYSHEV;
+  const bool f32 = o.precision == SA_FP32_VCYCLE;
+  Level &L0 = h->lv[0];
   for (int32_t k = 1; k <= o.max_iter; ++k) {
+    PcgScalars *cur = S + ((k - 1) & 1), *next = S + (k & 1);
     prof_begin(h, 0);
     spmv_store<double>(A, h->q, s);
     prof_end(h, 0, 2, 8);
-    dot_f64(h->p, h->q, n, &S->pq, h->dws, s);
-    pcg_alpha(S, s);
-    pcg_update_xr(n, h->x, h->r, h->p, h->q, S, s);
-    dot_f64(h->r, h->r, n, &S->rr, h->dws, s);
-    PcgScalars hs;
-    readback(&hs, S, sizeof(PcgScalars), s);
+    const DotParts pq = dot_parts(h->p, h->q, n, h->dws, s);
+    DotParts prr;
+    if (first && f32)
+      prr = pcg_update_xr(n, h->x, h->r, h->p, h->q, pq, cur, wrr,
+                          FirstCheb32{L0.ff, L0.sm_invDf, (float)L0.cheb_theta, L0.d1f, L0.uf,
+                                      o.degree == 1}, s);
+    else if (first)  // (z is not read again: with PR it is zold by then)
+      prr = pcg_update_xr(n, h->x, h->r, h->p, h->q, pq, cur, wrr,
+                          FirstCheb64{L0.sm_invD, L0.cheb_theta, L0.d1, pr ? zold : z,
+                                      o.degree == 1}, s);
+    else
+      prr = pcg_update_xr(n, h->x, h->r, h->p, h->q, pq, cur, wrr, FirstNone{}, s);
+    pcg_read(&hs, prr, cur, s);
     prof_collect(h);
     if (hs.err) return SA_ERR_BREAKDOWN;
     rr = hs.rr;
@@ -975,19 +992,13 @@ static sa_status solve_impl(sa_hierarchy *h, const double *b, double *x, sa_loca
       st = SA_OK;
       break;
     }
-    if (pr) SA_HIP(hipMemcpyAsync(h->zold, h->z, sizeof(double) * n, hipMemcpyDeviceToDevice, s));
-    precondition(h, h->r, h->z);
-    dot_f64(h->r, h->z, n, &S->rho1, h->dws, s);
-    if (pr) {
-      vec_sub(n, h->z, h->zold, h->w, s);
-      dot_f64(h->r, h->w, n, &S->rw, h->dws, s);
-    }
-    pcg_beta(S, pr, s);
-    pcg_update_p(n, h->p, h->z, S, s);
+    if (pr) std::swap(z, zold);
+    precondition(h, h->r, z, first);
+    dot_rz_parts(h->r, z, pr ? zold : nullptr, n, h->dws, &rz, &rw, s);
+    pcg_update_p(n, h->p, z, rz, rw, cur, next, pr, false, s);
   }
   if (st != SA_OK) {
-    PcgScalars hs;
-    readback(&hs, S, sizeof(PcgScalars), s);
+    readback(&hs, S + (o.max_iter & 1), sizeof(PcgScalars), s);
     if (hs.err) return SA_ERR_BREAKDOWN;
     its = o.max_iter;
   }

@@ -69,7 +69,7 @@ struct sa_hierarchy {
   double *As0 = nullptr;        // D_B A D_B values on level 0 (when scaled)
   // solve workspace
   double *x = nullptr, *r = nullptr, *z = nullptr, *p = nullptr, *q = nullptr, *zold = nullptr,
-         *w = nullptr, *dws = nullptr, *tmp64 = nullptr;
+         *dws = nullptr;
   sa::PcgScalars *S = nullptr;
   int32_t n = 0;
   // fine-level SpMV timing (sa_profile_enable)

@@ -94,10 +94,17 @@ template <class T>
 void spmv_cheb_start(const SpmvArgs<T> &a, const T *f, const T *invD, T theta, T *r, T *d,
                      hipStream_t s);
 // x = d: rout = rin - A d; dn = c1 d + c2 (invD .* rout); u = (uzero ? 0 : u) + d, and when
-// `last` also u += dn.  dout must differ from d (= a.x).
+// `last` also u += dn, and z = u in FP64 unless z is null.  dout must differ from d (= a.x).
 template <class T>
 void spmv_cheb_step(const SpmvArgs<T> &a, const T *rin, T *rout, const T *invD, T c1, T c2,
-                    T *u, bool uzero, T *dout, bool last, hipStream_t s);
+                    T *u, bool uzero, T *dout, bool last, double *z, hipStream_t s);
+// y = A x and the first smoother step on it from u = 0: Chebyshev d = (invD .* y) / theta (with
+// write_u also u = 0 + d), or Jacobi u = 0 + w (invD .* y).
+template <class T>
+void spmv_restrict_cheb(const SpmvArgs<T> &a, T *y, const T *invD, T theta, T *d, T *u,
+                        bool write_u, hipStream_t s);
+template <class T>
+void spmv_restrict_jacobi(const SpmvArgs<T> &a, T *y, const T *invD, T w, T *u, hipStream_t s);
 // x = u: u2 = u + w (invD .* (f - A u))
 template <class T>
 void spmv_jacobi(const SpmvArgs<T> &a, const T *f, const T *invD, T w, T *u2, hipStream_t s);
@@ -115,8 +122,10 @@ void jacobi_first(int32_t n, const T *f, const T *invD, T w, T *u, hipStream_t s
 void cast_f64_to_f32(const double *a, float *b, int64_t n, hipStream_t s);
 void cast_f32_to_f64(const float *a, double *b, int64_t n, hipStream_t s);
 
-// Dense y = M x for the coarsest level (M row-major n x n, float64).
-void gemv_f64(int32_t n, const double *M, const double *x, double *y, hipStream_t s);
+// Dense y = M x for the coarsest level (M row-major n x n, float64; float vectors are widened
+// and the result rounded).
+template <class T>
+void gemv(int32_t n, const double *M, const T *x, T *y, hipStream_t s);
 
 // ---- GMRES (solve_kernels.hip) ----------------------------------------------------------
 // Device state of one GMRES cycle with restart length m: the Hessenberg matrix (row-major,
@@ -158,19 +167,29 @@ struct PcgScalars {
   double rho, pq, alpha, rr, rho1, beta, rw, spare;
   int32_t err, pad;
 };
-// x = x + alpha p; r = r - alpha q  (alpha = S->alpha)
-void pcg_update_xr(int32_t n, double *x, double *r, const double *p, const double *q,
-                   const PcgScalars *S, hipStream_t s);
-// p = z + beta p
-void pcg_update_p(int32_t n, double *p, const double *z, const PcgScalars *S, hipStream_t s);
-// w = z - zold
-void vec_sub(int32_t n, const double *z, const double *zold, double *w, hipStream_t s);
-// alpha = rho / pq (err on pq <= 0)
-void pcg_alpha(PcgScalars *S, hipStream_t s);
-// beta (FR: rho1/rho; PR: rw/rho), err on rho1 <= 0, then rho = rho1
-void pcg_beta(PcgScalars *S, bool pr, hipStream_t s);
-// rho = rho1 (initial), err on <= 0
-void pcg_init_rho(PcgScalars *S, hipStream_t s);
+// Partials of a canonical inner product, at most 4096 of them: the kernels that use the value
+// take the last stage themselves.
+struct DotParts {
+  const double *p = nullptr;
+  int32_t m = 0;
+};
+DotParts dot_parts(const double *x, const double *y, int64_t n, double *ws, hipStream_t s);
+// r.z, and r.(z - zold) unless zold is null; ws holds 2 dot_ws_size(n) doubles.
+void dot_rz_parts(const double *r, const double *z, const double *zold, int64_t n, double *ws,
+                  DotParts *rz, DotParts *rw, hipStream_t s);
+// alpha = rho / p.q (S->err 1 on p.q <= 0); x += alpha p; r -= alpha q; the partials of the new
+// r.r (in ws, apart from p.q's); first: the next preconditioner application's first step on
+// r (FirstNone, FirstCheb64 or FirstCheb32 of solve_device.hpp).
+template <class First>
+DotParts pcg_update_xr(int64_t n, double *x, double *r, const double *p, const double *q,
+                       const DotParts &pq, PcgScalars *S, double *ws, const First &first,
+                       hipStream_t s);
+// rho1 = r.z (err 2 on rho1 <= 0), beta (FR: rho1 / rho; PR: r.(z - zold) / rho), p = z + beta p,
+// the scalars of cur carried on in next; init: p = z, rho = rho1 (cur may be next).
+void pcg_update_p(int64_t n, double *p, const double *z, const DotParts &rz, const DotParts &rw,
+                  const PcgScalars *cur, PcgScalars *next, bool pr, bool init, hipStream_t s);
+// r.r from its partials into S, and S to the host.
+void pcg_read(PcgScalars *host, const DotParts &rr, PcgScalars *S, hipStream_t s);
 
 // ---------------- setup kernels (setup_kernels.hip) ------------------------------------
 // Validates a CSR (ascending in-range columns, diagonal present, finite values); flags

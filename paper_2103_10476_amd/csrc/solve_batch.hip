@@ -62,14 +62,13 @@ __global__ __launch_bounds__(kBlock) void k_gspmv(const GSpmv<T, Epi> *segs,
 
 enum GVecOp : int32_t {
   G_CHEB_FIRST_D, G_CHEB_FIRST_F, G_VEC_ADD_D, G_VEC_ADD_F, G_JAC_FIRST_D, G_JAC_FIRST_F,
-  G_COPY_D, G_COPY_F, G_CAST_DF, G_CAST_FD, G_UPDATE_XR, G_UPDATE_P, G_VEC_SUB
+  G_COPY_D, G_COPY_F, G_CAST_DF, G_CAST_FD, G_CAST_CHEB_F
 };
 
 struct GVec {
   int32_t op, n;
   const void *a, *b;
-  void *c, *d;
-  const PcgScalars *S;
+  void *c, *d, *e;
   double sc;
   int32_t flag, pad;
 };
@@ -103,29 +102,28 @@ __global__ __launch_bounds__(kBlock) void k_gvec(const GVec *segs, const int32_t
     case G_COPY_F: ((float *)v.c)[i] = ((const float *)v.a)[i]; break;
     case G_CAST_DF: ((float *)v.c)[i] = (float)((const double *)v.a)[i]; break;
     case G_CAST_FD: ((double *)v.c)[i] = (double)((const float *)v.a)[i]; break;
-    case G_UPDATE_XR:
-      update_xr_at(i, (double *)v.c, (double *)v.d, (const double *)v.a, (const double *)v.b,
-                   v.S->alpha);
-      break;
-    case G_UPDATE_P: update_p_at(i, (double *)v.c, (const double *)v.a, v.S->beta); break;
-    case G_VEC_SUB:
-      vec_sub_at(i, (const double *)v.a, (const double *)v.b, (double *)v.c);
+    case G_CAST_CHEB_F:  // e = (float)a, then the first Chebyshev step on it
+      FirstCheb32{(float *)v.e, (const float *)v.b, (float)v.sc, (float *)v.c, (float *)v.d,
+                  v.flag != 0}(i, ((const double *)v.a)[i]);
       break;
     default: break;
   }
 }
 
 struct GGemv {
-  int32_t n, pad;
-  const double *M, *x;
-  double *y;
+  int32_t n, f32;
+  const double *M;
+  const void *x;
+  void *y;
 };
 __global__ __launch_bounds__(kBlock) void k_ggemv(const GGemv *segs, const int32_t *boff,
                                                   int32_t nseg) {
   const int32_t s = find_seg(boff, nseg, blockIdx.x);
   const GGemv a = segs[s];
   const int64_t row = (int64_t)(blockIdx.x - boff[s]) * (kBlock / 64) + (threadIdx.x >> 6);
-  if (row < a.n) gemv_row(row, a.n, a.M, a.x, a.y);
+  if (row >= a.n) return;
+  if (a.f32) gemv_row<float>(row, a.n, a.M, (const float *)a.x, (float *)a.y);
+  else gemv_row<double>(row, a.n, a.M, (const double *)a.x, (double *)a.y);
 }
 
 struct GDot {
@@ -142,23 +140,70 @@ __global__ __launch_bounds__(kBlock) void k_gdot(const GDot *segs, const int32_t
   dot_block(blk, a.x, a.y, a.n, a.out + blk, sh);
 }
 
-enum GScalOp : int32_t { G_ALPHA, G_BETA, G_INIT };
-struct GScal {
-  PcgScalars *S;
-  int32_t op, pr;
+struct GDotRz {
+  const double *r, *z, *zold;  // zold null: r.z only
+  int64_t n;
+  double *out, *outw;
 };
-__global__ void k_gscal(const GScal *segs, int32_t nseg) {
-  const int32_t s = blockIdx.x * blockDim.x + threadIdx.x;
-  if (s >= nseg) return;
-  const GScal a = segs[s];
-  if (a.op == G_ALPHA) pcg_alpha_on(a.S);
-  else if (a.op == G_BETA) pcg_beta_on(a.S, a.pr != 0);
-  else pcg_init_on(a.S);
+__global__ __launch_bounds__(kBlock) void k_gdot_rz(const GDotRz *segs, const int32_t *boff,
+                                                    int32_t nseg) {
+  __shared__ double sh[kBlock];
+  const int32_t s = find_seg(boff, nseg, blockIdx.x);
+  const GDotRz a = segs[s];
+  const int64_t blk = blockIdx.x - boff[s];
+  dot_rz_block(blk, a.r, a.z, a.zold, a.n, a.out + blk, a.zold ? a.outw + blk : nullptr, sh);
 }
 
-__global__ void k_ggather(PcgScalars *const *src, PcgScalars *dst, int32_t nseg) {
-  const int32_t s = blockIdx.x * blockDim.x + threadIdx.x;
-  if (s < nseg) dst[s] = *src[s];
+struct GXr {
+  int64_t n;
+  double *x, *r;
+  const double *p, *q, *part;
+  int32_t m, pad;
+  PcgScalars *S;
+  double *out;
+};
+__global__ __launch_bounds__(kBlock) void k_gxr(const GXr *segs, const int32_t *boff,
+                                                int32_t nseg) {
+  __shared__ double sh[kBlock];
+  const int32_t s = find_seg(boff, nseg, blockIdx.x);
+  const GXr a = segs[s];
+  pcg_xr_block(blockIdx.x - boff[s], a.n, a.x, a.r, a.p, a.q, a.part, a.m, a.S, a.out,
+               FirstNone{}, sh);
+}
+
+struct GP {
+  int64_t n;
+  double *p;
+  const double *z, *part, *partw;
+  int32_t m;
+  bool pr, init;
+  const PcgScalars *cur;
+  PcgScalars *next;
+};
+__global__ __launch_bounds__(kBlock) void k_gp(const GP *segs, const int32_t *boff,
+                                               int32_t nseg) {
+  __shared__ double sh[kBlock];
+  const int32_t s = find_seg(boff, nseg, blockIdx.x);
+  const GP a = segs[s];
+  pcg_p_block(blockIdx.x - boff[s], a.n, a.p, a.z, a.part, a.partw, a.m, a.cur, a.next, a.pr,
+              a.init, sh);
+}
+
+// A block per system: r.r from its partials (when given) into the system's scalars, and the
+// scalars into the readback's array.
+struct GGather {
+  PcgScalars *S;
+  const double *part;
+  int32_t m, pad;
+};
+__global__ __launch_bounds__(kBlock) void k_ggather(const GGather *segs, PcgScalars *dst) {
+  __shared__ double sh[kBlock];
+  const GGather a = segs[blockIdx.x];
+  if (a.part) {  // block-uniform
+    const double rr = dot_final(a.part, a.m, sh);
+    if (threadIdx.x == 0) a.S->rr = rr;
+  }
+  if (threadIdx.x == 0) dst[blockIdx.x] = *a.S;
 }
 
 // ---- host side: recording a tick ------------------------------------------------------------
@@ -190,8 +235,17 @@ void launch_gdot(const void *segs, const int32_t *boff, int32_t nseg, int32_t bl
                  hipStream_t s) {
   k_gdot<<<(unsigned)blocks, kBlock, 0, s>>>((const GDot *)segs, boff, nseg);
 }
-void launch_gscal(const void *segs, const int32_t *, int32_t nseg, int32_t, hipStream_t s) {
-  k_gscal<<<grid_for(nseg), kBlock, 0, s>>>((const GScal *)segs, nseg);
+void launch_gdot_rz(const void *segs, const int32_t *boff, int32_t nseg, int32_t blocks,
+                    hipStream_t s) {
+  k_gdot_rz<<<(unsigned)blocks, kBlock, 0, s>>>((const GDotRz *)segs, boff, nseg);
+}
+void launch_gxr(const void *segs, const int32_t *boff, int32_t nseg, int32_t blocks,
+                hipStream_t s) {
+  k_gxr<<<(unsigned)blocks, kBlock, 0, s>>>((const GXr *)segs, boff, nseg);
+}
+void launch_gp(const void *segs, const int32_t *boff, int32_t nseg, int32_t blocks,
+               hipStream_t s) {
+  k_gp<<<(unsigned)blocks, kBlock, 0, s>>>((const GP *)segs, boff, nseg);
 }
 
 // Builds the descriptor buffer of one tick.
@@ -268,7 +322,7 @@ void rec_vec(Recorder &rc, const std::vector<GVec> &segs) {
 }
 
 GVec gv(int32_t op, int32_t n, const void *a, const void *b, void *c, void *d = nullptr,
-        double sc = 0.0, int32_t flag = 0, const PcgScalars *S = nullptr) {
+        double sc = 0.0, int32_t flag = 0, void *e = nullptr) {
   GVec v;
   v.op = op;
   v.n = n;
@@ -276,59 +330,57 @@ GVec gv(int32_t op, int32_t n, const void *a, const void *b, void *c, void *d = 
   v.b = b;
   v.c = c;
   v.d = d;
-  v.S = S;
+  v.e = e;
   v.sc = sc;
   v.flag = flag;
   v.pad = 0;
   return v;
 }
 
-// Canonical inner products res_k = x_k . y_k, one per system, with the stage structure of
-// dot_f64: the first stage multiplies, later stages sum the previous stage's partials in the
-// system's workspace, the last stage writes res_k.
-struct DotJob {
-  const double *x, *y;
-  int64_t n;
-  double *res, *ws;
+int32_t dot_blocks(int64_t n) { return n > 0 ? (int32_t)ceil_div(n, 4096) : 1; }
+
+// Partials of canonical inner products, one set per system, reduced in stages (grouped over
+// the systems) until each has at most kDotFinal: the kernels that use the values take the
+// last stage themselves, as in the standalone solve.
+struct Parts {
+  double *p, *ws;  // partials, and the workspace behind them
+  int64_t m;
 };
-void rec_dots(Recorder &rc, const std::vector<DotJob> &jobs) {
-  struct St {
-    const double *in, *iny;
-    int64_t m;
-    double *out;
-    bool done;
-  };
-  std::vector<St> st;
-  for (const DotJob &j : jobs) st.push_back({j.x, j.y, j.n, j.ws, false});
+void rec_reduce(Recorder &rc, std::vector<Parts> &parts) {
   for (;;) {
     std::vector<GDot> segs;
     std::vector<int32_t> blocks;
-    bool any = false;
-    for (size_t k = 0; k < st.size(); ++k) {
-      St &a = st[k];
-      if (a.done) continue;
-      int64_t nb = ceil_div(a.m, 4096);
-      if (nb < 1) nb = 1;
-      double *dst = (nb == 1) ? jobs[k].res : a.out;
-      segs.push_back({a.in, a.iny, a.m, dst});
+    for (Parts &a : parts) {
+      if (a.m <= kDotFinal) continue;
+      const int64_t nb = ceil_div(a.m, 4096);
+      segs.push_back({a.p, nullptr, a.m, a.ws});
       blocks.push_back((int32_t)nb);
-      any = true;
-      if (nb == 1) {
-        a.done = true;
-      } else {
-        a.in = a.out;
-        a.iny = nullptr;
-        a.out += nb;
-        a.m = nb;
-      }
+      a.p = a.ws;
+      a.ws += nb;
+      a.m = nb;
     }
-    if (!any) break;
+    if (segs.empty()) break;
     rc.add(launch_gdot, segs, blocks);
   }
 }
-
-void rec_scal(Recorder &rc, const std::vector<GScal> &segs) {
-  rc.add(launch_gscal, segs, std::vector<int32_t>(segs.size(), 1));
+struct DotJob {
+  const double *x, *y;
+  int64_t n;
+  double *ws;
+};
+std::vector<Parts> rec_dots(Recorder &rc, const std::vector<DotJob> &jobs) {
+  std::vector<Parts> parts;
+  std::vector<GDot> segs;
+  std::vector<int32_t> blocks;
+  for (const DotJob &j : jobs) {
+    const int32_t nb = dot_blocks(j.n);
+    segs.push_back({j.x, j.y, j.n, j.ws});
+    blocks.push_back(nb);
+    parts.push_back({j.ws, j.ws + nb, nb});
+  }
+  rc.add(launch_gdot, segs, blocks);
+  rec_reduce(rc, parts);
+  return parts;
 }
 
 // ---- the grouped V-cycle (mirrors smooth / vcycle / coarse_apply of the standalone solve) --
@@ -337,10 +389,11 @@ struct Item {
   int level;
   const void *f;  // T*
   void *u;        // T*
+  double *z;      // the V-cycle's result in FP64 too (null: not wanted)
 };
 
 template <class T>
-void rec_smooth(Recorder &rc, const std::vector<Item> &its, bool uzero) {
+void rec_smooth(Recorder &rc, const std::vector<Item> &its, bool uzero, bool first_done) {
   if (its.empty()) return;
   const sa_options &o = its[0].h->opt;  // all items share smoother and degree
   std::vector<View<T>> v;
@@ -355,7 +408,7 @@ void rec_smooth(Recorder &rc, const std::vector<Item> &its, bool uzero) {
         g.push_back(gv(f32 ? G_JAC_FIRST_F : G_JAC_FIRST_D, L.A.n, its[k].f, v[k].invD,
                        its[k].u, nullptr, (double)(T)L.jac_w));
       }
-      rec_vec(rc, g);
+      if (!first_done) rec_vec(rc, g);
       sweep = 1;
     }
     for (; sweep < o.degree; ++sweep) {
@@ -391,7 +444,7 @@ void rec_smooth(Recorder &rc, const std::vector<Item> &its, bool uzero) {
                      its[k].u, (double)(T)L.cheb_theta, o.degree == 1 ? 1 : 0));
       rin.push_back((const T *)its[k].f);
     }
-    rec_vec(rc, g);
+    if (!first_done) rec_vec(rc, g);
   } else {
     std::vector<GSpmv<T, EpChebStart<T>>> sp;
     std::vector<int32_t> nb;
@@ -417,7 +470,8 @@ void rec_smooth(Recorder &rc, const std::vector<Item> &its, bool uzero) {
       sp.push_back(gspmv<T>(*v[k].A, v[k].Aval, dc[k],
                             EpChebStep<T>{dc[k], rin[k], v[k].invD, v[k].r, (T *)its[k].u,
                                           dn[k], (T)L.cheb_c1[m - 1], (T)L.cheb_c2[m - 1],
-                                          uzero && m == 1, last}));
+                                          uzero && m == 1, last,
+                                          last && !uzero ? its[k].z : nullptr}));
       nb.push_back(spmv_blocks(L.A));
       rin[k] = v[k].r;
       std::swap(dc[k], dn[k]);
@@ -431,36 +485,22 @@ void rec_coarse(Recorder &rc, const std::vector<Item> &its) {
   if (its.empty()) return;
   std::vector<GGemv> g;
   std::vector<int32_t> nb;
-  if (sizeof(T) == 8) {
-    for (const Item &it : its) {
-      const Level &L = it.h->lv[it.level];
-      g.push_back({L.A.n, 0, L.Ainv, (const double *)it.f, (double *)it.u});
-      nb.push_back((int32_t)ceil_div(L.A.n, kBlock / 64));
-    }
-    rc.add(launch_ggemv, g, nb);
-    return;
-  }
-  std::vector<GVec> c1, c2;
   for (const Item &it : its) {
-    Level &L = it.h->lv[it.level];
-    c1.push_back(gv(G_CAST_FD, L.A.n, it.f, nullptr, it.h->tmp64));
-    g.push_back({L.A.n, 0, L.Ainv, it.h->tmp64, L.u});
+    const Level &L = it.h->lv[it.level];
+    g.push_back({L.A.n, sizeof(T) == 4, L.Ainv, it.f, it.u});
     nb.push_back((int32_t)ceil_div(L.A.n, kBlock / 64));
-    c2.push_back(gv(G_CAST_DF, L.A.n, L.u, nullptr, it.u));
   }
-  rec_vec(rc, c1);
   rc.add(launch_ggemv, g, nb);
-  rec_vec(rc, c2);
 }
 
 template <class T>
-void rec_vcycle(Recorder &rc, const std::vector<Item> &its) {
+void rec_vcycle(Recorder &rc, const std::vector<Item> &its, bool first_done) {
   std::vector<Item> coarse, fine;
   for (const Item &it : its)
     (it.level + 1 == (int)it.h->lv.size() ? coarse : fine).push_back(it);
   rec_coarse<T>(rc, coarse);
   if (fine.empty()) return;
-  rec_smooth<T>(rc, fine, true);
+  rec_smooth<T>(rc, fine, true, first_done);
   std::vector<View<T>> v;
   for (const Item &it : fine) v.push_back(view_of(it.h->lv[it.level], T()));
   {
@@ -474,21 +514,38 @@ void rec_vcycle(Recorder &rc, const std::vector<Item> &its) {
     }
     rec_spmv(rc, sp, nb);
   }
+  // restriction; where the next level smooths, its first step rides along
   std::vector<Item> next;
   {
     std::vector<GSpmv<T, EpStore<T>>> sp;
-    std::vector<int32_t> nb;
+    std::vector<GSpmv<T, EpRestrictCheb<T>>> spc;
+    std::vector<GSpmv<T, EpRestrictJacobi<T>>> spj;
+    std::vector<int32_t> nb, nbc, nbj;
     for (size_t k = 0; k < fine.size(); ++k) {
       sa_hierarchy *h = fine[k].h;
       const Level &L = h->lv[fine[k].level];
+      const Level &Lc = h->lv[fine[k].level + 1];
       View<T> vc = view_of(h->lv[fine[k].level + 1], T());
-      sp.push_back(gspmv<T>(L.R, v[k].Rval, v[k].r, EpStore<T>{vc.f}));
-      nb.push_back(spmv_blocks(L.R));
-      next.push_back({h, fine[k].level + 1, vc.f, vc.u});
+      if (fine[k].level + 2 == (int)h->lv.size()) {
+        sp.push_back(gspmv<T>(L.R, v[k].Rval, v[k].r, EpStore<T>{vc.f}));
+        nb.push_back(spmv_blocks(L.R));
+      } else if (h->opt.smoother == SA_JACOBI) {
+        spj.push_back(gspmv<T>(L.R, v[k].Rval, v[k].r,
+                               EpRestrictJacobi<T>{vc.f, vc.invD, (T)Lc.jac_w, vc.u}));
+        nbj.push_back(spmv_blocks(L.R));
+      } else {
+        spc.push_back(gspmv<T>(L.R, v[k].Rval, v[k].r,
+                               EpRestrictCheb<T>{vc.f, vc.invD, (T)Lc.cheb_theta, vc.d1, vc.u,
+                                                 h->opt.degree == 1}));
+        nbc.push_back(spmv_blocks(L.R));
+      }
+      next.push_back({h, fine[k].level + 1, vc.f, vc.u, nullptr});
     }
     rec_spmv(rc, sp, nb);
+    rec_spmv(rc, spc, nbc);
+    rec_spmv(rc, spj, nbj);
   }
-  rec_vcycle<T>(rc, next);
+  rec_vcycle<T>(rc, next, true);
   {
     std::vector<GSpmv<T, EpAdd<T>>> sp;
     std::vector<int32_t> nb;
@@ -499,7 +556,7 @@ void rec_vcycle(Recorder &rc, const std::vector<Item> &its) {
     }
     rec_spmv(rc, sp, nb);
   }
-  rec_smooth<T>(rc, fine, false);
+  rec_smooth<T>(rc, fine, false, false);
 }
 
 // Systems whose V-cycles can share launches: same precision path, smoother and degree.
@@ -518,24 +575,30 @@ void rec_precondition(Recorder &rc, const std::vector<BatchSystem *> &sys) {
   for (int64_t sg : sigs) {
     std::vector<Item> d64, d32;
     std::vector<GVec> cin, cout;
+    const bool cheb = ((sg >> 32) & 0xff) == SA_CHEBYSHEV;
+    const bool fused_z = cheb && (sg & 0xffffffff) > 1;  // the last step writes z
     for (BatchSystem *b : sys) {
       sa_hierarchy *h = b->h;
       if (signature(h) != sg) continue;
       Level &L0 = h->lv[0];
       if (sg >> 40) {
-        cin.push_back(gv(G_CAST_DF, h->n, h->r, nullptr, L0.ff));
-        d32.push_back({h, 0, L0.ff, L0.uf});
+        if (cheb)
+          cin.push_back(gv(G_CAST_CHEB_F, h->n, h->r, L0.sm_invDf, L0.d1f, L0.uf,
+                           (double)(float)L0.cheb_theta, h->opt.degree == 1 ? 1 : 0, L0.ff));
+        else
+          cin.push_back(gv(G_CAST_DF, h->n, h->r, nullptr, L0.ff));
+        d32.push_back({h, 0, L0.ff, L0.uf, fused_z ? h->z : nullptr});
         cout.push_back(gv(G_CAST_FD, h->n, L0.uf, nullptr, h->z));
       } else {
-        d64.push_back({h, 0, h->r, h->z});
+        d64.push_back({h, 0, h->r, h->z, nullptr});
       }
     }
     if (!d32.empty()) {
       rec_vec(rc, cin);
-      rec_vcycle<float>(rc, d32);
-      rec_vec(rc, cout);
+      rec_vcycle<float>(rc, d32, cheb);
+      if (!fused_z) rec_vec(rc, cout);
     }
-    if (!d64.empty()) rec_vcycle<double>(rc, d64);
+    if (!d64.empty()) rec_vcycle<double>(rc, d64, false);
   }
 }
 
@@ -581,9 +644,9 @@ void BatchSolver::ensure(size_t desc_bytes, size_t nsys) {
 void BatchSolver::run(void *recorder, const std::vector<BatchSystem *> &gather) {
   Recorder &rc = *(Recorder *)recorder;
   const size_t nsys = gather.size();
-  std::vector<PcgScalars *> ptrs;
-  for (BatchSystem *b : gather) ptrs.push_back(b->h->S);
-  const size_t ptr_off = rc.put(ptrs.data(), sizeof(PcgScalars *) * nsys);
+  std::vector<GGather> gs;
+  for (BatchSystem *b : gather) gs.push_back({b->h->S + b->s_at, b->rr_part, b->rr_m, 0});
+  const size_t g_off = rc.put(gs.data(), sizeof(GGather) * nsys);
   ensure(rc.buf.size(), nsys);
   std::memcpy(hbuf_, rc.buf.data(), rc.buf.size());
   SA_HIP(hipMemcpyAsync(dbuf_, hbuf_, rc.buf.size(), hipMemcpyHostToDevice, stream_));
@@ -594,14 +657,18 @@ void BatchSolver::run(void *recorder, const std::vector<BatchSystem *> &gather) 
   }
   if (nsys > 0) {
     PcgScalars *dst = (PcgScalars *)gbuf_;
-    k_ggather<<<grid_for((int64_t)nsys), kBlock, 0, stream_>>>(
-        (PcgScalars *const *)(dbuf_ + ptr_off), dst, (int32_t)nsys);
+    k_ggather<<<(unsigned)nsys, kBlock, 0, stream_>>>((const GGather *)(dbuf_ + g_off), dst);
     SA_LAUNCH_CHECK();
-    SA_HIP(hipMemcpyAsync(hS_, dst, sizeof(PcgScalars) * nsys, hipMemcpyDeviceToHost,
-                          stream_));
+    // returns once the stream's work so far is done (the descriptor buffers are free again)
+    readback(hS_, dst, sizeof(PcgScalars) * nsys, stream_);
+  } else {
+    SA_HIP(hipStreamSynchronize(stream_));
   }
-  SA_HIP(hipStreamSynchronize(stream_));
 }
+
+// The part of a system's dot workspace that holds r.r's partials (the others are reused
+// before the gather reads them).
+static double *rr_ws(sa_hierarchy *h) { return h->dws + 2 * dot_ws_size(h->n); }
 
 static void finish_copy(BatchSystem *b, hipStream_t s) {
   sa_hierarchy *h = b->h;
@@ -623,7 +690,8 @@ void BatchSolver::add(BatchSystem *b) {
                         b->loc == SA_DEVICE ? hipMemcpyDeviceToDevice : hipMemcpyHostToDevice,
                         stream_));
   fill_f64(h->x, 0.0, h->n, stream_);
-  fill_i32((int32_t *)h->S, 0, sizeof(PcgScalars) / sizeof(int32_t), stream_);
+  fill_i32((int32_t *)h->S, 0, 2 * sizeof(PcgScalars) / sizeof(int32_t), stream_);
+  b->s_at = 0;
   joining_.push_back(b);
 }
 
@@ -635,8 +703,12 @@ void BatchSolver::tick(std::vector<BatchSystem *> &finished) {
   if (!joining_.empty()) {
     Recorder rc;
     std::vector<DotJob> dj;
-    for (BatchSystem *b : joining_) dj.push_back({b->h->r, b->h->r, b->h->n, &b->h->S->rr, b->h->dws});
-    rec_dots(rc, dj);
+    for (BatchSystem *b : joining_) dj.push_back({b->h->r, b->h->r, b->h->n, rr_ws(b->h)});
+    const std::vector<Parts> parts = rec_dots(rc, dj);
+    for (size_t k = 0; k < joining_.size(); ++k) {
+      joining_[k]->rr_part = parts[k].p;
+      joining_[k]->rr_m = (int32_t)parts[k].m;
+    }
     run(&rc, joining_);
     for (size_t k = 0; k < joining_.size(); ++k) {
       BatchSystem *b = joining_[k];
@@ -675,38 +747,36 @@ void BatchSolver::tick(std::vector<BatchSystem *> &finished) {
     if (b->phase != BatchSystem::kLastHalf) first.push_back(b);
   }
   // second half
-  {
-    std::vector<GVec> g;
-    for (BatchSystem *b : cont_pr) g.push_back(gv(G_COPY_D, b->h->n, b->h->z, nullptr, b->h->zold));
-    rec_vec(rc, g);
-  }
+  for (BatchSystem *b : cont_pr) std::swap(b->h->z, b->h->zold);
   rec_precondition(rc, all);
   {
-    std::vector<DotJob> dj;
-    for (BatchSystem *b : all) dj.push_back({b->h->r, b->h->z, b->h->n, &b->h->S->rho1, b->h->dws});
-    rec_dots(rc, dj);
-  }
-  if (!cont_pr.empty()) {
-    std::vector<GVec> g;
-    std::vector<DotJob> dj;
-    for (BatchSystem *b : cont_pr) {
-      g.push_back(gv(G_VEC_SUB, b->h->n, b->h->z, b->h->zold, b->h->w));
-      dj.push_back({b->h->r, b->h->w, b->h->n, &b->h->S->rw, b->h->dws});
-    }
-    rec_vec(rc, g);
-    rec_dots(rc, dj);
-  }
-  {
-    std::vector<GScal> sc;
-    std::vector<GVec> g;
+    std::vector<GDotRz> segs;
+    std::vector<int32_t> blocks;
+    std::vector<Parts> rz, rw;
     for (BatchSystem *b : all) {
-      const bool fresh = b->fresh;
-      sc.push_back({b->h->S, fresh ? G_INIT : G_BETA, b->pr ? 1 : 0});
-      if (fresh) g.push_back(gv(G_COPY_D, b->h->n, b->h->z, nullptr, b->h->p));
-      else g.push_back(gv(G_UPDATE_P, b->h->n, b->h->z, nullptr, b->h->p, nullptr, 0.0, 0, b->h->S));
+      sa_hierarchy *h = b->h;
+      const int32_t nb = dot_blocks(h->n);
+      double *w1 = h->dws, *w2 = h->dws + dot_ws_size(h->n);
+      const bool with_w = !b->fresh && b->pr;
+      segs.push_back({h->r, h->z, with_w ? h->zold : nullptr, h->n, w1, w2});
+      blocks.push_back(nb);
+      rz.push_back({w1, w1 + nb, nb});
+      rw.push_back({w2, w2 + nb, with_w ? nb : 0});
     }
-    rec_scal(rc, sc);
-    rec_vec(rc, g);
+    rc.add(launch_gdot_rz, segs, blocks);
+    rec_reduce(rc, rz);
+    rec_reduce(rc, rw);
+    std::vector<GP> gp;
+    for (size_t k = 0; k < all.size(); ++k) {
+      BatchSystem *b = all[k];
+      sa_hierarchy *h = b->h;
+      const int next = b->fresh ? b->s_at : b->s_at ^ 1;
+      gp.push_back({h->n, h->p, h->z, rz[k].p, rw[k].p, (int32_t)rz[k].m, b->pr, b->fresh,
+                    h->S + b->s_at, h->S + next});
+      b->s_at = next;
+      b->rr_part = nullptr;
+    }
+    rc.add(launch_gp, gp, blocks);
   }
   // first half of the next iteration
   if (!first.empty()) {
@@ -719,18 +789,27 @@ void BatchSolver::tick(std::vector<BatchSystem *> &finished) {
     }
     rec_spmv(rc, sp, nb);
     std::vector<DotJob> dj;
-    for (BatchSystem *b : first) dj.push_back({b->h->p, b->h->q, b->h->n, &b->h->S->pq, b->h->dws});
-    rec_dots(rc, dj);
-    std::vector<GScal> sc;
-    for (BatchSystem *b : first) sc.push_back({b->h->S, G_ALPHA, 0});
-    rec_scal(rc, sc);
-    std::vector<GVec> g;
-    for (BatchSystem *b : first)
-      g.push_back(gv(G_UPDATE_XR, b->h->n, b->h->p, b->h->q, b->h->x, b->h->r, 0.0, 0, b->h->S));
-    rec_vec(rc, g);
-    dj.clear();
-    for (BatchSystem *b : first) dj.push_back({b->h->r, b->h->r, b->h->n, &b->h->S->rr, b->h->dws});
-    rec_dots(rc, dj);
+    for (BatchSystem *b : first) dj.push_back({b->h->p, b->h->q, b->h->n, b->h->dws});
+    const std::vector<Parts> pq = rec_dots(rc, dj);
+    std::vector<GXr> gx;
+    std::vector<int32_t> blocks;
+    std::vector<Parts> rr;
+    for (size_t k = 0; k < first.size(); ++k) {
+      BatchSystem *b = first[k];
+      sa_hierarchy *h = b->h;
+      double *w = rr_ws(h);
+      const int32_t nbk = dot_blocks(h->n);
+      gx.push_back({h->n, h->x, h->r, h->p, h->q, pq[k].p, (int32_t)pq[k].m, 0, h->S + b->s_at,
+                    w});
+      blocks.push_back(nbk);
+      rr.push_back({w, w + nbk, nbk});
+    }
+    rc.add(launch_gxr, gx, blocks);
+    rec_reduce(rc, rr);
+    for (size_t k = 0; k < first.size(); ++k) {
+      first[k]->rr_part = rr[k].p;
+      first[k]->rr_m = (int32_t)rr[k].m;
+    }
   }
   run(&rc, all);
   std::vector<BatchSystem *> keep;

@@ -287,6 +287,42 @@ struct EpScaleMax {
     if (m != 0ull) atomicMax(slots + (b % kMaxSlots), m);
   }
 };
+// y = A x, the coarse residual of the restriction, and the first smoother step on it
+// (u = 0): Chebyshev d = (invD .* y) / theta, with write_u also u = 0 + d.
+template <class T>
+struct EpRestrictCheb {
+  T *y;
+  const T *invD;
+  T theta;
+  T *d, *u;
+  bool write_u;
+  struct Pre {
+    T invD;
+  };
+  __device__ Pre load(int32_t i) const { return {invD[i]}; }
+  __device__ void store(int32_t i, T s, const Pre &p) const {
+    y[i] = s;
+    const T di = (p.invD * s) / theta;
+    d[i] = di;
+    if (write_u) u[i] = T(0) + di;
+  }
+};
+// The same with Jacobi: u = 0 + w (invD .* y).
+template <class T>
+struct EpRestrictJacobi {
+  T *y;
+  const T *invD;
+  T w;
+  T *u;
+  struct Pre {
+    T invD;
+  };
+  __device__ Pre load(int32_t i) const { return {invD[i]}; }
+  __device__ void store(int32_t i, T s, const Pre &p) const {
+    y[i] = s;
+    u[i] = T(0) + w * (p.invD * s);
+  }
+};
 template <class T>
 struct EpResid {
   const T *f;
@@ -327,6 +363,7 @@ struct EpChebStep {
   T *rout, *u, *dout;
   T c1, c2;
   bool uzero, last;
+  double *z;  // the last step's u in FP64 too (null: not wanted)
   struct Pre {
     T d, rin, invD, u;
   };
@@ -340,7 +377,9 @@ struct EpChebStep {
     rout[i] = ri;
     T dn = c1 * di + c2 * (p.invD * ri);
     if (last) {
-      u[i] = ui + dn;
+      const T un = ui + dn;
+      u[i] = un;
+      if (z) z[i] = (double)un;
     } else {
       u[i] = ui;
       dout[i] = dn;
@@ -379,18 +418,6 @@ __device__ __forceinline__ void jacobi_first_at(int32_t i, const T *f, const T *
                                                 T *u) {
   u[i] = T(0) + w * (invD[i] * f[i]);
 }
-__device__ __forceinline__ void update_xr_at(int32_t i, double *x, double *r, const double *p,
-                                             const double *q, double a) {
-  x[i] = x[i] + a * p[i];
-  r[i] = r[i] - a * q[i];
-}
-__device__ __forceinline__ void update_p_at(int32_t i, double *p, const double *z, double beta) {
-  p[i] = z[i] + beta * p[i];
-}
-__device__ __forceinline__ void vec_sub_at(int32_t i, const double *z, const double *zo,
-                                           double *w) {
-  w[i] = z[i] - zo[i];
-}
 
 // ---- canonical inner product: one block of 4096 terms --------------------------------------
 // Lane t of 256 sums terms t + 256 m (m = 0..15) sequentially from 0 (products x[i]*y[i], or
@@ -415,31 +442,174 @@ __device__ __forceinline__ void dot_block(int64_t blk, const double *__restrict_
   if (t == 0) *out = sh[0];
 }
 
+// The two inner products r.z and r.(z - zold) of one block (zold null: the first only).
+__device__ __forceinline__ void dot_rz_block(int64_t blk, const double *__restrict__ r,
+                                             const double *__restrict__ z,
+                                             const double *__restrict__ zold, int64_t n,
+                                             double *__restrict__ out, double *__restrict__ outw,
+                                             double *sh) {
+  const int t = threadIdx.x;
+  const int64_t base = blk * 4096 + t;
+  double acc = 0.0, accw = 0.0;
+#pragma unroll
+  for (int m = 0; m < 16; ++m) {
+    const int64_t i = base + 256 * m;
+    if (i < n) {
+      const double ri = r[i], zi = z[i];
+      acc += ri * zi;
+      if (zold) accw += ri * (zi - zold[i]);
+    }
+  }
+  sh[t] = acc;
+  __syncthreads();
+  for (int w = kBlock / 2; w >= 1; w >>= 1) {
+    if (t < w) sh[t] = sh[t] + sh[t + w];
+    __syncthreads();
+  }
+  if (t == 0) *out = sh[0];
+  if (!zold) return;  // uniform
+  __syncthreads();
+  sh[t] = accw;
+  __syncthreads();
+  for (int w = kBlock / 2; w >= 1; w >>= 1) {
+    if (t < w) sh[t] = sh[t] + sh[t + w];
+    __syncthreads();
+  }
+  if (t == 0) *outw = sh[0];
+}
+
+// The last stage of the canonical inner product (m <= 4096 partials), taken by every block
+// that needs the value instead of by a launch of its own; all threads get the sum.
+constexpr int32_t kDotFinal = 4096;
+__device__ __forceinline__ double dot_final(const double *__restrict__ part, int32_t m,
+                                            double *sh) {
+  const int t = threadIdx.x;
+  double acc = 0.0;
+  for (int32_t i = t; i < m; i += kBlock) acc += part[i];
+  sh[t] = acc;
+  __syncthreads();
+  for (int w = kBlock / 2; w >= 1; w >>= 1) {
+    if (t < w) sh[t] = sh[t] + sh[t + w];
+    __syncthreads();
+  }
+  const double s = sh[0];
+  __syncthreads();
+  return s;
+}
+
 // ---- dense GEMV row (coarsest level): one wavefront per row --------------------------------
+template <class T>
 __device__ __forceinline__ void gemv_row(int64_t row, int32_t n, const double *__restrict__ M,
-                                         const double *__restrict__ x,
-                                         double *__restrict__ y) {
+                                         const T *__restrict__ x, T *__restrict__ y) {
   const int lane = threadIdx.x & 63;
   const double *m = M + row * n;
   double acc = 0.0;
-  for (int32_t j = lane; j < n; j += 64) acc += m[j] * x[j];
+  for (int32_t j = lane; j < n; j += 64) acc += m[j] * (double)x[j];
   for (int off = 32; off >= 1; off >>= 1) acc += __shfl_down(acc, off, 64);
-  if (lane == 0) y[row] = acc;
+  if (lane == 0) y[row] = (T)acc;
 }
 
-// ---- PCG scalar steps ------------------------------------------------------------------------
-__device__ __forceinline__ void pcg_alpha_on(PcgScalars *S) {
-  if (!(S->pq > 0.0)) S->err = 1;
-  S->alpha = S->rho / S->pq;
+// ---- PCG steps ---------------------------------------------------------------------------------
+// What a launch of CG work costs beyond its vectors is about 4.5 us, so the scalar steps and
+// the last stages of the inner products are not launches of their own: the blocks that use
+// alpha or beta each reduce the partials again (4 KB at n = 2M).  The scalars alternate
+// between two sets, because every block reads rho while block 0 writes the next one.
+
+// First smoother step of the next preconditioner application on the new residual.
+struct FirstNone {
+  __device__ void operator()(int64_t, double) const {}
+};
+struct FirstCheb64 {
+  const double *invD;
+  double theta;
+  double *d, *u;
+  bool write_u;
+  __device__ void operator()(int64_t i, double r) const {
+    const double di = (invD[i] * r) / theta;
+    d[i] = di;
+    if (write_u) u[i] = 0.0 + di;
+  }
+};
+struct FirstCheb32 {
+  float *f;
+  const float *invD;
+  float theta;
+  float *d, *u;
+  bool write_u;
+  __device__ void operator()(int64_t i, double r) const {
+    const float ri = (float)r;
+    f[i] = ri;
+    const float di = (invD[i] * ri) / theta;
+    d[i] = di;
+    if (write_u) u[i] = 0.0f + di;
+  }
+};
+
+// alpha = rho / p.q (partials part[0..m)), x += alpha p, r -= alpha q, and the block's share
+// of the new r.r: block blk takes the 4096 elements of its block of the inner product.
+template <class First>
+__device__ __forceinline__ void pcg_xr_block(int64_t blk, int64_t n, double *__restrict__ x,
+                                             double *__restrict__ r,
+                                             const double *__restrict__ p,
+                                             const double *__restrict__ q,
+                                             const double *__restrict__ part, int32_t m,
+                                             PcgScalars *S, double *__restrict__ out,
+                                             const First &first, double *sh) {
+  const int t = threadIdx.x;
+  const double pq = dot_final(part, m, sh);
+  const double alpha = S->rho / pq;
+  if (blk == 0 && t == 0) {
+    if (!(pq > 0.0)) S->err = 1;
+    S->pq = pq;
+    S->alpha = alpha;
+  }
+  const int64_t base = blk * 4096 + t;
+  double acc = 0.0;
+#pragma unroll 8
+  for (int k = 0; k < 16; ++k) {
+    const int64_t i = base + 256 * k;
+    if (i < n) {
+      x[i] = x[i] + alpha * p[i];
+      const double ri = r[i] - alpha * q[i];
+      r[i] = ri;
+      acc += ri * ri;
+      first(i, ri);
+    }
+  }
+  sh[t] = acc;
+  __syncthreads();
+  for (int w = kBlock / 2; w >= 1; w >>= 1) {
+    if (t < w) sh[t] = sh[t] + sh[t + w];
+    __syncthreads();
+  }
+  if (t == 0) out[blk] = sh[0];
 }
-__device__ __forceinline__ void pcg_beta_on(PcgScalars *S, bool pr) {
-  if (!(S->rho1 > 0.0)) S->err = 2;
-  S->beta = (pr ? S->rw : S->rho1) / S->rho;
-  S->rho = S->rho1;
-}
-__device__ __forceinline__ void pcg_init_on(PcgScalars *S) {
-  if (!(S->rho1 > 0.0)) S->err = 2;
-  S->rho = S->rho1;
+
+// rho1 = r.z and, with pr, rw = r.(z - zold) from their partials; beta; p = z + beta p (init:
+// p = z).  Reads the scalars cur, writes next (init: the same set).
+__device__ __forceinline__ void pcg_p_block(int64_t blk, int64_t n, double *__restrict__ p,
+                                            const double *__restrict__ z,
+                                            const double *__restrict__ part,
+                                            const double *__restrict__ partw, int32_t m,
+                                            const PcgScalars *cur, PcgScalars *next, bool pr,
+                                            bool init, double *sh) {
+  const int t = threadIdx.x;
+  const double rho1 = dot_final(part, m, sh);
+  const double rw = pr && !init ? dot_final(partw, m, sh) : 0.0;
+  const double beta = init ? 0.0 : (pr ? rw : rho1) / cur->rho;
+  const int64_t base = blk * 4096 + t;
+#pragma unroll 8
+  for (int k = 0; k < 16; ++k) {
+    const int64_t i = base + 256 * k;
+    if (i < n) p[i] = init ? z[i] : z[i] + beta * p[i];
+  }
+  if (blk == 0 && t == 0) {
+    next->rho1 = rho1;
+    next->rw = rw;
+    next->beta = beta;
+    next->rho = rho1;
+    next->err = !(rho1 > 0.0) ? 2 : cur->err;
+  }
 }
 
 }  // namespace sa

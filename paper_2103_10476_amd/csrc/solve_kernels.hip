@@ -300,8 +300,17 @@ void spmv_cheb_start(const SpmvArgs<T> &a, const T *f, const T *invD, T theta, T
 }
 template <class T>
 void spmv_cheb_step(const SpmvArgs<T> &a, const T *rin, T *rout, const T *invD, T c1, T c2,
-                    T *u, bool uzero, T *dout, bool last, hipStream_t s) {
-  launch_spmv(a, EpChebStep<T>{a.x, rin, invD, rout, u, dout, c1, c2, uzero, last}, s);
+                    T *u, bool uzero, T *dout, bool last, double *z, hipStream_t s) {
+  launch_spmv(a, EpChebStep<T>{a.x, rin, invD, rout, u, dout, c1, c2, uzero, last, z}, s);
+}
+template <class T>
+void spmv_restrict_cheb(const SpmvArgs<T> &a, T *y, const T *invD, T theta, T *d, T *u,
+                        bool write_u, hipStream_t s) {
+  launch_spmv(a, EpRestrictCheb<T>{y, invD, theta, d, u, write_u}, s);
+}
+template <class T>
+void spmv_restrict_jacobi(const SpmvArgs<T> &a, T *y, const T *invD, T w, T *u, hipStream_t s) {
+  launch_spmv(a, EpRestrictJacobi<T>{y, invD, w, u}, s);
 }
 template <class T>
 void spmv_jacobi(const SpmvArgs<T> &a, const T *f, const T *invD, T w, T *u2, hipStream_t s) {
@@ -318,7 +327,11 @@ void spmv_jacobi(const SpmvArgs<T> &a, const T *f, const T *invD, T w, T *u2, hi
   template void spmv_cheb_start<T>(const SpmvArgs<T> &, const T *, const T *, T, T *, T *,   \
                                    hipStream_t);                                            \
   template void spmv_cheb_step<T>(const SpmvArgs<T> &, const T *, T *, const T *, T, T, T *, \
-                                  bool, T *, bool, hipStream_t);                            \
+                                  bool, T *, bool, double *, hipStream_t);                  \
+  template void spmv_restrict_cheb<T>(const SpmvArgs<T> &, T *, const T *, T, T *, T *, bool, \
+                                      hipStream_t);                                         \
+  template void spmv_restrict_jacobi<T>(const SpmvArgs<T> &, T *, const T *, T, T *,        \
+                                        hipStream_t);                                       \
   template void spmv_jacobi<T>(const SpmvArgs<T> &, const T *, const T *, T, T *, hipStream_t);
 SA_INST_SPMV(double)
 SA_INST_SPMV(float)
@@ -427,60 +440,115 @@ void dot_f64(const double *x, const double *y, int64_t n, double *res, double *w
   }
 }
 
-// ---- dense GEMV for the coarsest level (one wavefront per row) -------------------------
-__global__ __launch_bounds__(kBlock) void k_gemv(int32_t n, const double *__restrict__ M,
-                                                 const double *__restrict__ x,
-                                                 double *__restrict__ y) {
-  const int64_t row = (int64_t)blockIdx.x * (kBlock / 64) + (threadIdx.x >> 6);
-  if (row < n) gemv_row(row, n, M, x, y);
+// Stages of partials until at most kDotFinal are left (one stage up to 16.7M terms).
+static DotParts reduce_parts(double *part, int64_t nb, double *ws, hipStream_t s) {
+  while (nb > kDotFinal) {
+    const int64_t nb2 = ceil_div(nb, 4096);
+    k_dot_stage<<<(unsigned)nb2, kBlock, 0, s>>>(part, nullptr, nb, ws);
+    SA_LAUNCH_CHECK();
+    part = ws;
+    ws += nb2;
+    nb = nb2;
+  }
+  return DotParts{part, (int32_t)nb};
 }
-void gemv_f64(int32_t n, const double *M, const double *x, double *y, hipStream_t s) {
-  if (n <= 0) return;
-  k_gemv<<<(unsigned)ceil_div(n, kBlock / 64), kBlock, 0, s>>>(n, M, x, y);
+static int64_t dot_blocks(int64_t n) { return n > 0 ? ceil_div(n, 4096) : 1; }
+
+DotParts dot_parts(const double *x, const double *y, int64_t n, double *ws, hipStream_t s) {
+  const int64_t nb = dot_blocks(n);
+  k_dot_stage<<<(unsigned)nb, kBlock, 0, s>>>(x, y, n, ws);
   SA_LAUNCH_CHECK();
+  return reduce_parts(ws, nb, ws + nb, s);
+}
+__global__ __launch_bounds__(kBlock) void k_dot_rz(const double *__restrict__ r,
+                                                   const double *__restrict__ z,
+                                                   const double *__restrict__ zold, int64_t n,
+                                                   double *__restrict__ part,
+                                                   double *__restrict__ partw) {
+  __shared__ double sh[kBlock];
+  dot_rz_block(blockIdx.x, r, z, zold, n, part + blockIdx.x, zold ? partw + blockIdx.x : nullptr,
+               sh);
+}
+void dot_rz_parts(const double *r, const double *z, const double *zold, int64_t n, double *ws,
+                  DotParts *rz, DotParts *rw, hipStream_t s) {
+  const int64_t nb = dot_blocks(n), tot = dot_ws_size(n);
+  double *w2 = ws + tot;
+  k_dot_rz<<<(unsigned)nb, kBlock, 0, s>>>(r, z, zold, n, ws, w2);
+  SA_LAUNCH_CHECK();
+  *rz = reduce_parts(ws, nb, ws + nb, s);
+  *rw = zold ? reduce_parts(w2, nb, w2 + nb, s) : DotParts{nullptr, 0};
 }
 
+// ---- dense GEMV for the coarsest level (one wavefront per row) -------------------------
+template <class T>
+__global__ __launch_bounds__(kBlock) void k_gemv(int32_t n, const double *__restrict__ M,
+                                                 const T *__restrict__ x, T *__restrict__ y) {
+  const int64_t row = (int64_t)blockIdx.x * (kBlock / 64) + (threadIdx.x >> 6);
+  if (row < n) gemv_row<T>(row, n, M, x, y);
+}
+template <class T>
+void gemv(int32_t n, const double *M, const T *x, T *y, hipStream_t s) {
+  if (n <= 0) return;
+  k_gemv<T><<<(unsigned)ceil_div(n, kBlock / 64), kBlock, 0, s>>>(n, M, x, y);
+  SA_LAUNCH_CHECK();
+}
+template void gemv<double>(int32_t, const double *, const double *, double *, hipStream_t);
+template void gemv<float>(int32_t, const double *, const float *, float *, hipStream_t);
+
 // ---- PCG updates ----------------------------------------------------------------------------
-__global__ void k_update_xr(int32_t n, double *x, double *r, const double *p, const double *q,
-                            const PcgScalars *S) {
-  int32_t i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) update_xr_at(i, x, r, p, q, S->alpha);
+template <class First>
+__global__ __launch_bounds__(kBlock) void k_pcg_xr(int64_t n, double *x, double *r,
+                                                   const double *p, const double *q,
+                                                   const double *part, int32_t m, PcgScalars *S,
+                                                   double *out, First first) {
+  __shared__ double sh[kBlock];
+  pcg_xr_block(blockIdx.x, n, x, r, p, q, part, m, S, out, first, sh);
 }
-void pcg_update_xr(int32_t n, double *x, double *r, const double *p, const double *q,
-                   const PcgScalars *S, hipStream_t s) {
-  k_update_xr<<<grid_for(n), kBlock, 0, s>>>(n, x, r, p, q, S);
+template <class First>
+DotParts pcg_update_xr(int64_t n, double *x, double *r, const double *p, const double *q,
+                       const DotParts &pq, PcgScalars *S, double *ws, const First &first,
+                       hipStream_t s) {
+  const int64_t nb = dot_blocks(n);
+  k_pcg_xr<First><<<(unsigned)nb, kBlock, 0, s>>>(n, x, r, p, q, pq.p, pq.m, S, ws, first);
+  SA_LAUNCH_CHECK();
+  return reduce_parts(ws, nb, ws + nb, s);
+}
+template DotParts pcg_update_xr<FirstNone>(int64_t, double *, double *, const double *,
+                                           const double *, const DotParts &, PcgScalars *,
+                                           double *, const FirstNone &, hipStream_t);
+template DotParts pcg_update_xr<FirstCheb64>(int64_t, double *, double *, const double *,
+                                             const double *, const DotParts &, PcgScalars *,
+                                             double *, const FirstCheb64 &, hipStream_t);
+template DotParts pcg_update_xr<FirstCheb32>(int64_t, double *, double *, const double *,
+                                             const double *, const DotParts &, PcgScalars *,
+                                             double *, const FirstCheb32 &, hipStream_t);
+__global__ __launch_bounds__(kBlock) void k_pcg_p(int64_t n, double *p, const double *z,
+                                                  const double *part, const double *partw,
+                                                  int32_t m, const PcgScalars *cur,
+                                                  PcgScalars *next, bool pr, bool init) {
+  __shared__ double sh[kBlock];
+  pcg_p_block(blockIdx.x, n, p, z, part, partw, m, cur, next, pr, init, sh);
+}
+void pcg_update_p(int64_t n, double *p, const double *z, const DotParts &rz, const DotParts &rw,
+                  const PcgScalars *cur, PcgScalars *next, bool pr, bool init, hipStream_t s) {
+  k_pcg_p<<<(unsigned)dot_blocks(n), kBlock, 0, s>>>(n, p, z, rz.p, rw.p, rz.m, cur, next, pr,
+                                                    init);
   SA_LAUNCH_CHECK();
 }
-__global__ void k_update_p(int32_t n, double *p, const double *z, const PcgScalars *S) {
-  int32_t i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) update_p_at(i, p, z, S->beta);
+// r.r from its partials into S, then S to the host's words and their tag.
+__global__ __launch_bounds__(kBlock) void k_pcg_post(const double *part, int32_t m, PcgScalars *S,
+                                                     HostWords host) {
+  __shared__ double sh[kBlock];
+  const double rr = dot_final(part, m, sh);
+  if (threadIdx.x == 0) S->rr = rr;
+  __syncthreads();
+  post_words(host, (const uint32_t *)S, (int32_t)(sizeof(PcgScalars) / 4));
 }
-void pcg_update_p(int32_t n, double *p, const double *z, const PcgScalars *S, hipStream_t s) {
-  k_update_p<<<grid_for(n), kBlock, 0, s>>>(n, p, z, S);
+void pcg_read(PcgScalars *host, const DotParts &rr, PcgScalars *S, hipStream_t s) {
+  const HostWords w = host_words();
+  k_pcg_post<<<1, kBlock, 0, s>>>(rr.p, rr.m, S, w);
   SA_LAUNCH_CHECK();
-}
-__global__ void k_vec_sub(int32_t n, const double *z, const double *zo, double *w) {
-  int32_t i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) vec_sub_at(i, z, zo, w);
-}
-void vec_sub(int32_t n, const double *z, const double *zold, double *w, hipStream_t s) {
-  k_vec_sub<<<grid_for(n), kBlock, 0, s>>>(n, z, zold, w);
-  SA_LAUNCH_CHECK();
-}
-__global__ void k_pcg_alpha(PcgScalars *S) { pcg_alpha_on(S); }
-void pcg_alpha(PcgScalars *S, hipStream_t s) {
-  k_pcg_alpha<<<1, 1, 0, s>>>(S);
-  SA_LAUNCH_CHECK();
-}
-__global__ void k_pcg_beta(PcgScalars *S, bool pr) { pcg_beta_on(S, pr); }
-void pcg_beta(PcgScalars *S, bool pr, hipStream_t s) {
-  k_pcg_beta<<<1, 1, 0, s>>>(S, pr);
-  SA_LAUNCH_CHECK();
-}
-__global__ void k_pcg_init(PcgScalars *S) { pcg_init_on(S); }
-void pcg_init_rho(PcgScalars *S, hipStream_t s) {
-  k_pcg_init<<<1, 1, 0, s>>>(S);
-  SA_LAUNCH_CHECK();
+  host_words_wait(w, host, sizeof(PcgScalars), s);
 }
 
 }  // namespace sa
