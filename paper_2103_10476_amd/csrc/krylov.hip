@@ -9,12 +9,12 @@ namespace sa {
 
 // ---- GMRES building blocks ----------------------------------------------------------------
 // Multi-vector canonical dot: the same blocks and trees as dot_f64, one per vector (grid.y).
-__global__ __launch_bounds__(kBlock) void k_mdot_stage(const double *__restrict__ x,
+__global__ __launch_bounds__(kDotBlock) void k_mdot_stage(const double *__restrict__ x,
                                                        int64_t ldx,
                                                        const double *__restrict__ y, int64_t m,
                                                        double *__restrict__ part,
                                                        int64_t ldp) {
-  __shared__ double sh[kBlock];
+  __shared__ DotShared sh;
   const int64_t v = blockIdx.y;
   dot_block(blockIdx.x, x + v * ldx, y, m, part + v * ldp + blockIdx.x, sh);
 }
@@ -31,7 +31,7 @@ void multi_dot_f64(const double *V, int64_t ldv, int32_t nv, const double *w, in
     if (nb < 1) nb = 1;
     double *dst = (nb == 1) ? c : out;
     const int64_t ldo = (nb == 1) ? 1 : nb;
-    k_mdot_stage<<<dim3((unsigned)nb, (unsigned)nv), kBlock, 0, s>>>(in, ldin, iny, m, dst, ldo);
+    k_mdot_stage<<<dim3((unsigned)nb, (unsigned)nv), kDotBlock, 0, s>>>(in, ldin, iny, m, dst, ldo);
     SA_LAUNCH_CHECK();
     if (nb == 1) break;
     in = out;

@@ -131,9 +131,9 @@ struct GDot {
   int64_t n;
   double *out;  // block k writes out[k]
 };
-__global__ __launch_bounds__(kBlock) void k_gdot(const GDot *segs, const int32_t *boff,
+__global__ __launch_bounds__(kDotBlock) void k_gdot(const GDot *segs, const int32_t *boff,
                                                  int32_t nseg) {
-  __shared__ double sh[kBlock];
+  __shared__ DotShared sh;
   const int32_t s = find_seg(boff, nseg, blockIdx.x);
   const GDot a = segs[s];
   const int64_t blk = blockIdx.x - boff[s];
@@ -145,9 +145,9 @@ struct GDotRz {
   int64_t n;
   double *out, *outw;
 };
-__global__ __launch_bounds__(kBlock) void k_gdot_rz(const GDotRz *segs, const int32_t *boff,
+__global__ __launch_bounds__(kDotBlock) void k_gdot_rz(const GDotRz *segs, const int32_t *boff,
                                                     int32_t nseg) {
-  __shared__ double sh[kBlock];
+  __shared__ DotShared sh;
   const int32_t s = find_seg(boff, nseg, blockIdx.x);
   const GDotRz a = segs[s];
   const int64_t blk = blockIdx.x - boff[s];
@@ -162,9 +162,9 @@ struct GXr {
   PcgScalars *S;
   double *out;
 };
-__global__ __launch_bounds__(kBlock) void k_gxr(const GXr *segs, const int32_t *boff,
+__global__ __launch_bounds__(kDotBlock) void k_gxr(const GXr *segs, const int32_t *boff,
                                                 int32_t nseg) {
-  __shared__ double sh[kBlock];
+  __shared__ DotShared sh;
   const int32_t s = find_seg(boff, nseg, blockIdx.x);
   const GXr a = segs[s];
   pcg_xr_block(blockIdx.x - boff[s], a.n, a.x, a.r, a.p, a.q, a.part, a.m, a.S, a.out,
@@ -180,9 +180,9 @@ struct GP {
   const PcgScalars *cur;
   PcgScalars *next;
 };
-__global__ __launch_bounds__(kBlock) void k_gp(const GP *segs, const int32_t *boff,
+__global__ __launch_bounds__(kDotBlock) void k_gp(const GP *segs, const int32_t *boff,
                                                int32_t nseg) {
-  __shared__ double sh[kBlock];
+  __shared__ DotShared sh;
   const int32_t s = find_seg(boff, nseg, blockIdx.x);
   const GP a = segs[s];
   pcg_p_block(blockIdx.x - boff[s], a.n, a.p, a.z, a.part, a.partw, a.m, a.cur, a.next, a.pr,
@@ -196,8 +196,8 @@ struct GGather {
   const double *part;
   int32_t m, pad;
 };
-__global__ __launch_bounds__(kBlock) void k_ggather(const GGather *segs, PcgScalars *dst) {
-  __shared__ double sh[kBlock];
+__global__ __launch_bounds__(kDotBlock) void k_ggather(const GGather *segs, PcgScalars *dst) {
+  __shared__ DotShared sh;
   const GGather a = segs[blockIdx.x];
   if (a.part) {  // block-uniform
     const double rr = dot_final(a.part, a.m, sh);
@@ -233,19 +233,19 @@ void launch_ggemv(const void *segs, const int32_t *boff, int32_t nseg, int32_t b
 }
 void launch_gdot(const void *segs, const int32_t *boff, int32_t nseg, int32_t blocks,
                  hipStream_t s) {
-  k_gdot<<<(unsigned)blocks, kBlock, 0, s>>>((const GDot *)segs, boff, nseg);
+  k_gdot<<<(unsigned)blocks, kDotBlock, 0, s>>>((const GDot *)segs, boff, nseg);
 }
 void launch_gdot_rz(const void *segs, const int32_t *boff, int32_t nseg, int32_t blocks,
                     hipStream_t s) {
-  k_gdot_rz<<<(unsigned)blocks, kBlock, 0, s>>>((const GDotRz *)segs, boff, nseg);
+  k_gdot_rz<<<(unsigned)blocks, kDotBlock, 0, s>>>((const GDotRz *)segs, boff, nseg);
 }
 void launch_gxr(const void *segs, const int32_t *boff, int32_t nseg, int32_t blocks,
                 hipStream_t s) {
-  k_gxr<<<(unsigned)blocks, kBlock, 0, s>>>((const GXr *)segs, boff, nseg);
+  k_gxr<<<(unsigned)blocks, kDotBlock, 0, s>>>((const GXr *)segs, boff, nseg);
 }
 void launch_gp(const void *segs, const int32_t *boff, int32_t nseg, int32_t blocks,
                hipStream_t s) {
-  k_gp<<<(unsigned)blocks, kBlock, 0, s>>>((const GP *)segs, boff, nseg);
+  k_gp<<<(unsigned)blocks, kDotBlock, 0, s>>>((const GP *)segs, boff, nseg);
 }
 
 // Builds the descriptor buffer of one tick.
@@ -657,7 +657,7 @@ void BatchSolver::run(void *recorder, const std::vector<BatchSystem *> &gather) 
   }
   if (nsys > 0) {
     PcgScalars *dst = (PcgScalars *)gbuf_;
-    k_ggather<<<(unsigned)nsys, kBlock, 0, stream_>>>((const GGather *)(dbuf_ + g_off), dst);
+    k_ggather<<<(unsigned)nsys, kDotBlock, 0, stream_>>>((const GGather *)(dbuf_ + g_off), dst);
     SA_LAUNCH_CHECK();
     // returns once the stream's work so far is done (the descriptor buffers are free again)
     readback(hS_, dst, sizeof(PcgScalars) * nsys, stream_);

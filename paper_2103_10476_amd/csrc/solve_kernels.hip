@@ -401,10 +401,10 @@ void cast_f32_to_f64(const float *a, double *b, int64_t n, hipStream_t s) {
 // ---- canonical inner product ------------------------------------------------------------
 // Blocks of 4096 terms; lane t of 256 sums terms t + 256 m (m = 0..15) sequentially from 0,
 // then s[t] += s[t + w] for w = 128 ... 1; block results are reduced by the same rule.
-__global__ __launch_bounds__(kBlock) void k_dot_stage(const double *__restrict__ x,
+__global__ __launch_bounds__(kDotBlock) void k_dot_stage(const double *__restrict__ x,
                                                       const double *__restrict__ y,
                                                       int64_t n, double *__restrict__ part) {
-  __shared__ double sh[kBlock];
+  __shared__ DotShared sh;
   dot_block(blockIdx.x, x, y, n, part + blockIdx.x, sh);
 }
 
@@ -430,7 +430,7 @@ void dot_f64(const double *x, const double *y, int64_t n, double *res, double *w
     int64_t nb = ceil_div(m, 4096);
     if (nb < 1) nb = 1;
     double *dst = (nb == 1) ? res : out;
-    k_dot_stage<<<(unsigned)nb, kBlock, 0, s>>>(in, iny, m, dst);
+    k_dot_stage<<<(unsigned)nb, kDotBlock, 0, s>>>(in, iny, m, dst);
     SA_LAUNCH_CHECK();
     if (nb == 1) break;
     in = out;
@@ -444,7 +444,7 @@ void dot_f64(const double *x, const double *y, int64_t n, double *res, double *w
 static DotParts reduce_parts(double *part, int64_t nb, double *ws, hipStream_t s) {
   while (nb > kDotFinal) {
     const int64_t nb2 = ceil_div(nb, 4096);
-    k_dot_stage<<<(unsigned)nb2, kBlock, 0, s>>>(part, nullptr, nb, ws);
+    k_dot_stage<<<(unsigned)nb2, kDotBlock, 0, s>>>(part, nullptr, nb, ws);
     SA_LAUNCH_CHECK();
     part = ws;
     ws += nb2;
@@ -456,16 +456,16 @@ static int64_t dot_blocks(int64_t n) { return n > 0 ? ceil_div(n, 4096) : 1; }
 
 DotParts dot_parts(const double *x, const double *y, int64_t n, double *ws, hipStream_t s) {
   const int64_t nb = dot_blocks(n);
-  k_dot_stage<<<(unsigned)nb, kBlock, 0, s>>>(x, y, n, ws);
+  k_dot_stage<<<(unsigned)nb, kDotBlock, 0, s>>>(x, y, n, ws);
   SA_LAUNCH_CHECK();
   return reduce_parts(ws, nb, ws + nb, s);
 }
-__global__ __launch_bounds__(kBlock) void k_dot_rz(const double *__restrict__ r,
+__global__ __launch_bounds__(kDotBlock) void k_dot_rz(const double *__restrict__ r,
                                                    const double *__restrict__ z,
                                                    const double *__restrict__ zold, int64_t n,
                                                    double *__restrict__ part,
                                                    double *__restrict__ partw) {
-  __shared__ double sh[kBlock];
+  __shared__ DotShared sh;
   dot_rz_block(blockIdx.x, r, z, zold, n, part + blockIdx.x, zold ? partw + blockIdx.x : nullptr,
                sh);
 }
@@ -473,7 +473,7 @@ void dot_rz_parts(const double *r, const double *z, const double *zold, int64_t 
                   DotParts *rz, DotParts *rw, hipStream_t s) {
   const int64_t nb = dot_blocks(n), tot = dot_ws_size(n);
   double *w2 = ws + tot;
-  k_dot_rz<<<(unsigned)nb, kBlock, 0, s>>>(r, z, zold, n, ws, w2);
+  k_dot_rz<<<(unsigned)nb, kDotBlock, 0, s>>>(r, z, zold, n, ws, w2);
   SA_LAUNCH_CHECK();
   *rz = reduce_parts(ws, nb, ws + nb, s);
   *rw = zold ? reduce_parts(w2, nb, w2 + nb, s) : DotParts{nullptr, 0};
@@ -497,11 +497,11 @@ template void gemv<float>(int32_t, const double *, const float *, float *, hipSt
 
 // ---- PCG updates ----------------------------------------------------------------------------
 template <class First>
-__global__ __launch_bounds__(kBlock) void k_pcg_xr(int64_t n, double *x, double *r,
+__global__ __launch_bounds__(kDotBlock) void k_pcg_xr(int64_t n, double *x, double *r,
                                                    const double *p, const double *q,
                                                    const double *part, int32_t m, PcgScalars *S,
                                                    double *out, First first) {
-  __shared__ double sh[kBlock];
+  __shared__ DotShared sh;
   pcg_xr_block(blockIdx.x, n, x, r, p, q, part, m, S, out, first, sh);
 }
 template <class First>
@@ -509,7 +509,7 @@ DotParts pcg_update_xr(int64_t n, double *x, double *r, const double *p, const d
                        const DotParts &pq, PcgScalars *S, double *ws, const First &first,
                        hipStream_t s) {
   const int64_t nb = dot_blocks(n);
-  k_pcg_xr<First><<<(unsigned)nb, kBlock, 0, s>>>(n, x, r, p, q, pq.p, pq.m, S, ws, first);
+  k_pcg_xr<First><<<(unsigned)nb, kDotBlock, 0, s>>>(n, x, r, p, q, pq.p, pq.m, S, ws, first);
   SA_LAUNCH_CHECK();
   return reduce_parts(ws, nb, ws + nb, s);
 }
@@ -522,23 +522,23 @@ template DotParts pcg_update_xr<FirstCheb64>(int64_t, double *, double *, const 
 template DotParts pcg_update_xr<FirstCheb32>(int64_t, double *, double *, const double *,
                                              const double *, const DotParts &, PcgScalars *,
                                              double *, const FirstCheb32 &, hipStream_t);
-__global__ __launch_bounds__(kBlock) void k_pcg_p(int64_t n, double *p, const double *z,
+__global__ __launch_bounds__(kDotBlock) void k_pcg_p(int64_t n, double *p, const double *z,
                                                   const double *part, const double *partw,
                                                   int32_t m, const PcgScalars *cur,
                                                   PcgScalars *next, bool pr, bool init) {
-  __shared__ double sh[kBlock];
+  __shared__ DotShared sh;
   pcg_p_block(blockIdx.x, n, p, z, part, partw, m, cur, next, pr, init, sh);
 }
 void pcg_update_p(int64_t n, double *p, const double *z, const DotParts &rz, const DotParts &rw,
                   const PcgScalars *cur, PcgScalars *next, bool pr, bool init, hipStream_t s) {
-  k_pcg_p<<<(unsigned)dot_blocks(n), kBlock, 0, s>>>(n, p, z, rz.p, rw.p, rz.m, cur, next, pr,
+  k_pcg_p<<<(unsigned)dot_blocks(n), kDotBlock, 0, s>>>(n, p, z, rz.p, rw.p, rz.m, cur, next, pr,
                                                     init);
   SA_LAUNCH_CHECK();
 }
 // r.r from its partials into S, then S to the host's words and their tag.
-__global__ __launch_bounds__(kBlock) void k_pcg_post(const double *part, int32_t m, PcgScalars *S,
+__global__ __launch_bounds__(kDotBlock) void k_pcg_post(const double *part, int32_t m, PcgScalars *S,
                                                      HostWords host) {
-  __shared__ double sh[kBlock];
+  __shared__ DotShared sh;
   const double rr = dot_final(part, m, sh);
   if (threadIdx.x == 0) S->rr = rr;
   __syncthreads();
@@ -546,7 +546,7 @@ __global__ __launch_bounds__(kBlock) void k_pcg_post(const double *part, int32_t
 }
 void pcg_read(PcgScalars *host, const DotParts &rr, PcgScalars *S, hipStream_t s) {
   const HostWords w = host_words();
-  k_pcg_post<<<1, kBlock, 0, s>>>(rr.p, rr.m, S, w);
+  k_pcg_post<<<1, kDotBlock, 0, s>>>(rr.p, rr.m, S, w);
   SA_LAUNCH_CHECK();
   host_words_wait(w, host, sizeof(PcgScalars), s);
 }
