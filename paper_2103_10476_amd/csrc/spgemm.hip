@@ -8,11 +8,11 @@
 // Rows are binned by their product count T:
 //   T <= 64      8, 16 or 32 lanes per row (8, 4 or 2 rows per wavefront): two products per
 //                lane, rank sort in LDS;
-//   T <= 256     one wavefront per row, 64 products per step sorted in registers, each run
-//                added to its column's sum in an LDS hash table;
-//   T <= 1024    one 256-thread block per row: the row's products sorted by (column,
-//                position) in LDS, each run reduced in order and written at its rank; for
-//                R (A P) the rank accumulator (k_esc_rank) takes these rows first;
+//   T <= 1024    one wavefront per row, all products (2, 4, 8 or 16 per lane) sorted by
+//                (column, position) in registers, each run added in order and written at its
+//                rank (k_esc_sort).  Where 32 bits do not hold column and position: up to 256
+//                products 64 per step sorted in registers, each run added to its column's
+//                sum in an LDS hash table; more, a 256-thread block per row sorts them in LDS;
 //   T > 1024     the row's dense column window in LDS when the output width fits (products
 //                taken 64 per step and sorted, or, for long Y rows, one X entry per step with
 //                its Y row across the lanes), else the wavefront kernel with a 2048-slot
@@ -36,11 +36,18 @@ namespace sa {
 constexpr int kWave = 64;
 constexpr int kChunk = 1024;  // products per block-level chunk
 
-// Bins by product count: <= 16, <= 32, <= 64 (rows sharing wavefronts), <= 256, <= 1024
-// (block per row, one chunk), longer.
-constexpr int kBins = 6;
+// Bins by product count: <= 16, <= 32, <= 64 (rows sharing wavefronts), <= 128, <= 256, <= 512,
+// <= 1024 (a wavefront per row, all products sorted at once), longer.
+constexpr int kBins = 8;
 __device__ __forceinline__ int bin_of(int64_t T) {
-  return T <= 16 ? 0 : T <= 32 ? 1 : T <= kWave ? 2 : T <= 256 ? 3 : T <= kChunk ? 4 : 5;
+  return T <= 16     ? 0
+         : T <= 32   ? 1
+         : T <= 64   ? 2
+         : T <= 128  ? 3
+         : T <= 256  ? 4
+         : T <= 512  ? 5
+         : T <= 1024 ? 6
+                     : 7;
 }
 
 // A block lists its rows per bin: counted in LDS, each non-empty bin's share reserved with one
@@ -343,15 +350,14 @@ template <int BS>
 __global__ __launch_bounds__(BS) void k_esc_single(
     const int32_t *rows, int32_t nrows, const int32_t *xrp, const int32_t *xcol,
     const double *xval, const int32_t *xpref, const int32_t *yrp, const int32_t *ycol,
-    const double *yval, const int64_t *poff, int32_t *ocol, double *oval, int32_t *ucnt,
-    const int32_t *dcount) {
+    const double *yval, const int64_t *poff, int32_t *ocol, double *oval, int32_t *ucnt) {
   constexpr int CH = 4 * BS;
   __shared__ uint64_t sk[CH];
   __shared__ double sv[CH];
   __shared__ int32_t s_scan[BS];
   const int tid = threadIdx.x;
   const int32_t slot = blockIdx.x;
-  if (slot >= (dcount ? *dcount : nrows)) return;  // block-uniform
+  if (slot >= nrows) return;  // block-uniform
   const int32_t i = rows[slot];
   const int64_t base = poff[i];
   const int32_t L = (int32_t)(poff[i + 1] - base);
@@ -616,172 +622,6 @@ __device__ __forceinline__ int32_t wave_prefix_max(int32_t x) {
   x = max(x, __builtin_amdgcn_update_dpp(-1, x, 0x142, 0xA, 0xF, false));  // row_bcast:15
   x = max(x, __builtin_amdgcn_update_dpp(-1, x, 0x143, 0xC, 0xF, false));  // row_bcast:31
   return x;
-}
-
-// ---- rank accumulator (257..1024 products, narrow output rows) -----------------------------
-// One wavefront per row.  The row's products are staged in LDS at their Gustavson positions
-// (consecutive products on consecutive lanes: each its Y entry's column and X_ik Y_kj, the
-// loads of several 64-product steps in flight together), the distinct columns marked in
-// a bitmap over the row's column window, and each X entry's products then added, in X order,
-// into an accumulator indexed by the column's rank among the row's distinct columns: the
-// columns of one Y row are distinct, so the adds of one X entry never collide, and the X
-// entries follow each other in the wavefront's program order, so every output entry receives
-// its products in ascending k, from 0, as in the sort-based bins.  Rows outside the stage's
-// limits are listed in rov for the sort-based kernel of their bin.
-constexpr int32_t kRankT = 1024;    // products
-constexpr int32_t kRankX = 64;      // X entries (the adds take one step per X entry)
-constexpr int32_t kRankW = 65536;   // column window
-constexpr int32_t kRankD = 256;     // distinct columns
-constexpr int kRankSteps = 8;       // 64-product steps whose loads are issued together
-static_assert(kRankX <= 64, "one X entry per lane while staging");
-__global__ __launch_bounds__(64) void k_esc_rank(const int32_t *rows, int32_t nrows,
-                                                 const int32_t *xrp, const int32_t *xcol,
-                                                 const double *xval, const int32_t *xpref,
-                                                 const int32_t *yrp, const int32_t *ycol,
-                                                 const double *yval, const int64_t *poff,
-                                                 int32_t *ocol, double *oval, int32_t *ucnt,
-                                                 int32_t *rov, int32_t *nrov) {
-  __shared__ int32_t s_c[kRankT];       // staged columns, then their ranks
-  __shared__ double s_v[kRankT];        // staged products
-  __shared__ uint32_t s_bits[kRankW / 32];
-  __shared__ uint16_t s_pre[kRankW / 32];  // set bits in the words before
-  __shared__ double s_acc[kRankD];
-  __shared__ int32_t s_xo[kRankX + 1];  // X entries' first positions, then T
-  __shared__ int32_t s_yb[kRankX], s_mark[64];
-  __shared__ double s_xv[kRankX];
-  const int lane = threadIdx.x;
-  const int32_t slot = blockIdx.x;
-  if (slot >= nrows) return;  // block-uniform
-  const int32_t i = rows[slot];
-  const int64_t base = poff[i];
-  const int32_t T = (int32_t)(poff[i + 1] - base);
-  const int32_t xb = xrp[i], nx = xrp[i + 1] - xb;
-  auto overflow = [&]() {
-    if (lane == 0) rov[atomicAdd(nrov, 1)] = i;
-  };
-  if (nx > kRankX || T > kRankT || T == 0) {  // wavefront-uniform
-    overflow();
-    return;
-  }
-  // stage the X entries (lane e holds entry e), then the products in Gustavson order, lane l
-  // taking products l, l + 64, ...: product p belongs to the last entry that starts at or
-  // before it (among entries with products).  Per 64-product step, each entry starting
-  // inside the step marks its first product's lane and a prefix maximum over the lanes, from
-  // the entry of the step's preceding product, gives every lane its entry.  kRankSteps steps'
-  // entries are found first, then their loads issued together, then their products staged.
-  int32_t my_o = 0, my_len = 0;
-  if (lane < nx) {
-    const int32_t k = xcol[xb + lane];
-    my_o = xpref[xb + lane];
-    const int32_t yb = yrp[k];
-    my_len = yrp[k + 1] - yb;
-    s_xo[lane] = my_o;
-    s_yb[lane] = yb;
-    s_xv[lane] = xval[xb + lane];
-  }
-  if (lane == 0) s_xo[nx] = T;
-  s_mark[lane] = -1;
-  __syncthreads();
-  const bool starts = lane < nx && my_len > 0;
-  int32_t lo = INT_MAX, hi = -1, carry = -1;
-  for (int32_t g0 = 0; g0 < T; g0 += 64 * kRankSteps) {
-    int32_t ed[kRankSteps], qd[kRankSteps];
-#pragma unroll
-    for (int d = 0; d < kRankSteps; ++d) {
-      const int32_t p0 = g0 + 64 * d;
-      ed[d] = 0;
-      qd[d] = 0;  // lanes past T load Y's first entry and discard it (T > 0: Y has entries)
-      if (p0 < T) {  // wavefront-uniform
-        if (starts && my_o >= p0 && my_o < p0 + 64) s_mark[my_o - p0] = lane;
-        __syncthreads();
-        int32_t e = s_mark[lane];
-        s_mark[lane] = -1;  // every slot is -1 again for the next step
-        e = max(wave_prefix_max(e), carry);
-        carry = __builtin_amdgcn_readlane(e, 63);
-        const int32_t p = p0 + lane;
-        if (p < T) {
-          ed[d] = e;
-          qd[d] = s_yb[e] + p - s_xo[e];
-        }
-      }
-    }
-    int32_t cd[kRankSteps];
-    double vd[kRankSteps];
-#pragma unroll
-    for (int d = 0; d < kRankSteps; ++d) {
-      cd[d] = ycol[qd[d]];
-      vd[d] = yval[qd[d]];
-    }
-#pragma unroll
-    for (int d = 0; d < kRankSteps; ++d) {
-      const int32_t p = g0 + 64 * d + lane;
-      if (p < T) {
-        s_c[p] = cd[d];
-        s_v[p] = s_xv[ed[d]] * vd[d];
-        lo = min(lo, cd[d]);
-        hi = max(hi, cd[d]);
-      }
-    }
-  }
-  for (int off = 32; off >= 1; off >>= 1) {
-    lo = min(lo, __shfl_xor(lo, off, 64));
-    hi = max(hi, __shfl_xor(hi, off, 64));
-  }
-  const int32_t W = hi - lo + 1;
-  if (W > kRankW) {  // wavefront-uniform; nothing written to global memory yet
-    overflow();
-    return;
-  }
-  const int32_t nw = (W + 31) >> 5;
-  for (int32_t w = lane; w < nw; w += 64) s_bits[w] = 0u;
-  __syncthreads();
-  for (int32_t p = lane; p < T; p += 64) {
-    const int32_t c = s_c[p] - lo;
-    atomicOr(&s_bits[c >> 5], 1u << (c & 31));
-  }
-  __syncthreads();
-  // popcount prefix over the words: lane l takes a contiguous run of them
-  const int32_t wl = (nw + 63) >> 6;
-  const int32_t w0 = min(nw, lane * wl), w1 = min(nw, w0 + wl);
-  int32_t cnt = 0;
-  for (int32_t w = w0; w < w1; ++w) cnt += __popc(s_bits[w]);
-  int32_t incl = cnt;
-  for (int off = 1; off < 64; off <<= 1) {
-    const int32_t v = __shfl_up(incl, off, 64);
-    if (lane >= off) incl += v;
-  }
-  const int32_t D = __shfl(incl, 63, 64);
-  if (D > kRankD) {  // wavefront-uniform
-    overflow();
-    return;
-  }
-  int32_t run = incl - cnt;
-  for (int32_t w = w0; w < w1; ++w) {
-    s_pre[w] = (uint16_t)run;
-    run += __popc(s_bits[w]);
-  }
-  for (int32_t r = lane; r < D; r += 64) s_acc[r] = 0.0;
-  __syncthreads();
-  // ranks (each position's own lane reads and overwrites it); the columns go out at theirs
-  for (int32_t p = lane; p < T; p += 64) {
-    const int32_t c = s_c[p] - lo;
-    const int32_t w = c >> 5;
-    const int32_t r = (int32_t)s_pre[w] + __popc(s_bits[w] & ((1u << (c & 31)) - 1u));
-    s_c[p] = r;
-    ocol[base + r] = c + lo;  // every position of a column writes the same value
-  }
-  __syncthreads();
-  // the X entries in order; within one, each lane adds its product to its column's sum
-  for (int32_t e = 0; e < nx; ++e) {
-    const int32_t o0 = s_xo[e], o1 = s_xo[e + 1];
-    for (int32_t j = o0 + lane; j < o1; j += 64) {
-      const int32_t r = s_c[j];
-      s_acc[r] = s_acc[r] + s_v[j];
-    }
-  }
-  __syncthreads();
-  for (int32_t r = lane; r < D; r += 64) oval[base + r] = s_acc[r];
-  if (lane == 0) ucnt[i] = D;
 }
 
 // ---- wavefront-per-row bins (T > 64) ------------------------------------------------------
@@ -1063,6 +903,229 @@ __global__ __launch_bounds__(64) void k_esc_wave(
   }
 }
 
+// ---- one wavefront per row, all products sorted at once (65..1024 products) -----------------
+// Lane partner exchange of the sort's first step of a merge: value of lane (lane ^ M), M = 2^m - 1
+// (1, 3: quad permutations; 7, 15: the mirrors within 8 and 16 lanes; 31, 63: LDS permutes).
+template <int M>
+__device__ __forceinline__ uint32_t flip_lane(uint32_t v) {
+  if constexpr (M == 1)
+    return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0xB1, 0xF, 0xF, false);  // [1,0,3,2]
+  else if constexpr (M == 3)
+    return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x1B, 0xF, 0xF, false);  // [3,2,1,0]
+  else if constexpr (M == 7)
+    return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x141, 0xF, 0xF, false);  // half mirror
+  else if constexpr (M == 15)
+    return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x140, 0xF, 0xF, false);  // row mirror
+  else
+    return (uint32_t)__shfl_xor((int)v, M, 64);
+}
+// Ascending bitonic sort of 64 P keys, element lane * P + q in k[q].  Merges start by comparing
+// mirrored elements, so every comparison puts the smaller key at the lower index: within a
+// lane a minimum and a maximum, across lanes a minimum or a maximum by a bit of the lane.
+template <int P, int J>
+__device__ __forceinline__ void sort_halves(uint32_t (&k)[P], int lane) {
+  if constexpr (J >= P) {
+    constexpr int L = J / P;
+    const bool lower = (lane & L) == 0;
+#pragma unroll
+    for (int q = 0; q < P; ++q) {
+      const uint32_t o = xor_lane<L>(k[q], lane);
+      k[q] = lower ? min(k[q], o) : max(k[q], o);
+    }
+  } else {
+#pragma unroll
+    for (int q = 0; q < P; ++q)
+      if ((q & J) == 0) {
+        const uint32_t x = k[q], y = k[q | J];
+        k[q] = min(x, y);
+        k[q | J] = max(x, y);
+      }
+  }
+  if constexpr (J > 1) sort_halves<P, J / 2>(k, lane);
+}
+template <int P, int K = 2>
+__device__ __forceinline__ void sort_keys(uint32_t (&k)[P], int lane) {
+  if constexpr (K <= P) {
+#pragma unroll
+    for (int q = 0; q < P; ++q) {
+      const int o = q ^ (K - 1);
+      if (q < o) {
+        const uint32_t x = k[q], y = k[o];
+        k[q] = min(x, y);
+        k[o] = max(x, y);
+      }
+    }
+  } else {
+    constexpr int L = K / P;
+    const bool lower = (lane & (L / 2)) == 0;
+    uint32_t o[P];
+#pragma unroll
+    for (int q = 0; q < P; ++q) o[q] = flip_lane<L - 1>(k[P - 1 - q]);
+#pragma unroll
+    for (int q = 0; q < P; ++q) k[q] = lower ? min(k[q], o[q]) : max(k[q], o[q]);
+  }
+  if constexpr (K > 2) sort_halves<P, K / 4>(k, lane);
+  if constexpr (K < 64 * P) sort_keys<P, K * 2>(k, lane);
+}
+
+// Products at their Gustavson positions p go to LDS as keys (column << B | p) and values; the
+// keys are sorted in registers (P per lane); then each run of equal columns is added in
+// position order by the lane that holds its first key: through that lane's registers, then on
+// through LDS.  Runs are written at their rank.  The whole sort is 21 exchanges between lanes
+// per key, most of them register moves (DPP), whatever the number of 64-product steps, and
+// nothing has to be looked up or extracted afterwards: what bounds it is the row's chain of
+// loads (X entries, their Y rows, the products) and, from 512 products on, the sort's own
+// instructions.  893K rows of 65..128 products: 854 us, against 2,130 with 64 products per step
+// sorted and added to a hash table; 178K rows of 456 products 565 us against 2,800 with a
+// 256-thread block sorting in LDS; R (A P) with 48K rows of 257..512: 175 us against 553 with
+// the products added X entry by X entry to the rank of their column in the row.
+template <int P>
+__global__ __launch_bounds__(64) void k_esc_sort(
+    const int32_t *rows, int32_t nrows, const int32_t *xrp, const int32_t *xcol,
+    const double *xval, const int32_t *yrp, const int32_t *ycol, const double *yval,
+    const int64_t *poff, int32_t *ocol, double *oval, int32_t *ucnt) {
+  constexpr int N = 64 * P;
+  constexpr int B = P == 2 ? 7 : P == 4 ? 8 : P == 8 ? 9 : 10;
+  constexpr int S = P < 8 ? P : 8;  // 64-product steps whose loads are issued together
+  constexpr uint32_t kNone = ~0u;
+  static_assert(N == 1 << B, "a position per key");
+  __shared__ uint32_t s_k[N];
+  __shared__ double s_v[N];
+  __shared__ int32_t s_ex[64], s_ys[64], s_mark[64];
+  __shared__ double s_a[64];
+  const int lane = threadIdx.x;
+  const int32_t slot = xcd_block(blockIdx.x, gridDim.x);
+  if (slot >= nrows) return;  // block-uniform
+  const int32_t i = rows[slot];
+  const int64_t base = poff[i];
+  const int32_t T = (int32_t)(poff[i + 1] - base);
+  const int32_t xb = xrp[i], xe = xrp[i + 1];
+  s_mark[lane] = -1;
+  int32_t at = 0;  // the chunk's first position
+  for (int32_t e0 = xb; e0 < xe; e0 += 64) {
+    const int32_t cnt = min(64, xe - e0);
+    int32_t len = 0, ys = 0;
+    double a = 0.0;
+    if (lane < cnt) {
+      const int32_t k = xcol[e0 + lane];
+      a = xval[e0 + lane];
+      ys = yrp[k];
+      len = yrp[k + 1] - ys;
+    }
+    int32_t incl = len;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+      const int32_t v = __shfl_up(incl, off, 64);
+      if (lane >= off) incl += v;
+    }
+    const int32_t tot = __shfl(incl, 63, 64);
+    const int32_t ex = incl - len;  // this entry's first product within the chunk
+    const bool starts = lane < cnt && len > 0;
+    __syncthreads();  // the previous chunk's reads are done
+    s_ex[lane] = ex;
+    s_ys[lane] = ys;
+    s_a[lane] = a;
+    __syncthreads();
+    // a product belongs to the last entry that starts at or before it: each entry that starts
+    // inside a 64-product step marks its first product's lane, and a prefix maximum over the
+    // lanes, from the entry of the step's preceding product, hands every lane its entry
+    int32_t carry = -1;
+    for (int32_t g0 = 0; g0 < tot; g0 += 64 * S) {
+      int32_t ed[S], qd[S];
+#pragma unroll
+      for (int d = 0; d < S; ++d) {
+        const int32_t p0 = g0 + 64 * d;
+        ed[d] = -1;
+        qd[d] = 0;  // lanes past the end load Y's first entry and drop it
+        if (p0 < tot) {  // wave-uniform
+          if (starts && ex >= p0 && ex < p0 + 64) s_mark[ex - p0] = lane;
+          __syncthreads();
+          int32_t g = s_mark[lane];
+          s_mark[lane] = -1;  // every slot is -1 again for the next step
+          g = max(wave_prefix_max(g), carry);
+          carry = __builtin_amdgcn_readlane(g, 63);
+          if (p0 + lane < tot) {
+            ed[d] = g;
+            qd[d] = s_ys[g] + (p0 + lane - s_ex[g]);
+          }
+          __syncthreads();
+        }
+      }
+      int32_t cd[S];
+      double vd[S];
+#pragma unroll
+      for (int d = 0; d < S; ++d) {
+        cd[d] = ycol[qd[d]];
+        vd[d] = yval[qd[d]];
+      }
+#pragma unroll
+      for (int d = 0; d < S; ++d)
+        if (ed[d] >= 0) {
+          const int32_t p = at + g0 + 64 * d + lane;
+          s_k[p] = ((uint32_t)cd[d] << B) | (uint32_t)p;
+          s_v[p] = s_a[ed[d]] * vd[d];
+        }
+    }
+    at += tot;
+  }
+  for (int32_t p = T + lane; p < N; p += 64) s_k[p] = kNone;
+  __syncthreads();
+  uint32_t k[P];
+#pragma unroll
+  for (int q = 0; q < P; ++q) k[q] = s_k[64 * q + lane];
+  sort_keys<P>(k, lane);
+  double v[P];
+#pragma unroll
+  for (int q = 0; q < P; ++q) v[q] = k[q] == kNone ? 0.0 : s_v[k[q] & (N - 1)];
+  __syncthreads();
+#pragma unroll
+  for (int q = 0; q < P; ++q) {
+    s_k[lane * P + q] = k[q];
+    s_v[lane * P + q] = v[q];
+  }
+  const uint32_t below = (uint32_t)__shfl_up((int)k[P - 1], 1, 64);
+  bool head[P];
+  int32_t nh = 0;
+#pragma unroll
+  for (int q = 0; q < P; ++q) {
+    const uint32_t prev = q > 0 ? k[q > 0 ? q - 1 : 0] : below;
+    head[q] = k[q] != kNone && ((lane == 0 && q == 0) || (prev >> B) != (k[q] >> B));
+    nh += head[q];
+  }
+  int32_t incl = nh;
+#pragma unroll
+  for (int off = 1; off < 64; off <<= 1) {
+    const int32_t t = __shfl_up(incl, off, 64);
+    if (lane >= off) incl += t;
+  }
+  __syncthreads();
+  int32_t w = incl - nh;  // rank of the lane's next run
+  bool open = false;
+  double sum = 0.0;
+  uint32_t col = 0;
+#pragma unroll
+  for (int q = 0; q < P; ++q) {
+    if (head[q]) {
+      if (open) {
+        ocol[base + w] = (int32_t)col;
+        oval[base + w] = sum;
+        ++w;
+      }
+      open = true;
+      col = k[q] >> B;
+      sum = 0.0;
+    }
+    if (open && k[q] != kNone) sum += v[q];
+  }
+  if (open) {  // the lane's last run may go on in the next lanes' keys
+    for (int32_t r = (lane + 1) * P; r < N && s_k[r] != kNone && (s_k[r] >> B) == col; ++r)
+      sum += s_v[r];
+    ocol[base + w] = (int32_t)col;
+    oval[base + w] = sum;
+  }
+  if (lane == 63) ucnt[i] = incl;
+}
+
 // Largest output width the LDS bin takes on this device: the opt-in LDS per workgroup less
 // the kernel's static LDS, at 8 bytes plus one bit per column (queried once per device).
 static int32_t lds_cols_max() {
@@ -1175,13 +1238,15 @@ static int32_t max_tiles() {
   return e ? std::atoi(e) : 8;
 }
 
-// k_esc_wave with 32-bit sort keys when every column of Y fits in 26 bits, else 64-bit keys
-// (the environment variable SAAMG_SPGEMM_KEY64=1 takes the 64-bit keys at any width).
+// SAAMG_SPGEMM_KEY64=1 takes the 64-bit sort keys at any width.
+static bool keys64() {
+  const char *e = std::getenv("SAAMG_SPGEMM_KEY64");
+  return e && std::atoi(e) != 0;
+}
+// k_esc_wave with 32-bit sort keys when every column of Y fits in 26 bits, else 64-bit keys.
 template <bool DENSE, int H, typename... Args>
 void launch_esc_wave(int32_t ncols, unsigned grid, size_t lds, hipStream_t s, Args... args) {
-  const char *e = std::getenv("SAAMG_SPGEMM_KEY64");
-  const bool key64 = e && std::atoi(e) != 0;
-  if (ncols < (1 << 26) && !key64)
+  if (ncols < (1 << 26) && !keys64())
     k_esc_wave<DENSE, H, uint32_t><<<grid, 64, lds, s>>>(args...);
   else
     k_esc_wave<DENSE, H, uint64_t><<<grid, 64, lds, s>>>(args...);
@@ -1200,8 +1265,8 @@ void spgemm(const Csr &X, const Csr &Y, Arena &ar, Csr &C, hipStream_t s) {
   int32_t *lists = tmp.alloc<int32_t>(kBins * (int64_t)(m > 0 ? m : 1));
   // kBins bin sizes, the overflow count, the widest row window, then the product total (64
   // bits)
-  int32_t *counters = tmp.alloc<int32_t>(10);
-  fill_i32(counters, 0, 8, s);
+  int32_t *counters = tmp.alloc<int32_t>(kBins + 4);
+  fill_i32(counters, 0, kBins + 2, s);
   // short rows: a thread per row, which also bins the row; longer: 16, 32 or 64 lanes per
   // row, binned after the scan (970K rows of 26 entries: 261 us and 48 for the binning,
   // against 640 with a thread per row, whose Y row lengths are a chain of gathers)
@@ -1228,18 +1293,20 @@ void spgemm(const Csr &X, const Csr &Y, Arena &ar, Csr &C, hipStream_t s) {
     SA_LAUNCH_CHECK();
   }
   // the bin sizes and the product total in one readback
-  k_put_total<<<1, 1, 0, s>>>(poff + m, (int64_t *)(counters + 8));
+  k_put_total<<<1, 1, 0, s>>>(poff + m, (int64_t *)(counters + kBins + 2));
   SA_LAUNCH_CHECK();
-  int32_t hc[10];
+  static_assert(kBins % 2 == 0, "the 64-bit total is 8-byte aligned");
+  int32_t hc[kBins + 4];
   readback(hc, counters, sizeof(hc), s);
   int64_t total = 0;
-  std::memcpy(&total, hc + 8, sizeof(total));
+  std::memcpy(&total, hc + kBins + 2, sizeof(total));
   int32_t *ocol = tmp.alloc<int32_t>(total > 0 ? total : 1);
   double *oval = tmp.alloc<double>(total > 0 ? total : 1);
   int32_t *ucnt = tmp.alloc<int32_t>(m + 1);
   const int32_t *lg[3] = {lists, lists + m, lists + 2 * (int64_t)m};
-  const int32_t *l1 = lists + 3 * (int64_t)m, *l2 = lists + 4 * (int64_t)m,
-                *l3 = lists + 5 * (int64_t)m;
+  const int32_t *ls[4];  // the wavefront-per-row bins: <= 128, 256, 512, 1024 products
+  for (int q = 0; q < 4; ++q) ls[q] = lists + (3 + q) * (int64_t)m;
+  const int32_t *l3 = lists + 7 * (int64_t)m;
   // two products per lane: 8, 4 and 2 rows per wavefront for the <= 16, <= 32, <= 64 bins
   if (hc[0] > 0)
     k_esc_group<8, 2><<<(unsigned)ceil_div(hc[0], kWave / 8), kWave, 0, s>>>(
@@ -1251,36 +1318,33 @@ void spgemm(const Csr &X, const Csr &Y, Arena &ar, Csr &C, hipStream_t s) {
     k_esc_group<32, 2><<<(unsigned)ceil_div(hc[2], kWave / 32), kWave, 0, s>>>(
         lg[2], hc[2], X.rp, X.col, X.val, Y.rp, Y.col, Y.val, poff, ocol, oval, ucnt);
   SA_LAUNCH_CHECK();
-  const int32_t n256 = hc[3], n1024 = hc[4], nlong = hc[5];  // wavefront-per-row bins
+  const int32_t nlong = hc[7];
   int32_t *ovf = nullptr;
-  if (n256 > 0 || n1024 > 0 || nlong > 0) ovf = tmp.alloc<int32_t>(n256 + n1024 + nlong);
-  // T <= 256: the wavefront kernel with a 512-slot hash table (at least 2T slots: it never
-  // overflows); T <= 1024: one block per row, the whole row sorted in LDS.  With Y rows of 8
-  // entries or more on average (R (AP)), the rank-accumulator kernel takes the rows of the
-  // second bin first and leaves those outside its limits to the block sort (their count read
-  // on the device).
-  const bool rank = Y.nnz >= 8 * (int64_t)Y.n && n1024 > 0;
-  const int32_t *r1024 = l2, *c1024 = nullptr;
-  if (rank) {
-    int32_t *rov = tmp.alloc<int32_t>(n1024);
-    int32_t *rc = tmp.alloc<int32_t>(1);
-    fill_i32(rc, 0, 1, s);
-    k_esc_rank<<<(unsigned)n1024, 64, 0, s>>>(l2, n1024, X.rp, X.col, X.val, xpref, Y.rp, Y.col,
-                                              Y.val, poff, ocol, oval, ucnt, rov, rc);
-    SA_LAUNCH_CHECK();
-    r1024 = rov;
-    c1024 = rc;
-  }
-  if (n256 > 0) {
-    launch_esc_wave<false, 512>(Y.ncols, (unsigned)n256, 16 * 512, s, l1, n256, X.rp, X.col,
-                                X.val, Y.rp, Y.col, Y.val, 0, nullptr, poff, ocol, oval, ucnt,
-                                ovf, counters + kBins, nullptr, 0, 0);
-    SA_LAUNCH_CHECK();
-  }
-  if (n1024 > 0) {
-    k_esc_single<256><<<(unsigned)n1024, 256, 0, s>>>(r1024, n1024, X.rp, X.col, X.val, xpref,
-                                                      Y.rp, Y.col, Y.val, poff, ocol, oval,
-                                                      ucnt, c1024);
+  if (hc[3] + hc[4] + nlong > 0) ovf = tmp.alloc<int32_t>(hc[3] + hc[4] + nlong);
+  // the sort's 32-bit keys hold 25 bits of column at 128 products, 22 at 1024; wider outputs
+  // (and SAAMG_SPGEMM_KEY64=1) take the hash and the block sort
+  for (int q = 0; q < 4; ++q) {
+    const int32_t nr = hc[3 + q];
+    if (nr == 0) continue;
+    const bool wide = keys64() || Y.ncols >= (1 << (25 - q));
+    const int32_t *rows = ls[q];
+    auto sort = [&](auto pc) {
+      constexpr int P = decltype(pc)::value;
+      k_esc_sort<P><<<(unsigned)nr, 64, 0, s>>>(rows, nr, X.rp, X.col, X.val, Y.rp, Y.col, Y.val,
+                                               poff, ocol, oval, ucnt);
+    };
+    if (wide && q < 2)
+      // the hash table has at least 2T slots: it never overflows
+      launch_esc_wave<false, 512>(Y.ncols, (unsigned)nr, 16 * 512, s, rows, nr, X.rp, X.col,
+                                  X.val, Y.rp, Y.col, Y.val, 0, nullptr, poff, ocol, oval, ucnt,
+                                  ovf, counters + kBins, nullptr, 0, 0);
+    else if (wide)
+      k_esc_single<256><<<(unsigned)nr, 256, 0, s>>>(rows, nr, X.rp, X.col, X.val, xpref, Y.rp,
+                                                     Y.col, Y.val, poff, ocol, oval, ucnt);
+    else if (q == 0) sort(std::integral_constant<int, 2>{});
+    else if (q == 1) sort(std::integral_constant<int, 4>{});
+    else if (q == 2) sort(std::integral_constant<int, 8>{});
+    else sort(std::integral_constant<int, 16>{});
     SA_LAUNCH_CHECK();
   }
   // long rows: the dense window accumulator when Y's width fits the LDS (sized to the widest
