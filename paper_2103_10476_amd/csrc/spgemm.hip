@@ -10,16 +10,12 @@
 //                lane, rank sort in LDS;
 //   T <= 1024    one wavefront per row, all products (2, 4, 8 or 16 per lane) sorted by
 //                (column, position) in registers, each run added in order and written at its
-//                rank (k_esc_sort).  Where 32 bits do not hold column and position: up to 256
-//                products 64 per step sorted in registers, each run added to its column's
-//                sum in an LDS hash table; more, a 256-thread block per row sorts them in LDS;
-//   T > 1024     the row's dense column window in LDS when the output width fits (products
-//                taken 64 per step and sorted, or, for long Y rows, one X entry per step with
-//                its Y row across the lanes), else the wavefront kernel with a 2048-slot
-//                hash table;
-//   hash > 1/2   long rows with more than 1024 distinct columns are redone over their column
-//                windows in LDS tiles (one launch per tile, up to 8), or with a dense
-//                accumulator in global memory when the windows need more tiles.
+//                rank (k_esc_sort), while 32 bits hold column and position;
+//   T > 1024     a wavefront or a block per row, sums in LDS at the rank of their column
+//                in the row (k_esc_rows);
+//   otherwise    (wide keys; column windows of more than 8 tiles) one wavefront per row, sums
+//                in an LDS hash table (k_esc_table) of 512 or 2048 slots, and a dense
+//                accumulator in global memory for rows of more than 1536 distinct columns.
 // Results go to per-row slots at the row's product offset (room for T >= distinct entries)
 // and are compacted into CSR afterwards.
 #include <algorithm>
@@ -37,8 +33,9 @@ constexpr int kWave = 64;
 constexpr int kChunk = 1024;  // products per block-level chunk
 
 // Bins by product count: <= 16, <= 32, <= 64 (rows sharing wavefronts), <= 128, <= 256, <= 512,
-// <= 1024 (a wavefront per row, all products sorted at once), longer.
-constexpr int kBins = 8;
+// <= 1024 (a wavefront per row, all products sorted at once), <= 2048, <= 8192, <= 32768, longer
+// (sums in LDS).
+constexpr int kBins = 11;
 __device__ __forceinline__ int bin_of(int64_t T) {
   return T <= 16     ? 0
          : T <= 32   ? 1
@@ -47,7 +44,10 @@ __device__ __forceinline__ int bin_of(int64_t T) {
          : T <= 256  ? 4
          : T <= 512  ? 5
          : T <= 1024 ? 6
-                     : 7;
+         : T <= 2048 ? 7
+         : T <= 8192 ? 8
+         : T <= 32768 ? 9
+                     : 10;
 }
 
 // A block lists its rows per bin: counted in LDS, each non-empty bin's share reserved with one
@@ -314,10 +314,6 @@ __device__ inline int32_t next_pow2(int32_t x) {
   return p;
 }
 
-__device__ inline uint32_t hash_slot(int32_t key, uint32_t mask) {
-  return ((uint32_t)key * 2654435761u) & mask;
-}
-
 // Loads products c0 .. c0+L-1 of row i into sk (column << 32 | position) / sv and sorts sk;
 // after it, equal columns are adjacent in position (= Gustavson) order.
 __device__ inline void load_sorted_chunk(int32_t c0, int32_t L, int32_t xb, int32_t xe,
@@ -344,51 +340,8 @@ __device__ inline void load_sorted_chunk(int32_t c0, int32_t L, int32_t xb, int3
 
 __device__ inline uint32_t key_of(uint64_t x) { return (uint32_t)(x >> 32); }
 
-// Single chunk: T <= 4*BS products, one block of BS threads per row; each run of equal columns
-// is summed in position order by its first lane and written at the run's rank.
-template <int BS>
-__global__ __launch_bounds__(BS) void k_esc_single(
-    const int32_t *rows, int32_t nrows, const int32_t *xrp, const int32_t *xcol,
-    const double *xval, const int32_t *xpref, const int32_t *yrp, const int32_t *ycol,
-    const double *yval, const int64_t *poff, int32_t *ocol, double *oval, int32_t *ucnt) {
-  constexpr int CH = 4 * BS;
-  __shared__ uint64_t sk[CH];
-  __shared__ double sv[CH];
-  __shared__ int32_t s_scan[BS];
-  const int tid = threadIdx.x;
-  const int32_t slot = blockIdx.x;
-  if (slot >= nrows) return;  // block-uniform
-  const int32_t i = rows[slot];
-  const int64_t base = poff[i];
-  const int32_t L = (int32_t)(poff[i + 1] - base);
-  load_sorted_chunk(0, L, xrp[i], xrp[i + 1], xpref, xcol, xval, yrp, ycol, yval, sk, sv);
-  int32_t nh = 0;
-  for (int32_t r = tid * 4; r < tid * 4 + 4; ++r)
-    if (r < L && (r == 0 || key_of(sk[r]) != key_of(sk[r - 1]))) ++nh;
-  s_scan[tid] = nh;
-  __syncthreads();
-  for (int off = 1; off < BS; off <<= 1) {
-    const int32_t add = (tid >= off) ? s_scan[tid - off] : 0;
-    __syncthreads();
-    s_scan[tid] += add;
-    __syncthreads();
-  }
-  int32_t idx = s_scan[tid] - nh;
-  for (int32_t r = tid * 4; r < tid * 4 + 4; ++r) {
-    if (r < L && (r == 0 || key_of(sk[r]) != key_of(sk[r - 1]))) {
-      const uint32_t key = key_of(sk[r]);
-      double sum = 0.0;
-      for (int32_t q = r; q < L && key_of(sk[q]) == key; ++q) sum += sv[(uint32_t)sk[q]];
-      ocol[base + idx] = (int32_t)key;
-      oval[base + idx] = sum;
-      ++idx;
-    }
-  }
-  if (tid == BS - 1) ucnt[i] = s_scan[BS - 1];
-}
-
-// Rows with more distinct columns than the LDS table holds, when their column windows need
-// more LDS tiles than the limit: a dense accumulator of ncols entries per block in global
+// Rows with more distinct columns than the large LDS table takes and windows beyond the tile
+// limit: a dense accumulator of ncols entries per block in global
 // memory (first touch starts from 0, adds in position order as above); the result is
 // extracted in column order by a block-wide scan of the touched flags.
 __global__ __launch_bounds__(kBlock) void k_esc_dense(
@@ -450,196 +403,146 @@ __global__ __launch_bounds__(kBlock) void k_esc_dense(
   }
 }
 
-// Long rows whose output columns fit in LDS (the dense coarse levels): one wavefront per row
-// with a dense accumulator of ncols doubles and a touched-column bitmap in LDS.  The row's
-// entries k are taken in ascending order; for each, the lanes add the products of Y's row k
-// into their own columns (distinct within a row of Y), and the adds of successive k are
-// ordered (one wavefront executes them in program order; a wave barrier separates them), so
-// every output entry receives its products in ascending k from 0, as in the sort-based bins.
-// The row's X entries and Y row ranges are staged in LDS 64 at a time, and the steps (64-entry
-// slices of Y rows) are taken D at a time, their loads issued together before they are added,
-// so D steps share one memory latency even at one wavefront per CU (the widest windows fill
-// the LDS).
-// The result is extracted in column order with ballots.  Rows wider than the LDS (those that
-// overflow the hash bin) are taken in column tiles, one launch per tile, each appending its
-// entries to the row's earlier ones.
-__device__ __forceinline__ void lds_add(double *acc, uint32_t *bits, int32_t j, double v) {
-  acc[j] = acc[j] + v;
-  atomicOr(&bits[j >> 5], 1u << (j & 31));
-}
-// Column window of each long row (rows[slot]): from the smallest first column to the largest
-// last column of the Y rows it touches (Y's rows are sorted, as every matrix the setup
-// builds); win[slot] = (first column, width), and *maxw the largest width.
-// One wavefront per row (X rows of the long bin reach thousands of entries): lanes take the
-// row's entries, then a shuffle minimum / maximum.
-__global__ __launch_bounds__(kBlock) void k_row_window(const int32_t *rows, int32_t nrows,
-                                                       const int32_t *xrp, const int32_t *xcol,
-                                                       const int32_t *yrp, const int32_t *ycol,
-                                                       int2 *win, int32_t *maxw) {
-  __shared__ int32_t s_w[kBlock / 64];
-  const int64_t slot = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
-  const int lane = threadIdx.x & 63;
-  int32_t lo = 0x7fffffff, hi = -1;
-  if (slot < nrows) {  // wave-uniform
-    const int32_t i = rows[slot];
-    for (int32_t e = xrp[i] + lane; e < xrp[i + 1]; e += 64) {
-      const int32_t k = xcol[e];
-      const int32_t b = yrp[k], en = yrp[k + 1];
-      if (b < en) {
-        lo = min(lo, ycol[b]);
-        hi = max(hi, ycol[en - 1]);
-      }
-    }
-  }
-  for (int off = 32; off >= 1; off >>= 1) {
-    lo = min(lo, __shfl_xor(lo, off, 64));
-    hi = max(hi, __shfl_xor(hi, off, 64));
-  }
-  const int32_t w = hi >= lo ? hi - lo + 1 : 0;
-  if (lane == 0) {
-    if (slot < nrows) win[slot] = make_int2(hi >= lo ? lo : 0, w);
-    s_w[threadIdx.x >> 6] = w;
-  }
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    int32_t m = s_w[0];
-    for (int q = 1; q < kBlock / 64; ++q) m = max(m, s_w[q]);
-    // only a wider window touches the shared maximum: an atomic per row took 2,020 us for
-    // 176K rows, all on one word (a wavefront each, reading the word first, 118 us)
-    if (m > __hip_atomic_load(maxw, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
-      atomicMax(maxw, m);
-  }
-}
-
-constexpr int kLdsDepth = 8;  // steps whose loads k_esc_lds issues together
-template <int D>
-__global__ __launch_bounds__(64) void k_esc_lds(const int32_t *rows, int32_t nrows,
-                                                const int32_t *xrp, const int32_t *xcol,
-                                                const double *xval, const int32_t *yrp,
-                                                const int32_t *ycol, const double *yval,
-                                                int32_t ncols, const int2 *win,
-                                                const int64_t *poff, int32_t *ocol,
-                                                double *oval, int32_t *ucnt, int32_t tile,
-                                                int32_t tw) {
-  extern __shared__ double lds_acc[];
-  double *acc = lds_acc;
-  uint32_t *bits = (uint32_t *)(acc + ncols);
-  __shared__ double s_a[64];
-  __shared__ int32_t s_b[64], s_e[64];
-  const int lane = threadIdx.x;
-  const int32_t slot = blockIdx.x;
-  if (slot >= nrows) return;  // block-uniform
-  const int32_t i = rows[slot];
-  // the row's window: accumulator index j - lo for output column j, rw <= ncols entries
-  // (no windows: the whole width); with tiles (tw > 0) this pass takes columns
-  // [lo + tile tw, lo + (tile + 1) tw) of the window and appends to the earlier tiles' entries
-  const int2 wn = win ? win[slot] : make_int2(0, ncols);
-  int32_t lo = wn.x, rw = wn.y, prior = 0;
-  if (tw > 0) {
-    const int32_t off = tile * tw;
-    if (tile > 0 && off >= rw) return;  // block-uniform: the row's window ended earlier
-    lo += off;
-    rw = min(tw, rw - off);
-    if (tile > 0) prior = ucnt[i];
-  }
-  const int32_t nw = (rw + 31) >> 5;
-  for (int32_t c = lane; c < rw; c += 64) acc[c] = 0.0;
-  for (int32_t c = lane; c < nw; c += 64) bits[c] = 0u;
-  const int32_t xb = xrp[i], xe = xrp[i + 1];
-  for (int32_t e0 = xb; e0 < xe; e0 += 64) {
-    const int32_t cnt = min(64, xe - e0);
-    __syncthreads();
-    if (lane < cnt) {
-      const int32_t k = xcol[e0 + lane];
-      s_a[lane] = xval[e0 + lane];
-      s_b[lane] = yrp[k];
-      s_e[lane] = yrp[k + 1];
-    }
-    __syncthreads();
-    // steps (g, 64-entry slice of Y's row k_g) in order, D at a time: the D steps' loads are
-    // issued together, then the steps are added in order (steps past the chunk are empty).
-    // Every lane loads (lanes past the Y row, or steps past the chunk, read the chunk's first
-    // Y entry and discard it), so each step waits only for its own loads.  The block is one
-    // wavefront, whose LDS operations complete in program order, and one step's adds go to
-    // distinct columns (one Y row's): no barrier between steps, which would also wait for the
-    // loads in flight.
-    const int32_t qsafe = s_b[0] < s_e[0] ? s_b[0] : 0;
-    int32_t gp = 0, qp = s_b[0];
-    while (gp < cnt) {
-      int32_t jq[D], gq[D];
-      double vq[D];
-      bool okq[D];
-#pragma unroll
-      for (int d = 0; d < D; ++d) {
-        gq[d] = gp;
-        const bool live = gp < cnt;
-        const int32_t ge = live ? s_e[gp] : 0;
-        okq[d] = live && qp + lane < ge;
-        const int32_t q = okq[d] ? qp + lane : qsafe;
-        jq[d] = ycol[q];
-        vq[d] = yval[q];
-        if (live) {
-          qp += 64;
-          if (qp >= ge) {
-            ++gp;
-            qp = (gp < cnt) ? s_b[gp] : 0;
-          }
-        }
-      }
-#pragma unroll
-      for (int d = 0; d < D; ++d) {
-        const int32_t j = jq[d];
-        if (okq[d] && (uint32_t)(j - lo) < (uint32_t)rw)
-          lds_add(acc, bits, j - lo, s_a[gq[d]] * vq[d]);
-      }
-    }
-  }
-  __syncthreads();
-  const int64_t base = poff[i] + prior;
-  int32_t w = 0;
-  for (int32_t c0 = 0; c0 < rw; c0 += 64) {
-    const int32_t c = c0 + lane;
-    const bool f = c < rw && ((bits[c >> 5] >> (c & 31)) & 1u);
-    const unsigned long long bm = __ballot(f);
-    if (f) {
-      const int32_t pos = w + __popcll(bm & ((1ull << lane) - 1ull));
-      ocol[base + pos] = lo + c;
-      oval[base + pos] = acc[c];
-    }
-    w += __popcll(bm);
-  }
-  if (lane == 0) ucnt[i] = prior + w;
-}
-
-// Inclusive prefix maximum over the wavefront's lanes: row shifts by 1, 2, 4 and 8 within
-// each 16-lane row (lanes shifted in from outside the row read -1), then the last lane of
-// row 0 (of row 2) into row 1 (row 3), then the last lane of row 1 into rows 2 and 3.
-__device__ __forceinline__ int32_t wave_prefix_max(int32_t x) {
-  x = max(x, __builtin_amdgcn_update_dpp(-1, x, 0x111, 0xF, 0xF, false));  // row_shr:1
-  x = max(x, __builtin_amdgcn_update_dpp(-1, x, 0x112, 0xF, 0xF, false));  // row_shr:2
-  x = max(x, __builtin_amdgcn_update_dpp(-1, x, 0x114, 0xF, 0xF, false));  // row_shr:4
-  x = max(x, __builtin_amdgcn_update_dpp(-1, x, 0x118, 0xF, 0xF, false));  // row_shr:8
-  x = max(x, __builtin_amdgcn_update_dpp(-1, x, 0x142, 0xA, 0xF, false));  // row_bcast:15
-  x = max(x, __builtin_amdgcn_update_dpp(-1, x, 0x143, 0xC, 0xF, false));  // row_bcast:31
+// Inclusive prefix sum over the wavefront's lanes: row shifts by 1, 2, 4 and 8 within each
+// 16-lane row (lanes shifted in from outside the row read 0), then the last lane of row 0 (of
+// row 2) into row 1 (row 3), then the last lane of row 1 into rows 2 and 3.
+__device__ __forceinline__ int32_t wave_prefix_sum(int32_t x) {
+  x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xF, 0xF, false);  // row_shr:1
+  x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xF, 0xF, false);  // row_shr:2
+  x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xF, 0xF, false);  // row_shr:4
+  x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xF, 0xF, false);  // row_shr:8
+  x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xA, 0xF, false);  // row_bcast:15
+  x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xC, 0xF, false);  // row_bcast:31
   return x;
+}
+// One wavefront's LDS operations complete in its program order: between its lanes only the
+// compiler has to keep that order.
+__device__ __forceinline__ void wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
 }
 
 // ---- wavefront-per-row bins (T > 64) ------------------------------------------------------
-// One wavefront (a 64-thread block) per row.  The row's products are taken 64 at a time in
-// Gustavson order: its X entries are staged 64 at a time with a wave scan of their Y-row
-// lengths, and each lane finds its product's entry by binary search over the scan.  A step's
-// 64 products are sorted in registers by (column, lane) -- lane order is product order -- and
-// the first lane of each run of equal columns adds the run, in order, to that column's
-// accumulator in LDS.  Steps follow each other in product order, so every output entry
-// receives its products in ascending k, from 0.
-//   DENSE  the accumulator is the row's column window (values and a touched bitmap), read
-//          out in column order with ballots; rows wider than the LDS (those that overflow the
-//          hash bin) are taken in column tiles, one launch per tile, each appending its
-//          entries to the row's earlier ones;
-//   HASH   an open-addressing table of H slots (every column claimed by an LDS compare-and-
-//          swap, its sum starting from 0); a row whose distinct columns pass H/2 is listed in
-//          ovf[] to be redone (LDS column tiles, or k_esc_dense).  At the end the occupied
-//          slots are compacted and sorted by column (bitonic, in LDS).
+// A wavefront goes over the products X_ik Y_kj of a row in Gustavson order, 64 to a step
+// (product p0 + 64 d + lane in step d), S steps' loads issued together: f gets each step's X
+// entry (ed, numbering the chunk's non-empty Y rows; -1 past the end) and that of its last
+// product, the columns and, with VALS, the products; it returns false to stop.  The X entries
+// are taken 64 at a time (chunks first, first + stride, ...).  Each non-empty Y row sets the
+// bit of its first product in its step's 64-bit word, and a lane's entry is the number of bits
+// up to its own: the words of S steps are one LDS atomic per entry, whatever the row lengths.
+// With clip, only the products with columns cA <= j < cB (Y's rows are sorted).
+struct ProductStage {
+  uint64_t start[8];
+  int32_t off[64];
+  double a[64];
+};
+// [b, e) to the entries with columns cA <= j < cB: both ends searched at once.
+__device__ __forceinline__ void clip_cols(const int32_t *ycol, int32_t &b, int32_t &e,
+                                          int32_t cA, int32_t cB) {
+  int32_t h1 = e, l2 = b;
+  while (b < h1 || l2 < e) {
+    const int32_t m1 = (b + h1) >> 1, m2 = (l2 + e) >> 1;
+    const int32_t c1 = b < h1 ? ycol[m1] : cA, c2 = l2 < e ? ycol[m2] : cB;
+    if (c1 < cA) b = m1 + 1;
+    else h1 = m1;
+    if (c2 < cB) l2 = m2 + 1;
+    else e = m2;
+  }
+}
+template <int S, bool VALS, typename F>
+__device__ __forceinline__ void row_products(ProductStage &st, int lane, int32_t xb, int32_t xe,
+                                             int32_t first, int32_t stride, bool clip,
+                                             int32_t cA, int32_t cB, const int32_t *xcol,
+                                             const double *xval, const int32_t *yrp,
+                                             const int32_t *ycol, const double *yval, F f) {
+  static_assert(S <= 8, "a start word per step");
+  // the next chunk's Y row bounds and the one after's X entries are loaded a chunk ahead
+  const int32_t hop = 64 * stride;
+  int32_t e0 = xb + 64 * first;
+  auto entry = [&](int32_t e, int32_t &k, double &a) {
+    k = -1;
+    a = 0.0;
+    if (e < xe) {
+      k = xcol[e];
+      if (VALS) a = xval[e];
+    }
+  };
+  auto bounds = [&](int32_t k, int32_t &b, int32_t &e) {
+    b = e = 0;
+    if (k >= 0) {
+      b = yrp[k];
+      e = yrp[k + 1];
+    }
+  };
+  int32_t k1, k2, yb1, ye1;
+  double a1, a2;
+  entry(e0 + lane, k1, a1);
+  entry(e0 + hop + lane, k2, a2);
+  bounds(k1, yb1, ye1);
+  int32_t at = 0;  // the chunk's first position
+  for (; e0 < xe; e0 += hop) {
+    int32_t ys = yb1, ye = ye1;
+    const double a = a1;
+    a1 = a2;
+    bounds(k2, yb1, ye1);
+    entry(e0 + 2 * hop + lane, k2, a2);
+    if (clip) clip_cols(ycol, ys, ye, cA, cB);
+    const int32_t len = ye - ys;
+    const int32_t incl = wave_prefix_sum(len);
+    const int32_t tot = __builtin_amdgcn_readlane(incl, 63);
+    const int32_t ex = incl - len;  // this entry's first product within the chunk
+    const unsigned long long some = __ballot(len > 0);
+    wave_sync();  // the previous chunk's reads come before
+    if (len > 0) {
+      const int32_t g = __popcll(some & ((1ull << lane) - 1ull));
+      st.off[g] = ys - ex;
+      if (VALS) st.a[g] = a;
+    }
+    int32_t seen = 0;  // entries that start before the step
+    for (int32_t g0 = 0; g0 < tot; g0 += 64 * S) {
+      if (lane < S) st.start[lane] = 0;
+      wave_sync();
+      if (len > 0 && ex >= g0 && ex < g0 + 64 * S)
+        atomicOr((unsigned long long *)&st.start[(ex - g0) >> 6], 1ull << ((ex - g0) & 63));
+      wave_sync();
+      uint32_t wl[S], wh[S];
+#pragma unroll
+      for (int d = 0; d < S; ++d) {
+        wl[d] = (uint32_t)st.start[d];
+        wh[d] = (uint32_t)(st.start[d] >> 32);
+      }
+      int32_t ed[S], last[S], qd[S];
+#pragma unroll
+      for (int d = 0; d < S; ++d) {
+        const uint64_t w = (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)wh[d]) << 32 |
+                           (uint32_t)__builtin_amdgcn_readfirstlane((int)wl[d]);
+        const uint64_t up = w >> 1;  // bits 1 .. lane of w are those below `lane` of this
+        const int32_t g = __builtin_amdgcn_mbcnt_hi(
+            (uint32_t)(up >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)up, seen - 1 + (int)(w & 1)));
+        seen += __popcll(w);
+        last[d] = seen - 1;
+        const int32_t p = g0 + 64 * d + lane;
+        ed[d] = p < tot ? g : -1;
+        qd[d] = p < tot ? st.off[g] + p : 0;  // lanes past the end load Y's first entry
+      }
+      int32_t cd[S];
+      double vd[S];
+#pragma unroll
+      for (int d = 0; d < S; ++d) {
+        cd[d] = ycol[qd[d]];
+        if (VALS) vd[d] = yval[qd[d]];
+      }
+      if (VALS) {
+#pragma unroll
+        for (int d = 0; d < S; ++d)
+          if (ed[d] >= 0) vd[d] = st.a[ed[d]] * vd[d];
+      }
+      if (!f(at + g0, ed, last, cd, vd)) return;
+    }
+    at += tot;
+  }
+}
+
 // Value of lane (lane ^ J) of the wavefront.  J = 1, 2: a quad permutation (DPP); J = 4, 8:
 // the row shifts by J toward the lower lanes (row_shl, lane i reads i + J) and the higher
 // lanes (row_shr, lane i reads i - J), of which each lane keeps the one inside its J-group
@@ -660,249 +563,6 @@ __device__ __forceinline__ uint32_t xor_lane(uint32_t v, int lane) {
     return (uint32_t)__shfl_xor((int)v, J, 64);
   }
 }
-template <int J>
-__device__ __forceinline__ uint64_t xor_lane(uint64_t v, int lane) {
-  const uint32_t lo = xor_lane<J>((uint32_t)v, lane);
-  const uint32_t hi = xor_lane<J>((uint32_t)(v >> 32), lane);
-  return ((uint64_t)hi << 32) | lo;
-}
-// Ascending bitonic sort of one key per lane across the wavefront (keys distinct).  Keys are
-// (column << 6 | lane): 32 bits while the columns stay below 2^26 (one cross-lane move per
-// stage), else 64.  Merge K's stage J pairs lanes i and i ^ J.
-template <int K, int J, typename KT>
-__device__ __forceinline__ KT bitonic_merge(KT key, int lane) {
-  const KT other = xor_lane<J>(key, lane);
-  const bool up = (lane & K) == 0;
-  const bool lower = (lane & J) == 0;
-  key = (lower == up) ? (key < other ? key : other) : (key > other ? key : other);
-  if constexpr (J > 1)
-    return bitonic_merge<K, J / 2>(key, lane);
-  else
-    return key;
-}
-template <typename KT, int K = 2>
-__device__ __forceinline__ KT wave_sort(KT key, int lane) {
-  key = bitonic_merge<K, K / 2>(key, lane);
-  if constexpr (K < 64)
-    return wave_sort<KT, K * 2>(key, lane);
-  else
-    return key;
-}
-
-template <bool DENSE, int H, typename KT>
-__global__ __launch_bounds__(64) void k_esc_wave(
-    const int32_t *rows, int32_t nrows, const int32_t *xrp, const int32_t *xcol,
-    const double *xval, const int32_t *yrp, const int32_t *ycol, const double *yval,
-    int32_t width, const int2 *win, const int64_t *poff, int32_t *ocol, double *oval,
-    int32_t *ucnt, int32_t *ovf, int32_t *novf, const int32_t *dcount, int32_t tile,
-    int32_t tw) {
-  extern __shared__ double lds_dyn[];
-  __shared__ int32_t s_incl[64], s_ys[64], s_mark[64];
-  __shared__ double s_a[64], s_v[64];
-  __shared__ int32_t s_cnt;
-  const int lane = threadIdx.x;
-  s_mark[lane] = -1;
-  const int32_t slot = blockIdx.x;
-  if (slot >= (dcount ? *dcount : nrows)) return;  // block-uniform
-  const int32_t i = rows[slot];
-  const int64_t base = poff[i];
-  // DENSE: acc[width] then the bitmap; HASH: hv[H], hk[H], then the sort keys (H/2)
-  double *acc = lds_dyn;
-  uint32_t *bits = reinterpret_cast<uint32_t *>(acc + width);
-  double *hv = lds_dyn;
-  int32_t *hk = reinterpret_cast<int32_t *>(hv + H);
-  uint64_t *sk = reinterpret_cast<uint64_t *>(hk + H);
-  int32_t lo = 0, rw = width, prior = 0;
-  if (DENSE) {
-    if (win) {
-      const int2 w = win[slot];
-      lo = w.x;
-      rw = w.y;
-    }
-    if (tw > 0) {  // column tile `tile` of the window, appended to the earlier tiles' entries
-      const int32_t off = tile * tw;
-      if (tile > 0 && off >= rw) return;  // block-uniform: the row's window ended earlier
-      lo += off;
-      rw = min(tw, rw - off);
-      if (tile > 0) prior = ucnt[i];
-    }
-    for (int32_t c = lane; c < rw; c += 64) acc[c] = 0.0;
-    for (int32_t c = lane; c < ((rw + 31) >> 5); c += 64) bits[c] = 0u;
-  } else {
-    for (int32_t c = lane; c < H; c += 64) {
-      hk[c] = -1;
-      hv[c] = 0.0;
-    }
-    if (lane == 0) s_cnt = 0;
-  }
-  __syncthreads();
-  bool over = false;  // block-uniform
-  const int32_t xb = xrp[i], xe = xrp[i + 1];
-  for (int32_t e0 = xb; e0 < xe && !over; e0 += 64) {
-    const int32_t cnt = min(64, xe - e0);
-    int32_t len = 0, ys = 0;
-    double a = 0.0;
-    if (lane < cnt) {
-      const int32_t k = xcol[e0 + lane];
-      a = xval[e0 + lane];
-      ys = yrp[k];
-      len = yrp[k + 1] - ys;
-    }
-    int32_t incl = len;
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-      const int32_t v = __shfl_up(incl, off, 64);
-      if (lane >= off) incl += v;
-    }
-    const int32_t tot = __shfl(incl, 63, 64);
-    __syncthreads();  // the previous chunk's searches are done
-    s_incl[lane] = incl;
-    s_ys[lane] = ys;
-    s_a[lane] = a;
-    __syncthreads();
-    // product p of the chunk belongs to the last staged entry g that starts at or before it
-    // (among entries with products), at offset p - s_incl[g-1] in its row of Y.  For a step
-    // of 64 products, each entry starting inside the step marks its first product's lane, and
-    // a prefix maximum over the lanes, from the entry of the step's preceding product, gives
-    // every lane its entry.  The next step's entry is loaded before this step is sorted and
-    // added, so its latency overlaps them (the product is formed when it is used).
-    const int32_t ex = incl - len;  // this lane's entry's first product
-    const bool starts = lane < cnt && len > 0;
-    int32_t carry = -1;  // entry of the product before the step being fetched (wave-uniform)
-    int32_t jn = -1;
-    double yn = 0.0, an = 0.0;
-    auto fetch = [&](int32_t p0) {
-      jn = -1;
-      if (p0 >= tot) return;  // wave-uniform
-      if (starts && ex >= p0 && ex < p0 + 64) s_mark[ex - p0] = lane;
-      __syncthreads();
-      int32_t g = s_mark[lane];
-      s_mark[lane] = -1;  // every slot is -1 again for the next step
-      g = max(wave_prefix_max(g), carry);
-      carry = __builtin_amdgcn_readlane(g, 63);
-      const int32_t p = p0 + lane;
-      if (p < tot) {
-        const int32_t q = s_ys[g] + p - (g > 0 ? s_incl[g - 1] : 0);
-        jn = ycol[q];
-        yn = yval[q];
-        an = s_a[g];
-      }
-    };
-    fetch(0);
-    for (int32_t p0 = 0; p0 < tot; p0 += 64) {
-      const int32_t j = jn;
-      const double y = yn, a = an;
-      fetch(p0 + 64);
-      constexpr KT kNone = ~KT(0);
-      KT key = kNone;
-      double v = 0.0;
-      if (j >= 0) {
-        v = a * y;
-        key = ((KT)(uint32_t)j << 6) | (KT)lane;
-      }
-      key = wave_sort<KT>(key, lane);
-      const double sv = __shfl(v, (int)(key & 63u), 64);
-      const int32_t col = key == kNone ? -1 : (int32_t)(key >> 6);
-      // runs of equal columns: a run starts where the column differs from the lane below;
-      // it ends at the next start or at the last product (empty keys sort last)
-      const int32_t below = __shfl_up(col, 1, 64);
-      const bool head = col >= 0 && (lane == 0 || below != col);
-      const uint64_t heads = __ballot(head);
-      const int32_t nprod = __popcll(__ballot(col >= 0));
-      const uint64_t later = lane < 63 ? heads >> (lane + 1) : 0ull;
-      const int32_t end = later ? lane + 1 + (int32_t)__builtin_ctzll(later) : nprod;
-      s_v[lane] = sv;
-      __syncthreads();
-      if (head) {
-        if (DENSE) {
-          const int32_t c = col - lo;  // outside the window only with tiles
-          if ((uint32_t)c < (uint32_t)rw) {
-            double t = acc[c];
-            for (int r = lane; r < end; ++r) t += s_v[r];
-            acc[c] = t;
-            atomicOr(&bits[c >> 5], 1u << (c & 31));
-          }
-        } else {
-          uint32_t h = hash_slot(col, H - 1);
-          for (int probe = 0; probe < H; ++probe) {
-            const int32_t old = atomicCAS(&hk[h], -1, col);
-            if (old == -1) {
-              atomicAdd(&s_cnt, 1);
-              break;
-            }
-            if (old == col) break;
-            h = (h + 1) & (H - 1);
-          }
-          double t = hv[h];
-          for (int r = lane; r < end; ++r) t += s_v[r];
-          hv[h] = t;
-        }
-      }
-      __syncthreads();
-      if (!DENSE && 2 * s_cnt > H) {  // block-uniform: too many columns for the table
-        over = true;
-        break;
-      }
-    }
-  }
-  if (over) {
-    if (lane == 0) ovf[atomicAdd(novf, 1)] = i;
-    return;
-  }
-  if (DENSE) {
-    int32_t w = 0;
-    for (int32_t c0 = 0; c0 < rw; c0 += 64) {
-      const int32_t c = c0 + lane;
-      const bool f = c < rw && ((bits[c >> 5] >> (c & 31)) & 1u);
-      const unsigned long long bm = __ballot(f);
-      if (f) {
-        const int32_t pos = w + __popcll(bm & ((1ull << lane) - 1ull));
-        ocol[base + prior + pos] = lo + c;
-        oval[base + prior + pos] = acc[c];
-      }
-      w += __popcll(bm);
-    }
-    if (lane == 0) ucnt[i] = prior + w;
-  } else {
-    // compact the occupied slots as (column << 32 | slot) keys, sort them, write in order
-    int32_t u = 0;
-    for (int32_t c0 = 0; c0 < H; c0 += 64) {
-      const int32_t c = c0 + lane;
-      const int32_t kc = hk[c];
-      const bool f = kc >= 0;
-      const unsigned long long bm = __ballot(f);
-      if (f)
-        sk[u + __popcll(bm & ((1ull << lane) - 1ull))] =
-            ((uint64_t)(uint32_t)kc << 32) | (uint32_t)c;
-      u += __popcll(bm);
-    }
-    int32_t up = 1;
-    while (up < u) up <<= 1;
-    for (int32_t q = u + lane; q < up; q += 64) sk[q] = ~0ull;
-    __syncthreads();
-    for (int32_t kk = 2; kk <= up; kk <<= 1) {
-      for (int32_t j = kk >> 1; j > 0; j >>= 1) {
-        for (int32_t idx = lane; idx < up; idx += 64) {
-          const int32_t ixj = idx ^ j;
-          if (ixj > idx) {
-            const uint64_t x = sk[idx], y = sk[ixj];
-            if ((x > y) == ((idx & kk) == 0)) {
-              sk[idx] = y;
-              sk[ixj] = x;
-            }
-          }
-        }
-        __syncthreads();
-      }
-    }
-    for (int32_t r = lane; r < u; r += 64) {
-      ocol[base + r] = (int32_t)(sk[r] >> 32);
-      oval[base + r] = hv[(uint32_t)sk[r]];
-    }
-    if (lane == 0) ucnt[i] = u;
-  }
-}
-
 // ---- one wavefront per row, all products sorted at once (65..1024 products) -----------------
 // Lane partner exchange of the sort's first step of a merge: value of lane (lane ^ M), M = 2^m - 1
 // (1, 3: quad permutations; 7, 15: the mirrors within 8 and 16 lanes; 31, 63: LDS permutes).
@@ -986,88 +646,31 @@ __global__ __launch_bounds__(64) void k_esc_sort(
     const int64_t *poff, int32_t *ocol, double *oval, int32_t *ucnt) {
   constexpr int N = 64 * P;
   constexpr int B = P == 2 ? 7 : P == 4 ? 8 : P == 8 ? 9 : 10;
-  constexpr int S = P < 8 ? P : 8;  // 64-product steps whose loads are issued together
   constexpr uint32_t kNone = ~0u;
   static_assert(N == 1 << B, "a position per key");
   __shared__ uint32_t s_k[N];
   __shared__ double s_v[N];
-  __shared__ int32_t s_ex[64], s_ys[64], s_mark[64];
-  __shared__ double s_a[64];
+  __shared__ ProductStage st;
   const int lane = threadIdx.x;
   const int32_t slot = xcd_block(blockIdx.x, gridDim.x);
   if (slot >= nrows) return;  // block-uniform
   const int32_t i = rows[slot];
   const int64_t base = poff[i];
   const int32_t T = (int32_t)(poff[i + 1] - base);
-  const int32_t xb = xrp[i], xe = xrp[i + 1];
-  s_mark[lane] = -1;
-  int32_t at = 0;  // the chunk's first position
-  for (int32_t e0 = xb; e0 < xe; e0 += 64) {
-    const int32_t cnt = min(64, xe - e0);
-    int32_t len = 0, ys = 0;
-    double a = 0.0;
-    if (lane < cnt) {
-      const int32_t k = xcol[e0 + lane];
-      a = xval[e0 + lane];
-      ys = yrp[k];
-      len = yrp[k + 1] - ys;
-    }
-    int32_t incl = len;
+  constexpr int S = P < 8 ? P : 8;
+  row_products<S, true>(
+      st, lane, xrp[i], xrp[i + 1], 0, 1, false, 0, 0, xcol, xval, yrp, ycol, yval,
+      [&](int32_t p0, const int32_t (&ed)[S], const int32_t (&)[S], const int32_t (&cd)[S],
+          const double (&vd)[S]) {
 #pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-      const int32_t v = __shfl_up(incl, off, 64);
-      if (lane >= off) incl += v;
-    }
-    const int32_t tot = __shfl(incl, 63, 64);
-    const int32_t ex = incl - len;  // this entry's first product within the chunk
-    const bool starts = lane < cnt && len > 0;
-    __syncthreads();  // the previous chunk's reads are done
-    s_ex[lane] = ex;
-    s_ys[lane] = ys;
-    s_a[lane] = a;
-    __syncthreads();
-    // a product belongs to the last entry that starts at or before it: each entry that starts
-    // inside a 64-product step marks its first product's lane, and a prefix maximum over the
-    // lanes, from the entry of the step's preceding product, hands every lane its entry
-    int32_t carry = -1;
-    for (int32_t g0 = 0; g0 < tot; g0 += 64 * S) {
-      int32_t ed[S], qd[S];
-#pragma unroll
-      for (int d = 0; d < S; ++d) {
-        const int32_t p0 = g0 + 64 * d;
-        ed[d] = -1;
-        qd[d] = 0;  // lanes past the end load Y's first entry and drop it
-        if (p0 < tot) {  // wave-uniform
-          if (starts && ex >= p0 && ex < p0 + 64) s_mark[ex - p0] = lane;
-          __syncthreads();
-          int32_t g = s_mark[lane];
-          s_mark[lane] = -1;  // every slot is -1 again for the next step
-          g = max(wave_prefix_max(g), carry);
-          carry = __builtin_amdgcn_readlane(g, 63);
-          if (p0 + lane < tot) {
-            ed[d] = g;
-            qd[d] = s_ys[g] + (p0 + lane - s_ex[g]);
+        for (int d = 0; d < S; ++d)
+          if (ed[d] >= 0) {
+            const int32_t p = p0 + 64 * d + lane;
+            s_k[p] = ((uint32_t)cd[d] << B) | (uint32_t)p;
+            s_v[p] = vd[d];
           }
-          __syncthreads();
-        }
-      }
-      int32_t cd[S];
-      double vd[S];
-#pragma unroll
-      for (int d = 0; d < S; ++d) {
-        cd[d] = ycol[qd[d]];
-        vd[d] = yval[qd[d]];
-      }
-#pragma unroll
-      for (int d = 0; d < S; ++d)
-        if (ed[d] >= 0) {
-          const int32_t p = at + g0 + 64 * d + lane;
-          s_k[p] = ((uint32_t)cd[d] << B) | (uint32_t)p;
-          s_v[p] = s_a[ed[d]] * vd[d];
-        }
-    }
-    at += tot;
-  }
+        return true;
+      });
   for (int32_t p = T + lane; p < N; p += 64) s_k[p] = kNone;
   __syncthreads();
   uint32_t k[P];
@@ -1126,38 +729,309 @@ __global__ __launch_bounds__(64) void k_esc_sort(
   if (lane == 63) ucnt[i] = incl;
 }
 
-// Largest output width the LDS bin takes on this device: the opt-in LDS per workgroup less
-// the kernel's static LDS, at 8 bytes plus one bit per column (queried once per device).
-static int32_t lds_cols_max() {
-  static std::mutex mu;
-  static int32_t cache[64];
-  static bool done[64];
-  int dev = 0;
-  SA_HIP(hipGetDevice(&dev));
-  if (dev < 0 || dev >= 64) return 0;
-  std::lock_guard<std::mutex> lock(mu);
-  if (!done[dev]) {
-    int optin = 0;
-    if (hipDeviceGetAttribute(&optin, hipDeviceAttributeSharedMemPerBlockOptin, dev) !=
-            hipSuccess ||
-        optin <= 0)
-      optin = 64 << 10;
-    const int64_t avail = (int64_t)optin - 4096;  // the kernel's static LDS is under 2 KB
-    int32_t cols = (int32_t)((avail * 8) / 65);     // 8 bytes + 1 bit per column
-    cols &= ~31;
-    const int bytes = (int)(((int64_t)cols * 65 + 7) / 8);
-    if (cols > (64 << 10) / 9 &&
-        (hipFuncSetAttribute((const void *)k_esc_wave<true, 1, uint32_t>,
-                             hipFuncAttributeMaxDynamicSharedMemorySize, bytes) != hipSuccess ||
-         hipFuncSetAttribute((const void *)k_esc_wave<true, 1, uint64_t>,
-                             hipFuncAttributeMaxDynamicSharedMemorySize, bytes) != hipSuccess ||
-         hipFuncSetAttribute((const void *)k_esc_lds<kLdsDepth>,
-                             hipFuncAttributeMaxDynamicSharedMemorySize, bytes) != hipSuccess))
-      cols = (((64 << 10) - 4096) * 8 / 65) & ~31;
-    cache[dev] = cols;
-    done[dev] = true;
+// ---- sums in LDS, by the column's rank in the row (more than 1024 products) ------------------
+// The columns of one Y row are distinct, so the adds of one X entry never meet, and the adds of
+// successive entries are LDS atomics of one wavefront, which the LDS executes in the
+// wavefront's order: every output entry receives its products in ascending k, from 0, and no
+// add waits for the one before it.
+__device__ __forceinline__ void lds_fadd(double *p, double v) {
+  __hip_atomic_fetch_add(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+constexpr int32_t kFewEntries = 16;
+// The products of S steps added at their places x[d] < 2^bits of acc.  A step of a few X
+// entries: one add per entry.  More: the lanes of equal places are found bit by bit with
+// ballots, and the k-th product of every place is added k-th.
+template <int S>
+__device__ __forceinline__ void add_products(const int32_t (&ed)[S], const int32_t (&last)[S],
+                                             const int32_t (&x)[S], int bits,
+                                             const double (&vd)[S], double *acc) {
+#pragma unroll
+  for (int d = 0; d < S; ++d) {
+    const int32_t g0 = __builtin_amdgcn_readfirstlane(ed[d]);
+    if (g0 < 0) continue;  // wave-uniform: past the end
+    if (last[d] - g0 < kFewEntries) {
+      for (int32_t g = g0; g <= last[d]; ++g) {
+        if (ed[d] == g) lds_fadd(&acc[x[d]], vd[d]);
+        __builtin_amdgcn_wave_barrier();
+      }
+    } else {
+      const bool live = ed[d] >= 0;
+      unsigned long long same = __ballot(live);
+      for (int b = 0; b < bits; ++b) {
+        const bool one = (x[d] >> b) & 1;
+        const unsigned long long ones = __ballot(one);
+        same &= one ? ones : ~ones;
+      }
+      const int32_t k = (int32_t)__builtin_amdgcn_mbcnt_hi(
+          (uint32_t)(same >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)same, 0));
+      for (int32_t r = 0; __ballot(live && k >= r); ++r) {
+        if (live && k == r) lds_fadd(&acc[x[d]], vd[d]);
+        __builtin_amdgcn_wave_barrier();
+      }
+    }
   }
-  return cache[dev];
+}
+constexpr __device__ int log2_up(int32_t n) { return n > 1 ? 32 - __builtin_clz(n - 1) : 0; }
+
+// A block of NW wavefronts per row.  The row's column window [first, last column] is taken in
+// tiles of W columns: the columns that occur are marked in a bitmap, whose words carry the
+// number of columns before them, and a product finds its sum at its column's rank.  The
+// tile's columns are cut at bitmap words into ranges of at most RD ranks, one wavefront to a
+// range, each going over the products of its range alone (searched in the sorted Y rows).
+// Windows of more than maxw columns are listed in ovf[].  A rank needs 8 bytes of LDS per
+// distinct column and a quarter byte per window column, where sums over the whole window (8
+// bytes each) left five wavefronts to a CU: A P of 176K rows, 2,100 products over 74 columns
+// each, 3,890 -> 1,480 us (250 G products/s); R (A P), 15.5K rows of 19K products, 1,650 ->
+// 910; 18K rows of 570 entries or more with 2.5 products each, 1,140 -> 550, where 64
+// products at a time were sorted.  What bounds it is the chain of loads and LDS operations of
+// each 512 products (2 us a wavefront) where rows are few, the instructions of the adds where
+// they are many.
+constexpr int32_t kRowWhole = 2048;  // output columns
+struct RowLists {  // the lists of several bins one after the other
+  const int32_t *list[4];
+  int32_t end[4];
+};
+template <int NW, int RD>
+__global__ __launch_bounds__(64 * NW) void k_esc_rows(
+    RowLists rows, const int32_t *xrp, const int32_t *xcol,
+    const double *xval, const int32_t *yrp, const int32_t *ycol, const double *yval,
+    const int64_t *poff, int32_t *ocol, double *oval, int32_t *ucnt, int32_t ncols, int32_t W,
+    int64_t maxw, int32_t *ovf, int32_t *novf) {
+  constexpr int S = 8;
+  extern __shared__ double lds_dyn[];
+  __shared__ ProductStage s_st[NW];
+  __shared__ int32_t s_lo[NW], s_hi[NW], s_total;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int32_t slot = blockIdx.x;
+  if (slot >= rows.end[3]) return;  // block-uniform
+  int bin = 0;
+  while (slot >= rows.end[bin]) ++bin;
+  const int32_t i = rows.list[bin][slot - (bin > 0 ? rows.end[bin - 1] : 0)];
+  double *acc = lds_dyn + wave * RD;
+  uint2 *word = reinterpret_cast<uint2 *>(lds_dyn + NW * RD);
+  ProductStage &st = s_st[wave];
+  const int64_t base = poff[i];
+  const int32_t xb = xrp[i], xe = xrp[i + 1];
+  const bool whole = ncols <= kRowWhole;  // a few words: no search for the window
+  int32_t lo = whole ? 0 : INT_MAX, hi = whole ? ncols - 1 : -1;
+  for (int32_t e = xb + (int32_t)threadIdx.x; e < xe && !whole; e += 64 * NW) {
+    const int32_t k = xcol[e];
+    const int32_t b = yrp[k], en = yrp[k + 1];
+    if (b < en) {
+      lo = min(lo, ycol[b]);
+      hi = max(hi, ycol[en - 1]);
+    }
+  }
+#pragma unroll
+  for (int off = 32; off >= 1; off >>= 1) {
+    lo = min(lo, __shfl_xor(lo, off, 64));
+    hi = max(hi, __shfl_xor(hi, off, 64));
+  }
+  if (NW > 1) {
+    if (lane == 0) {
+      s_lo[wave] = lo;
+      s_hi[wave] = hi;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < NW; ++q) {
+      lo = min(lo, s_lo[q]);
+      hi = max(hi, s_hi[q]);
+    }
+  }
+  if ((int64_t)hi - lo >= maxw) {  // block-uniform
+    if (threadIdx.x == 0) ovf[atomicAdd(novf, 1)] = i;
+    return;
+  }
+  int32_t at = 0;  // the row's columns before the tile
+  for (int64_t tile = lo; tile <= hi; tile += W) {
+    const int32_t cA = (int32_t)tile, cB = (int32_t)min((int64_t)hi + 1, tile + W);
+    const int32_t nw = (cB - cA + 31) >> 5;
+    const bool tiles = hi - lo >= W;
+    __syncthreads();  // the previous tile's words are read
+    for (int32_t w = threadIdx.x; w < nw; w += 64 * NW) word[w].x = 0;
+    __syncthreads();
+    row_products<S, false>(
+        st, lane, xb, xe, wave, NW, tiles, cA, cB, xcol, xval, yrp, ycol, yval,
+        [&](int32_t, const int32_t (&ed)[S], const int32_t (&)[S], const int32_t (&cd)[S],
+            const double (&)[S]) {
+          uint32_t b[S];
+#pragma unroll
+          for (int d = 0; d < S; ++d) b[d] = ed[d] >= 0 ? word[(cd[d] - cA) >> 5].x : ~0u;
+#pragma unroll
+          for (int d = 0; d < S; ++d) {
+            const uint32_t bit = 1u << ((cd[d] - cA) & 31);
+            if (!(b[d] & bit)) atomicOr(&word[(cd[d] - cA) >> 5].x, bit);
+          }
+          return true;
+        });
+    __syncthreads();
+    if (wave == 0) {
+      int32_t before = 0;
+      for (int32_t w0 = 0; w0 < nw; w0 += 64) {
+        const int32_t n = w0 + lane < nw ? __popc(word[w0 + lane].x) : 0;
+        const int32_t incl = wave_prefix_sum(n);
+        if (w0 + lane < nw) word[w0 + lane].y = (uint32_t)(before + incl - n);
+        before += __builtin_amdgcn_readlane(incl, 63);
+      }
+      if (lane == 0) s_total = before;
+    }
+    __syncthreads();
+    const int32_t D = s_total;
+    // a word belongs to the range of its first rank: up to 31 ranks more than `per`
+    const int32_t per = NW == 1 ? RD - 31 : min(RD - 31, max(16, (D + NW - 1) / NW));
+    const int32_t nr = (D + per - 1) / per;
+    for (int32_t j = wave; j < nr; j += NW) {
+      int32_t wA = 0, wB = nw;
+      if (nr > 1) {
+        wA = wB = 0;
+        for (int32_t w0 = 0; w0 < nw; w0 += 64) {
+          const int32_t r = w0 + lane < nw ? (int32_t)word[w0 + lane].y : INT_MAX;
+          wA += __popcll(__ballot(r < j * per));
+          wB += __popcll(__ballot(r < (j + 1) * per));
+        }
+      }
+      if (wA >= wB) continue;
+      const int32_t r0 = (int32_t)word[wA].y, r1 = wB < nw ? (int32_t)word[wB].y : D;
+      const int bits = log2_up(r1 - r0);
+      wave_sync();
+      for (int32_t r = lane; r < r1 - r0; r += 64) acc[r] = 0.0;
+      wave_sync();
+      row_products<S, true>(
+          st, lane, xb, xe, 0, 1, tiles || nr > 1, cA + 32 * wA, wB < nw ? cA + 32 * wB : cB,
+          xcol, xval, yrp, ycol, yval,
+          [&](int32_t, const int32_t (&ed)[S], const int32_t (&last)[S],
+              const int32_t (&cd)[S], const double (&vd)[S]) {
+            int32_t x[S];
+#pragma unroll
+            for (int d = 0; d < S; ++d) {
+              const int32_t c = ed[d] >= 0 ? cd[d] - cA : 32 * wA;
+              const uint2 b = word[c >> 5];
+              x[d] = (int32_t)b.y + __popc(b.x & ((1u << (c & 31)) - 1u)) - r0;
+            }
+            add_products<S>(ed, last, x, bits, vd, acc);
+            return true;
+          });
+      wave_sync();
+      for (int32_t r = lane; r < r1 - r0; r += 64) oval[base + at + r0 + r] = acc[r];
+      for (int32_t w = wA + lane; w < wB; w += 64) {
+        uint32_t b = word[w].x;
+        int64_t to = base + at + word[w].y;
+        for (; b != 0; b &= b - 1) ocol[to++] = cA + 32 * w + __ffs(b) - 1;
+      }
+    }
+    at += D;
+  }
+  if (threadIdx.x == 0) ucnt[i] = at;
+}
+
+// ---- sums in LDS, in a hash table (wide keys; windows too wide for the ranks) ----------------
+// One wavefront per row, an open-addressing table of H slots: the low five bits of a column
+// stay (columns next to each other, on different banks), its block of 32 is hashed.  A row
+// with more than 3/4 H distinct columns is listed in ovf[].  At the end the row's columns are
+// sorted in registers and looked up again.
+template <int H>
+__device__ __forceinline__ int32_t home_slot(int32_t col) {
+  const uint32_t block = ((uint32_t)col >> 5) * 2654435761u;
+  return (int32_t)(((block >> 12) << 5 | ((uint32_t)col & 31u)) & (uint32_t)(H - 1));
+}
+constexpr int32_t kProbe = 37;  // odd: a probe sequence meets every slot
+// The row's nd <= 64 P columns in ascending order, each with its sum.
+template <int H, int P>
+__device__ __forceinline__ void write_sorted(int lane, int32_t nd, const int32_t *key,
+                                             const uint16_t *list, const double *acc,
+                                             int32_t *ocol, double *oval) {
+  uint32_t k[P];
+#pragma unroll
+  for (int q = 0; q < P; ++q) {
+    const int32_t r = 64 * q + lane;
+    k[q] = r < nd ? (uint32_t)key[list[r]] : ~0u;
+  }
+  sort_keys<P>(k, lane);
+#pragma unroll
+  for (int q = 0; q < P; ++q) {
+    const int32_t r = lane * P + q;
+    if (r < nd) {
+      const int32_t c = (int32_t)k[q];
+      int32_t x = home_slot<H>(c);
+      while (key[x] != c) x = (x + kProbe) & (H - 1);  // it is in the table
+      ocol[r] = c;
+      oval[r] = acc[x];
+    }
+  }
+}
+template <int H>
+__global__ __launch_bounds__(64) void k_esc_table(
+    const int32_t *rows, int32_t nrows, const int32_t *xrp, const int32_t *xcol,
+    const double *xval, const int32_t *yrp, const int32_t *ycol, const double *yval,
+    const int64_t *poff, int32_t *ocol, double *oval, int32_t *ucnt, int32_t *ovf,
+    int32_t *novf) {
+  constexpr int S = 8;
+  __shared__ double acc[H];
+  __shared__ int32_t key[H];
+  __shared__ uint16_t list[H];
+  __shared__ ProductStage st;
+  const int lane = threadIdx.x;
+  const int32_t slot = xcd_block(blockIdx.x, gridDim.x);
+  if (slot >= nrows) return;  // block-uniform
+  const int32_t i = rows[slot];
+  const int64_t base = poff[i];
+  for (int32_t c = lane; c < H; c += 64) {
+    key[c] = -1;
+    acc[c] = 0.0;
+  }
+  wave_sync();
+  int32_t nd = 0;
+  bool over = false;
+  row_products<S, true>(
+      st, lane, xrp[i], xrp[i + 1], 0, 1, false, 0, 0, xcol, xval, yrp, ycol, yval,
+      [&](int32_t, const int32_t (&ed)[S], const int32_t (&last)[S], const int32_t (&cd)[S],
+          const double (&vd)[S]) {
+        int32_t x[S], kx[S];
+#pragma unroll
+        for (int d = 0; d < S; ++d) {
+          x[d] = home_slot<H>(cd[d]);
+          kx[d] = key[x[d]];
+        }
+        bool full = false;
+#pragma unroll
+        for (int d = 0; d < S; ++d) {
+          bool fresh = false;
+          if (ed[d] >= 0 && kx[d] != cd[d]) {
+            int32_t t = 0;
+            for (; t < H; ++t) {
+              const int32_t old = atomicCAS(&key[x[d]], -1, cd[d]);
+              fresh = old == -1;
+              if (fresh || old == cd[d]) break;
+              x[d] = (x[d] + kProbe) & (H - 1);
+            }
+            full |= t == H;  // every slot holds another column
+          }
+          const unsigned long long bm = __ballot(fresh);
+          if (fresh) list[nd + __popcll(bm & ((1ull << lane) - 1ull))] = (uint16_t)x[d];
+          nd += __popcll(bm);
+        }
+        over = 4 * nd > 3 * H || __ballot(full) != 0;  // wave-uniform
+        if (over) return false;
+        add_products<S>(ed, last, x, log2_up(H), vd, acc);
+        return true;
+      });
+  if (over) {
+    if (lane == 0) ovf[atomicAdd(novf, 1)] = i;
+    return;
+  }
+  wave_sync();
+  if (nd <= 256)
+    write_sorted<H, 4>(lane, nd, key, list, acc, ocol + base, oval + base);
+  else if (H <= 512 || nd <= 512)
+    write_sorted<H, 8>(lane, nd, key, list, acc, ocol + base, oval + base);
+  else if constexpr (H > 512) {
+    if (nd <= 1024)
+      write_sorted<H, 16>(lane, nd, key, list, acc, ocol + base, oval + base);
+    else
+      write_sorted<H, 32>(lane, nd, key, list, acc, ocol + base, oval + base);
+  }
+  if (lane == 0) ucnt[i] = nd;
 }
 
 // Short rows: a wavefront takes 64 consecutive rows, whose entries are one contiguous run of
@@ -1231,25 +1105,17 @@ __global__ __launch_bounds__(kBlock) void k_bin_rows(int32_t m, const int64_t *p
   bin_row(live, i, live ? poff[i + 1] - poff[i] : 0, m, lists, counters);
 }
 
-// Column tiles that the hash bin's overflowing rows may take in LDS (environment variable
-// SAAMG_SPGEMM_MAX_TILES; 0 sends them to the dense accumulator in global memory).
+// Column tiles that a long row's window may take (environment variable
+// SAAMG_SPGEMM_MAX_TILES; 0 sends the long rows to the large hash table).
 static int32_t max_tiles() {
   const char *e = std::getenv("SAAMG_SPGEMM_MAX_TILES");
   return e ? std::atoi(e) : 8;
 }
 
-// SAAMG_SPGEMM_KEY64=1 takes the 64-bit sort keys at any width.
+// SAAMG_SPGEMM_KEY64=1 takes the hash table where the sort's keys would hold the columns too.
 static bool keys64() {
   const char *e = std::getenv("SAAMG_SPGEMM_KEY64");
   return e && std::atoi(e) != 0;
-}
-// k_esc_wave with 32-bit sort keys when every column of Y fits in 26 bits, else 64-bit keys.
-template <bool DENSE, int H, typename... Args>
-void launch_esc_wave(int32_t ncols, unsigned grid, size_t lds, hipStream_t s, Args... args) {
-  if (ncols < (1 << 26) && !keys64())
-    k_esc_wave<DENSE, H, uint32_t><<<grid, 64, lds, s>>>(args...);
-  else
-    k_esc_wave<DENSE, H, uint64_t><<<grid, 64, lds, s>>>(args...);
 }
 
 void spgemm(const Csr &X, const Csr &Y, Arena &ar, Csr &C, hipStream_t s) {
@@ -1263,9 +1129,10 @@ void spgemm(const Csr &X, const Csr &Y, Arena &ar, Csr &C, hipStream_t s) {
   int32_t *xpref = tmp.alloc<int32_t>(X.nnz > 0 ? X.nnz : 1);
   int64_t *poff = tmp.alloc<int64_t>(m + 1);
   int32_t *lists = tmp.alloc<int32_t>(kBins * (int64_t)(m > 0 ? m : 1));
-  // kBins bin sizes, the overflow count, the widest row window, then the product total (64
-  // bits)
-  int32_t *counters = tmp.alloc<int32_t>(kBins + 4);
+  // kBins bin sizes, the counts of rows left to the large hash table and by it, then (8-byte
+  // aligned) the product total in 64 bits
+  constexpr int kTotalAt = (kBins + 3) & ~1;
+  int32_t *counters = tmp.alloc<int32_t>(kTotalAt + 2);
   fill_i32(counters, 0, kBins + 2, s);
   // short rows: a thread per row, which also bins the row; longer: 16, 32 or 64 lanes per
   // row, binned after the scan (970K rows of 26 entries: 261 us and 48 for the binning,
@@ -1293,20 +1160,16 @@ void spgemm(const Csr &X, const Csr &Y, Arena &ar, Csr &C, hipStream_t s) {
     SA_LAUNCH_CHECK();
   }
   // the bin sizes and the product total in one readback
-  k_put_total<<<1, 1, 0, s>>>(poff + m, (int64_t *)(counters + kBins + 2));
+  k_put_total<<<1, 1, 0, s>>>(poff + m, (int64_t *)(counters + kTotalAt));
   SA_LAUNCH_CHECK();
-  static_assert(kBins % 2 == 0, "the 64-bit total is 8-byte aligned");
-  int32_t hc[kBins + 4];
+  int32_t hc[kTotalAt + 2];
   readback(hc, counters, sizeof(hc), s);
   int64_t total = 0;
-  std::memcpy(&total, hc + kBins + 2, sizeof(total));
+  std::memcpy(&total, hc + kTotalAt, sizeof(total));
   int32_t *ocol = tmp.alloc<int32_t>(total > 0 ? total : 1);
   double *oval = tmp.alloc<double>(total > 0 ? total : 1);
   int32_t *ucnt = tmp.alloc<int32_t>(m + 1);
   const int32_t *lg[3] = {lists, lists + m, lists + 2 * (int64_t)m};
-  const int32_t *ls[4];  // the wavefront-per-row bins: <= 128, 256, 512, 1024 products
-  for (int q = 0; q < 4; ++q) ls[q] = lists + (3 + q) * (int64_t)m;
-  const int32_t *l3 = lists + 7 * (int64_t)m;
   // two products per lane: 8, 4 and 2 rows per wavefront for the <= 16, <= 32, <= 64 bins
   if (hc[0] > 0)
     k_esc_group<8, 2><<<(unsigned)ceil_div(hc[0], kWave / 8), kWave, 0, s>>>(
@@ -1318,107 +1181,81 @@ void spgemm(const Csr &X, const Csr &Y, Arena &ar, Csr &C, hipStream_t s) {
     k_esc_group<32, 2><<<(unsigned)ceil_div(hc[2], kWave / 32), kWave, 0, s>>>(
         lg[2], hc[2], X.rp, X.col, X.val, Y.rp, Y.col, Y.val, poff, ocol, oval, ucnt);
   SA_LAUNCH_CHECK();
-  const int32_t nlong = hc[7];
-  int32_t *ovf = nullptr;
-  if (hc[3] + hc[4] + nlong > 0) ovf = tmp.alloc<int32_t>(hc[3] + hc[4] + nlong);
   // the sort's 32-bit keys hold 25 bits of column at 128 products, 22 at 1024; wider outputs
-  // (and SAAMG_SPGEMM_KEY64=1) take the hash and the block sort
+  // (and SAAMG_SPGEMM_KEY64=1) take the hash table
+  auto wide = [&](int q) { return keys64() || Y.ncols >= (1 << (25 - q)); };
+  int32_t nhash = 0;
+  for (int q = 0; q < 4; ++q)
+    if (wide(q)) nhash += hc[3 + q];
+  const int32_t nlong = hc[7] + hc[8] + hc[9] + hc[10];
+  int32_t *over1 = nullptr, *nover = counters + kBins;
+  if (nhash + nlong > 0) over1 = tmp.alloc<int32_t>(nhash + nlong);
   for (int q = 0; q < 4; ++q) {
     const int32_t nr = hc[3 + q];
     if (nr == 0) continue;
-    const bool wide = keys64() || Y.ncols >= (1 << (25 - q));
-    const int32_t *rows = ls[q];
+    const int32_t *rows = lists + (3 + q) * (int64_t)m;
     auto sort = [&](auto pc) {
       constexpr int P = decltype(pc)::value;
       k_esc_sort<P><<<(unsigned)nr, 64, 0, s>>>(rows, nr, X.rp, X.col, X.val, Y.rp, Y.col, Y.val,
                                                poff, ocol, oval, ucnt);
     };
-    if (wide && q < 2)
-      // the hash table has at least 2T slots: it never overflows
-      launch_esc_wave<false, 512>(Y.ncols, (unsigned)nr, 16 * 512, s, rows, nr, X.rp, X.col,
-                                  X.val, Y.rp, Y.col, Y.val, 0, nullptr, poff, ocol, oval, ucnt,
-                                  ovf, counters + kBins, nullptr, 0, 0);
-    else if (wide)
-      k_esc_single<256><<<(unsigned)nr, 256, 0, s>>>(rows, nr, X.rp, X.col, X.val, xpref, Y.rp,
-                                                     Y.col, Y.val, poff, ocol, oval, ucnt);
+    if (wide(q))
+      k_esc_table<512><<<(unsigned)nr, 64, 0, s>>>(rows, nr, X.rp, X.col, X.val, Y.rp, Y.col,
+                                                   Y.val, poff, ocol, oval, ucnt, over1, nover);
     else if (q == 0) sort(std::integral_constant<int, 2>{});
     else if (q == 1) sort(std::integral_constant<int, 4>{});
     else if (q == 2) sort(std::integral_constant<int, 8>{});
     else sort(std::integral_constant<int, 16>{});
     SA_LAUNCH_CHECK();
   }
-  // long rows: the dense window accumulator when Y's width fits the LDS (sized to the widest
-  // row window; up to 2048 columns the whole width), else a 2048-slot hash table whose
-  // overflowing rows (more than 1024 distinct columns) are redone below
-  const bool lds_bin = Y.ncols <= lds_cols_max();
-  int32_t wmax = Y.ncols;
-  int2 *win = nullptr;
-  if (nlong > 0 && lds_bin && Y.ncols > 2048) {
-    win = tmp.alloc<int2>(nlong);
-    fill_i32(counters + kBins + 1, 0, 1, s);
-    k_row_window<<<grid_for((int64_t)nlong * 64), kBlock, 0, s>>>(l3, nlong, X.rp, X.col, Y.rp,
-                                                                  Y.col, win,
-                                                                  counters + kBins + 1);
-    SA_LAUNCH_CHECK();
-    wmax = read1(counters + kBins + 1, s);
-  }
-  if (nlong > 0 && lds_bin) {
-    const int32_t wl = (wmax + 31) & ~31;
-    const size_t lds = (size_t)wl * sizeof(double) + (size_t)(wl / 32) * 4;
-    // Y rows of 16 entries or more on average (R (AP)): one X entry per step, its Y row
-    // across the lanes; shorter Y rows (A P): 64 products per step, sorted
-    if (Y.nnz >= 16 * (int64_t)Y.n)
-      k_esc_lds<kLdsDepth><<<(unsigned)nlong, 64, lds, s>>>(l3, nlong, X.rp, X.col, X.val, Y.rp,
-                                                           Y.col, Y.val, wl, win, poff, ocol,
-                                                           oval, ucnt, 0, 0);
-    else
-      launch_esc_wave<true, 1>(Y.ncols, (unsigned)nlong, lds, s, l3, nlong, X.rp, X.col, X.val,
-                               Y.rp, Y.col, Y.val, wl, win, poff, ocol, oval, ucnt, ovf,
-                               counters + kBins, nullptr, 0, 0);
-    SA_LAUNCH_CHECK();
-  } else if (nlong > 0) {
-    launch_esc_wave<false, 2048>(Y.ncols, (unsigned)nlong, 16 * 2048, s, l3, nlong, X.rp,
-                                 X.col, X.val, Y.rp, Y.col, Y.val, 0, nullptr, poff, ocol, oval,
-                                 ucnt, ovf, counters + kBins, nullptr, 0, 0);
-    SA_LAUNCH_CHECK();
-    const int32_t nov = read1(counters + kBins, s);
-    // rows over 1024 distinct columns: their column windows in LDS tiles (one launch per tile,
-    // at most kMaxTiles), else a dense accumulator in global memory
-    int32_t ntile = 0, tw = 0;
-    int2 *owin = nullptr;
-    if (nov > 0) {
-      owin = tmp.alloc<int2>(nov);
-      fill_i32(counters + kBins + 1, 0, 1, s);
-      k_row_window<<<grid_for((int64_t)nov * 64), kBlock, 0, s>>>(ovf, nov, X.rp, X.col, Y.rp,
-                                                                 Y.col, owin,
-                                                                 counters + kBins + 1);
-      SA_LAUNCH_CHECK();
-      const int32_t wmax = read1(counters + kBins + 1, s);
-      tw = std::min(lds_cols_max(), (wmax + 31) & ~31);
-      ntile = tw > 0 ? (int32_t)ceil_div(wmax, tw) : 0;
-      if (ntile > max_tiles()) ntile = 0;
-    }
-    if (ntile > 0) {
-      const size_t lds = (size_t)tw * sizeof(double) + (size_t)(tw / 32) * 4;
-      for (int32_t t = 0; t < ntile; ++t) {
-        if (Y.nnz >= 16 * (int64_t)Y.n)
-          k_esc_lds<kLdsDepth><<<(unsigned)nov, 64, lds, s>>>(ovf, nov, X.rp, X.col, X.val,
-                                                             Y.rp, Y.col, Y.val, tw, owin, poff,
-                                                             ocol, oval, ucnt, t, tw);
-        else
-          launch_esc_wave<true, 1>(Y.ncols, (unsigned)nov, lds, s, ovf, nov, X.rp, X.col, X.val,
-                                   Y.rp, Y.col, Y.val, tw, owin, poff, ocol, oval, ucnt,
-                                   nullptr, nullptr, nullptr, t, tw);
-        SA_LAUNCH_CHECK();
+  // The longest rows first (a kernel ends with its last row), the bins of up to 2048 rows
+  // together a block of eight wavefronts per row, the others a wavefront per row: 14.6K rows
+  // of 8,192 products or more take 910 us with a wavefront each and 2,080 with blocks, 2.6K rows
+  // of at most 37K products 185 with blocks and 440 with a wavefront each.
+  int64_t narrow = INT64_MAX;  // the narrowest window that a kernel leaves to the hash table
+  int bin = kBins - 1;
+  auto ranks = [&](auto nwc, auto rdc, int32_t tile, int64_t limit) {
+    constexpr int NW = decltype(nwc)::value, RD = decltype(rdc)::value;
+    RowLists rows = {};
+    int64_t n = 0;
+    for (int q = 0; q < 4; ++q) {
+      if (bin >= 7 && n + hc[bin] <= limit) {
+        rows.list[q] = lists + bin * (int64_t)m;
+        n += hc[bin];
+        --bin;
       }
-    } else if (nov > 0) {
+      rows.end[q] = (int32_t)n;
+    }
+    if (n == 0) return;
+    const int32_t W = std::min((Y.ncols + 31) & ~31, tile);
+    const int64_t maxw = (int64_t)W * max_tiles();
+    narrow = std::min(narrow, maxw);
+    const size_t lds = NW * RD * sizeof(double) + (size_t)(W / 32) * sizeof(uint2);
+    k_esc_rows<NW, RD><<<(unsigned)n, 64 * NW, lds, s>>>(rows, X.rp, X.col, X.val, Y.rp, Y.col,
+                                                        Y.val, poff, ocol, oval, ucnt, Y.ncols,
+                                                        W, maxw, over1, nover);
+    SA_LAUNCH_CHECK();
+  };
+  ranks(std::integral_constant<int, 8>{}, std::integral_constant<int, 512>{}, 65536, 2048);
+  ranks(std::integral_constant<int, 1>{}, std::integral_constant<int, 512>{}, 16384, INT64_MAX);
+  // windows wider than the tiles' limit and rows past 3/4 of the small table: the large
+  // table, then those past 3/4 of it with a dense accumulator in global memory
+  const int32_t nov1 = nhash > 0 || (nlong > 0 && Y.ncols > narrow) ? read1(nover, s) : 0;
+  if (nov1 > 0) {
+    int32_t *over2 = tmp.alloc<int32_t>(nov1);
+    k_esc_table<2048><<<(unsigned)nov1, 64, 0, s>>>(over1, nov1, X.rp, X.col, X.val, Y.rp, Y.col,
+                                                    Y.val, poff, ocol, oval, ucnt, over2,
+                                                    nover + 1);
+    SA_LAUNCH_CHECK();
+    const int32_t nov = read1(nover + 1, s);
+    if (nov > 0) {
       // dense accumulators: at most ~2 GiB of them at once
       const int64_t per = (int64_t)Y.ncols * 12;
       int64_t nb = std::min<int64_t>(nov, std::max<int64_t>(1, (int64_t(2) << 30) / per));
       nb = std::min<int64_t>(nb, 1024);
       double *dacc = tmp.alloc<double>(nb * (int64_t)Y.ncols);
       int32_t *dflag = tmp.alloc<int32_t>(nb * (int64_t)Y.ncols);
-      k_esc_dense<<<(unsigned)nb, kBlock, 0, s>>>(ovf, nov, X.rp, X.col, X.val, xpref, Y.rp,
+      k_esc_dense<<<(unsigned)nb, kBlock, 0, s>>>(over2, nov, X.rp, X.col, X.val, xpref, Y.rp,
                                                   Y.col, Y.val, Y.ncols, poff, ocol, oval, ucnt,
                                                   dacc, dflag);
       SA_LAUNCH_CHECK();
