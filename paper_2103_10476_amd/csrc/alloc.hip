@@ -13,6 +13,7 @@
 #include <chrono>
 #include <cstdlib>
 #include <cstring>
+#include <deque>
 #include <map>
 #include <mutex>
 #include <unordered_map>
@@ -234,6 +235,29 @@ __global__ void k_copy_words(HostWords w, const uint32_t *src, int32_t nw) {
   post_words(w, src, nw);
 }
 
+static thread_local std::deque<std::function<bool()>> t_beside;
+static thread_local hipStream_t t_beside_main = nullptr;
+BesideScope::BesideScope(hipStream_t main) {
+  t_beside.clear();
+  t_beside_main = main;
+}
+BesideScope::~BesideScope() { t_beside.clear(); }
+void beside_push(std::function<bool()> job) { t_beside.push_back(std::move(job)); }
+bool beside_step() {
+  if (t_beside.empty()) return false;
+  try {
+    if (!t_beside.front()()) t_beside.pop_front();
+  } catch (...) {
+    (void)hipStreamSynchronize(t_beside_main);
+    throw;
+  }
+  return true;
+}
+void beside_drain() {
+  while (beside_step()) {
+  }
+}
+
 HostWords host_words() {
   uint32_t *st = (uint32_t *)pinned_buffer(t_words, 4 * (kWordsMax + 1));
   uint32_t *dst = nullptr;
@@ -260,6 +284,7 @@ void host_words_wait(const HostWords &w, void *host, size_t bytes, hipStream_t s
         seen = true;
         break;
       }
+      if (beside_step()) continue;
       if ((polls & 255u) == 255u &&
           std::chrono::duration_cast<std::chrono::nanoseconds>(std::chrono::steady_clock::now() -
                                                                t0)

@@ -5,6 +5,7 @@
 
 #include <cstdint>
 #include <cstdio>
+#include <functional>
 #include <stdexcept>
 #include <string>
 #include <vector>
@@ -89,6 +90,19 @@ __device__ __forceinline__ void post_words(const HostWords &w, const uint32_t *s
   __syncthreads();
   if (threadIdx.x == 0) *(volatile uint32_t *)(w.dev + kWordsMax) = w.seq;
 }
+// Launches for a second stream, queued by the calling thread where it would wait for the first:
+// while it polls for a readback or a status word, beside_step() makes one call of the oldest
+// job pushed (a job returns false with its last launches queued; beside_step returns false with
+// no job left).  beside_drain makes the rest, before a join of the streams.  Jobs
+// live within the scope object of their thread's call; a call that throws leaves the main
+// stream synchronised, so nothing it still runs writes a word that a later wait polls.
+struct BesideScope {
+  explicit BesideScope(hipStream_t main);
+  ~BesideScope();  // drops the jobs that a failed call left
+};
+void beside_push(std::function<bool()> job);
+bool beside_step();
+void beside_drain();
 // A per-thread pinned host buffer of at least `bytes`, separate from the readback staging:
 // kernels write it through its device mapping while the calling thread polls it.
 void *pinned_status(size_t bytes);

@@ -185,12 +185,23 @@ static void numeric_lump(sa_hierarchy *h, int l, bool fresh) {
     take_values(abar, L.Abar, s);
   }
 }
-static void numeric_damping(sa_hierarchy *h, int l, hipStream_t s, int32_t *err) {
+// As launches to be queued one call at a time (false: all are queued), like power_steps.
+static std::function<bool()> damping_steps(sa_hierarchy *h, int l, hipStream_t s, int32_t *err) {
   const sa_options &o = h->opt;
   Level &L = h->lv[l];
   const bool unit = (o.variants & SA_1NORM) != 0 && o.one_norm_power == 0;
-  if (!unit) power_method(L.Abar, L.invD, o.power_iters, o.seed, l, 0, L.lam_d, s);
-  damping(L.lam_d, L.omega_d, unit, err, s);
+  std::function<bool()> power;
+  if (!unit) power = power_steps(L.Abar, L.invD, o.power_iters, o.seed, l, 0, L.lam_d, s);
+  double *lam = L.lam_d, *omega = L.omega_d;
+  return [=]() {
+    if (power && power()) return true;
+    damping(lam, omega, unit, err, s);
+    return false;
+  };
+}
+static void run_steps(const std::function<bool()> &steps) {
+  while (steps()) {
+  }
 }
 static void numeric_prolong(sa_hierarchy *h, int l, bool fresh) {
   const hipStream_t s = h->stream;
@@ -223,7 +234,7 @@ static void numeric_prolong(sa_hierarchy *h, int l, bool fresh) {
 static void numeric_level(sa_hierarchy *h, int l, bool fresh) {
   numeric_lump(h, l, fresh);
   check_err(h, E_ZERO_FDIAG, SA_ERR_NONPOSITIVE_DIAG, "zero diagonal in the filtered matrix");
-  numeric_damping(h, l, h->stream, h->err);
+  run_steps(damping_steps(h, l, h->stream, h->err));
   check_err(h, E_LAMBDA, SA_ERR_NEGATIVE_EIGENVALUE, "eigenvalue estimate not positive");
   numeric_prolong(h, l, fresh);
 }
@@ -320,15 +331,18 @@ static bool build_level(sa_hierarchy *h, int l) {
   }
   // Lumping needs the labels only, so it runs before the aggregation, and the power method
   // for the damping factor runs on the side stream (its own error word) while the root
-  // selection runs here.  Errors are checked in the sequential order afterwards; a level that
-  // turns out to be the coarsest ignores the lumping.
+  // selection runs here; its launches are queued where the host waits for the selection, whose
+  // stream stood still for them (some 30, 0.1 ms) otherwise.  Errors are checked in the
+  // sequential order afterwards; a level that turns out to be the coarsest ignores the
+  // lumping.
   numeric_lump(h, l, true);
   if (!h->side) h->side = side_stream(s);
   stream_after(h->side, s);
-  numeric_damping(h, l, h->side, h->err + 2);
+  beside_push(damping_steps(h, l, h->side, h->err + 2));
   L.nc = aggregate(n, nnzG, grp, gcol, o.agg_order, o.seed, l,
                    o.isolated == SA_ISOLATED_SINGLETON, L.agg, L.is_root, tmp, &root_vertex,
                    &L.mis_rounds, s);
+  beside_drain();
   stream_after(s, h->side);
   if (nnzG == 0) {  // no strong connection: the coarsest level, which keeps no numeric part
     L.Abar = Csr{};
@@ -436,25 +450,37 @@ __global__ void k_gather_scalars(ScalarGather g, double *out, int32_t zeros) {
   if (i < zeros) out[g.n + i] = 0.0;
 }
 
-// GPU part of level l's smoother set-up on stream s: the inverse diagonal of A_l and the
-// power method for its largest eigenvalue (non-positive diagonals flag E_DIAG in *err).
-static void smoother_gpu(sa_hierarchy *h, int l, bool fresh, hipStream_t s, int32_t *err) {
+// GPU part of level l's smoother set-up on stream s, as launches to be queued one call at a
+// time like power_steps: the inverse diagonal of A_l and the power method for its largest
+// eigenvalue (non-positive diagonals flag E_DIAG in *err).
+static std::function<bool()> smoother_steps(sa_hierarchy *h, int l, bool fresh, hipStream_t s,
+                                            int32_t *err) {
   Level &L = h->lv[l];
-  Arena tmp;
-  tmp.stream = s;
-  double *dval = tmp.alloc<double>(L.A.n);
-  find_diag(L.A.n, L.A.rp, L.A.col, L.A.val, dval, s);
   if (fresh && !L.sm_invD) {
     L.sm_invD = h->ar.alloc<double>(L.A.n);
     L.sm_lam_d = h->ar.alloc<double>(1);
   }
-  inv_diag(L.A.n, dval, L.sm_invD, err, s);
-  power_method(L.A, L.sm_invD, h->opt.power_iters, h->opt.seed, l, 1, L.sm_lam_d, s);
+  double *invD = L.sm_invD;
+  const Csr A = L.A;
+  const auto power =
+      power_steps(A, invD, h->opt.power_iters, h->opt.seed, l, 1, L.sm_lam_d, s);
+  bool first = true;
+  return [=]() mutable {
+    if (!first) return power();
+    first = false;
+    Arena tmp;
+    tmp.stream = s;
+    double *dval = tmp.alloc<double>(A.n);
+    find_diag(A.n, A.rp, A.col, A.val, dval, s);
+    inv_diag(A.n, dval, invD, err, s);
+    return true;
+  };
 }
 
-// Queues level l's smoother set-up on the side stream (level l is known not to be the
+// Queues level l's smoother set-up for the side stream (level l is known not to be the
 // coarsest): after the main stream's work so far (A_l, and any earlier use of blocks handed
-// out below), with its own error word; finish_setup joins it.
+// out below), with its own error word, its launches where the host waits for the main stream;
+// finish_setup joins it.
 static void smoother_async(sa_hierarchy *h, int l, bool fresh) {
   Level &L = h->lv[l];
   if (fresh) {
@@ -463,7 +489,7 @@ static void smoother_async(sa_hierarchy *h, int l, bool fresh) {
   }
   if (!h->side) h->side = side_stream(h->stream);
   stream_after(h->side, h->stream);
-  smoother_gpu(h, l, fresh, h->side, h->err + 1);
+  beside_push(smoother_steps(h, l, fresh, h->side, h->err + 1));
   L.sm_pending = true;
 }
 
@@ -477,8 +503,9 @@ static void finish_setup(sa_hierarchy *h, bool fresh) {
   bool joined = false;
   for (int l = 0; l + 1 < nl; ++l) {
     Level &L = h->lv[l];
-    if (!L.sm_pending) smoother_gpu(h, l, fresh, s, h->err);
+    if (!L.sm_pending) run_steps(smoother_steps(h, l, fresh, s, h->err));
     else if (!joined) {  // the levels queued on the side stream: join them once
+      beside_drain();
       stream_after(s, h->side);
       joined = true;
     }
@@ -650,6 +677,7 @@ static void validate_values(sa_hierarchy *h) {
 static void setup_impl(sa_hierarchy *h, const sa_csr *A, const double *B,
                        const double *coords, int32_t dim, int32_t bs = 1,
                        const double *Bm = nullptr, int32_t k = 0) {
+  BesideScope beside(h->stream);
   const double t0 = now_s();
   const hipStream_t s = h->stream;
   sa_options &o = h->opt;
@@ -718,6 +746,7 @@ static void setup_impl(sa_hierarchy *h, const sa_csr *A, const double *B,
 // Sprsfy drops, aggregates, the patterns of the filtered matrices, P, R and every A_l) and
 // the numbers are recomputed in the setup's order, each into the existing arrays.
 static void resetup_impl(sa_hierarchy *h, const double *val, const double *B, sa_location loc) {
+  BesideScope beside(h->stream);
   if (h->k > 0 && B) throw Error(SA_ERR_INVALID_ARG, "a systems hierarchy keeps its nullspace");
   const double t0 = now_s();
   const hipStream_t s = h->stream;

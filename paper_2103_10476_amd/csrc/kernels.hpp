@@ -262,8 +262,9 @@ void sprsfy(int32_t n, const int32_t *rp, const int32_t *col, uint8_t *mask,
 int64_t lump(int32_t n, int64_t nnz_a, const int32_t *rp, const int32_t *col, const double *val,
              const uint8_t *mask, bool offlmp, double tau, bool one_norm, double mult,
              bool wave, Arena &ar, Csr &abar, double *invD, int32_t *err, hipStream_t s);
-// Power method; writes the estimate to *lam (device).  ws: 3n doubles + dot workspace.
-void power_method(const Csr &M, const double *invD, int32_t iters, uint64_t seed,
+// Power method; writes the estimate to *lam (device).  The launches of one iteration per call,
+// until it returns false (see BesideScope).
+std::function<bool()> power_steps(const Csr &M, const double *invD, int32_t iters, uint64_t seed,
                   int32_t level, int32_t stream_id, double *lam, hipStream_t s);
 // omega = 4/(3 lambda) (or lambda = 1 first when `unit`), err bit 16 if lambda <= 0.
 void damping(double *lam, double *omega, bool unit, int32_t *err, hipStream_t s);

@@ -10,6 +10,7 @@
 #include <chrono>
 #include <climits>
 #include <cstdlib>
+#include <memory>
 #include <type_traits>
 
 #include "kernels.hpp"
@@ -1180,6 +1181,7 @@ static int32_t aggregate_impl(int32_t n, int64_t nnzG, const int32_t *grp, const
       launch_round(launched++);
       continue;
     }
+    if (beside_step()) continue;
     const auto now = std::chrono::steady_clock::now();
     if (std::chrono::duration_cast<std::chrono::nanoseconds>(now - wait_from).count() <
         spin_ns)
@@ -1948,37 +1950,53 @@ __global__ void k_rayleigh(const double *xy, const double *xx, const int32_t *de
   *lam = (*dead) ? 0.0 : (*xy / *xx);
 }
 
-void power_method(const Csr &M, const double *invD, int32_t iters, uint64_t seed, int32_t level,
-                  int32_t stream_id, double *lam, hipStream_t s) {
+// The iterations as launches to be queued one call at a time (false: the last one is queued):
+// beside a stage of the main stream whose launches the host must not fall behind with.
+std::function<bool()> power_steps(const Csr &M, const double *invD, int32_t iters, uint64_t seed,
+                                  int32_t level, int32_t stream_id, double *lam,
+                                  hipStream_t s) {
+  struct State {
+    Arena tmp;
+    double *x, *y, *ws, *sc;
+    unsigned long long *mx;
+    int32_t *dead;
+    int32_t t = 0;
+  };
+  const auto st = std::make_shared<State>();
   const int32_t n = M.n;
-  Arena tmp;
-  tmp.stream = s;
-  double *x = tmp.alloc<double>(n);
-  double *y = tmp.alloc<double>(n);
-  double *ws = tmp.alloc<double>(dot_ws_size(n));
-  double *sc = tmp.alloc<double>(4);
-  // two sets of kMaxSlots maxima (iteration t fills set t mod 2), then the dead flag
-  unsigned long long *mx = tmp.alloc<unsigned long long>(2 * kMaxSlots + 1);
-  int32_t *dead = (int32_t *)(mx + 2 * kMaxSlots);
-  fill_i32((int32_t *)mx, 0, 2 * (2 * kMaxSlots + 1), s);
-  k_power_init<<<grid_for(n), kBlock, 0, s>>>(n, seed, level, stream_id, x);
-  SA_LAUNCH_CHECK();
-  SpmvArgs<double> a = spmv_args<double>(M, M.val, x);
-  a.plain = true;  // the estimate decides the hierarchy: every row in sequential order
-  for (int32_t t = 1; t <= iters; ++t) {
-    unsigned long long *cur = mx + (t & 1) * kMaxSlots, *nxt = mx + ((t + 1) & 1) * kMaxSlots;
-    if (t == iters) spmv_scale<double>(a, invD, y, s);
-    else spmv_scale_max<double>(a, invD, y, cur, s);
-    if (t == iters) {
-      dot_f64(x, y, n, sc + 0, ws, s);
-      dot_f64(x, x, n, sc + 1, ws, s);
-      k_rayleigh<<<1, 1, 0, s>>>(sc + 0, sc + 1, dead, lam);
+  return [=]() {
+    const int32_t t = st->t++;
+    if (t == 0) {
+      st->tmp.stream = s;
+      st->x = st->tmp.alloc<double>(n);
+      st->y = st->tmp.alloc<double>(n);
+      st->ws = st->tmp.alloc<double>(dot_ws_size(n));
+      st->sc = st->tmp.alloc<double>(4);
+      // two sets of kMaxSlots maxima (iteration t fills set t mod 2), then the dead flag
+      st->mx = st->tmp.alloc<unsigned long long>(2 * kMaxSlots + 1);
+      st->dead = (int32_t *)(st->mx + 2 * kMaxSlots);
+      fill_i32((int32_t *)st->mx, 0, 2 * (2 * kMaxSlots + 1), s);
+      k_power_init<<<grid_for(n), kBlock, 0, s>>>(n, seed, level, stream_id, st->x);
       SA_LAUNCH_CHECK();
-      break;
+      return true;
     }
-    k_normalize<<<grid_for(n), kBlock, 0, s>>>(n, y, cur, nxt, x, dead);
+    SpmvArgs<double> a = spmv_args<double>(M, M.val, st->x);
+    a.plain = true;  // the estimate decides the hierarchy: every row in sequential order
+    unsigned long long *cur = st->mx + (t & 1) * kMaxSlots;
+    unsigned long long *nxt = st->mx + ((t + 1) & 1) * kMaxSlots;
+    if (t < iters) {
+      spmv_scale_max<double>(a, invD, st->y, cur, s);
+      k_normalize<<<grid_for(n), kBlock, 0, s>>>(n, st->y, cur, nxt, st->x, st->dead);
+      SA_LAUNCH_CHECK();
+      return true;
+    }
+    spmv_scale<double>(a, invD, st->y, s);
+    dot_f64(st->x, st->y, n, st->sc + 0, st->ws, s);
+    dot_f64(st->x, st->x, n, st->sc + 1, st->ws, s);
+    k_rayleigh<<<1, 1, 0, s>>>(st->sc + 0, st->sc + 1, st->dead, lam);
     SA_LAUNCH_CHECK();
-  }
+    return false;
+  };
 }
 
 __global__ void k_damping(double *lam, double *omega, bool unit, int32_t *err) {
