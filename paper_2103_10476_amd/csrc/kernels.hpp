@@ -80,13 +80,19 @@ void sort_rows(int32_t n, const int32_t *rp, int32_t *col, double *val, hipStrea
 
 template <class T> void spmv_store(const SpmvArgs<T> &a, T *y, hipStream_t s);
 template <class T> void spmv_scale(const SpmvArgs<T> &a, const T *d, T *y, hipStream_t s);
-// y = d (A x), plus max |y_i| (bit patterns of non-negative doubles) maximised atomically
-// into slots[0..kMaxSlots), one atomic per row block of the CSR kernels (the sliced-ELL copy,
-// if set, is not used)
+// y = d (A x'), plus max |y_i| (bit patterns of non-negative doubles) maximised atomically
+// into cur[0..kMaxSlots), one atomic per row block (the sliced-ELL copy, if set, is not used),
+// with x' = x scaled by the power of two of the maximum in prev (null: x).  Rows in sequential
+// order.
 constexpr int kMaxSlots = 256;
+struct MaxSlots {
+  unsigned long long *cur;         // filled
+  const unsigned long long *prev;  // read, or null
+  unsigned long long *next;        // cleared
+  int32_t *dead;                   // set where prev's maximum is zero or not finite
+};
 template <class T>
-void spmv_scale_max(const SpmvArgs<T> &a, const T *d, T *y, unsigned long long *slots,
-                    hipStream_t s);
+void spmv_scale_max(const SpmvArgs<T> &a, const T *d, T *y, const MaxSlots &m, hipStream_t s);
 template <class T> void spmv_resid(const SpmvArgs<T> &a, const T *f, T *r, hipStream_t s);
 template <class T> void spmv_add(const SpmvArgs<T> &a, T *u, hipStream_t s);
 // r = f - A u; d = (invD .* r) / theta
@@ -143,6 +149,9 @@ struct GmresScalars {
 // ws holds nv * dot_ws_size(n) doubles.
 void multi_dot_f64(const double *V, int64_t ldv, int32_t nv, const double *w, int64_t n,
                    double *c, double *ws, hipStream_t s);
+// res[0] = <x, y>, res[1] = <x, x>, each bitwise dot_f64's; ws of 2 dot_ws_size(n).
+void dot_xy_xx(const double *x, const double *y, int64_t n, double *res, double *ws,
+               hipStream_t s);
 // w[k] = w[k] - c[0] V_0[k] - c[1] V_1[k] - ... (nv terms in ascending order); with add,
 // w[k] = w[k] + c[0] V_0[k] + ... instead.
 void multi_axpy_f64(const double *V, int64_t ldv, int32_t nv, const double *c, double *w,

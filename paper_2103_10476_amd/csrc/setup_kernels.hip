@@ -12,6 +12,7 @@
 #include <cstdlib>
 #include <memory>
 #include <type_traits>
+#include <utility>
 
 #include "kernels.hpp"
 
@@ -1910,21 +1911,23 @@ int64_t lump(int32_t n, int64_t nnz_a, const int32_t *rp, const int32_t *col, co
 }
 
 // ---- power method (Sec. 1.1 damping; Sec. 3.1 ten sweeps) --------------------------------
-__global__ void k_power_init(int32_t n, uint64_t seed, int32_t level, int32_t stream,
-                             double *x) {
+// The start vector; block 0 clears the words of the maxima and the dead flag.
+__global__ __launch_bounds__(kBlock) void k_power_init(int32_t n, uint64_t seed, int32_t level,
+                                                       int32_t stream, double *x,
+                                                       unsigned long long *mx, int32_t words) {
+  if (blockIdx.x == 0)
+    for (int q = threadIdx.x; q < words; q += kBlock) mx[q] = 0ull;
   SA_ROW_KERNEL_BEGIN(n)
   const uint64_t z = splitmix64_dev(seed, stream_key_dev(stream, level, i));
   const double u = (double)(z >> 11) * (1.0 / 9007199254740992.0);
   x[i] = 2.0 * u - 1.0;
 }
 // x = y / 2^ilogb(m) with m = max |y_i|: every block reduces the kMaxSlots maxima that the
-// SpMV left (bit patterns of non-negative doubles, monotone), and block 0 clears the other
-// slot set, which the next iteration's SpMV fills.  A zero or non-finite maximum marks the
-// iteration dead.
+// SpMV left (bit patterns of non-negative doubles, monotone).  A zero or non-finite maximum
+// marks the iteration dead.  The last iteration's; the others scale x as they gather it.
 __global__ __launch_bounds__(kBlock) void k_normalize(int32_t n, const double *y,
                                                       const unsigned long long *slots,
-                                                      unsigned long long *next, double *x,
-                                                      int32_t *dead) {
+                                                      double *x, int32_t *dead) {
   static_assert(kMaxSlots == kBlock, "one slot per thread");
   __shared__ unsigned long long wm[kBlock / 64];
   unsigned long long m = slots[threadIdx.x];
@@ -1933,7 +1936,6 @@ __global__ __launch_bounds__(kBlock) void k_normalize(int32_t n, const double *y
     m = o > m ? o : m;
   }
   if ((threadIdx.x & 63) == 0) wm[threadIdx.x >> 6] = m;
-  if (blockIdx.x == 0) next[threadIdx.x] = 0ull;
   __syncthreads();
 #pragma unroll
   for (int q = 0; q < kBlock / 64; ++q) m = wm[q] > m ? wm[q] : m;
@@ -1957,7 +1959,7 @@ std::function<bool()> power_steps(const Csr &M, const double *invD, int32_t iter
                                   hipStream_t s) {
   struct State {
     Arena tmp;
-    double *x, *y, *ws, *sc;
+    double *v[2], *ws, *sc;
     unsigned long long *mx;
     int32_t *dead;
     int32_t t = 0;
@@ -1968,31 +1970,36 @@ std::function<bool()> power_steps(const Csr &M, const double *invD, int32_t iter
     const int32_t t = st->t++;
     if (t == 0) {
       st->tmp.stream = s;
-      st->x = st->tmp.alloc<double>(n);
-      st->y = st->tmp.alloc<double>(n);
-      st->ws = st->tmp.alloc<double>(dot_ws_size(n));
-      st->sc = st->tmp.alloc<double>(4);
-      // two sets of kMaxSlots maxima (iteration t fills set t mod 2), then the dead flag
-      st->mx = st->tmp.alloc<unsigned long long>(2 * kMaxSlots + 1);
-      st->dead = (int32_t *)(st->mx + 2 * kMaxSlots);
-      fill_i32((int32_t *)st->mx, 0, 2 * (2 * kMaxSlots + 1), s);
-      k_power_init<<<grid_for(n), kBlock, 0, s>>>(n, seed, level, stream_id, st->x);
+      st->v[0] = st->tmp.alloc<double>(n);
+      st->v[1] = st->tmp.alloc<double>(n);
+      st->ws = st->tmp.alloc<double>(2 * dot_ws_size(n));
+      st->sc = st->tmp.alloc<double>(2);
+      // three sets of kMaxSlots maxima (iteration t reads set t - 1, fills set t and clears set
+      // t + 1, mod 3), then the dead flag
+      st->mx = st->tmp.alloc<unsigned long long>(3 * kMaxSlots + 1);
+      st->dead = (int32_t *)(st->mx + 3 * kMaxSlots);
+      k_power_init<<<grid_for(n), kBlock, 0, s>>>(n, seed, level, stream_id, st->v[0], st->mx,
+                                                  3 * kMaxSlots + 1);
       SA_LAUNCH_CHECK();
       return true;
     }
-    SpmvArgs<double> a = spmv_args<double>(M, M.val, st->x);
-    a.plain = true;  // the estimate decides the hierarchy: every row in sequential order
-    unsigned long long *cur = st->mx + (t & 1) * kMaxSlots;
-    unsigned long long *nxt = st->mx + ((t + 1) & 1) * kMaxSlots;
+    auto set = [&](int32_t q) { return st->mx + (q % 3) * kMaxSlots; };
+    double *x = st->v[(t - 1) & 1], *y = st->v[t & 1];
     if (t < iters) {
-      spmv_scale_max<double>(a, invD, st->y, cur, s);
-      k_normalize<<<grid_for(n), kBlock, 0, s>>>(n, st->y, cur, nxt, st->x, st->dead);
-      SA_LAUNCH_CHECK();
+      const SpmvArgs<double> a = spmv_args<double>(M, M.val, x);
+      spmv_scale_max<double>(
+          a, invD, y, {set(t), t > 1 ? set(t - 1) : nullptr, set(t + 1), st->dead}, s);
       return true;
     }
-    spmv_scale<double>(a, invD, st->y, s);
-    dot_f64(st->x, st->y, n, st->sc + 0, st->ws, s);
-    dot_f64(st->x, st->x, n, st->sc + 1, st->ws, s);
+    if (t > 1) {
+      k_normalize<<<grid_for(n), kBlock, 0, s>>>(n, x, set(t - 1), y, st->dead);
+      SA_LAUNCH_CHECK();
+      std::swap(x, y);
+    }
+    SpmvArgs<double> a = spmv_args<double>(M, M.val, x);
+    a.plain = true;  // the estimate decides the hierarchy: every row in sequential order
+    spmv_scale<double>(a, invD, y, s);
+    dot_xy_xx(x, y, n, st->sc, st->ws, s);
     k_rayleigh<<<1, 1, 0, s>>>(st->sc + 0, st->sc + 1, st->dead, lam);
     SA_LAUNCH_CHECK();
     return false;

@@ -279,11 +279,11 @@ void spmv_scale(const SpmvArgs<T> &a, const T *d, T *y, hipStream_t s) {
   launch_spmv(a, EpScale<T>{d, y}, s);
 }
 template <class T>
-void spmv_scale_max(const SpmvArgs<T> &a, const T *d, T *y, unsigned long long *part,
-                    hipStream_t s) {
+void spmv_scale_max(const SpmvArgs<T> &a, const T *d, T *y, const MaxSlots &m, hipStream_t s) {
   SpmvArgs<T> c = a;
-  c.sval = nullptr;  // the CSR kernels carry the maximum
-  launch_spmv(c, EpScaleMax<T>{d, y, part}, s);
+  c.sval = nullptr;  // the row-block kernel carries the maximum and the scale
+  c.plain = true;
+  launch_spmv(c, EpScaleMax<T>{d, y, m.cur, m.prev, m.next, m.dead}, s);
 }
 template <class T>
 void spmv_resid(const SpmvArgs<T> &a, const T *f, T *r, hipStream_t s) {
@@ -320,7 +320,7 @@ void spmv_jacobi(const SpmvArgs<T> &a, const T *f, const T *invD, T w, T *u2, hi
 #define SA_INST_SPMV(T)                                                                     \
   template void spmv_store<T>(const SpmvArgs<T> &, T *, hipStream_t);                       \
   template void spmv_scale<T>(const SpmvArgs<T> &, const T *, T *, hipStream_t);            \
-  template void spmv_scale_max<T>(const SpmvArgs<T> &, const T *, T *, unsigned long long *, \
+  template void spmv_scale_max<T>(const SpmvArgs<T> &, const T *, T *, const MaxSlots &,      \
                                   hipStream_t);                                             \
   template void spmv_resid<T>(const SpmvArgs<T> &, const T *, T *, hipStream_t);            \
   template void spmv_add<T>(const SpmvArgs<T> &, T *, hipStream_t);                         \
@@ -435,6 +435,36 @@ void dot_f64(const double *x, const double *y, int64_t n, double *res, double *w
     if (nb == 1) break;
     in = out;
     iny = nullptr;
+    out += nb;
+    m = nb;
+  }
+}
+
+// <x, y> and <x, x> as two dot_f64, stage by stage in the same launches.
+__global__ __launch_bounds__(kDotBlock) void k_dot2_stage(const double *__restrict__ x,
+                                                       const double *__restrict__ y0,
+                                                       const double *__restrict__ y1, int64_t n,
+                                                       int64_t step, double *__restrict__ part,
+                                                       int64_t pstep) {
+  __shared__ DotShared sh;
+  const int64_t k = blockIdx.y;
+  dot_block(blockIdx.x, x + k * step, k == 0 ? y0 : y1, n, part + k * pstep + blockIdx.x, sh);
+}
+void dot_xy_xx(const double *x, const double *y, int64_t n, double *res, double *ws,
+               hipStream_t s) {
+  const int64_t half = dot_ws_size(n);
+  int64_t m = n, step = 0;
+  const double *in = x, *y0 = y, *y1 = x;
+  double *out = ws;
+  for (;;) {
+    const int64_t nb = std::max<int64_t>(ceil_div(m, 4096), 1);
+    k_dot2_stage<<<dim3((unsigned)nb, 2), kDotBlock, 0, s>>>(
+        in, y0, y1, m, step, nb == 1 ? res : out, nb == 1 ? 1 : half);
+    SA_LAUNCH_CHECK();
+    if (nb == 1) break;
+    in = out;
+    y0 = y1 = nullptr;
+    step = half;
     out += nb;
     m = nb;
   }
