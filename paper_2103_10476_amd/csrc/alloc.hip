@@ -297,6 +297,24 @@ void host_words_wait(const HostWords &w, void *host, size_t bytes, hipStream_t s
   std::memcpy(host, w.host, bytes);
 }
 
+__global__ void k_copy_runs(HostWords w, WordRuns r) {
+  int32_t at = 0;
+  for (int k = 0; k < r.count; ++k) {
+    const uint32_t *src = (const uint32_t *)r.p[k];
+    for (int32_t i = threadIdx.x; i < r.n[k]; i += blockDim.x) w.dev[at + i] = src[i];
+    at += r.n[k];
+  }
+  __threadfence_system();
+  __syncthreads();
+  if (threadIdx.x == 0) *(volatile uint32_t *)(w.dev + kWordsMax) = w.seq;
+}
+void readback_runs(void *host, const WordRuns &r, hipStream_t s) {
+  const HostWords w = host_words();
+  k_copy_runs<<<1, kBlock, 0, s>>>(w, r);
+  SA_LAUNCH_CHECK();
+  host_words_wait(w, host, 4 * (size_t)r.words, s);
+}
+
 void readback(void *host, const void *dev, size_t bytes, hipStream_t s) {
   if (bytes == 0) return;
   if (bytes > (size_t(1) << 20)) {  // bulk copies: straight into the caller's memory

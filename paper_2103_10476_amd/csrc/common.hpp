@@ -90,6 +90,25 @@ __device__ __forceinline__ void post_words(const HostWords &w, const uint32_t *s
   __syncthreads();
   if (threadIdx.x == 0) *(volatile uint32_t *)(w.dev + kWordsMax) = w.seq;
 }
+// Blocking readback of several short runs of words, one after the other into host (at most
+// kWordsMax in all).
+struct WordRuns {
+  const void *p[4] = {};
+  int32_t n[4] = {};
+  int32_t count = 0, words = 0;
+  void add(const void *dev, int32_t nw) {
+    p[count] = dev;
+    n[count++] = nw;
+    words += nw;
+  }
+};
+void readback_runs(void *host, const WordRuns &r, hipStream_t s);
+// Words that a function is to fetch with its own first readback.
+struct ReadAlong {
+  const void *dev = nullptr;
+  int32_t words = 0;
+  void *host = nullptr;
+};
 // Launches for a second stream, queued by the calling thread where it would wait for the first:
 // while it polls for a readback or a status word, beside_step() makes one call of the oldest
 // job pushed (a job returns false with its last launches queued; beside_step returns false with

@@ -160,7 +160,8 @@ static void take_values(const Csr &src, Csr &dst, hipStream_t s) {
 // Numeric part of level l, in three steps (the second can run on the side stream):
 // lumping into Abar and the smoothing diagonal; the damping factor from the power method on
 // D^-1 Abar; the prolongator.
-static void numeric_lump(sa_hierarchy *h, int l, bool fresh) {
+// counted: the filtered matrix with its row pointers and nnz known already.
+static void numeric_lump(sa_hierarchy *h, int l, bool fresh, const Csr *counted = nullptr) {
   const hipStream_t s = h->stream;
   const sa_options &o = h->opt;
   Level &L = h->lv[l];
@@ -175,6 +176,12 @@ static void numeric_lump(sa_hierarchy *h, int l, bool fresh) {
     L.omega_d = L.lam_d + 1;
   }
   Csr abar;
+  if (counted) {
+    abar = *counted;
+  } else {
+    lump_count(n, L.As.rp, L.As.col, L.mask, L.wave_rows, fresh ? ar : tmp, abar, s);
+    abar.nnz = read1(abar.rp + n, s);
+  }
   lump(n, L.As.nnz, L.As.rp, L.As.col, L.As.val, L.mask, (o.variants & SA_OFFLMP) != 0, o.tau,
        one_norm, safeguard_mult(o.sigma), L.wave_rows, fresh ? ar : tmp, abar, L.invD, h->err,
        s);
@@ -203,7 +210,7 @@ static void run_steps(const std::function<bool()> &steps) {
   while (steps()) {
   }
 }
-static void numeric_prolong(sa_hierarchy *h, int l, bool fresh) {
+static void numeric_prolong(sa_hierarchy *h, int l, bool fresh, const ReadAlong &along = {}) {
   const hipStream_t s = h->stream;
   const sa_options &o = h->opt;
   Level &L = h->lv[l];
@@ -222,10 +229,10 @@ static void numeric_prolong(sa_hierarchy *h, int l, bool fresh) {
     return;
   }
   if (fresh) {
-    prolongator(L.Abar, L.invD, L.agg, L.nc, L.omega_d, ar, L.P, s, L.wave_rows);
+    prolongator(L.Abar, L.invD, L.agg, L.nc, L.omega_d, ar, L.P, s, L.wave_rows, along);
   } else {
     Csr P;
-    prolongator(L.Abar, L.invD, L.agg, L.nc, L.omega_d, tmp, P, s, L.wave_rows);
+    prolongator(L.Abar, L.invD, L.agg, L.nc, L.omega_d, tmp, P, s, L.wave_rows, along);
     take_values(P, L.P, s);
   }
   if (o.variants & SA_CNSTRNT) cnstrnt(L.P, L.agg, s);
@@ -266,17 +273,19 @@ static bool build_level_system(sa_hierarchy *h, int l) {
   } else {
     block_strength(L.As, bs, L.Gn, o.theta, L.nmask, scount, s);
   }
-  L.As.maxrow = L.A.maxrow = max_row_length(n, L.As.rp, s);  // A and As share the pattern
+  if (L.A.maxrow < 0) L.A.maxrow = max_row_length(n, L.As.rp, s);
+  L.As.maxrow = L.A.maxrow;  // A and As share the pattern
   L.wave_rows = long_rows(L.As.maxrow, L.As.nnz, n);
   L.mask = ar.alloc<uint8_t>(L.As.nnz);
   dof_mask(L.As, bs, L.Gn, L.nmask, L.mask, s);
   int32_t *grp = nullptr, *gcol = nullptr;
-  const int64_t nnzG = strength_graph(m, L.Gn.rp, L.Gn.col, L.nmask, scount, gwave, tmp, &grp,
-                                      &gcol, s);
+  int32_t maxdeg = -1;
+  const int64_t nnzG = strength_graph(m, L.Gn.nnz, L.Gn.rp, L.Gn.col, L.nmask, scount, gwave,
+                                      tmp, &grp, &gcol, &maxdeg, {}, s);
   L.agg = ar.alloc<int32_t>(m);
   L.is_root = ar.alloc<uint8_t>(m);
   int32_t *root_vertex = nullptr;
-  L.nc = aggregate(m, nnzG, grp, gcol, o.agg_order, o.seed, l, false, L.agg, L.is_root, tmp,
+  L.nc = aggregate(m, nnzG, grp, gcol, maxdeg, o.agg_order, o.seed, l, false, L.agg, L.is_root, tmp,
                    &root_vertex, &L.mis_rounds, s);
   if (L.nc == 0) return false;
   if ((int64_t)L.nc * h->k >= n) throw Error(SA_ERR_COARSEN_STALLED, "coarsening stalled");
@@ -307,20 +316,29 @@ static bool build_level(sa_hierarchy *h, int l) {
   } else {
     find_diag(n, L.As.rp, L.As.col, L.As.val, dval, s);
   }
-  L.As.maxrow = L.A.maxrow = max_row_length(n, L.As.rp, s);  // A and As share the pattern
+  if (L.A.maxrow < 0) L.A.maxrow = max_row_length(n, L.As.rp, s);
+  L.As.maxrow = L.A.maxrow;  // A and As share the pattern
   L.wave_rows = long_rows(L.As.maxrow, L.As.nnz, n);
   L.mask = ar.alloc<uint8_t>(L.As.nnz);
   int32_t *scount = tmp.alloc<int32_t>(n + 1);
   strength(n, L.As.rp, L.As.col, sval, dval, o.theta * o.theta, L.mask, scount, L.wave_rows,
            s);
   int32_t *grp = nullptr, *gcol = nullptr;
-  const int64_t nnzG = strength_graph(n, L.As.rp, L.As.col, L.mask, scount, L.wave_rows, tmp,
-                                      &grp, &gcol, s);
+  // the filtered matrix' row pointers need the labels only: counted first, so that their total
+  // comes with the graph's readback (each costs the stream some 20 us)
+  const bool lump_now = (o.variants & SA_SPRSFY) == 0;
+  Csr abar;
+  int32_t nnz_abar = 0, maxdeg = -1;
+  if (lump_now) lump_count(n, L.As.rp, L.As.col, L.mask, L.wave_rows, ar, abar, s);
+  const int64_t nnzG = strength_graph(
+      n, L.As.nnz, L.As.rp, L.As.col, L.mask, scount, L.wave_rows, tmp, &grp, &gcol, &maxdeg,
+      lump_now ? ReadAlong{abar.rp + n, 1, &nnz_abar} : ReadAlong{}, s);
+  abar.nnz = nnz_abar;
   L.agg = ar.alloc<int32_t>(n);
   L.is_root = ar.alloc<uint8_t>(n);
   int32_t *root_vertex = nullptr;
-  if (o.variants & SA_SPRSFY) {  // the drops change the labels lumping reads: in sequence
-    L.nc = aggregate(n, nnzG, grp, gcol, o.agg_order, o.seed, l,
+  if (!lump_now) {  // the drops change the labels lumping reads: in sequence
+    L.nc = aggregate(n, nnzG, grp, gcol, maxdeg, o.agg_order, o.seed, l,
                      o.isolated == SA_ISOLATED_SINGLETON, L.agg, L.is_root, tmp, &root_vertex,
                      &L.mis_rounds, s);
     if (nnzG == 0) return false;  // no strong connection: the coarsest level
@@ -335,11 +353,11 @@ static bool build_level(sa_hierarchy *h, int l) {
   // stream stood still for them (some 30, 0.1 ms) otherwise.  Errors are checked in the
   // sequential order afterwards; a level that turns out to be the coarsest ignores the
   // lumping.
-  numeric_lump(h, l, true);
+  numeric_lump(h, l, true, &abar);
   if (!h->side) h->side = side_stream(s);
   stream_after(h->side, s);
   beside_push(damping_steps(h, l, h->side, h->err + 2));
-  L.nc = aggregate(n, nnzG, grp, gcol, o.agg_order, o.seed, l,
+  L.nc = aggregate(n, nnzG, grp, gcol, maxdeg, o.agg_order, o.seed, l,
                    o.isolated == SA_ISOLATED_SINGLETON, L.agg, L.is_root, tmp, &root_vertex,
                    &L.mis_rounds, s);
   beside_drain();
@@ -350,12 +368,12 @@ static bool build_level(sa_hierarchy *h, int l) {
     return false;
   }
   if (L.nc >= n) throw Error(SA_ERR_COARSEN_STALLED, "coarsening stalled");
-  int32_t ew[4];  // main word (lumping) and the damping word, in one readback
-  readback(ew, h->err, sizeof(ew), s);
+  // main word (lumping) and the damping word, with the prolongator's readback
+  int32_t ew[3] = {0, 0, 0};
+  numeric_prolong(h, l, true, ReadAlong{h->err, 3, ew});
   if (ew[0] & E_ZERO_FDIAG)
     throw Error(SA_ERR_NONPOSITIVE_DIAG, "zero diagonal in the filtered matrix");
   if (ew[2] & E_LAMBDA) throw Error(SA_ERR_NEGATIVE_EIGENVALUE, "eigenvalue estimate not positive");
-  numeric_prolong(h, l, true);
   return true;
 }
 
@@ -397,18 +415,23 @@ static void galerkin(sa_hierarchy *h, int l, bool fresh, const double *dB) {
   }
   Arena tmp;
   tmp.stream = s;
+  // the transpose's longer rows are sorted after A P: their count comes with its readback
+  Csr R;
+  RowSort sort;
+  int32_t words[kRowSortWords];
+  transpose(L.P, fresh ? h->ar : tmp, R, sort, s);
+  Csr AP, Ac;
+  spgemm(L.A, L.P, tmp, AP, s, -1, false, ReadAlong{sort.words, kRowSortWords, words});
+  sort_rows_end(sort, words, s);
   if (fresh) {
-    transpose(L.P, h->ar, L.R, s);
+    L.R = R;
     spmv_plan(L.R, h->ar, s);
   } else {
-    Csr R;
-    transpose(L.P, tmp, R, s);
     take_values(R, L.R, s);
   }
-  Csr AP, Ac;
-  spgemm(L.A, L.P, tmp, AP, s);
+  const int32_t rmax = words[2] ? 65 : 64;
   if (fresh) {
-    spgemm(L.R, AP, h->ar, Ac, s);
+    spgemm(L.R, AP, h->ar, Ac, s, rmax, true);
     spmv_plan(Ac, h->ar, s);
     double *cxyz = nullptr;  // coarse coordinates: the aggregates' centroids
     if (h->dim > 0) {
@@ -425,7 +448,7 @@ static void galerkin(sa_hierarchy *h, int l, bool fresh, const double *dB) {
       h->lv[l + 1].B = Bnext;
     }
   } else {
-    spgemm(L.R, AP, tmp, Ac, s);
+    spgemm(L.R, AP, tmp, Ac, s, rmax);
     take_values(Ac, h->lv[l + 1].A, s);  // As shares A's arrays on coarse levels
     if (plans) {  // the first re-setup: keep A P and build the plans for the next ones
       L.APk = keep_copy(AP, h->ar, s);

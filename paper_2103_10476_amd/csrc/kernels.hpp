@@ -77,6 +77,21 @@ void sell_values(const Csr &A, const Sell &S, hipStream_t s);
 // Sorts the entries of every row by column (values follow when val != nullptr); keys within a
 // row must be distinct.  Short rows per thread, long rows per block (bitonic in LDS).
 void sort_rows(int32_t n, const int32_t *rp, int32_t *col, double *val, hipStream_t s);
+// The same in two parts, for a caller that has a readback of its own to make in between: begin
+// sorts the rows of up to 32 entries and leaves three words on the device (rows of up to 256
+// entries, longer rows, whether any row has more than 64), end takes them and sorts the rest.
+struct RowSort {
+  int32_t n = 0;
+  const int32_t *rp = nullptr;
+  int32_t *col = nullptr;
+  double *val = nullptr;
+  int32_t *words = nullptr, *mid = nullptr, *rows = nullptr;
+  Arena tmp;
+};
+constexpr int32_t kRowSortWords = 3;
+void sort_rows_begin(int32_t n, const int32_t *rp, int32_t *col, double *val, RowSort &job,
+                     hipStream_t s);
+void sort_rows_end(RowSort &job, const int32_t *words, hipStream_t s);
 
 template <class T> void spmv_store(const SpmvArgs<T> &a, T *y, hipStream_t s);
 template <class T> void spmv_scale(const SpmvArgs<T> &a, const T *d, T *y, hipStream_t s);
@@ -251,41 +266,48 @@ void check_finite(const double *x, int64_t m, int32_t *err, int32_t ebit, hipStr
 // cxyz[J] = centroid of aggregate J's members (nc x dim), summed in ascending vertex order.
 void aggregate_centroids(int32_t n, const int32_t *agg, int32_t nc, const double *xyz,
                          int32_t dim, double *cxyz, hipStream_t s);
-// Symmetrised strength graph G = S u S^T as CSR (grp[n+1], gcol[nnzG]); returns nnzG.
-int64_t strength_graph(int32_t n, const int32_t *rp, const int32_t *col, const uint8_t *mask,
-                       const int32_t *scount, bool wave, Arena &ar, int32_t **grp,
-                       int32_t **gcol, hipStream_t s);
+// Symmetrised strength graph G = S u S^T as CSR (grp[n+1], gcol[nnzG]) of the n-row CSR with
+// nnz_a entries; returns nnzG, and G's longest row in *maxdeg (-1: not computed, for levels that
+// one workgroup takes).
+int64_t strength_graph(int32_t n, int64_t nnz_a, const int32_t *rp, const int32_t *col,
+                       const uint8_t *mask, const int32_t *scount, bool wave, Arena &ar,
+                       int32_t **grp, int32_t **gcol, int32_t *maxdeg, const ReadAlong &along,
+                       hipStream_t s);
 // Aggregation (roots = lexicographically-first distance-2 MIS in priority order; phase-2
 // join).  A vertex without strong connections joins no aggregate (agg -1), or is the root of
 // a singleton aggregate when `singletons` is set (the covering reading).  Returns nc;
-// agg[n], is_root[n], root_vertex[nc].
-int32_t aggregate(int32_t n, int64_t nnzG, const int32_t *grp, const int32_t *gcol, int32_t order,
-                  uint64_t seed, int32_t level, bool singletons, int32_t *agg,
+// agg[n], is_root[n], root_vertex[nc].  maxdeg: the graph's longest row, or -1.
+int32_t aggregate(int32_t n, int64_t nnzG, const int32_t *grp, const int32_t *gcol,
+                  int32_t maxdeg, int32_t order, uint64_t seed, int32_t level, bool singletons, int32_t *agg,
                   uint8_t *is_root, Arena &ar, int32_t **root_vertex, int32_t *rounds,
                   hipStream_t s);
 // Sprsfy: marks dropped strong entries (mask 1 -> 2).
 void sprsfy(int32_t n, const int32_t *rp, const int32_t *col, uint8_t *mask,
             const int32_t *agg, const int32_t *root_vertex, int32_t nc, hipStream_t s);
+// The filtered matrix' row pointers (abar.nnz is still to be read back: abar.rp[n]).
+void lump_count(int32_t n, const int32_t *rp, const int32_t *col, const uint8_t *mask, bool wave,
+                Arena &ar, Csr &abar, hipStream_t s);
 // Filtered matrix (plain or OffLmp) and the smoothing diagonal inverse of the n-row CSR with
-// nnz_a entries; returns nnz(Abar).  err bit 8: zero filtered diagonal with the plain diagonal.
+// nnz_a entries, from abar's row pointers and nnz; returns nnz(Abar).  err bit 8: zero filtered diagonal with the plain diagonal.
 int64_t lump(int32_t n, int64_t nnz_a, const int32_t *rp, const int32_t *col, const double *val,
              const uint8_t *mask, bool offlmp, double tau, bool one_norm, double mult,
              bool wave, Arena &ar, Csr &abar, double *invD, int32_t *err, hipStream_t s);
 // Power method; writes the estimate to *lam (device).  The launches of one iteration per call,
 // until it returns false (see BesideScope).
-std::function<bool()> power_steps(const Csr &M, const double *invD, int32_t iters, uint64_t seed,
-                  int32_t level, int32_t stream_id, double *lam, hipStream_t s);
+std::function<bool()> power_steps(const Csr &M, const double *invD, int32_t iters,
+                                  uint64_t seed, int32_t level, int32_t stream_id, double *lam,
+                                  hipStream_t s);
 // omega = 4/(3 lambda) (or lambda = 1 first when `unit`), err bit 16 if lambda <= 0.
 void damping(double *lam, double *omega, bool unit, int32_t *err, hipStream_t s);
 // P = (I - omega invD Abar) Ptent; returns nnz(P).  long_rows: the per-aggregate sums come
 // from a SpGEMM with the 0/1 aggregate matrix (the same sums in the same order).
 int64_t prolongator(const Csr &abar, const double *invD, const int32_t *agg, int32_t nc,
-                    const double *omega, Arena &ar, Csr &P, hipStream_t s,
-                    bool long_rows = false);
+                    const double *omega, Arena &ar, Csr &P, hipStream_t s, bool long_rows,
+                    const ReadAlong &along);
 void cnstrnt(const Csr &P, const int32_t *agg, hipStream_t s);
 void scale_rows(const Csr &P, const double *B, hipStream_t s);
-// R = P^T with ascending columns per row.
-void transpose(const Csr &P, Arena &ar, Csr &R, hipStream_t s);
+// R = P^T with ascending columns per row, once sort_rows_end has finished sort.
+void transpose(const Csr &P, Arena &ar, Csr &R, RowSort &sort, hipStream_t s);
 // 1/A_ii with err bit 32 when A_ii <= 0.
 void inv_diag(int32_t n, const double *dval, double *invD, int32_t *err, hipStream_t s);
 // Ahat = D_B A D_B
@@ -294,8 +316,13 @@ void scale_sym(int32_t n, const int32_t *rp, const int32_t *col, const double *v
 
 // ---------------- SpGEMM (spgemm.hip) --------------------------------------------------
 // C = X * Y with Gustavson-order accumulation per output entry (ascending inner index);
-// output rows sorted; cancellations stored.  C's arrays are allocated from `ar`.
-void spgemm(const Csr &X, const Csr &Y, Arena &ar, Csr &C, hipStream_t s);
+// output rows sorted; cancellations stored.  C's arrays are allocated from `ar`.  xmax: X's
+// longest row, or 65 for any above 64 (-1: X.maxrow, or found here); max_row: C.maxrow too.
+void spgemm(const Csr &X, const Csr &Y, Arena &ar, Csr &C, hipStream_t s, int32_t xmax = -1,
+            bool max_row = false, const ReadAlong &along = {});
+// Longest row to out[0] (device), by two launches; part: row_max_words(n) words.
+int32_t row_max_words(int32_t n);
+void row_max(int32_t n, const int32_t *rp, int32_t *part, int32_t *out, hipStream_t s);
 // Numeric plan of C = X Y on a fixed pattern (re-setup): for each entry p of C, the products
 // that form it in ascending position of X's row (ascending inner index), as pairs of an X
 // entry le[t] and a Y entry lq[t] for t in [lrp[p], lrp[p+1]).

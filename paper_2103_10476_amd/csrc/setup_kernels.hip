@@ -10,6 +10,7 @@
 #include <chrono>
 #include <climits>
 #include <cstdlib>
+#include <cstring>
 #include <memory>
 #include <type_traits>
 #include <utility>
@@ -457,34 +458,61 @@ __global__ void k_union(int32_t n, const int32_t *arp, const int32_t *acol, cons
   if (ocnt) ocnt[i] = cnt;
 }
 
-int64_t strength_graph(int32_t n, const int32_t *rp, const int32_t *col, const uint8_t *mask,
-                       const int32_t *scount, bool wave, Arena &ar, int32_t **grp_out,
-                       int32_t **gcol_out, hipStream_t s) {
+// Levels of at most this many vertices have their roots selected in one workgroup (default of
+// SAAMG_MIS_WG_MAX_N).
+constexpr int64_t kMisWgMaxN = 4096;
+
+int64_t strength_graph(int32_t n, int64_t nnz_a, const int32_t *rp, const int32_t *col,
+                       const uint8_t *mask, const int32_t *scount, bool wave, Arena &ar,
+                       int32_t **grp_out, int32_t **gcol_out, int32_t *maxdeg,
+                       const ReadAlong &along, hipStream_t s) {
   Arena tmp;
   tmp.stream = s;
   int32_t *srp = tmp.alloc<int32_t>(n + 1);
   exclusive_scan_i32(scount, srp, n, s);
-  const int32_t nnzS = read1(srp + n, s);
-  int32_t *scol = tmp.alloc<int32_t>(nnzS);
+  // S has at most A's entries: no readback of its count
+  int32_t *scol = tmp.alloc<int32_t>(nnz_a);
   int32_t *tcnt = tmp.alloc<int32_t>(n + 1);
   fill_i32(tcnt, 0, n + 1, s);
-  int32_t *trank = tmp.alloc<int32_t>(nnzS);
+  int32_t *trank = tmp.alloc<int32_t>(nnz_a);
   if (wave) k_fill_strong_w<<<(unsigned)n, kW, 0, s>>>(n, rp, col, mask, srp, scol, tcnt, trank);
   else k_fill_strong<<<grid_for(n), kBlock, 0, s>>>(n, rp, col, mask, srp, scol, tcnt, trank);
   SA_LAUNCH_CHECK();
   int32_t *trp = tmp.alloc<int32_t>(n + 1);
   exclusive_scan_i32(tcnt, trp, n, s);
-  int32_t *tcol = tmp.alloc<int32_t>(nnzS);
+  int32_t *tcol = tmp.alloc<int32_t>(nnz_a);
   k_scatter_ranked<false><<<grid_for(n), kBlock, 0, s>>>(n, srp, scol, nullptr, trank, trp, tcol,
                                                          nullptr);
   SA_LAUNCH_CHECK();
-  sort_rows(n, trp, tcol, nullptr, s);
+  RowSort sort;
+  sort_rows_begin(n, trp, tcol, nullptr, sort, s);
+  constexpr int kAlong = 8;
+  int32_t hw[kRowSortWords + kAlong];
+  WordRuns runs;
+  runs.add(sort.words, kRowSortWords);
+  if (along.words > 0) runs.add(along.dev, std::min(along.words, kAlong));
+  readback_runs(hw, runs, s);
+  if (along.words > 0)
+    std::memcpy(along.host, hw + kRowSortWords, 4 * std::min(along.words, kAlong));
+  sort_rows_end(sort, hw, s);
   int32_t *gcnt = tmp.alloc<int32_t>(n + 1);
   k_union<<<grid_for(n), kBlock, 0, s>>>(n, srp, scol, trp, tcol, nullptr, nullptr, gcnt);
   SA_LAUNCH_CHECK();
   int32_t *grp = ar.alloc<int32_t>(n + 1);
   exclusive_scan_i32(gcnt, grp, n, s);
-  const int32_t nnzG = read1(grp + n, s);
+  int32_t hg[2] = {0, -1};
+  if (n > kMisWgMaxN) {
+    int32_t *mx = tmp.alloc<int32_t>(row_max_words(n) + 1);
+    row_max(n, grp, mx + 1, mx, s);
+    WordRuns last;
+    last.add(grp + n, 1);
+    last.add(mx, 1);
+    readback_runs(hg, last, s);
+  } else {
+    hg[0] = read1(grp + n, s);
+  }
+  const int32_t nnzG = hg[0];
+  *maxdeg = hg[1];
   int32_t *gcol = ar.alloc<int32_t>(nnzG);
   k_union<<<grid_for(n), kBlock, 0, s>>>(n, srp, scol, trp, tcol, grp, gcol, nullptr);
   SA_LAUNCH_CHECK();
@@ -565,6 +593,23 @@ __device__ __forceinline__ uint64_t group_ballot(bool p) {
   return (m >> sh) & ((1ull << (G & 63)) - 1ull);
 }
 
+// Inclusive prefix sums over the G lanes of a group: row shifts within 16 lanes, then the last
+// lane of each row into the next rows (rounds of 32 or 64 lanes 5-10% shorter than with LDS
+// permutes: 128^3, 100 rounds of 8.8 us -> 8.2).
+template <int G>
+__device__ __forceinline__ int32_t group_prefix(int32_t x, int j) {
+  auto add = [&](int off, int32_t o) {
+    if (G >= 16 || j >= off) x += o;
+  };
+  add(1, __builtin_amdgcn_update_dpp(0, x, 0x111, 0xF, 0xF, false));
+  add(2, __builtin_amdgcn_update_dpp(0, x, 0x112, 0xF, 0xF, false));
+  add(4, __builtin_amdgcn_update_dpp(0, x, 0x114, 0xF, 0xF, false));
+  if constexpr (G >= 16) add(8, __builtin_amdgcn_update_dpp(0, x, 0x118, 0xF, 0xF, false));
+  if constexpr (G >= 32) add(16, __builtin_amdgcn_update_dpp(0, x, 0x142, 0xA, 0xF, false));
+  if constexpr (G >= 64) add(32, __builtin_amdgcn_update_dpp(0, x, 0x143, 0xC, 0xF, false));
+  return x;
+}
+
 // Row ranges of the strength graph as a look reads them.  On the grid the range of every
 // entry's own row is stored beside the entry (gext), which takes a dependent load out of the
 // chain; in one workgroup the row pointers are in LDS.
@@ -603,12 +648,7 @@ __device__ __forceinline__ void mis_ball(int32_t v, int32_t b, int32_t e, int j,
       rows.entry(k0 + j, u, ub, len);
       ++len;
     }
-    int32_t end = len;  // inclusive prefix sums of the lists' lengths
-#pragma unroll
-    for (int off = 1; off < G; off <<= 1) {
-      const int32_t o = __shfl_up(end, off, G);
-      if (j >= off) end += o;
-    }
+    const int32_t end = group_prefix<G>(len, j);  // of the lists' lengths
     const int32_t start = end - len;
     const int32_t total = __shfl(end, G - 1, G);
     for (int32_t p0 = 0; p0 < total; p0 += 8 * G) {  // group-uniform
@@ -841,7 +881,6 @@ __global__ void k_mis_age(int32_t nw, uint32_t *st) {
 // else 16 lanes.  result[0] = the reported round count (bit 31: max_rounds reached); the same
 // word goes to the host-mapped post.
 constexpr int kMisWg = 1024;
-constexpr int64_t kMisWgMaxN = 4096;  // default level size limit (SAAMG_MIS_WG_MAX_N)
 // (64^2 grid and 128^3 cube: within 1% of the grid's rounds at this size, with no launches)
 constexpr int kMisWgV = 5;            // vertices per thread: levels up to 5120 vertices fit LDS
 constexpr int64_t kMisWgLdsMaxN = kMisWgV * kMisWg;
@@ -969,13 +1008,18 @@ __global__ void k_max_i32(int32_t n, const int32_t *a, int32_t *out) {
   }
   if (threadIdx.x == 0) *out = sh[0];
 }
+int32_t row_max_words(int32_t n) { return n > 0 ? (int32_t)grid_for(n) : 0; }
+void row_max(int32_t n, const int32_t *rp, int32_t *part, int32_t *out, hipStream_t s) {
+  const unsigned nb = grid_for(n);
+  k_rowlen_max_stage<<<nb, kBlock, 0, s>>>(n, rp, part);
+  k_max_i32<<<1, kBlock, 0, s>>>((int32_t)nb, part, out);
+  SA_LAUNCH_CHECK();
+}
 int32_t max_row_length(int32_t n, const int32_t *rp, hipStream_t s) {
   if (n <= 0) return 0;
-  const unsigned nb = grid_for(n);
+  const int32_t nb = row_max_words(n);
   int32_t *part = (int32_t *)dev_alloc(sizeof(int32_t) * (nb + 1), s);
-  k_rowlen_max_stage<<<nb, kBlock, 0, s>>>(n, rp, part);
-  k_max_i32<<<1, kBlock, 0, s>>>((int32_t)nb, part, part + nb);
-  SA_LAUNCH_CHECK();
+  row_max(n, rp, part, part + nb, s);
   const int32_t m = read1(part + nb, s);
   dev_free(part, s);
   return m;
@@ -1069,7 +1113,7 @@ __global__ void k_agg_phase2(int32_t n, const int32_t *grp, const int32_t *gcol,
 
 template <class O>
 static int32_t aggregate_impl(int32_t n, int64_t nnzG, const int32_t *grp, const int32_t *gcol,
-                              O ord, bool singletons, int32_t *agg,
+                              int32_t maxdeg, O ord, bool singletons, int32_t *agg,
                               uint8_t *is_root, Arena &ar, int32_t **root_vertex,
                               int32_t *rounds_out, hipStream_t s) {
   Arena tmp;
@@ -1104,7 +1148,7 @@ static int32_t aggregate_impl(int32_t n, int64_t nnzG, const int32_t *grp, const
   // lanes per look: the longest row's neighbours in one step where 64 lanes hold them.  8 on
   // every level took the 128^3 setup from 20.7 to 25.3 ms; 64 on every level but those of
   // rows up to 8 took the 100^3 27-point cube's from 17.8 to 19.2 ms
-  const int32_t maxdeg = one_wg ? 0 : max_row_length(n, grp, s);
+  if (!one_wg && maxdeg < 0) maxdeg = max_row_length(n, grp, s);
   int2 *gext = nullptr;
   if (!one_wg && nnzG > 0) {
     gext = tmp.alloc<int2>(nnzG);
@@ -1228,13 +1272,13 @@ static int32_t aggregate_impl(int32_t n, int64_t nnzG, const int32_t *grp, const
 }
 
 int32_t aggregate(int32_t n, int64_t nnzG, const int32_t *grp, const int32_t *gcol,
-                  int32_t order, uint64_t seed, int32_t level, bool singletons, int32_t *agg,
+                  int32_t maxdeg, int32_t order, uint64_t seed, int32_t level, bool singletons, int32_t *agg,
                   uint8_t *is_root, Arena &ar, int32_t **root_vertex, int32_t *rounds,
                   hipStream_t s) {
   if (order == 0)
-    return aggregate_impl(n, nnzG, grp, gcol, NaturalOrder{}, singletons, agg, is_root, ar,
+    return aggregate_impl(n, nnzG, grp, gcol, maxdeg, NaturalOrder{}, singletons, agg, is_root, ar,
                           root_vertex, rounds, s);
-  return aggregate_impl(n, nnzG, grp, gcol, HashedOrder{seed, level}, singletons, agg, is_root,
+  return aggregate_impl(n, nnzG, grp, gcol, maxdeg, HashedOrder{seed, level}, singletons, agg, is_root,
                         ar, root_vertex, rounds, s);
 }
 
@@ -1873,9 +1917,8 @@ __global__ __launch_bounds__(kW) void k_lump_fill_w(int32_t n, const int32_t *rp
   if (lane == 0) invD[i] = 1.0 / D;
 }
 
-int64_t lump(int32_t n, int64_t nnz_a, const int32_t *rp, const int32_t *col, const double *val,
-             const uint8_t *mask, bool offlmp, double tau, bool one_norm, double mult,
-             bool wave, Arena &ar, Csr &abar, double *invD, int32_t *err, hipStream_t s) {
+void lump_count(int32_t n, const int32_t *rp, const int32_t *col, const uint8_t *mask, bool wave,
+                Arena &ar, Csr &abar, hipStream_t s) {
   int32_t *cnt = (int32_t *)dev_alloc(sizeof(int32_t) * (n + 1), s);
   if (wave) k_lump_count_w<<<(unsigned)n, kW, 0, s>>>(n, rp, col, mask, cnt);
   else k_lump_count<<<grid_for(n), kBlock, 0, s>>>(n, rp, col, mask, cnt);
@@ -1884,7 +1927,10 @@ int64_t lump(int32_t n, int64_t nnz_a, const int32_t *rp, const int32_t *col, co
   abar.rp = ar.alloc<int32_t>(n + 1);
   exclusive_scan_i32(cnt, abar.rp, n, s);
   dev_free(cnt, s);
-  abar.nnz = read1(abar.rp + n, s);
+}
+int64_t lump(int32_t n, int64_t nnz_a, const int32_t *rp, const int32_t *col, const double *val,
+             const uint8_t *mask, bool offlmp, double tau, bool one_norm, double mult,
+             bool wave, Arena &ar, Csr &abar, double *invD, int32_t *err, hipStream_t s) {
   abar.col = ar.alloc<int32_t>(abar.nnz);
   abar.val = ar.alloc<double>(abar.nnz);
   if (wave)
@@ -2169,7 +2215,8 @@ __global__ void k_P_from_sums(int32_t n, const int32_t *prp, const int32_t *pcol
 }
 
 int64_t prolongator(const Csr &abar, const double *invD, const int32_t *agg, int32_t nc,
-                    const double *omega, Arena &ar, Csr &P, hipStream_t s, bool long_rows) {
+                    const double *omega, Arena &ar, Csr &P, hipStream_t s, bool long_rows,
+                    const ReadAlong &along) {
   const int32_t n = abar.n;
   if (long_rows && n > 0) {
     Arena tmp;
@@ -2182,12 +2229,12 @@ int64_t prolongator(const Csr &abar, const double *invD, const int32_t *agg, int
     T.ncols = nc;
     T.rp = tmp.alloc<int32_t>(n + 1);
     exclusive_scan_i32(f, T.rp, n, s);
-    T.nnz = read1(T.rp + n, s);
-    T.col = tmp.alloc<int32_t>(T.nnz > 0 ? T.nnz : 1);
-    T.val = tmp.alloc<double>(T.nnz > 0 ? T.nnz : 1);
+    T.nnz = n;  // at most
+    T.col = tmp.alloc<int32_t>(n);
+    T.val = tmp.alloc<double>(n);
     k_agg_matrix<<<grid_for(n), kBlock, 0, s>>>(n, agg, T.rp, T.col, T.val);
     SA_LAUNCH_CHECK();
-    spgemm(abar, T, ar, P, s);
+    spgemm(abar, T, ar, P, s, 65, false, along);
     k_P_from_sums<<<grid_for(n), kBlock, 0, s>>>(n, P.rp, P.col, P.val, invD, agg, omega);
     SA_LAUNCH_CHECK();
     return P.nnz;
@@ -2200,7 +2247,14 @@ int64_t prolongator(const Csr &abar, const double *invD, const int32_t *agg, int
   P.rp = ar.alloc<int32_t>(n + 1);
   exclusive_scan_i32(cnt, P.rp, n, s);
   dev_free(cnt, s);
-  P.nnz = read1(P.rp + n, s);
+  constexpr int kAlong = 8;
+  int32_t h[1 + kAlong];
+  WordRuns runs;
+  runs.add(P.rp + n, 1);
+  if (along.words > 0) runs.add(along.dev, std::min(along.words, kAlong));
+  readback_runs(h, runs, s);
+  if (along.words > 0) std::memcpy(along.host, h + 1, 4 * std::min(along.words, kAlong));
+  P.nnz = h[0];
   P.col = ar.alloc<int32_t>(P.nnz);
   P.val = ar.alloc<double>(P.nnz);
   k_P_fill<<<grid_for(n), kBlock, 0, s>>>(n, abar.rp, abar.col, abar.val, invD, agg, omega, P.rp,
@@ -2334,6 +2388,7 @@ __global__ __launch_bounds__(kBlock) void k_sort_short(int32_t n, const int32_t 
   const int32_t L = live ? rp[i + 1] - b : 0;
   wave_append(j == 0 && L > kSortShort && L <= kSortMid, nlist, mid, i);
   wave_append(j == 0 && L > kSortMid, nlist + 1, longrows, i);
+  if (L > 64) nlist[2] = 1;  // (every writer writes the same)
   if (L <= 1 || L > kSortShort) return;  // uniform over the row's lanes
   int32_t k[4], place[4] = {0, 0, 0, 0};
   double x[4];
@@ -2464,33 +2519,52 @@ __global__ void k_sort_caps(int32_t nrows, const int32_t *rows, const int32_t *r
   caps[t] = (L <= kSortLds) ? 0 : L;
 }
 
-void sort_rows(int32_t n, const int32_t *rp, int32_t *col, double *val, hipStream_t s) {
+void sort_rows_begin(int32_t n, const int32_t *rp, int32_t *col, double *val, RowSort &job,
+                     hipStream_t s) {
+  job.n = n;
+  job.rp = rp;
+  job.col = col;
+  job.val = val;
+  job.tmp.stream = s;
+  job.words = job.tmp.alloc<int32_t>(kRowSortWords);
+  fill_i32(job.words, 0, kRowSortWords, s);
   if (n <= 0) return;
-  Arena tmp;
-  tmp.stream = s;
-  int32_t *nlist = tmp.alloc<int32_t>(2);
-  int32_t *mid = tmp.alloc<int32_t>(n), *rows = tmp.alloc<int32_t>(n);
-  fill_i32(nlist, 0, 2, s);
-  k_sort_short<<<grid_for((int64_t)n * 8), kBlock, 0, s>>>(n, rp, col, val, nlist, mid, rows);
+  job.mid = job.tmp.alloc<int32_t>(n);
+  job.rows = job.tmp.alloc<int32_t>(n);
+  k_sort_short<<<grid_for((int64_t)n * 8), kBlock, 0, s>>>(n, rp, col, val, job.words, job.mid,
+                                                           job.rows);
   SA_LAUNCH_CHECK();
-  int32_t hn[2];
-  readback(hn, nlist, sizeof(hn), s);
-  if (hn[0] > 0) {
-    k_sort_mid<<<(unsigned)ceil_div(hn[0], kBlock / 64), kBlock, 0, s>>>(mid, hn[0], rp, col, val);
+}
+void sort_rows_end(RowSort &job, const int32_t *words, hipStream_t s) {
+  if (words[0] > 0) {
+    k_sort_mid<<<(unsigned)ceil_div(words[0], kBlock / 64), kBlock, 0, s>>>(
+        job.mid, words[0], job.rp, job.col, job.val);
     SA_LAUNCH_CHECK();
   }
-  const int32_t nl = hn[1];
-  if (nl == 0) return;
-  int64_t *caps = tmp.alloc<int64_t>(nl + 1);
-  int64_t *goff = tmp.alloc<int64_t>(nl + 1);
-  k_sort_caps<<<grid_for(nl), kBlock, 0, s>>>(nl, rows, rp, caps);
-  SA_LAUNCH_CHECK();
-  exclusive_scan_i64(caps, goff, nl, s);
-  const int64_t gtot = read1(goff + nl, s);
-  int32_t *gk = tmp.alloc<int32_t>(gtot > 0 ? gtot : 1);
-  double *gv = tmp.alloc<double>(gtot > 0 ? gtot : 1);
-  k_sort_long<<<(unsigned)nl, kBlock, 0, s>>>(rows, nl, rp, col, val, gk, gv, goff);
-  SA_LAUNCH_CHECK();
+  const int32_t nl = words[1];
+  if (nl > 0) {
+    Arena &tmp = job.tmp;
+    int64_t *caps = tmp.alloc<int64_t>(nl + 1);
+    int64_t *goff = tmp.alloc<int64_t>(nl + 1);
+    k_sort_caps<<<grid_for(nl), kBlock, 0, s>>>(nl, job.rows, job.rp, caps);
+    SA_LAUNCH_CHECK();
+    exclusive_scan_i64(caps, goff, nl, s);
+    const int64_t gtot = read1(goff + nl, s);
+    int32_t *gk = tmp.alloc<int32_t>(gtot > 0 ? gtot : 1);
+    double *gv = tmp.alloc<double>(gtot > 0 ? gtot : 1);
+    k_sort_long<<<(unsigned)nl, kBlock, 0, s>>>(job.rows, nl, job.rp, job.col, job.val, gk, gv,
+                                                goff);
+    SA_LAUNCH_CHECK();
+  }
+  job.tmp.release();
+}
+void sort_rows(int32_t n, const int32_t *rp, int32_t *col, double *val, hipStream_t s) {
+  if (n <= 0) return;
+  RowSort job;
+  sort_rows_begin(n, rp, col, val, job, s);
+  int32_t words[kRowSortWords];
+  readback(words, job.words, sizeof(words), s);
+  sort_rows_end(job, words, s);
 }
 
 // ---- transpose with values ---------------------------------------------------------------
@@ -2501,7 +2575,7 @@ __global__ void k_count_cols(int64_t nnz, const int32_t *col, int32_t *cnt, int3
   const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (e < nnz) rank[e] = atomicAdd(&cnt[col[e]], 1);
 }
-void transpose(const Csr &P, Arena &ar, Csr &R, hipStream_t s) {
+void transpose(const Csr &P, Arena &ar, Csr &R, RowSort &sort, hipStream_t s) {
   const int32_t m = P.ncols;
   Arena tmp;
   tmp.stream = s;
@@ -2524,7 +2598,7 @@ void transpose(const Csr &P, Arena &ar, Csr &R, hipStream_t s) {
                                                             R.col, R.val);
     SA_LAUNCH_CHECK();
   }
-  sort_rows(m, R.rp, R.col, R.val, s);
+  sort_rows_begin(m, R.rp, R.col, R.val, sort, s);
 }
 
 __global__ void k_inv_diag(int32_t n, const double *d, double *inv, int32_t *err) {

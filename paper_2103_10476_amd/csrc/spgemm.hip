@@ -1118,7 +1118,8 @@ static bool keys64() {
   return e && std::atoi(e) != 0;
 }
 
-void spgemm(const Csr &X, const Csr &Y, Arena &ar, Csr &C, hipStream_t s) {
+void spgemm(const Csr &X, const Csr &Y, Arena &ar, Csr &C, hipStream_t s, int32_t xmax,
+            bool max_row, const ReadAlong &along) {
   const int32_t m = X.n;
   C.n = m;
   C.ncols = Y.ncols;
@@ -1137,7 +1138,7 @@ void spgemm(const Csr &X, const Csr &Y, Arena &ar, Csr &C, hipStream_t s) {
   // short rows: a thread per row, which also bins the row; longer: 16, 32 or 64 lanes per
   // row, binned after the scan (970K rows of 26 entries: 261 us and 48 for the binning,
   // against 640 with a thread per row, whose Y row lengths are a chain of gathers)
-  const int32_t xmax = m > 0 ? (X.maxrow >= 0 ? X.maxrow : max_row_length(m, X.rp, s)) : 0;
+  if (xmax < 0) xmax = m > 0 ? (X.maxrow >= 0 ? X.maxrow : max_row_length(m, X.rp, s)) : 0;
   const bool wave_count = m > 0 && (xmax > 64 || X.nnz > 8 * (int64_t)m);
   auto count_rows = [&](auto gc) {
     constexpr int G = decltype(gc)::value;
@@ -1162,8 +1163,14 @@ void spgemm(const Csr &X, const Csr &Y, Arena &ar, Csr &C, hipStream_t s) {
   // the bin sizes and the product total in one readback
   k_put_total<<<1, 1, 0, s>>>(poff + m, (int64_t *)(counters + kTotalAt));
   SA_LAUNCH_CHECK();
-  int32_t hc[kTotalAt + 2];
-  readback(hc, counters, sizeof(hc), s);
+  constexpr int kAlong = 8;
+  int32_t hc[kTotalAt + 2 + kAlong];
+  WordRuns runs;
+  runs.add(counters, kTotalAt + 2);
+  if (along.words > 0) runs.add(along.dev, std::min(along.words, kAlong));
+  readback_runs(hc, runs, s);
+  if (along.words > 0)
+    std::memcpy(along.host, hc + kTotalAt + 2, 4 * std::min(along.words, kAlong));
   int64_t total = 0;
   std::memcpy(&total, hc + kTotalAt, sizeof(total));
   int32_t *ocol = tmp.alloc<int32_t>(total > 0 ? total : 1);
@@ -1263,7 +1270,19 @@ void spgemm(const Csr &X, const Csr &Y, Arena &ar, Csr &C, hipStream_t s) {
   }
   C.rp = ar.alloc<int32_t>(m + 1);
   exclusive_scan_i32(ucnt, C.rp, m, s);
-  C.nnz = read1(C.rp + m, s);
+  if (max_row && m > 0) {
+    int32_t *mx = tmp.alloc<int32_t>(row_max_words(m) + 1);
+    row_max(m, C.rp, mx + 1, mx, s);
+    WordRuns last;
+    last.add(C.rp + m, 1);
+    last.add(mx, 1);
+    int32_t h[2];
+    readback_runs(h, last, s);
+    C.nnz = h[0];
+    C.maxrow = h[1];
+  } else {
+    C.nnz = read1(C.rp + m, s);
+  }
   C.col = ar.alloc<int32_t>(C.nnz);
   C.val = ar.alloc<double>(C.nnz);
   if (C.nnz > 0) {
