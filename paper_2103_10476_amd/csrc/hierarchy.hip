@@ -38,7 +38,6 @@ enum ErrBits {
   E_SPAN = 2048
 };
 
-constexpr int32_t kMaxRestart = 1024;  // GMRES restart length limit
 
 static double now_s() {
   return std::chrono::duration<double>(std::chrono::steady_clock::now().time_since_epoch())
@@ -1070,7 +1069,8 @@ static sa_status solve_impl(sa_hierarchy *h, const double *b, double *x, sa_loca
 
 // GMRES workspace for n unknowns and restart m, carved from one block in this order, each
 // part starting on a 256-byte boundary: V ((m+1) n), Z (m n), H ((m+1) m), cs, sn (m), g
-// (m+1), y (m), c (m+1), the inner-product partials ((m+1) dot_ws_size(n)), the scalars.
+// (m+1), y (m), m+1 spare words (kept: the size bounds what the scratch array takes), the
+// inner-product partials ((m+1) dot_ws_size(n)), the scalars.
 static size_t gmres_part(int64_t count, size_t elem) {
   return ((size_t)(count > 0 ? count : 1) * elem + 255) & ~(size_t)255;
 }
@@ -1097,7 +1097,7 @@ GmresWork gmres_work_carve(void *base, int32_t n, int32_t m) {
   w.sn = (double *)take(M, 8);
   w.g = (double *)take(M + 1, 8);
   w.y = (double *)take(M, 8);
-  w.c = (double *)take(M + 1, 8);
+  take(M + 1, 8);
   w.ws = (double *)take((M + 1) * dot_ws_size(N), 8);
   w.S = (GmresScalars *)take(1, sizeof(GmresScalars));
   return w;
@@ -1122,8 +1122,9 @@ sa_status gmres_run(sa_hierarchy *h, const double *b, double *x, sa_location loc
   const int32_t n = h->n;
   const int32_t m = restart;
   double *V = wk.V, *Z = wk.Z, *H = wk.H, *cs = wk.cs, *sn = wk.sn, *g = wk.g, *y = wk.y,
-         *c = wk.c, *ws = wk.ws;
+         *ws = wk.ws;
   GmresScalars *S = wk.S;
+  Level &L0 = h->lv[0];
   auto read_scalars = [&](GmresScalars *hs) {
     if (direct_reads) {
       SA_HIP(hipMemcpyAsync(hs, S, sizeof(GmresScalars), hipMemcpyDeviceToHost, s));
@@ -1164,22 +1165,30 @@ sa_status gmres_run(sa_hierarchy *h, const double *b, double *x, sa_location loc
   bool converged = false;
   for (;;) {
     int32_t kdim = 0;
+    bool first = false;
     for (int32_t j = 0; j < m && total < o.max_iter; ++j) {
       double *vj = V + (int64_t)j * n, *zj = Z + (int64_t)j * n, *w = V + (int64_t)(j + 1) * n;
-      precondition(h, vj, zj);
+      precondition(h, vj, zj, first);
       A.x = zj;
       prof_begin(h, 0);
       spmv_store<double>(A, w, s);
       prof_end(h, 0, 2, 8);
-      for (int32_t pass = 0; pass < 2; ++pass) {
-        multi_dot_f64(V, n, j + 1, w, n, c, ws, s);
-        multi_axpy_f64(V, n, j + 1, c, w, n, false, s);
-        gmres_accum(H, m, j, c, pass, s);
-      }
-      dot_f64(w, w, n, &S->hn2, h->dws, s);
-      gmres_normalize(S, H, m, j, w, w, n, s);
-      gmres_givens(H, m, j, cs, sn, g, S, s);
-      read_scalars(&hs);
+      gmres_project(V, n, j + 1, ws, H, m, 0, w, n, nullptr, s);
+      const DotParts ww = gmres_project(V, n, j + 1, ws, H, m, 1, w, n, h->dws, s);
+      // the next step's first Chebyshev step rides along (its vector is the next V and Z)
+      first = j + 1 < m && h->lv.size() > 1 && o.smoother == SA_CHEBYSHEV;
+      const HostWords hw = direct_reads ? HostWords{} : host_words();
+      if (first && o.precision == SA_FP32_VCYCLE)
+        gmres_next(ww, w, n, H, m, j, cs, sn, g, S,
+                   FirstCheb32{L0.ff, L0.sm_invDf, (float)L0.cheb_theta, L0.d1f, L0.uf,
+                               o.degree == 1}, hw, s);
+      else if (first)
+        gmres_next(ww, w, n, H, m, j, cs, sn, g, S,
+                   FirstCheb64{L0.sm_invD, L0.cheb_theta, L0.d1, zj + n, o.degree == 1}, hw, s);
+      else
+        gmres_next(ww, w, n, H, m, j, cs, sn, g, S, FirstNone{}, hw, s);
+      if (direct_reads) read_scalars(&hs);
+      else host_words_wait(hw, &hs, sizeof(hs), s);
       prof_collect(h);
       ++total;
       kdim = j + 1;

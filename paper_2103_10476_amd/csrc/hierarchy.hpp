@@ -89,7 +89,7 @@ void hierarchy_release_nosync(sa_hierarchy *h);
 
 // Restarted flexible GMRES on a set-up hierarchy with a caller-provided workspace.
 struct GmresWork {
-  double *V, *Z, *H, *cs, *sn, *g, *y, *c, *ws;
+  double *V, *Z, *H, *cs, *sn, *g, *y, *ws;
   GmresScalars *S;
 };
 // Bytes of the workspace for n unknowns and restart m (parts 256-byte aligned), and its

@@ -160,10 +160,6 @@ struct GmresScalars {
   double beta; // its norm
   int32_t err, pad;
 };
-// c[i] = dot(V_i, w) for i < nv, V_i = V + i * ldv (the canonical dot, each independently);
-// ws holds nv * dot_ws_size(n) doubles.
-void multi_dot_f64(const double *V, int64_t ldv, int32_t nv, const double *w, int64_t n,
-                   double *c, double *ws, hipStream_t s);
 // res[0] = <x, y>, res[1] = <x, x>, each bitwise dot_f64's; ws of 2 dot_ws_size(n).
 void dot_xy_xx(const double *x, const double *y, int64_t n, double *res, double *ws,
                hipStream_t s);
@@ -171,14 +167,6 @@ void dot_xy_xx(const double *x, const double *y, int64_t n, double *res, double 
 // w[k] = w[k] + c[0] V_0[k] + ... instead.
 void multi_axpy_f64(const double *V, int64_t ldv, int32_t nv, const double *c, double *w,
                     int64_t n, bool add, hipStream_t s);
-// H[i][j] = c[i] (pass 0) or H[i][j] + c[i] (pass 1), i <= j.
-void gmres_accum(double *H, int32_t m, int32_t j, const double *c, int32_t pass, hipStream_t s);
-// hn = sqrt(hn2), H[j+1][j] = hn; v = w / hn when hn > 0 (elementwise, in place allowed).
-void gmres_normalize(GmresScalars *S, double *H, int32_t m, int32_t j, const double *w,
-                     double *v, int64_t n, hipStream_t s);
-// Rotations of column j and the new one; g updated, S->res = |g[j+1]|.
-void gmres_givens(double *H, int32_t m, int32_t j, double *cs, double *sn, double *g,
-                  GmresScalars *S, hipStream_t s);
 // y = H[0:k,0:k]^{-1} g (back substitution); err 1 on a zero diagonal entry.
 void gmres_backsolve(const double *H, int32_t m, int32_t k, const double *g, double *y,
                      GmresScalars *S, hipStream_t s);
@@ -197,6 +185,8 @@ struct DotParts {
   const double *p = nullptr;
   int32_t m = 0;
 };
+// The partials part[0..nb) reduced to at most 4096, stage by stage in ws.
+DotParts reduce_parts(double *part, int64_t nb, double *ws, hipStream_t s);
 DotParts dot_parts(const double *x, const double *y, int64_t n, double *ws, hipStream_t s);
 // r.z, and r.(z - zold) unless zold is null; ws holds 2 dot_ws_size(n) doubles.
 void dot_rz_parts(const double *r, const double *z, const double *zold, int64_t n, double *ws,
@@ -212,6 +202,20 @@ DotParts pcg_update_xr(int64_t n, double *x, double *r, const double *p, const d
 // the scalars of cur carried on in next; init: p = z, rho = rho1 (cur may be next).
 void pcg_update_p(int64_t n, double *p, const double *z, const DotParts &rz, const DotParts &rw,
                   const PcgScalars *cur, PcgScalars *next, bool pr, bool init, hipStream_t s);
+// One Gram-Schmidt pass of GMRES: c_i = V_i . w (the canonical dot, each independently) for the
+// nv = j + 1 vectors V_i = V + i ldv, w -= c_0 V_0 + c_1 V_1 + ..., H[i][j] = c_i (pass 0) or
+// H[i][j] + c_i.  ws holds nv dot_ws_size(n) doubles.  With wpart (dot_ws_size(n) doubles): the
+// partials of the new w.w.
+DotParts gmres_project(const double *V, int64_t ldv, int32_t nv, double *ws, double *H, int32_t m,
+                       int32_t pass, double *w, int64_t n, double *wpart, hipStream_t s);
+// hn = sqrt(w.w), H[j+1][j] = hn; w = w / hn when hn > 0, and first (FirstNone, FirstCheb64 or
+// FirstCheb32) on it; the rotations of column j and the new one, g updated, S->res = |g[j+1]|;
+// S to the host words unless host.dev is null.
+template <class First>
+void gmres_next(const DotParts &ww, double *w, int64_t n, double *H, int32_t m, int32_t j,
+                double *cs, double *sn, double *g, GmresScalars *S, const First &first,
+                const HostWords &host, hipStream_t s);
+constexpr int32_t kMaxRestart = 1024;  // GMRES restart length limit
 // r.r from its partials into S, and S to the host.
 void pcg_read(PcgScalars *host, const DotParts &rr, PcgScalars *S, hipStream_t s);
 
