@@ -193,6 +193,23 @@ struct CsrF {  // float copy of the values for the FP32 V-cycle
   float *val = nullptr;
 };
 
+// Inclusive prefix sums over the G lanes of a group: row shifts within 16 lanes, then the last
+// lane of each row into the next rows (rounds of 32 or 64 lanes 5-10% shorter than with LDS
+// permutes: 128^3, 100 rounds of 8.8 us -> 8.2).
+template <int G>
+__device__ __forceinline__ int32_t group_prefix(int32_t x, int j) {
+  auto add = [&](int off, int32_t o) {
+    if (G >= 16 || j >= off) x += o;
+  };
+  add(1, __builtin_amdgcn_update_dpp(0, x, 0x111, 0xF, 0xF, false));
+  add(2, __builtin_amdgcn_update_dpp(0, x, 0x112, 0xF, 0xF, false));
+  add(4, __builtin_amdgcn_update_dpp(0, x, 0x114, 0xF, 0xF, false));
+  if constexpr (G >= 16) add(8, __builtin_amdgcn_update_dpp(0, x, 0x118, 0xF, 0xF, false));
+  if constexpr (G >= 32) add(16, __builtin_amdgcn_update_dpp(0, x, 0x142, 0xA, 0xF, false));
+  if constexpr (G >= 64) add(32, __builtin_amdgcn_update_dpp(0, x, 0x143, 0xC, 0xF, false));
+  return x;
+}
+
 // Blocking readback of one value.
 template <class T>
 T read1(const T *dptr, hipStream_t s) {

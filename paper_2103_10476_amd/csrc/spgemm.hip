@@ -6,8 +6,8 @@
 // cancellations stay stored.
 //
 // Rows are binned by their product count T:
-//   T <= 64      8, 16 or 32 lanes per row (8, 4 or 2 rows per wavefront): two products per
-//                lane, rank sort in LDS;
+//   T <= 64      8, 16 or 32 lanes per row (8, 4 or 2 rows per wavefront), two products per
+//                lane, sorted as below (k_esc_group);
 //   T <= 1024    one wavefront per row, all products (2, 4, 8 or 16 per lane) sorted by
 //                (column, position) in registers, each run added in order and written at its
 //                rank (k_esc_sort), while 32 bits hold column and position;
@@ -134,146 +134,6 @@ __global__ __launch_bounds__(kBlock) void k_count_products_w(int32_t m,
     base += __shfl(incl, G - 1, G);
   }
   if (lane == 0) cnt[i] = base;
-}
-
-// ---- G lanes per row (T <= G P), 64/G rows per wavefront -----------------------------------
-// A wavefront takes 64/G rows, G lanes each, P products per lane: short rows share a
-// wavefront instead of leaving most of its lanes idle, and the more rows a wavefront holds,
-// the more of their (dependent) loads are in flight together.  Per row: the X entries G at a
-// time (a segmented scan of their Y-row lengths), the products by binary search over the scan
-// (lane l takes products l, l+G, ...), a rank sort of the T <= G P products in LDS by
-// (column, position), and one lane per run of equal columns summing it in order.  The chunk
-// loop runs to the longest X row of the wavefront, so every lane passes every barrier.
-template <int G, int P>
-__global__ __launch_bounds__(kWave) void k_esc_group(
-    const int32_t *rows, int32_t nrows, const int32_t *xrp, const int32_t *xcol,
-    const double *xval, const int32_t *yrp, const int32_t *ycol, const double *yval,
-    const int64_t *poff, int32_t *ocol, double *oval, int32_t *ucnt) {
-  static_assert((G == 8 || G == 16 || G == 32 || G == 64) && (P == 1 || P == 2),
-                "group width, products per lane");
-  constexpr int CAP = G * P;  // products of one row at most
-  __shared__ int32_t keys[kWave * P];
-  __shared__ double vals[kWave * P];
-  __shared__ int32_t skeys[kWave * P];
-  __shared__ double svals[kWave * P];
-  __shared__ int32_t s_incl[kWave], s_ys[kWave];
-  __shared__ double s_a[kWave];
-  const int lane = threadIdx.x;
-  const int gl = lane % G, gb = lane - gl;  // lane in the group, the group's first lane
-  const int pb = (lane / G) * CAP;          // the row's product slots in keys/vals
-  // consecutive rows share the Y rows of their neighbours: each XCD takes a contiguous run of
-  // the bin's rows (bins list rows roughly in row order), so those reads hit its L2
-  const int64_t r64 = (int64_t)xcd_block(blockIdx.x, gridDim.x) * (kWave / G) + lane / G;
-  const bool live = r64 < nrows;
-  const int32_t i = live ? rows[r64] : 0;
-  const int64_t base = live ? poff[i] : 0;
-  const int32_t T = live ? (int32_t)(poff[i + 1] - base) : 0;
-  const int32_t xb = live ? xrp[i] : 0, xe = live ? xrp[i + 1] : 0;
-  int32_t nch = (xe - xb + G - 1) / G;  // chunks of this row; the wavefront runs the most
-  for (int off = 32; off >= 1; off >>= 1) nch = max(nch, __shfl_xor(nch, off, kWave));
-  // expansion in Gustavson order: position = products of earlier X entries + offset in Y row
-  int32_t filled = 0;
-  for (int32_t c = 0; c < nch; ++c) {
-    const int32_t e = xb + c * G + gl;
-    int32_t len = 0, ys = 0;
-    double a = 0.0;
-    if (e < xe) {
-      const int32_t k = xcol[e];
-      a = xval[e];
-      ys = yrp[k];
-      len = yrp[k + 1] - ys;
-    }
-    // inclusive scan of len within the group
-    int32_t incl = len;
-    for (int off = 1; off < G; off <<= 1) {
-      const int32_t v = __shfl_up(incl, off, G);
-      if (gl >= off) incl += v;
-    }
-    const int32_t tot = __shfl(incl, G - 1, G);
-    s_incl[lane] = incl;
-    s_ys[lane] = ys;
-    s_a[lane] = a;
-    __syncthreads();
-    // product p of this chunk comes from the first entry s with incl[s] > p, at offset
-    // p - incl[s-1] in its row of Y: loads independent across lanes.  A lane's products are
-    // gl, gl + G, ... (at most P, since tot <= T <= G P): all are located first, then their
-    // loads issued together
-    int32_t qu[P], su[P];
-#pragma unroll
-    for (int u = 0; u < P; ++u) {
-      const int32_t p = gl + u * G;
-      su[u] = -1;
-      if (p < tot) {
-        int32_t lo = 0, hi = G - 1;
-        while (lo < hi) {
-          const int32_t mid = (lo + hi) >> 1;
-          if (s_incl[gb + mid] > p) hi = mid;
-          else lo = mid + 1;
-        }
-        su[u] = lo;
-        qu[u] = s_ys[gb + lo] + p - (lo > 0 ? s_incl[gb + lo - 1] : 0);
-      }
-    }
-    int32_t cu[P];
-    double yu[P];
-#pragma unroll
-    for (int u = 0; u < P; ++u) {
-      if (su[u] >= 0) {
-        cu[u] = ycol[qu[u]];
-        yu[u] = yval[qu[u]];
-      }
-    }
-#pragma unroll
-    for (int u = 0; u < P; ++u) {
-      if (su[u] >= 0) {
-        const int32_t p = gl + u * G;
-        keys[pb + filled + p] = cu[u];
-        vals[pb + filled + p] = s_a[gb + su[u]] * yu[u];
-      }
-    }
-    __syncthreads();
-    filled += tot;
-  }
-  // rank sort: positions q G + gl of the row, ordered by (column, position)
-#pragma unroll
-  for (int q = 0; q < P; ++q) {
-    const int32_t pos = q * G + gl;
-    if (pos < T) {
-      const int32_t key = keys[pb + pos];
-      int32_t rank = 0;
-      for (int32_t r = 0; r < T; ++r) {
-        const int32_t kr = keys[pb + r];
-        rank += (kr < key) || (kr == key && r < pos);
-      }
-      skeys[pb + rank] = key;
-      svals[pb + rank] = vals[pb + pos];
-    }
-  }
-  __syncthreads();
-  // one lane per run of equal columns adds it in order from 0 and writes it at the run's rank
-  int32_t before = 0;  // runs in the earlier position slices of the row
-#pragma unroll
-  for (int q = 0; q < P; ++q) {
-    const int32_t pos = q * G + gl;
-    bool head = false;
-    int32_t key = 0;
-    double sum = 0.0;
-    if (pos < T) {
-      key = skeys[pb + pos];
-      head = (pos == 0) || (skeys[pb + pos - 1] != key);
-      if (head)
-        for (int32_t r = pos; r < T && skeys[pb + r] == key; ++r) sum += svals[pb + r];
-    }
-    const unsigned long long gm =
-        (__ballot(head) >> gb) & (~0ull >> (64 - G));  // this group's heads in slice q
-    const int32_t idx = before + __popcll(gm & ((1ull << gl) - 1ull));
-    if (head) {
-      ocol[base + idx] = key;
-      oval[base + idx] = sum;
-    }
-    before += __popcll(gm);
-  }
-  if (live && gl == 0) ucnt[i] = before;
 }
 
 // ---- block-level rows (T > 64) -------------------------------------------------------------
@@ -403,18 +263,6 @@ __global__ __launch_bounds__(kBlock) void k_esc_dense(
   }
 }
 
-// Inclusive prefix sum over the wavefront's lanes: row shifts by 1, 2, 4 and 8 within each
-// 16-lane row (lanes shifted in from outside the row read 0), then the last lane of row 0 (of
-// row 2) into row 1 (row 3), then the last lane of row 1 into rows 2 and 3.
-__device__ __forceinline__ int32_t wave_prefix_sum(int32_t x) {
-  x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xF, 0xF, false);  // row_shr:1
-  x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xF, 0xF, false);  // row_shr:2
-  x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xF, 0xF, false);  // row_shr:4
-  x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xF, 0xF, false);  // row_shr:8
-  x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xA, 0xF, false);  // row_bcast:15
-  x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xC, 0xF, false);  // row_bcast:31
-  return x;
-}
 // One wavefront's LDS operations complete in its program order: between its lanes only the
 // compiler has to keep that order.
 __device__ __forceinline__ void wave_sync() {
@@ -488,7 +336,7 @@ __device__ __forceinline__ void row_products(ProductStage &st, int lane, int32_t
     entry(e0 + 2 * hop + lane, k2, a2);
     if (clip) clip_cols(ycol, ys, ye, cA, cB);
     const int32_t len = ye - ys;
-    const int32_t incl = wave_prefix_sum(len);
+    const int32_t incl = group_prefix<64>(len, lane);
     const int32_t tot = __builtin_amdgcn_readlane(incl, 63);
     const int32_t ex = incl - len;  // this entry's first product within the chunk
     const unsigned long long some = __ballot(len > 0);
@@ -543,31 +391,38 @@ __device__ __forceinline__ void row_products(ProductStage &st, int lane, int32_t
   }
 }
 
-// Value of lane (lane ^ J) of the wavefront.  J = 1, 2: a quad permutation (DPP); J = 4, 8:
-// the row shifts by J toward the lower lanes (row_shl, lane i reads i + J) and the higher
-// lanes (row_shr, lane i reads i - J), of which each lane keeps the one inside its J-group
-// pair (both stay inside the 16-lane row); J = 16, 32: an LDS permute.
+// Both values of a pair of lanes (lane, lane ^ J), in either order.  J = 1, 2: a quad permutation
+// (DPP); J = 4, 8: the row shifts by J toward the lower lanes (row_shl, lane i reads i + J) and
+// the higher lanes (row_shr, lane i reads i - J), of which each lane keeps the one inside its
+// J-group pair (both stay inside the 16-lane row); J = 16, 32: a swap of rows of 16 or of 32.
+struct Pair {
+  uint32_t a, b;
+};
 template <int J>
-__device__ __forceinline__ uint32_t xor_lane(uint32_t v, int lane) {
+__device__ __forceinline__ Pair xor_pair(uint32_t v, int lane) {
   if constexpr (J == 1) {
-    return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0xB1, 0xF, 0xF, false);  // [1,0,3,2]
+    return {v, (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0xB1, 0xF, 0xF, false)};  // [1,0,3,2]
   } else if constexpr (J == 2) {
-    return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x4E, 0xF, 0xF, false);  // [2,3,0,1]
+    return {v, (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x4E, 0xF, 0xF, false)};  // [2,3,0,1]
   } else if constexpr (J == 4 || J == 8) {
     const uint32_t from_up =
         (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x100 + J, 0xF, 0xF, false);  // row_shl
     const uint32_t from_dn =
         (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x110 + J, 0xF, 0xF, false);  // row_shr
-    return (lane & J) ? from_dn : from_up;
+    return {v, (lane & J) ? from_dn : from_up};
+  } else if constexpr (J == 16) {
+    const auto r = __builtin_amdgcn_permlane16_swap(v, v, false, false);
+    return {r[0], r[1]};
   } else {
-    return (uint32_t)__shfl_xor((int)v, J, 64);
+    const auto r = __builtin_amdgcn_permlane32_swap(v, v, false, false);
+    return {r[0], r[1]};
   }
 }
 // ---- one wavefront per row, all products sorted at once (65..1024 products) -----------------
-// Lane partner exchange of the sort's first step of a merge: value of lane (lane ^ M), M = 2^m - 1
-// (1, 3: quad permutations; 7, 15: the mirrors within 8 and 16 lanes; 31, 63: LDS permutes).
+// Value of lane (lane ^ M), M = 2^m - 1, the partner in a merge's first step (1, 3: quad permutations; 7, 15: the mirrors within 8 and 16 lanes; 31, 63: the
+// mirror and row swaps).
 template <int M>
-__device__ __forceinline__ uint32_t flip_lane(uint32_t v) {
+__device__ __forceinline__ uint32_t flip_lane(uint32_t v, int lane) {
   if constexpr (M == 1)
     return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0xB1, 0xF, 0xF, false);  // [1,0,3,2]
   else if constexpr (M == 3)
@@ -576,12 +431,18 @@ __device__ __forceinline__ uint32_t flip_lane(uint32_t v) {
     return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x141, 0xF, 0xF, false);  // half mirror
   else if constexpr (M == 15)
     return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x140, 0xF, 0xF, false);  // row mirror
-  else
-    return (uint32_t)__shfl_xor((int)v, M, 64);
+  else if constexpr (M == 31) {
+    const Pair p = xor_pair<16>(flip_lane<15>(v, lane), lane);
+    return (lane & 16) ? p.a : p.b;
+  } else {
+    const Pair p = xor_pair<32>(flip_lane<31>(v, lane), lane);
+    return (lane & 32) ? p.a : p.b;
+  }
 }
-// Ascending bitonic sort of 64 P keys, element lane * P + q in k[q].  Merges start by comparing
-// mirrored elements, so every comparison puts the smaller key at the lower index: within a
-// lane a minimum and a maximum, across lanes a minimum or a maximum by a bit of the lane.
+// Ascending bitonic sort of N keys, element gl * P + q in k[q] of the gl-th of N / P lanes (a
+// power of two, aligned; other groups sort their own).  Merges start by comparing mirrored
+// elements, so every comparison puts the smaller key at the lower index: within a lane a
+// minimum and a maximum, across lanes a minimum or a maximum by a bit of the lane.
 template <int P, int J>
 __device__ __forceinline__ void sort_halves(uint32_t (&k)[P], int lane) {
   if constexpr (J >= P) {
@@ -589,8 +450,8 @@ __device__ __forceinline__ void sort_halves(uint32_t (&k)[P], int lane) {
     const bool lower = (lane & L) == 0;
 #pragma unroll
     for (int q = 0; q < P; ++q) {
-      const uint32_t o = xor_lane<L>(k[q], lane);
-      k[q] = lower ? min(k[q], o) : max(k[q], o);
+      const Pair p = xor_pair<L>(k[q], lane);
+      k[q] = lower ? min(p.a, p.b) : max(p.a, p.b);
     }
   } else {
 #pragma unroll
@@ -603,7 +464,7 @@ __device__ __forceinline__ void sort_halves(uint32_t (&k)[P], int lane) {
   }
   if constexpr (J > 1) sort_halves<P, J / 2>(k, lane);
 }
-template <int P, int K = 2>
+template <int P, int N = 64 * P, int K = 2>
 __device__ __forceinline__ void sort_keys(uint32_t (&k)[P], int lane) {
   if constexpr (K <= P) {
 #pragma unroll
@@ -620,12 +481,134 @@ __device__ __forceinline__ void sort_keys(uint32_t (&k)[P], int lane) {
     const bool lower = (lane & (L / 2)) == 0;
     uint32_t o[P];
 #pragma unroll
-    for (int q = 0; q < P; ++q) o[q] = flip_lane<L - 1>(k[P - 1 - q]);
+    for (int q = 0; q < P; ++q) o[q] = flip_lane<L - 1>(k[P - 1 - q], lane);
 #pragma unroll
     for (int q = 0; q < P; ++q) k[q] = lower ? min(k[q], o[q]) : max(k[q], o[q]);
   }
   if constexpr (K > 2) sort_halves<P, K / 4>(k, lane);
-  if constexpr (K < 64 * P) sort_keys<P, K * 2>(k, lane);
+  if constexpr (K < N) sort_keys<P, N, K * 2>(k, lane);
+}
+
+// ---- G lanes per row (T <= 2 G), 64/G rows per wavefront -------------------------------------
+// A wavefront takes 64/G rows, G lanes each, two products per lane: short rows share a
+// wavefront instead of leaving most of its lanes idle, and the more rows a wavefront holds,
+// the more of their (dependent) loads are in flight together.  Per row: the X entries G at a
+// time, each non-empty Y row's first product a bit of the chunk's word, a product's entry the
+// bits up to its own; the (column, position) keys sorted in registers (sort_keys); and each
+// run of equal columns added in position order by the lane that holds its first key.  The chunk
+// loop runs to the longest X row of the wavefront.  The ranks by comparing every pair of
+// products in LDS, before, made the instructions the bound: 524K rows of 33..64 products 372 us,
+// now 216, 477K of 17..32 150 -> 103; 1.6M of at most 16 210 -> 169, where the chain of loads is.
+template <int G>
+__global__ __launch_bounds__(kWave) void k_esc_group(
+    const int32_t *rows, int32_t nrows, const int32_t *xrp, const int32_t *xcol,
+    const double *xval, const int32_t *yrp, const int32_t *ycol, const double *yval,
+    const int64_t *poff, int32_t *ocol, double *oval, int32_t *ucnt) {
+  constexpr int N = 2 * G;  // products of one row at most
+  constexpr int B = G == 8 ? 4 : G == 16 ? 5 : 6;
+  constexpr uint32_t kNone = ~0u;
+  static_assert(N == 1 << B, "a position per key");
+  __shared__ uint32_t s_k[2 * kWave];
+  __shared__ double s_v[2 * kWave];
+  __shared__ unsigned long long s_start[kWave / G];
+  __shared__ int32_t s_off[kWave];
+  __shared__ double s_a[kWave];
+  const int lane = threadIdx.x;
+  const int gl = lane % G, gb = lane - gl;  // lane in the group, the group's first lane
+  const int pb = gb * 2;                    // the row's product slots
+  // consecutive rows share the Y rows of their neighbours: each XCD takes a contiguous run of
+  // the bin's rows (bins list rows roughly in row order), so those reads hit its L2
+  const int64_t r64 = (int64_t)xcd_block(blockIdx.x, gridDim.x) * (kWave / G) + lane / G;
+  const bool live = r64 < nrows;
+  const int32_t i = live ? rows[r64] : 0;
+  const int64_t base = live ? poff[i] : 0;
+  const int32_t xb = live ? xrp[i] : 0, xe = live ? xrp[i + 1] : 0;
+  int32_t nch = (xe - xb + G - 1) / G;  // chunks of this row; the wavefront runs the most
+  for (int off = 32; off >= G; off >>= 1) nch = max(nch, __shfl_xor(nch, off, kWave));
+  // expansion in Gustavson order: position = products of earlier X entries + offset in Y row
+  int32_t filled = 0;
+  for (int32_t c = 0; c < nch; ++c) {
+    const int32_t e = xb + c * G + gl;
+    int32_t len = 0, ys = 0;
+    double a = 0.0;
+    if (e < xe) {
+      const int32_t k = xcol[e];
+      a = xval[e];
+      ys = yrp[k];
+      len = yrp[k + 1] - ys;
+    }
+    const int32_t incl = group_prefix<G>(len, gl);
+    const int32_t tot = __shfl(incl, G - 1, G), ex = incl - len;
+    const unsigned long long some = __ballot(len > 0) >> gb & ((1ull << G) - 1ull);
+    if (gl == 0) s_start[lane / G] = 0;
+    wave_sync();  // (the previous chunk's reads come before, too)
+    if (len > 0) {
+      const int g = __popcll(some & ((1ull << gl) - 1ull));
+      s_off[gb + g] = ys - ex;
+      s_a[gb + g] = a;
+      atomicOr(&s_start[lane / G], 1ull << ex);
+    }
+    wave_sync();
+    const unsigned long long w = s_start[lane / G];
+    int32_t g[2], cu[2];
+    double yu[2];
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      const int32_t p = gl + u * G;
+      g[u] = gb + __popcll(w & ((2ull << p) - 1ull)) - 1;
+      const int32_t q = p < tot ? s_off[g[u]] + p : 0;  // lanes past the end load Y's first entry
+      cu[u] = ycol[q];
+      yu[u] = yval[q];
+    }
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      const int32_t p = gl + u * G;
+      if (p < tot) {
+        s_k[pb + filled + p] = (uint32_t)cu[u] << B | (uint32_t)(filled + p);
+        s_v[pb + filled + p] = s_a[g[u]] * yu[u];
+      }
+    }
+    filled += tot;
+  }
+  for (int32_t p = filled + gl; p < N; p += G) s_k[pb + p] = kNone;
+  wave_sync();
+  uint32_t k[2] = {s_k[pb + gl], s_k[pb + G + gl]};
+  sort_keys<2, N>(k, lane);
+  double v[2];
+#pragma unroll
+  for (int q = 0; q < 2; ++q) v[q] = k[q] == kNone ? 0.0 : s_v[pb + (k[q] & (N - 1))];
+  wave_sync();
+#pragma unroll
+  for (int q = 0; q < 2; ++q) {
+    s_k[pb + 2 * gl + q] = k[q];
+    s_v[pb + 2 * gl + q] = v[q];
+  }
+  const uint32_t below = (uint32_t)__shfl_up((int)k[1], 1, 64);
+  const bool h0 = k[0] != kNone && (gl == 0 || (below >> B) != (k[0] >> B));
+  const bool h1 = k[1] != kNone && (k[0] >> B) != (k[1] >> B);
+  const int32_t nh = (int)h0 + (int)h1;
+  const int32_t incl = group_prefix<G>(nh, gl);
+  wave_sync();
+  int32_t at = incl - nh;  // rank of the lane's next run
+  if (h0 && (h1 || k[1] == kNone)) {  // a run of one
+    ocol[base + at] = (int32_t)(k[0] >> B);
+    oval[base + at] = 0.0 + v[0];
+    ++at;
+  }
+  if (h1 || (h0 && k[1] != kNone)) {  // the lane's last run may go on in the next lanes' keys
+    const uint32_t col = k[1] >> B;
+    double sum = 0.0;
+    if (!h1) sum += v[0];
+    sum += v[1];
+    for (int32_t r = 2 * gl + 2; r < N; ++r) {
+      const uint32_t kr = s_k[pb + r];
+      if (kr == kNone || (kr >> B) != col) break;
+      sum += s_v[pb + r];
+    }
+    ocol[base + at] = (int32_t)col;
+    oval[base + at] = sum;
+  }
+  if (live && gl == G - 1) ucnt[i] = incl;
 }
 
 // Products at their Gustavson positions p go to LDS as keys (column << B | p) and values; the
@@ -870,7 +853,7 @@ __global__ __launch_bounds__(64 * NW) void k_esc_rows(
       int32_t before = 0;
       for (int32_t w0 = 0; w0 < nw; w0 += 64) {
         const int32_t n = w0 + lane < nw ? __popc(word[w0 + lane].x) : 0;
-        const int32_t incl = wave_prefix_sum(n);
+        const int32_t incl = group_prefix<64>(n, lane);
         if (w0 + lane < nw) word[w0 + lane].y = (uint32_t)(before + incl - n);
         before += __builtin_amdgcn_readlane(incl, 63);
       }
@@ -1176,42 +1159,38 @@ void spgemm(const Csr &X, const Csr &Y, Arena &ar, Csr &C, hipStream_t s, int32_
   int32_t *ocol = tmp.alloc<int32_t>(total > 0 ? total : 1);
   double *oval = tmp.alloc<double>(total > 0 ? total : 1);
   int32_t *ucnt = tmp.alloc<int32_t>(m + 1);
-  const int32_t *lg[3] = {lists, lists + m, lists + 2 * (int64_t)m};
-  // two products per lane: 8, 4 and 2 rows per wavefront for the <= 16, <= 32, <= 64 bins
-  if (hc[0] > 0)
-    k_esc_group<8, 2><<<(unsigned)ceil_div(hc[0], kWave / 8), kWave, 0, s>>>(
-        lg[0], hc[0], X.rp, X.col, X.val, Y.rp, Y.col, Y.val, poff, ocol, oval, ucnt);
-  if (hc[1] > 0)
-    k_esc_group<16, 2><<<(unsigned)ceil_div(hc[1], kWave / 16), kWave, 0, s>>>(
-        lg[1], hc[1], X.rp, X.col, X.val, Y.rp, Y.col, Y.val, poff, ocol, oval, ucnt);
-  if (hc[2] > 0)
-    k_esc_group<32, 2><<<(unsigned)ceil_div(hc[2], kWave / 32), kWave, 0, s>>>(
-        lg[2], hc[2], X.rp, X.col, X.val, Y.rp, Y.col, Y.val, poff, ocol, oval, ucnt);
-  SA_LAUNCH_CHECK();
-  // the sort's 32-bit keys hold 25 bits of column at 128 products, 22 at 1024; wider outputs
-  // (and SAAMG_SPGEMM_KEY64=1) take the hash table
-  auto wide = [&](int q) { return keys64() || Y.ncols >= (1 << (25 - q)); };
+  // the sorts' 32-bit keys hold 28 bits of column at 16 products, 22 at 1024; wider outputs (and
+  // SAAMG_SPGEMM_KEY64=1) take the hash table
+  auto wide = [&](int bin) { return keys64() || Y.ncols >= (1 << (28 - bin)); };
   int32_t nhash = 0;
-  for (int q = 0; q < 4; ++q)
-    if (wide(q)) nhash += hc[3 + q];
+  for (int bin = 0; bin < 7; ++bin)
+    if (wide(bin)) nhash += hc[bin];
   const int32_t nlong = hc[7] + hc[8] + hc[9] + hc[10];
   int32_t *over1 = nullptr, *nover = counters + kBins;
   if (nhash + nlong > 0) over1 = tmp.alloc<int32_t>(nhash + nlong);
-  for (int q = 0; q < 4; ++q) {
-    const int32_t nr = hc[3 + q];
+  for (int bin = 0; bin < 7; ++bin) {
+    const int32_t nr = hc[bin];
     if (nr == 0) continue;
-    const int32_t *rows = lists + (3 + q) * (int64_t)m;
+    const int32_t *rows = lists + bin * (int64_t)m;
+    auto group = [&](auto gc) {
+      constexpr int G = decltype(gc)::value;
+      k_esc_group<G><<<(unsigned)ceil_div(nr, kWave / G), kWave, 0, s>>>(
+          rows, nr, X.rp, X.col, X.val, Y.rp, Y.col, Y.val, poff, ocol, oval, ucnt);
+    };
     auto sort = [&](auto pc) {
       constexpr int P = decltype(pc)::value;
       k_esc_sort<P><<<(unsigned)nr, 64, 0, s>>>(rows, nr, X.rp, X.col, X.val, Y.rp, Y.col, Y.val,
                                                poff, ocol, oval, ucnt);
     };
-    if (wide(q))
+    if (wide(bin))
       k_esc_table<512><<<(unsigned)nr, 64, 0, s>>>(rows, nr, X.rp, X.col, X.val, Y.rp, Y.col,
                                                    Y.val, poff, ocol, oval, ucnt, over1, nover);
-    else if (q == 0) sort(std::integral_constant<int, 2>{});
-    else if (q == 1) sort(std::integral_constant<int, 4>{});
-    else if (q == 2) sort(std::integral_constant<int, 8>{});
+    else if (bin == 0) group(std::integral_constant<int, 8>{});
+    else if (bin == 1) group(std::integral_constant<int, 16>{});
+    else if (bin == 2) group(std::integral_constant<int, 32>{});
+    else if (bin == 3) sort(std::integral_constant<int, 2>{});
+    else if (bin == 4) sort(std::integral_constant<int, 4>{});
+    else if (bin == 5) sort(std::integral_constant<int, 8>{});
     else sort(std::integral_constant<int, 16>{});
     SA_LAUNCH_CHECK();
   }
