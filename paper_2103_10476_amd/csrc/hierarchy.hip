@@ -295,7 +295,8 @@ static bool build_level_system(sa_hierarchy *h, int l) {
   return true;
 }
 
-static bool build_level(sa_hierarchy *h, int l) {
+// diag (may be null): the diagonal of the matrix that the strength test reads.
+static bool build_level(sa_hierarchy *h, int l, const double *diag) {
   if (h->k > 0) return build_level_system(h, l);
   const hipStream_t s = h->stream;
   const sa_options &o = h->opt;
@@ -304,7 +305,7 @@ static bool build_level(sa_hierarchy *h, int l) {
   const int32_t n = L.A.n;
   Arena tmp;
   tmp.stream = s;
-  double *dval = tmp.alloc<double>(n);
+  double *dval = diag ? nullptr : tmp.alloc<double>(n);
   const double *sval = L.As.val;  // the matrix the strength test reads: A, or L^(d)
   if (h->dim > 0) {
     double *w = tmp.alloc<double>(L.As.nnz);
@@ -313,14 +314,15 @@ static bool build_level(sa_hierarchy *h, int l) {
     check_err(h, E_COORD, SA_ERR_INVALID_ARG, "coincident coordinates of connected nodes");
     sval = w;
   } else {
-    find_diag(n, L.As.rp, L.As.col, L.As.val, dval, s);
+    if (!diag) find_diag(n, L.As.rp, L.As.col, L.As.val, dval, s);
   }
+  if (!diag) diag = dval;
   if (L.A.maxrow < 0) L.A.maxrow = max_row_length(n, L.As.rp, s);
   L.As.maxrow = L.A.maxrow;  // A and As share the pattern
   L.wave_rows = long_rows(L.As.maxrow, L.As.nnz, n);
   L.mask = ar.alloc<uint8_t>(L.As.nnz);
   int32_t *scount = tmp.alloc<int32_t>(n + 1);
-  strength(n, L.As.rp, L.As.col, sval, dval, o.theta * o.theta, L.mask, scount, L.wave_rows,
+  strength(n, L.As.rp, L.As.col, sval, diag, o.theta * o.theta, L.mask, scount, L.wave_rows,
            s);
   int32_t *grp = nullptr, *gcol = nullptr;
   // the filtered matrix' row pointers need the labels only: counted first, so that their total
@@ -686,9 +688,9 @@ static double *apply_nullspace(sa_hierarchy *h, const double *B, sa_location loc
 
 // The input matrix's structure and values, one readback: row pointers spanning [0, nnz]
 // first, then values, columns and diagonals.
-static void validate_values(sa_hierarchy *h) {
+static void validate_values(sa_hierarchy *h, double *dval = nullptr) {
   Level &L0 = h->lv[0];
-  validate_csr(h->n, L0.A.nnz, L0.A.rp, L0.A.col, L0.A.val, h->err, h->stream);
+  validate_csr(h->n, L0.A.nnz, L0.A.rp, L0.A.col, L0.A.val, dval, h->err, h->stream);
   const int32_t e = read_err(h);
   if (e & E_SPAN) throw Error(SA_ERR_BAD_CSR, "row pointers do not span nnz");
   if (e & E_NONFINITE) throw Error(SA_ERR_INVALID_ARG, "non-finite matrix value");
@@ -722,7 +724,10 @@ static void setup_impl(sa_hierarchy *h, const sa_csr *A, const double *B,
   copy_in(L0.A.rp, A->row_ptr, sizeof(int32_t) * (n + 1), A->loc, s);
   copy_in(L0.A.col, A->col, sizeof(int32_t) * A->nnz, A->loc, s);
   copy_in(L0.A.val, A->val, sizeof(double) * A->nnz, A->loc, s);
-  validate_values(h);
+  Arena tmp;  // the diagonal, for the first level's strength
+  tmp.stream = s;
+  double *diag = k == 0 && !coords ? tmp.alloc<double>(n) : nullptr;
+  validate_values(h, diag);
   if (k > 0) {  // systems SA
     if (bs < 1 || bs > 16 || n % bs != 0)
       throw Error(SA_ERR_INVALID_ARG, "block size not in 1..16 or not dividing n");
@@ -749,7 +754,9 @@ static void setup_impl(sa_hierarchy *h, const sa_csr *A, const double *B,
   const double *dB = apply_nullspace(h, B, A->loc);
   for (int l = 0;; ++l) {
     if (h->lv[l].A.n <= o.max_coarse || l + 1 >= o.max_levels) break;
-    if (!build_level(h, l)) {
+    const bool more = build_level(h, l, l == 0 && L0.As.val == L0.A.val ? diag : nullptr);
+    if (l == 0) tmp.release();
+    if (!more) {
       Level &Lc = h->lv[l];
       Lc.nc = 0;
       Lc.mask = nullptr;

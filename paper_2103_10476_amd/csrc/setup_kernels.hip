@@ -66,12 +66,13 @@ __device__ inline bool wave_any(bool p) { return __ballot(p) != 0; }
 // Entry-parallel (a block owns kBlock rows, whose row pointers it stages in LDS and checks
 // first; coalesced reads of col and val): bit 1 a row pointer or column out of range or
 // columns not ascending, 2 a row without its diagonal entry, 4 a non-finite value, 2048 row
-// pointers that do not start at 0 and end at nnz.
+// pointers that do not start at 0 and end at nnz.  dval (may be null) gets the diagonal, which
+// a search of its own in 970K rows of 26 entries took 206 us to find again.
 __global__ __launch_bounds__(kBlock) void k_validate(int32_t n, int64_t nnz,
                                                      const int32_t *__restrict__ rp,
                                                      const int32_t *__restrict__ col,
                                                      const double *__restrict__ val,
-                                                     int32_t *err) {
+                                                     double *__restrict__ dval, int32_t *err) {
   __shared__ int32_t s_rp[kBlock + 1];
   __shared__ uint8_t s_diag[kBlock];
   const int t = threadIdx.x;
@@ -100,7 +101,10 @@ __global__ __launch_bounds__(kBlock) void k_validate(int32_t n, int64_t nnz,
     const int32_t c = col[e];
     if (c < 0 || c >= n) flags |= 1;
     if (e > s_rp[lo] && c <= col[e - 1]) flags |= 1;
-    if (c == (int32_t)r0 + lo) s_diag[lo] = 1;
+    if (c == (int32_t)r0 + lo) {
+      s_diag[lo] = 1;
+      if (dval) dval[c] = val[e];
+    }
     if (val && !isfinite(val[e])) flags |= 4;
   }
   __syncthreads();
@@ -110,8 +114,8 @@ __global__ __launch_bounds__(kBlock) void k_validate(int32_t n, int64_t nnz,
 
 // nnz: the length of col and val (rp[n] is checked against it on the device).
 void validate_csr(int32_t n, int64_t nnz, const int32_t *rp, const int32_t *col,
-                  const double *val, int32_t *err, hipStream_t s) {
-  k_validate<<<grid_for(n), kBlock, 0, s>>>(n, nnz, rp, col, val, err);
+                  const double *val, double *dval, int32_t *err, hipStream_t s) {
+  k_validate<<<grid_for(n), kBlock, 0, s>>>(n, nnz, rp, col, val, dval, err);
   SA_LAUNCH_CHECK();
 }
 __global__ void k_find_diag(int32_t n, const int32_t *rp, const int32_t *col, const double *val,
@@ -2358,56 +2362,63 @@ constexpr int32_t kSortShort = 32;
 constexpr int32_t kSortMid = 256;
 constexpr int32_t kSortLds = 4096;
 
-__device__ inline void wave_append(bool pred, int32_t *counter, int32_t *list, int32_t value) {
-  const unsigned long long m = __ballot(pred);
-  if (!m) return;
-  const int lane = threadIdx.x & 63;
-  const int leader = __ffsll((long long)m) - 1;
-  int32_t base = 0;
-  if (lane == leader) base = atomicAdd(counter, __popcll(m));
-  base = __shfl(base, leader, 64);
-  if (pred) list[base + __popcll(m & ((1ull << lane) - 1ull))] = value;
-}
-
-// nlist[0], nlist[1]: the rows listed for the wavefront and the block sort (mid, longrows).
+// nlist[0], nlist[1]: the rows listed for the wavefront and the block sort (mid, longrows), by
+// one atomic per block and list (one per wavefront took 221 us where most of 89K rows are
+// listed, now 65); nlist[2]: whether a row has more than 64 entries.  A block has 32 PASS
+// rows.
+template <int PASS>
 __global__ __launch_bounds__(kBlock) void k_sort_short(int32_t n, const int32_t *__restrict__ rp,
                                                        int32_t *c, double *v, int32_t *nlist,
                                                        int32_t *mid, int32_t *longrows) {
-  const int64_t i64 = ((int64_t)blockIdx.x * kBlock + threadIdx.x) >> 3;
-  const int j = threadIdx.x & 7;
-  const bool live = i64 < n;
-  const int32_t i = live ? (int32_t)i64 : 0;
-  const int32_t b = live ? rp[i] : 0;
-  const int32_t L = live ? rp[i + 1] - b : 0;
-  wave_append(j == 0 && L > kSortShort && L <= kSortMid, nlist, mid, i);
-  wave_append(j == 0 && L > kSortMid, nlist + 1, longrows, i);
-  if (L > 64) nlist[2] = 1;  // (every writer writes the same)
-  if (L <= 1 || L > kSortShort) return;  // uniform over the row's lanes
-  int32_t k[4], place[4] = {0, 0, 0, 0};
-  double x[4];
+  __shared__ int32_t s_list[2][32 * PASS], s_n[2], s_base[2], s_any;
+  const int t = threadIdx.x, j = t & 7;
+  if (t < 2) s_n[t] = 0;
+  if (t == 0) s_any = 0;
+  __syncthreads();
+  for (int pass = 0; pass < PASS; ++pass) {
+    const int64_t i64 = ((int64_t)blockIdx.x * PASS + pass) * 32 + (t >> 3);
+    const bool live = i64 < n;
+    const int32_t i = live ? (int32_t)i64 : 0;
+    const int32_t b = live ? rp[i] : 0;
+    const int32_t L = live ? rp[i + 1] - b : 0;
+    if (j == 0 && L > kSortShort) {
+      const int which = L > kSortMid;
+      s_list[which][atomicAdd(&s_n[which], 1)] = i;
+      if (L > 64) s_any = 1;
+    }
+    if (L <= 1 || L > kSortShort) continue;  // uniform over the row's lanes
+    int32_t k[4], place[4] = {0, 0, 0, 0};
+    double x[4];
 #pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    const bool in = j + 8 * q < L;
-    k[q] = in ? c[b + j + 8 * q] : INT_MAX;
-    x[q] = v && in ? v[b + j + 8 * q] : 0.0;
-  }
+    for (int q = 0; q < 4; ++q) {
+      const bool in = j + 8 * q < L;
+      k[q] = in ? c[b + j + 8 * q] : INT_MAX;
+      x[q] = v && in ? v[b + j + 8 * q] : 0.0;
+    }
 #pragma unroll
-  for (int p = 0; p < 4; ++p) {
-    if (8 * p < L) {
+    for (int p = 0; p < 4; ++p) {
+      if (8 * p < L) {
 #pragma unroll
-      for (int o = 0; o < 8; ++o) {
-        const int32_t other = __shfl(k[p], o, 8);
+        for (int o = 0; o < 8; ++o) {
+          const int32_t other = __shfl(k[p], o, 8);
 #pragma unroll
-        for (int q = 0; q < 4; ++q) place[q] += other < k[q] ? 1 : 0;
+          for (int q = 0; q < 4; ++q) place[q] += other < k[q] ? 1 : 0;
+        }
       }
     }
-  }
 #pragma unroll
-  for (int q = 0; q < 4; ++q)
-    if (j + 8 * q < L) {
-      c[b + place[q]] = k[q];
-      if (v) v[b + place[q]] = x[q];
-    }
+    for (int q = 0; q < 4; ++q)
+      if (j + 8 * q < L) {
+        c[b + place[q]] = k[q];
+        if (v) v[b + place[q]] = x[q];
+      }
+  }
+  __syncthreads();
+  if (t < 2 && s_n[t] > 0) s_base[t] = atomicAdd(nlist + t, s_n[t]);
+  if (t == 0 && s_any) nlist[2] = 1;  // (every writer writes the same)
+  __syncthreads();
+  for (int q = t; q < s_n[0]; q += kBlock) mid[s_base[0] + q] = s_list[0][q];
+  for (int q = t; q < s_n[1]; q += kBlock) longrows[s_base[1] + q] = s_list[1][q];
 }
 
 __global__ __launch_bounds__(kBlock) void k_sort_mid(const int32_t *rows, int32_t nrows,
@@ -2524,8 +2535,12 @@ void sort_rows_begin(int32_t n, const int32_t *rp, int32_t *col, double *val, Ro
   if (n <= 0) return;
   job.mid = job.tmp.alloc<int32_t>(n);
   job.rows = job.tmp.alloc<int32_t>(n);
-  k_sort_short<<<grid_for((int64_t)n * 8), kBlock, 0, s>>>(n, rp, col, val, job.words, job.mid,
-                                                           job.rows);
+  if (n > 16384)  // (small: the passes' latency counts)
+    k_sort_short<8><<<(unsigned)ceil_div(n, 256), kBlock, 0, s>>>(n, rp, col, val, job.words,
+                                                                 job.mid, job.rows);
+  else
+    k_sort_short<1><<<(unsigned)ceil_div(n, 32), kBlock, 0, s>>>(n, rp, col, val, job.words,
+                                                                job.mid, job.rows);
   SA_LAUNCH_CHECK();
 }
 void sort_rows_end(RowSort &job, const int32_t *words, hipStream_t s) {

@@ -67,73 +67,90 @@ __device__ __forceinline__ void bin_row(bool live, int32_t i, int64_t T, int32_t
   if (live) lists[(int64_t)bin * m + s_base[bin] + local] = i;
 }
 
-// Thread per row of X: the row's product count T, the products before each of its entries
-// (xpref), and the row's place in its bin's list.  The block's prefixes are gathered in LDS
-// and written out as one contiguous run (a thread's own entries are a short strided run, whose
-// partial-line writes cost several times their bytes), unless the block's X entries exceed
-// the buffer.
-constexpr int32_t kCountLds = 4096;
-__global__ __launch_bounds__(kBlock) void k_count_products(int32_t m, const int32_t *xrp,
-                                                           const int32_t *xcol,
-                                                           const int32_t *yrp, int64_t *cnt,
-                                                           int32_t *xpref, int32_t *lists,
-                                                           int32_t *counters) {
-  __shared__ int32_t s_xp[kCountLds];
-  const int64_t r0 = (int64_t)blockIdx.x * blockDim.x;
-  const int32_t e0 = xrp[r0], e1 = xrp[min((int64_t)m, r0 + blockDim.x)];
-  const bool staged = e1 - e0 <= kCountLds;  // block-uniform
-  const int64_t i64 = r0 + threadIdx.x;
-  const bool live = i64 < m;
-  const int32_t i = live ? (int32_t)i64 : 0;
-  int64_t t = 0;
-  if (live) {
-    for (int32_t e = xrp[i]; e < xrp[i + 1]; ++e) {
-      // products before entry e within the row (T < 2^31 checked)
-      if (staged) s_xp[e - e0] = (int32_t)t;
-      else xpref[e] = (int32_t)t;
-      const int32_t k = xcol[e];
-      t += yrp[k + 1] - yrp[k];
-    }
-    cnt[i] = t;
-  }
-  bin_row(live, i, t, m, lists, counters);  // every thread passes the barriers
-  if (staged) {
-    __syncthreads();
-    for (int32_t q = threadIdx.x; q < e1 - e0; q += blockDim.x) xpref[e0 + q] = s_xp[q];
-  }
-}
-
-// G lanes per row of X (longer rows): xpref by a prefix sum over the lanes.
+// The rows' product counts, G lanes per row, four rows of a group at a time so that their loads
+// go out together, and the rows' places in their bins' lists (a block has 256 rows: one atomic
+// per bin and block).
 template <int G>
+__global__ __launch_bounds__(kBlock) void k_count_products(int32_t m,
+                                                           const int32_t *__restrict__ xrp,
+                                                           const int32_t *__restrict__ xcol,
+                                                           const int32_t *__restrict__ yrp,
+                                                           int64_t *__restrict__ cnt,
+                                                           int32_t *lists, int32_t *counters) {
+  constexpr int R = kBlock / G, U = 4;  // rows at once, rows per group and step
+  __shared__ int32_t s_rp[kBlock + 1];
+  __shared__ int64_t s_t[kBlock];
+  const int t = threadIdx.x, lane = t % G;
+  const int64_t r0 = (int64_t)blockIdx.x * kBlock;
+  const int32_t nr = (int32_t)min<int64_t>(kBlock, (int64_t)m - r0);
+  if (t <= nr) s_rp[t] = xrp[r0 + t];
+  if (t == 0) s_rp[nr] = xrp[r0 + nr];  // nr can be kBlock: no thread t == nr
+  __syncthreads();
+  for (int32_t q = t / G; q < nr; q += U * R) {  // uniform over the group
+    int32_t b[U], e[U], k[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int32_t r = q + u * R;
+      b[u] = r < nr ? s_rp[r] + lane : 0;
+      e[u] = r < nr ? s_rp[r + 1] : 0;
+      k[u] = b[u] < e[u] ? xcol[b[u]] : -1;
+    }
+    int64_t sum[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) sum[u] = k[u] >= 0 ? yrp[k[u] + 1] - yrp[k[u]] : 0;
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      for (int32_t c = b[u] + G; c < e[u]; c += G) {
+        const int32_t j = xcol[c];
+        sum[u] += yrp[j + 1] - yrp[j];
+      }
+#pragma unroll
+      for (int off = G / 2; off >= 1; off >>= 1) sum[u] += __shfl_xor(sum[u], off, G);
+      if (lane == 0 && q + u * R < nr) s_t[q + u * R] = sum[u];
+    }
+  }
+  __syncthreads();
+  const bool live = t < nr;
+  if (live) cnt[r0 + t] = s_t[t];
+  bin_row(live, live ? (int32_t)(r0 + t) : 0, live ? s_t[t] : 0, m, lists, counters);
+}
+// A wavefront per row (rows of more than 64 entries among them), binned by a launch of its own.
 __global__ __launch_bounds__(kBlock) void k_count_products_w(int32_t m,
                                                              const int32_t *__restrict__ xrp,
                                                              const int32_t *__restrict__ xcol,
                                                              const int32_t *__restrict__ yrp,
-                                                             int64_t *__restrict__ cnt,
-                                                             int32_t *__restrict__ xpref) {
-  const int64_t i64 = ((int64_t)blockIdx.x * kBlock + threadIdx.x) / G;
-  if (i64 >= m) return;  // uniform over the row's lanes
-  const int32_t i = (int32_t)i64;
-  const int lane = threadIdx.x % G;
+                                                             int64_t *__restrict__ cnt) {
+  const int64_t i = ((int64_t)blockIdx.x * kBlock + threadIdx.x) / kWave;
+  if (i >= m) return;  // uniform over the row's lanes
+  const int lane = threadIdx.x % kWave;
   const int32_t end = xrp[i + 1];
-  int64_t base = 0;
-  for (int32_t c = xrp[i]; c < end; c += G) {
+  int64_t sum = 0;
+  for (int32_t e = xrp[i] + lane; e < end; e += kWave) {
+    const int32_t k = xcol[e];
+    sum += yrp[k + 1] - yrp[k];
+  }
+#pragma unroll
+  for (int off = kWave / 2; off >= 1; off >>= 1) sum += __shfl_xor(sum, off, kWave);
+  if (lane == 0) cnt[i] = sum;
+}
+// The products before each entry of the listed rows (a wavefront per row), for k_esc_dense.
+__global__ __launch_bounds__(kWave) void k_row_prefix(const int32_t *rows, const int32_t *xrp,
+                                                      const int32_t *xcol, const int32_t *yrp,
+                                                      int32_t *xpref) {
+  const int lane = threadIdx.x;
+  const int32_t i = rows[blockIdx.x], end = xrp[i + 1];
+  int32_t base = 0;
+  for (int32_t c = xrp[i]; c < end; c += kWave) {
     const int32_t e = c + lane;
     int32_t len = 0;
     if (e < end) {
       const int32_t k = xcol[e];
       len = yrp[k + 1] - yrp[k];
     }
-    int32_t incl = len;
-#pragma unroll
-    for (int off = 1; off < G; off <<= 1) {
-      const int32_t v = __shfl_up(incl, off, G);
-      if (lane >= off) incl += v;
-    }
-    if (e < end) xpref[e] = (int32_t)(base + incl - len);
-    base += __shfl(incl, G - 1, G);
+    const int32_t incl = group_prefix<64>(len, lane);
+    if (e < end) xpref[e] = base + incl - len;
+    base += __builtin_amdgcn_readlane(incl, 63);
   }
-  if (lane == 0) cnt[i] = base;
 }
 
 // ---- block-level rows (T > 64) -------------------------------------------------------------
@@ -1110,7 +1127,6 @@ void spgemm(const Csr &X, const Csr &Y, Arena &ar, Csr &C, hipStream_t s, int32_
   Arena tmp;
   tmp.stream = s;
   int64_t *cnt = tmp.alloc<int64_t>(m + 1);
-  int32_t *xpref = tmp.alloc<int32_t>(X.nnz > 0 ? X.nnz : 1);
   int64_t *poff = tmp.alloc<int64_t>(m + 1);
   int32_t *lists = tmp.alloc<int32_t>(kBins * (int64_t)(m > 0 ? m : 1));
   // kBins bin sizes, the counts of rows left to the large hash table and by it, then (8-byte
@@ -1118,25 +1134,26 @@ void spgemm(const Csr &X, const Csr &Y, Arena &ar, Csr &C, hipStream_t s, int32_
   constexpr int kTotalAt = (kBins + 3) & ~1;
   int32_t *counters = tmp.alloc<int32_t>(kTotalAt + 2);
   fill_i32(counters, 0, kBins + 2, s);
-  // short rows: a thread per row, which also bins the row; longer: 16, 32 or 64 lanes per
-  // row, binned after the scan (970K rows of 26 entries: 261 us and 48 for the binning,
-  // against 640 with a thread per row, whose Y row lengths are a chain of gathers)
+  // rows of up to 64 entries: 8, 16 or 32 lanes each, counted and binned in one launch; longer
+  // ones a wavefront each, binned after the scan (a block of few rows would add its atomics to
+  // the bins' counters too often).  970K rows of 26 entries: 261 us and 48 for the binning with
+  // the products before each entry written out too, now 103; 600K of 16, a thread per row, 117,
+  // now 56
   if (xmax < 0) xmax = m > 0 ? (X.maxrow >= 0 ? X.maxrow : max_row_length(m, X.rp, s)) : 0;
-  const bool wave_count = m > 0 && (xmax > 64 || X.nnz > 8 * (int64_t)m);
+  const bool wave_count = m > 0 && xmax > 64;
   auto count_rows = [&](auto gc) {
     constexpr int G = decltype(gc)::value;
-    k_count_products_w<G><<<grid_for((int64_t)m * G), kBlock, 0, s>>>(m, X.rp, X.col, Y.rp, cnt,
-                                                                     xpref);
+    k_count_products<G><<<grid_for(m), kBlock, 0, s>>>(m, X.rp, X.col, Y.rp, cnt, lists,
+                                                      counters);
   };
-  if (wave_count && xmax > 64)
-    count_rows(std::integral_constant<int, 64>{});
-  else if (wave_count && X.nnz > 20 * (int64_t)m)
+  if (wave_count)
+    k_count_products_w<<<grid_for((int64_t)m * kWave), kBlock, 0, s>>>(m, X.rp, X.col, Y.rp, cnt);
+  else if (m > 0 && X.nnz > 20 * (int64_t)m)
     count_rows(std::integral_constant<int, 32>{});
-  else if (wave_count)
+  else if (m > 0 && X.nnz > 10 * (int64_t)m)
     count_rows(std::integral_constant<int, 16>{});
   else if (m > 0)
-    k_count_products<<<grid_for(m), kBlock, 0, s>>>(m, X.rp, X.col, Y.rp, cnt, xpref, lists,
-                                                    counters);
+    count_rows(std::integral_constant<int, 8>{});
   SA_LAUNCH_CHECK();
   exclusive_scan_i64(cnt, poff, m, s);
   if (wave_count) {
@@ -1239,6 +1256,9 @@ void spgemm(const Csr &X, const Csr &Y, Arena &ar, Csr &C, hipStream_t s, int32_
       const int64_t per = (int64_t)Y.ncols * 12;
       int64_t nb = std::min<int64_t>(nov, std::max<int64_t>(1, (int64_t(2) << 30) / per));
       nb = std::min<int64_t>(nb, 1024);
+      int32_t *xpref = tmp.alloc<int32_t>(X.nnz);
+      k_row_prefix<<<(unsigned)nov, kWave, 0, s>>>(over2, X.rp, X.col, Y.rp, xpref);
+      SA_LAUNCH_CHECK();
       double *dacc = tmp.alloc<double>(nb * (int64_t)Y.ncols);
       int32_t *dflag = tmp.alloc<int32_t>(nb * (int64_t)Y.ncols);
       k_esc_dense<<<(unsigned)nb, kBlock, 0, s>>>(over2, nov, X.rp, X.col, X.val, xpref, Y.rp,
