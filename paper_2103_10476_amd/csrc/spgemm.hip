@@ -409,24 +409,22 @@ __device__ __forceinline__ void row_products(ProductStage &st, int lane, int32_t
 }
 
 // Both values of a pair of lanes (lane, lane ^ J), in either order.  J = 1, 2: a quad permutation
-// (DPP); J = 4, 8: the row shifts by J toward the lower lanes (row_shl, lane i reads i + J) and
-// the higher lanes (row_shr, lane i reads i - J), of which each lane keeps the one inside its
-// J-group pair (both stay inside the 16-lane row); J = 16, 32: a swap of rows of 16 or of 32.
+// (DPP); J = 4, 8: a row shift by J toward the lower lanes (row_shl, lane i reads i + J) for the
+// lower lanes of a pair, one toward the higher lanes for the others (by bank masks); J = 16, 32: a
+// swap of rows of 16 or of 32.
 struct Pair {
   uint32_t a, b;
 };
 template <int J>
-__device__ __forceinline__ Pair xor_pair(uint32_t v, int lane) {
+__device__ __forceinline__ Pair xor_pair(uint32_t v) {
   if constexpr (J == 1) {
     return {v, (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0xB1, 0xF, 0xF, false)};  // [1,0,3,2]
   } else if constexpr (J == 2) {
     return {v, (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x4E, 0xF, 0xF, false)};  // [2,3,0,1]
   } else if constexpr (J == 4 || J == 8) {
-    const uint32_t from_up =
-        (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x100 + J, 0xF, 0xF, false);  // row_shl
-    const uint32_t from_dn =
-        (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x110 + J, 0xF, 0xF, false);  // row_shr
-    return {v, (lane & J) ? from_dn : from_up};
+    constexpr int low = J == 4 ? 0x5 : 0x3;  // banks (of 4 lanes) of the pairs' lower lanes
+    const int x = __builtin_amdgcn_update_dpp((int)v, (int)v, 0x100 + J, 0xF, low, false);
+    return {v, (uint32_t)__builtin_amdgcn_update_dpp(x, (int)v, 0x110 + J, 0xF, 0xF ^ low, false)};
   } else if constexpr (J == 16) {
     const auto r = __builtin_amdgcn_permlane16_swap(v, v, false, false);
     return {r[0], r[1]};
@@ -435,7 +433,15 @@ __device__ __forceinline__ Pair xor_pair(uint32_t v, int lane) {
     return {r[0], r[1]};
   }
 }
-// ---- one wavefront per row, all products sorted at once (65..1024 products) -----------------
+// The smaller of a and b where e is 0, the larger where it is all ones (one median of three).
+__device__ __forceinline__ uint32_t pick(uint32_t a, uint32_t b, uint32_t e) {
+  return max(min(a, b), min(max(a, b), e));
+}
+// 0 in the lanes that keep the smaller of a pair (lane, lane ^ J), all ones in the others.
+template <int J>
+__device__ __forceinline__ uint32_t upper_of(int lane) {
+  return (lane & J) ? ~0u : 0u;
+}
 // Value of lane (lane ^ M), M = 2^m - 1, the partner in a merge's first step (1, 3: quad permutations; 7, 15: the mirrors within 8 and 16 lanes; 31, 63: the
 // mirror and row swaps).
 template <int M>
@@ -449,10 +455,10 @@ __device__ __forceinline__ uint32_t flip_lane(uint32_t v, int lane) {
   else if constexpr (M == 15)
     return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x140, 0xF, 0xF, false);  // row mirror
   else if constexpr (M == 31) {
-    const Pair p = xor_pair<16>(flip_lane<15>(v, lane), lane);
+    const Pair p = xor_pair<16>(flip_lane<15>(v, lane));
     return (lane & 16) ? p.a : p.b;
   } else {
-    const Pair p = xor_pair<32>(flip_lane<31>(v, lane), lane);
+    const Pair p = xor_pair<32>(flip_lane<31>(v, lane));
     return (lane & 32) ? p.a : p.b;
   }
 }
@@ -464,11 +470,11 @@ template <int P, int J>
 __device__ __forceinline__ void sort_halves(uint32_t (&k)[P], int lane) {
   if constexpr (J >= P) {
     constexpr int L = J / P;
-    const bool lower = (lane & L) == 0;
+    const uint32_t up = upper_of<L>(lane);
 #pragma unroll
     for (int q = 0; q < P; ++q) {
-      const Pair p = xor_pair<L>(k[q], lane);
-      k[q] = lower ? min(p.a, p.b) : max(p.a, p.b);
+      const Pair p = xor_pair<L>(k[q]);
+      k[q] = pick(p.a, p.b, up);
     }
   } else {
 #pragma unroll
@@ -495,12 +501,12 @@ __device__ __forceinline__ void sort_keys(uint32_t (&k)[P], int lane) {
     }
   } else {
     constexpr int L = K / P;
-    const bool lower = (lane & (L / 2)) == 0;
+    const uint32_t up = upper_of<L / 2>(lane);
     uint32_t o[P];
 #pragma unroll
     for (int q = 0; q < P; ++q) o[q] = flip_lane<L - 1>(k[P - 1 - q], lane);
 #pragma unroll
-    for (int q = 0; q < P; ++q) k[q] = lower ? min(k[q], o[q]) : max(k[q], o[q]);
+    for (int q = 0; q < P; ++q) k[q] = pick(k[q], o[q], up);
   }
   if constexpr (K > 2) sort_halves<P, K / 4>(k, lane);
   if constexpr (K < N) sort_keys<P, N, K * 2>(k, lane);
@@ -515,7 +521,7 @@ __device__ __forceinline__ void sort_keys(uint32_t (&k)[P], int lane) {
 // run of equal columns added in position order by the lane that holds its first key.  The chunk
 // loop runs to the longest X row of the wavefront.  The ranks by comparing every pair of
 // products in LDS, before, made the instructions the bound: 524K rows of 33..64 products 372 us,
-// now 216, 477K of 17..32 150 -> 103; 1.6M of at most 16 210 -> 169, where the chain of loads is.
+// now 190, 477K of 17..32 150 -> 92; 1.6M of at most 16 210 -> 161, where the chain of loads is.
 template <int G>
 __global__ __launch_bounds__(kWave) void k_esc_group(
     const int32_t *rows, int32_t nrows, const int32_t *xrp, const int32_t *xcol,
@@ -635,10 +641,12 @@ __global__ __launch_bounds__(kWave) void k_esc_group(
 // per key, most of them register moves (DPP), whatever the number of 64-product steps, and
 // nothing has to be looked up or extracted afterwards: what bounds it is the row's chain of
 // loads (X entries, their Y rows, the products) and, from 512 products on, the sort's own
-// instructions.  893K rows of 65..128 products: 854 us, against 2,130 with 64 products per step
-// sorted and added to a hash table; 178K rows of 456 products 565 us against 2,800 with a
-// 256-thread block sorting in LDS; R (A P) with 48K rows of 257..512: 175 us against 553 with
-// the products added X entry by X entry to the rank of their column in the row.
+// instructions (two to a key and exchange: a move and a median of three; 854 us in the first line
+// below with a minimum, a maximum and a choice).  893K rows of 65..128 products: 739 us, against
+// 2,130 with 64 products per step sorted and added to a hash table; 178K rows of 456 products
+// 440 us against 2,800 with a 256-thread block sorting in LDS; R (A P) with 52K rows of
+// 257..512: 141 us against 553 with the products added X entry by X entry to the rank of their
+// column in the row.
 template <int P>
 __global__ __launch_bounds__(64) void k_esc_sort(
     const int32_t *rows, int32_t nrows, const int32_t *xrp, const int32_t *xcol,
