@@ -323,10 +323,44 @@ __global__ void k_agg_qr(int32_t nc, int32_t bs, int32_t k, const int32_t *mrp,
   }
 }
 
+// The sum over i = from..to-1 of a[i k] * b[i k], added one by one from `from` upward.  The next
+// eight products are formed while the current eight are added.
+__device__ __forceinline__ double chain_dot(const double *a, const double *b, int32_t k,
+                                            int32_t from, int32_t to) {
+  double cur[8], nxt[8], t = 0.0;
+  auto load = [&](int32_t i0, double *p) {
+    const double *x = a + i0 * k, *y = b + i0 * k;
+#pragma unroll
+    for (int q = 0; q < 8; ++q) p[q] = x[q * k] * y[q * k];
+  };
+  int32_t i = from;
+  if (i + 8 <= to) load(i, cur);
+  for (; i + 8 <= to; i += 8) {
+    const bool more = i + 16 <= to;
+    if (more) load(i + 8, nxt);
+#pragma unroll
+    for (int q = 0; q < 8; ++q) t = t + cur[q];
+    if (more) {
+#pragma unroll
+      for (int q = 0; q < 8; ++q) cur[q] = nxt[q];
+    }
+  }
+#pragma unroll
+  for (int q = 0; q < 7; ++q)  // the last rows: clamped reads, then the additions
+    nxt[q] = i < to ? a[min(i + q, to - 1) * k] * b[min(i + q, to - 1) * k] : 0.0;
+#pragma unroll
+  for (int q = 0; q < 7; ++q)
+    if (i + q < to) t = t + nxt[q];
+  return t;
+}
+
 // The same QR with one wavefront per aggregate and M, V, Q in LDS (rows x k each, rows <=
 // maxrows): every sum keeps k_agg_qr's order (one lane runs it from i = j upward), so the
-// results are bitwise the same.  Lane 0 forms each Householder vector; the column loops,
-// independent across columns, run one lane per column.
+// results are bitwise the same.  Bound by those sums' chains of dependent additions: a column
+// takes two of them (its norm; then V.V and V with every column left, one lane each, at once),
+// Q's columns one.  The updates between them take a row per lane.  (2,592 aggregates of about 70
+// rows, k = 6: 241 us with lane 0 forming the vectors and a lane per column the updates, now 120;
+// 99 aggregates of about 157 rows: 424, now 176.)
 __global__ __launch_bounds__(64) void k_agg_qr_lds(int32_t nc, int32_t bs, int32_t k,
                                                    int32_t maxrows, const int32_t *mrp,
                                                    const int32_t *mem, const double *B,
@@ -334,8 +368,7 @@ __global__ __launch_bounds__(64) void k_agg_qr_lds(int32_t nc, int32_t bs, int32
                                                    double *ptval, double *Bc, int32_t *err,
                                                    int32_t ebit) {
   extern __shared__ double qr_lds[];
-  __shared__ double s_vv[kMaxBs];
-  __shared__ int s_skip;
+  __shared__ double s_vv[kMaxBs], s_f[kMaxBs];
   const int32_t J = blockIdx.x;
   const int lane = threadIdx.x;
   const int32_t m0 = mrp[J], cntn = mrp[J + 1] - m0;
@@ -349,75 +382,63 @@ __global__ __launch_bounds__(64) void k_agg_qr_lds(int32_t nc, int32_t bs, int32
   for (int32_t e = lane; e < rows * k; e += 64) {
     const int32_t q = e / k, c = e % k;
     M[e] = B[dof(q) * k + c];
-    V[e] = 0.0;
+    Q[e] = q == c ? 1.0 : 0.0;
   }
   __syncthreads();
   for (int j = 0; j < k; ++j) {
-    if (lane == 0) {
-      double vvj = 0.0;
-      int skip = 1;
-      double sigma = 0.0;
-      for (int32_t i = j; i < rows; ++i) sigma = sigma + M[(int64_t)i * k + j] * M[(int64_t)i * k + j];
-      const double nrm = sqrt(sigma);
-      if (nrm != 0.0) {
-        const double ajj = M[(int64_t)j * k + j];
-        const double alpha = ajj > 0.0 ? -nrm : nrm;
-        for (int32_t i = j; i < rows; ++i) V[(int64_t)i * k + j] = M[(int64_t)i * k + j];
-        V[(int64_t)j * k + j] = ajj - alpha;
-        double d = 0.0;
-        for (int32_t i = j; i < rows; ++i) d = d + V[(int64_t)i * k + j] * V[(int64_t)i * k + j];
-        vvj = d;
-        skip = d == 0.0;
-      }
-      s_vv[j] = vvj;
-      s_skip = skip;
+    const double nrm = sqrt(chain_dot(M + j, M + j, k, j, rows));  // the same in every lane
+    if (nrm == 0.0) {
+      if (lane == 0) s_vv[j] = 0.0;
+      __syncthreads();
+      continue;
     }
+    const double ajj = M[(int64_t)j * k + j];
+    const double alpha = ajj > 0.0 ? -nrm : nrm;
+    for (int32_t i = j + lane; i < rows; i += 64)
+      V[(int64_t)i * k + j] = i == j ? ajj - alpha : M[(int64_t)i * k + j];
     __syncthreads();
-    if (!s_skip) {
-      const int c = j + lane;
-      if (c < k) {
-        const double d = s_vv[j];
-        double t = 0.0;
-        for (int32_t i = j; i < rows; ++i) t = t + V[(int64_t)i * k + j] * M[(int64_t)i * k + c];
-        const double f = (t + t) / d;
-        for (int32_t i = j; i < rows; ++i)
-          M[(int64_t)i * k + c] = M[(int64_t)i * k + c] - f * V[(int64_t)i * k + j];
+    const int c = j + lane;  // lane k - j: V.V
+    const double t = c <= k ? chain_dot(V + j, c < k ? M + c : V + j, k, j, rows) : 0.0;
+    const double d = __shfl(t, k - j);
+    if (c < k) s_f[c] = (t + t) / d;
+    if (lane == 0) s_vv[j] = d;
+    __syncthreads();
+    if (d != 0.0)
+      for (int32_t i = j + lane; i < rows; i += 64) {
+        const double v = V[(int64_t)i * k + j];
+#pragma unroll 4
+        for (int cc = j; cc < k; ++cc)
+          M[(int64_t)i * k + cc] = M[(int64_t)i * k + cc] - s_f[cc] * v;
       }
-    }
     __syncthreads();
   }
-  for (int32_t e = lane; e < rows * k; e += 64) Q[e] = (e / k == e % k) ? 1.0 : 0.0;
-  __syncthreads();
   for (int j = k - 1; j >= 0; --j) {
     const double vj = s_vv[j];
     if (vj == 0.0) continue;  // block-uniform
-    const int c = lane;
-    if (c < k) {
-      double t = 0.0;
-      for (int32_t i = j; i < rows; ++i) t = t + V[(int64_t)i * k + j] * Q[(int64_t)i * k + c];
-      const double f = (t + t) / vj;
-      for (int32_t i = j; i < rows; ++i)
-        Q[(int64_t)i * k + c] = Q[(int64_t)i * k + c] - f * V[(int64_t)i * k + j];
+    if (lane < k) {
+      const double t = chain_dot(V + j, Q + lane, k, j, rows);
+      s_f[lane] = (t + t) / vj;
+    }
+    __syncthreads();
+    for (int32_t i = j + lane; i < rows; i += 64) {
+      const double v = V[(int64_t)i * k + j];
+#pragma unroll 4
+      for (int c = 0; c < k; ++c)
+        Q[(int64_t)i * k + c] = Q[(int64_t)i * k + c] - s_f[c] * v;
     }
     __syncthreads();
   }
-  if (lane < k) {  // row r = lane of R, and the sign of Q's column r
-    const int r = lane;
-    const bool flip = M[(int64_t)r * k + r] < 0.0;
-    for (int c = 0; c < k; ++c) {
-      double rv = (c >= r) ? M[(int64_t)r * k + c] : 0.0;
-      if (flip) rv = -rv;
-      Bc[((int64_t)J * k + r) * k + c] = rv;
-    }
-    if (flip)
-      for (int32_t q = 0; q < rows; ++q) Q[(int64_t)q * k + r] = -Q[(int64_t)q * k + r];
+  for (int32_t e = lane; e < k * k; e += 64) {  // R; its rows' signs go to Q's columns
+    const int r = e / k, c = e % k;
+    double rv = (c >= r) ? M[e] : 0.0;
+    if (M[(int64_t)r * k + r] < 0.0) rv = -rv;
+    Bc[(int64_t)J * k * k + e] = rv;
   }
-  __syncthreads();
   for (int32_t e = lane; e < rows * k; e += 64) {
     const int32_t q = e / k, c = e % k;
     const int64_t i = dof(q);
     ptcol[ptrp[i] + c] = J * k + c;
-    ptval[ptrp[i] + c] = Q[e];
+    ptval[ptrp[i] + c] = M[(int64_t)c * k + c] < 0.0 ? -Q[e] : Q[e];
   }
 }
 
