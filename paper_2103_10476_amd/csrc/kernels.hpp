@@ -75,11 +75,12 @@ bool sell_build(const Csr &A, Sell &S, bool f32, Arena &ar, hipStream_t s);
 // Copies A's current values into a built copy (after a numeric re-setup).
 void sell_values(const Csr &A, const Sell &S, hipStream_t s);
 // Sorts the entries of every row by column (values follow when val != nullptr); keys within a
-// row must be distinct.  Short rows per thread, long rows per block (bitonic in LDS).
+// row must be distinct.
 void sort_rows(int32_t n, const int32_t *rp, int32_t *col, double *val, hipStream_t s);
 // The same in two parts, for a caller that has a readback of its own to make in between: begin
-// sorts the rows of up to 32 entries and leaves three words on the device (rows of up to 256
-// entries, longer rows, whether any row has more than 64), end takes them and sorts the rest.
+// sorts the rows of up to 32 entries and leaves four words on the device (rows of up to 256
+// entries, longer rows, whether any row has more than 64, more than 1024), end takes them and
+// sorts the rest.
 struct RowSort {
   int32_t n = 0;
   const int32_t *rp = nullptr;
@@ -88,7 +89,7 @@ struct RowSort {
   int32_t *words = nullptr, *mid = nullptr, *rows = nullptr;
   Arena tmp;
 };
-constexpr int32_t kRowSortWords = 3;
+constexpr int32_t kRowSortWords = 4;
 void sort_rows_begin(int32_t n, const int32_t *rp, int32_t *col, double *val, RowSort &job,
                      hipStream_t s);
 void sort_rows_end(RowSort &job, const int32_t *words, hipStream_t s);

@@ -2409,26 +2409,29 @@ void scale_sym(int32_t n, const int32_t *rp, const int32_t *col, const double *v
 // Keys within a row are distinct, so the order is unique.  Up to kSortShort entries: 8 lanes
 // per row hold 4 keys each and count, for each of theirs, the row's smaller keys (its place).
 // Up to kSortMid: a wavefront per row does the same with 4 keys per lane read against the
-// row's keys in LDS.  Longer rows: one block per row, bitonic sort in LDS (kSortLds entries)
-// or, beyond that, in a global scratch region sized for the row.  (A sorting network in one
-// thread's registers for the short rows: 131 us for the 600K rows of the 128^3 cube's first
-// R; a block's bitonic sort for the middle ones: 690 us for 54K rows of about 40, now 57.)
+// row's keys in LDS.  Up to kSortBlock: a block per row in the same way; its comparisons grow
+// with the square of the length, by their count of instructions they reach the bitonic sort's
+// time at about 1,400.  Longer rows: one block per row, bitonic sort in LDS (kSortLds entries) or, beyond that, in a global
+// scratch region sized for the row.  (A sorting network in one thread's registers for the short
+// rows: 131 us for the 600K rows of the 128^3 cube's first R; a block's bitonic sort for the
+// middle ones: 690 us for 54K rows of about 40, now 57; and for 9,114 rows of 257 and more,
+// about 400: 395 us, now 112; 582 longer ones: 89, now 42.)
 constexpr int32_t kSortShort = 32;
 constexpr int32_t kSortMid = 256;
+constexpr int32_t kSortBlock = 1024;
 constexpr int32_t kSortLds = 4096;
 
 // nlist[0], nlist[1]: the rows listed for the wavefront and the block sort (mid, longrows), by
 // one atomic per block and list (one per wavefront took 221 us where most of 89K rows are
-// listed, now 65); nlist[2]: whether a row has more than 64 entries.  A block has 32 PASS
-// rows.
+// listed, now 65); nlist[2]: whether a row has more than 64 entries; nlist[3]: more than
+// kSortBlock.  A block has 32 PASS rows.
 template <int PASS>
 __global__ __launch_bounds__(kBlock) void k_sort_short(int32_t n, const int32_t *__restrict__ rp,
                                                        int32_t *c, double *v, int32_t *nlist,
                                                        int32_t *mid, int32_t *longrows) {
-  __shared__ int32_t s_list[2][32 * PASS], s_n[2], s_base[2], s_any;
+  __shared__ int32_t s_list[2][32 * PASS], s_n[2], s_base[2], s_any[2];
   const int t = threadIdx.x, j = t & 7;
-  if (t < 2) s_n[t] = 0;
-  if (t == 0) s_any = 0;
+  if (t < 2) s_n[t] = s_any[t] = 0;
   __syncthreads();
   for (int pass = 0; pass < PASS; ++pass) {
     const int64_t i64 = ((int64_t)blockIdx.x * PASS + pass) * 32 + (t >> 3);
@@ -2439,7 +2442,8 @@ __global__ __launch_bounds__(kBlock) void k_sort_short(int32_t n, const int32_t 
     if (j == 0 && L > kSortShort) {
       const int which = L > kSortMid;
       s_list[which][atomicAdd(&s_n[which], 1)] = i;
-      if (L > 64) s_any = 1;
+      if (L > 64) s_any[0] = 1;
+      if (L > kSortBlock) s_any[1] = 1;
     }
     if (L <= 1 || L > kSortShort) continue;  // uniform over the row's lanes
     int32_t k[4], place[4] = {0, 0, 0, 0};
@@ -2470,7 +2474,7 @@ __global__ __launch_bounds__(kBlock) void k_sort_short(int32_t n, const int32_t 
   }
   __syncthreads();
   if (t < 2 && s_n[t] > 0) s_base[t] = atomicAdd(nlist + t, s_n[t]);
-  if (t == 0 && s_any) nlist[2] = 1;  // (every writer writes the same)
+  if (t < 2 && s_any[t]) nlist[2 + t] = 1;  // (every writer writes the same)
   __syncthreads();
   for (int q = t; q < s_n[0]; q += kBlock) mid[s_base[0] + q] = s_list[0][q];
   for (int q = t; q < s_n[1]; q += kBlock) longrows[s_base[1] + q] = s_list[1][q];
@@ -2509,6 +2513,45 @@ __global__ __launch_bounds__(kBlock) void k_sort_mid(const int32_t *rows, int32_
     }
 }
 
+template <int Q>
+__device__ __forceinline__ void count_smaller(const int32_t *s_k, int32_t L, const int32_t *k,
+                                              int32_t *place) {
+  for (int32_t o = 0; o < L; o += 4) {  // past the row the keys are INT_MAX
+    const int4 t = *(const int4 *)&s_k[o];
+#pragma unroll
+    for (int q = 0; q < Q; ++q)
+      place[q] += (t.x < k[q]) + (t.y < k[q]) + (t.z < k[q]) + (t.w < k[q]);
+  }
+}
+__global__ __launch_bounds__(kBlock) void k_sort_block(const int32_t *rows,
+                                                       const int32_t *__restrict__ rp,
+                                                       int32_t *c, double *v) {
+  static_assert(kSortBlock == 4 * kBlock, "four keys a thread");
+  __shared__ __attribute__((aligned(16))) int32_t s_k[kSortBlock];
+  const int t = threadIdx.x;
+  const int32_t i = rows[blockIdx.x];
+  const int32_t b = rp[i], L = rp[i + 1] - b;
+  if (L > kSortBlock) return;  // block-uniform
+  int32_t k[4], place[4] = {0, 0, 0, 0};
+  double x[4];
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const bool in = t + kBlock * q < L;
+    k[q] = in ? c[b + t + kBlock * q] : INT_MAX;
+    x[q] = v && in ? v[b + t + kBlock * q] : 0.0;
+    s_k[t + kBlock * q] = k[q];
+  }
+  __syncthreads();
+  if (L <= 2 * kBlock) count_smaller<2>(s_k, L, k, place);
+  else count_smaller<4>(s_k, L, k, place);
+#pragma unroll
+  for (int q = 0; q < 4; ++q)
+    if (t + kBlock * q < L) {
+      c[b + place[q]] = k[q];
+      if (v) v[b + place[q]] = x[q];
+    }
+}
+
 __device__ inline void bitonic_kv_any(int32_t *k, double *v, int32_t L) {
   for (int32_t kk = 2; kk <= L; kk <<= 1) {
     for (int32_t j = kk >> 1; j > 0; j >>= 1) {
@@ -2533,7 +2576,8 @@ __device__ inline void bitonic_kv_any(int32_t *k, double *v, int32_t L) {
   }
 }
 
-// One block per long row; rows longer than kSortLds use gk/gv at goff[slot].
+// One block per row of more than kSortBlock entries; those longer than kSortLds use gk/gv at
+// goff[slot].
 __global__ __launch_bounds__(kBlock) void k_sort_long(const int32_t *rows, int32_t nrows,
                                                       const int32_t *rp, int32_t *c, double *v,
                                                       int32_t *gk, double *gv,
@@ -2544,6 +2588,7 @@ __global__ __launch_bounds__(kBlock) void k_sort_long(const int32_t *rows, int32
   if (slot >= nrows) return;
   const int32_t i = rows[slot];
   const int32_t b = rp[i], len = rp[i + 1] - b;
+  if (len <= kSortBlock) return;  // k_sort_block's
   int32_t L = 1;
   while (L < len) L <<= 1;
   int32_t *kk;
@@ -2606,6 +2651,10 @@ void sort_rows_end(RowSort &job, const int32_t *words, hipStream_t s) {
   }
   const int32_t nl = words[1];
   if (nl > 0) {
+    k_sort_block<<<(unsigned)nl, kBlock, 0, s>>>(job.rows, job.rp, job.col, job.val);
+    SA_LAUNCH_CHECK();
+  }
+  if (words[3] != 0) {  // a listed row has more than kSortBlock entries
     Arena &tmp = job.tmp;
     int64_t *caps = tmp.alloc<int64_t>(nl + 1);
     int64_t *goff = tmp.alloc<int64_t>(nl + 1);
