@@ -180,10 +180,14 @@ __global__ __launch_bounds__(256) void k_potrf_inv(int32_t ld, int32_t k0, doubl
 }
 
 // Panel below the diagonal block: L_ik = A_ik L_kk^{-T}, a 64 x 64 block per workgroup on the
-// matrix cores, in place (9 us; forward substitution, a row per thread, took 31 us).
+// matrix cores, in place.  The product with the explicit inverse alone leaves a residual that
+// grows with the condition of L_kk (the factor's backward error 1e-15 to 3e-12 on Gaussian
+// kernels, and pivots lost from a condition of about 1e12 on), so one correction follows:
+// Q = A X^T with X = L_kk^{-1}, then Q += (A - Q L_kk^T) X^T, which brings the backward error
+// to forward substitution's (2e-16).  A wavefront works on its own 16 rows throughout.
 __device__ __forceinline__ void panel_tile(int32_t blk, int32_t ld, int32_t k0, const double *Li,
                                            double *D, double (*As)[kNB + 1],
-                                           double (*Xs)[kNB + 1]) {
+                                           double (*Xs)[kNB + 1], double (*Ls)[kNB + 1]) {
   constexpr int LD = kNB + 1;
   const int tid = threadIdx.x, w = tid >> 6;
   const int64_t r0 = (int64_t)k0 + (int64_t)kNB * (1 + blk);
@@ -191,16 +195,35 @@ __device__ __forceinline__ void panel_tile(int32_t blk, int32_t ld, int32_t k0, 
     const int r = q / kNB, k = q % kNB;
     As[r][k] = D[(r0 + r) * ld + k0 + k];
     Xs[r][k] = Li[(int64_t)(k0 + r) * ld + k0 + k];
+    Ls[r][k] = k <= r ? D[(int64_t)(k0 + r) * ld + k0 + k] : 0.0;
   }
   __syncthreads();
   const int lr = tid & 15, lk = (tid & 63) >> 4;
+  const v4d zero = {0.0, 0.0, 0.0, 0.0};
+  v4d a[4], l[4];
 #pragma unroll
   for (int ct = 0; ct < 4; ++ct) {
-    const v4d acc =
-        mfma_16<64>(&As[16 * w][0], LD, &Xs[16 * ct][0], 1, LD, v4d{0.0, 0.0, 0.0, 0.0});
+    l[ct] = mfma_16<64>(&As[16 * w][0], LD, &Xs[16 * ct][0], 1, LD, zero);
+#pragma unroll
+    for (int v = 0; v < 4; ++v) a[ct][v] = As[16 * w + 4 * v + lk][16 * ct + lr];
+  }
+  __syncthreads();
+#pragma unroll
+  for (int ct = 0; ct < 4; ++ct) put_16(&As[16 * w][16 * ct], LD, l[ct], 1.0, false);
+  __syncthreads();
+#pragma unroll
+  for (int ct = 0; ct < 4; ++ct)
+    a[ct] = a[ct] - mfma_16<64>(&As[16 * w][0], LD, &Ls[16 * ct][0], 1, LD, zero);
+  __syncthreads();
+#pragma unroll
+  for (int ct = 0; ct < 4; ++ct) put_16(&As[16 * w][16 * ct], LD, a[ct], 1.0, false);
+  __syncthreads();
+#pragma unroll
+  for (int ct = 0; ct < 4; ++ct) {
+    const v4d d = mfma_16<64>(&As[16 * w][0], LD, &Xs[16 * ct][0], 1, LD, zero);
 #pragma unroll
     for (int v = 0; v < 4; ++v)
-      D[(r0 + 16 * w + 4 * v + lk) * ld + k0 + 16 * ct + lr] = acc[v];
+      D[(r0 + 16 * w + 4 * v + lk) * ld + k0 + 16 * ct + lr] = l[ct][v] + d[v];
   }
 }
 
@@ -380,9 +403,9 @@ static void trinv_blocks(int32_t ld, int32_t nbk, const double *L, double *Li, h
 // counts.
 __global__ __launch_bounds__(256) void k_step_panels(int32_t ld, int32_t kb, int32_t nbk,
                                                      double *D, double *Li) {
-  __shared__ double As[kNB][kNB + 1], Bs[kNB][kNB + 1];
+  __shared__ double As[kNB][kNB + 1], Bs[kNB][kNB + 1], Cs[kNB][kNB + 1];
   const int32_t m = nbk - kb - 1, t = (int32_t)blockIdx.x;
-  if (t < m) panel_tile(t, ld, kb * kNB, Li, D, As, Bs);
+  if (t < m) panel_tile(t, ld, kb * kNB, Li, D, As, Bs, Cs);
   else trinv_finalize_tile(t - m, ld, kb, Li, As, Bs);
 }
 __global__ __launch_bounds__(256) void k_step_updates(int32_t ld, int32_t kb, int32_t nbk,
