@@ -59,13 +59,41 @@ __device__ __forceinline__ void put_16(double *c, int ldc, v4d acc, double sign,
   }
 }
 
+// The lower-left H x H block at (o + H, o) of a triangular inverse from its two diagonal blocks,
+// tile (ti, tj) by this wavefront (live: it has one): Z = -X22 Y with Y = L21 X11, then
+// Z -= X22 (Y + L22 Z).  Without the correction the inverse's residual L X - I is 50 to 10,000
+// times that of a forward substitution by columns, and so is the error of L^{-1} from there on;
+// with it they are the same.  t: H x H scratch.
+template <int H>
+__device__ __forceinline__ void trtri_corner(const double (*l)[kNB + 1], double (*x)[kNB + 1],
+                                             double *t, int o, int ti, int tj, bool live) {
+  constexpr int LD = kNB + 1;
+  const v4d zero = {0.0, 0.0, 0.0, 0.0};
+  double *z = &x[o + H + ti][o + tj], *tt = t + ti * 33 + tj;
+  const double *x22 = &x[o + H + ti][o + H];
+  v4d y = zero;
+  if (live) {
+    y = mfma_16<H>(&l[o + H + ti][o], LD, &x[o][o + tj], LD, 1, zero);
+    put_16(tt, 33, y, 1.0, false);
+  }
+  __syncthreads();
+  if (live) put_16(z, LD, mfma_16<H>(x22, LD, t + tj, 33, 1, zero), -1.0, false);
+  __syncthreads();
+  if (live) {
+    y = mfma_16<H>(&l[o + H + ti][o + H], LD, &x[o + H][o + tj], LD, 1, y);
+    put_16(tt, 33, y, 1.0, false);
+  }
+  __syncthreads();
+  if (live) put_16(z, LD, mfma_16<H>(x22, LD, t + tj, 33, 1, zero), -1.0, true);
+  __syncthreads();
+}
+
 // Inverse of the lower-triangular 64 x 64 block l into x (both with leading dimension
-// kNB + 1 in LDS, rd[i] = 1 / l[i][i]; x zero above its diagonal): the four 16 x 16 diagonal
-// blocks by forward substitution, a wavefront each (lane c: column c), then
-// X21 = -X22 (L21 X11) for the two 32 x 32 halves and for the whole block on the matrix cores.
+// kNB + 1 in LDS, zero above their diagonals, rd[i] = 1 / l[i][i]): the four 16 x 16 diagonal
+// blocks by forward substitution, a wavefront each (lane c: column c), then the corners of the
+// two 32 x 32 halves and of the whole block on the matrix cores.
 __device__ __forceinline__ void trtri_64(const double (*l)[kNB + 1], double (*x)[kNB + 1],
                                          const double *rd, double (*t)[33]) {
-  constexpr int LD = kNB + 1;
   const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63;
   for (int q = tid; q < kNB * kNB; q += 256) x[q / kNB][q % kNB] = 0.0;
   __syncthreads();
@@ -84,26 +112,8 @@ __device__ __forceinline__ void trtri_64(const double (*l)[kNB + 1], double (*x)
       if (i >= lane) x[o + i][o + lane] = y[i];
   }
   __syncthreads();
-  if (w < 2) {  // 32 x 32 halves
-    const int o = 32 * w;
-    const v4d a = mfma_16<16>(&l[o + 16][o], LD, &x[o][o], LD, 1, v4d{0.0, 0.0, 0.0, 0.0});
-    put_16(&t[16 * w][0], 33, a, 1.0, false);
-  }
-  __syncthreads();
-  if (w < 2) {
-    const int o = 32 * w;
-    const v4d a =
-        mfma_16<16>(&x[o + 16][o + 16], LD, &t[16 * w][0], 33, 1, v4d{0.0, 0.0, 0.0, 0.0});
-    put_16(&x[o + 16][o], LD, a, -1.0, false);
-  }
-  __syncthreads();
-  const int ti = 16 * (w >> 1), tj = 16 * (w & 1);  // the 32 x 32 lower-left block's tiles
-  v4d a = mfma_16<32>(&l[32 + ti][0], LD, &x[0][tj], LD, 1, v4d{0.0, 0.0, 0.0, 0.0});
-  put_16(&t[ti][tj], 33, a, 1.0, false);
-  __syncthreads();
-  a = mfma_16<32>(&x[32 + ti][32], LD, &t[0][tj], 33, 1, v4d{0.0, 0.0, 0.0, 0.0});
-  put_16(&x[32 + ti][tj], LD, a, -1.0, false);
-  __syncthreads();
+  trtri_corner<16>(l, x, &t[16 * (w & 1)][0], 32 * (w & 1), 0, 0, w < 2);
+  trtri_corner<32>(l, x, &t[0][0], 0, 16 * (w >> 1), 16 * (w & 1), true);
 }
 
 // 1 / sqrt(d) to about an ulp: the hardware estimate and three Newton steps.
@@ -171,6 +181,9 @@ __global__ __launch_bounds__(256) void k_potrf_inv(int32_t ld, int32_t k0, doubl
         }
     __syncthreads();
   }
+  // (the updates of the diagonal tiles wrote above the diagonal too)
+  for (int q = tid; q < kNB * kNB; q += 256)
+    if (q % kNB > q / kNB) a[q / kNB][q % kNB] = 0.0;
   trtri_64(a, x, rd, t);
   for (int q = tid; q < kNB * kNB; q += 256) {
     const int i = q / kNB, j = q % kNB;

@@ -73,3 +73,9 @@ def test_accepted(n, shift):
 @pytest.mark.parametrize("shift", [1e-8, 1e-10, 1e-12])
 def test_panels(shift):
     check_error(kernel_matrix(512, 0.05, shift))
+
+
+@pytest.mark.parametrize("n,shift", [(200, 1e-12), (512, 1e-10), (512, 1e-12), (512, 1e-13)])
+def test_diagonal_blocks(n, shift):
+    # the narrower kernel: the 64-blocks' own inverses decide
+    check_error(kernel_matrix(n, 0.02, shift))
