@@ -186,8 +186,8 @@ struct DotParts {
   const double *p = nullptr;
   int32_t m = 0;
 };
-// The partials part[0..nb) reduced to at most 4096, stage by stage in ws.
-DotParts reduce_parts(double *part, int64_t nb, double *ws, hipStream_t s);
+// The partials part[0..nb) reduced to at most `most` (4096 or fewer), stage by stage in ws.
+DotParts reduce_parts(double *part, int64_t nb, double *ws, hipStream_t s, int64_t most = 4096);
 DotParts dot_parts(const double *x, const double *y, int64_t n, double *ws, hipStream_t s);
 // r.z, and r.(z - zold) unless zold is null; ws holds 2 dot_ws_size(n) doubles.
 void dot_rz_parts(const double *r, const double *z, const double *zold, int64_t n, double *ws,

@@ -20,13 +20,21 @@ __global__ __launch_bounds__(kDotBlock) void k_mdot_stage(const double *__restri
   const int64_t v = blockIdx.y;
   dot_block(blockIdx.x, x + v * ldx, y, m, part + v * ldp + blockIdx.x, sh);
 }
-// Stages of partials until at most kDotFinal are left per vector (one stage up to 16.7M terms).
+// Partials per vector that k_gmres_project reduces itself: every block of the basis' length
+// reads those of every vector, nb blocks nb partials each, so their traffic grows with the square
+// of the length (as much as the vectors' own at 4,096).  Beyond this a stage of one block per
+// vector comes between, 4.5 us a pass (GMRES of 20 steps, without and with it: 1.2M and 2.1M
+// unknowns 14.0 and 17.7 ms either way, 3.0M 26.5 and 26.3, 8.0M 72.5 and 70.7, 16.6M 165.6 and
+// 157.0).
+constexpr int64_t kProjectParts = 512;
+static_assert(kProjectParts <= kDotFinal, "the projection takes one last stage");
+// Stages of partials until at most kProjectParts are left per vector.
 static DotParts multi_dot_parts(const double *V, int64_t ldv, int32_t nv, const double *w,
                                 int64_t n, double *ws, hipStream_t s) {
   int64_t nb = std::max<int64_t>(ceil_div(n, kDotTerms), 1);
   k_mdot_stage<<<dim3((unsigned)nb, (unsigned)nv), kDotBlock, 0, s>>>(V, ldv, w, n, ws, nb);
   SA_LAUNCH_CHECK();
-  while (nb > kDotFinal) {
+  while (nb > kProjectParts) {
     const int64_t nb2 = ceil_div(nb, kDotTerms);
     double *out = ws + nb * nv;
     k_mdot_stage<<<dim3((unsigned)nb2, (unsigned)nv), kDotBlock, 0, s>>>(ws, nb, nullptr, nb, out,
@@ -106,7 +114,7 @@ DotParts gmres_project(const double *V, int64_t ldv, int32_t nv, double *ws, dou
   k_gmres_project<<<(unsigned)nb, kDotBlock, 0, s>>>(V, ldv, nv, c.p, c.m, H, m, pass, w, n,
                                                     wpart);
   SA_LAUNCH_CHECK();
-  return wpart ? reduce_parts(wpart, nb, wpart + nb, s) : DotParts{};
+  return wpart ? reduce_parts(wpart, nb, wpart + nb, s, 2048) : DotParts{};
 }
 __global__ void k_multi_axpy(const double *__restrict__ V, int64_t ldv, int32_t nv,
                              const double *__restrict__ c, double *__restrict__ w, int64_t n,

@@ -470,9 +470,8 @@ void dot_xy_xx(const double *x, const double *y, int64_t n, double *res, double 
   }
 }
 
-// Stages of partials until at most kDotFinal are left (one stage up to 16.7M terms).
-DotParts reduce_parts(double *part, int64_t nb, double *ws, hipStream_t s) {
-  while (nb > kDotFinal) {
+DotParts reduce_parts(double *part, int64_t nb, double *ws, hipStream_t s, int64_t most) {
+  while (nb > most) {
     const int64_t nb2 = ceil_div(nb, 4096);
     k_dot_stage<<<(unsigned)nb2, kDotBlock, 0, s>>>(part, nullptr, nb, ws);
     SA_LAUNCH_CHECK();
