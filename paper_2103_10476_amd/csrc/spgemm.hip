@@ -1211,7 +1211,12 @@ void spgemm(const Csr &X, const Csr &Y, Arena &ar, Csr &C, hipStream_t s, int32_
   // The longest rows first (a kernel ends with its last row), the bins of up to 2048 rows
   // together a block of eight wavefronts per row, the others a wavefront per row: 14.6K rows
   // of 8,192 products or more take 910 us with a wavefront each and 2,080 with blocks, 2.6K rows
-  // of at most 37K products 185 with blocks and 440 with a wavefront each.
+  // of at most 37K products 185 with blocks and 440 with a wavefront each.  Rows past 32,768
+  // products stay with blocks up to 8192 of them: many of their columns are distinct, and a
+  // wavefront goes over such a row once per 481 columns while the chip has room (graphs of random
+  // neighbours, whole setup: 2.5K rows of 4.7M products 203 ms with a wavefront each, 98 with
+  // blocks; 6K of 1M 108 and 86; 5.9K of 75K 22.1 and 20.9; 7.6K of 35K 11.2 both; 21K rows 49
+  // and 71).
   int64_t narrow = INT64_MAX;  // the narrowest window that a kernel leaves to the hash table
   int bin = kBins - 1;
   auto ranks = [&](auto nwc, auto rdc, int32_t tile, int64_t limit) {
@@ -1219,7 +1224,8 @@ void spgemm(const Csr &X, const Csr &Y, Arena &ar, Csr &C, hipStream_t s, int32_
     RowLists rows = {};
     int64_t n = 0;
     for (int q = 0; q < 4; ++q) {
-      if (bin >= 7 && n + hc[bin] <= limit) {
+      const int64_t most = bin == kBins - 1 ? std::max<int64_t>(limit, 8192) : limit;
+      if (bin >= 7 && n + hc[bin] <= most) {
         rows.list[q] = lists + bin * (int64_t)m;
         n += hc[bin];
         --bin;
