@@ -227,11 +227,17 @@ static void numeric_prolong(sa_hierarchy *h, int l, bool fresh, const ReadAlong 
     }
     return;
   }
+  // Beyond 32 entries the thread that fills a row of P reads the row again for each of its
+  // aggregates, so longer rows on average take the sparse product.  Setup of random graphs, 33
+  // neighbours in as many aggregates: 50K rows 18.3 -> 17.1 ms, 400K 98.6 -> 79.5; 47, 200K rows
+  // 94.6 -> 82.5; rows of 35 and 45 points of a plane grid, which meet few aggregates: 7.2 ms
+  // either way; 33-point rows of a box (32 on average) stay below, 5.9 against 6.1.
+  const bool by_product = L.wave_rows || L.Abar.nnz > 32 * (int64_t)L.Abar.n;
   if (fresh) {
-    prolongator(L.Abar, L.invD, L.agg, L.nc, L.omega_d, ar, L.P, s, L.wave_rows, along);
+    prolongator(L.Abar, L.invD, L.agg, L.nc, L.omega_d, ar, L.P, s, by_product, along);
   } else {
     Csr P;
-    prolongator(L.Abar, L.invD, L.agg, L.nc, L.omega_d, tmp, P, s, L.wave_rows, along);
+    prolongator(L.Abar, L.invD, L.agg, L.nc, L.omega_d, tmp, P, s, by_product, along);
     take_values(P, L.P, s);
   }
   if (o.variants & SA_CNSTRNT) cnstrnt(L.P, L.agg, s);

@@ -1,7 +1,8 @@
 """Setups on graphs of random neighbours, where nearly every neighbour lies in another aggregate.
 
 The coarse operator is dense, so R (A P) has thousands of rows of more than 32,768 products (a
-block each).  Every level's arrays against the oracle, bitwise, and again
+block each), and rows of 33 to 64 entries meet as many aggregates in P (the sparse product
+where the average row has more than 32).  Every level's arrays against the oracle, bitwise, and again
 after a numeric re-setup with the values doubled, which has to give the doubled operators.
 """
 import numpy as np
@@ -67,3 +68,10 @@ def test_long_products():
     AP = (sp.csr_matrix((L.A[2], L.A[1], L.A[0])) @ sp.csr_matrix((L.P[2], L.P[1], L.P[0])))
     T = products(L.R, (AP.indptr, AP.indices))
     assert 2048 < np.count_nonzero(T > 32768) <= 8192
+
+
+@pytest.mark.parametrize("degree,extra", [(32, 0), (24, 4), (46, 0), (62, 0)])
+def test_many_aggregates(degree, extra):
+    p = random_graph(6000, degree, extra)
+    assert np.diff(p.rp).max() > 32
+    check(p)
