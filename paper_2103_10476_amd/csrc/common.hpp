@@ -51,6 +51,22 @@ inline unsigned grid_for(int64_t n, int block = kBlock) {
   return (unsigned)(g < 1 ? 1 : g);
 }
 
+// Blocks for n rows of `lanes` threads each, as many as one launch may have (2^32 - 1 threads:
+// 67M rows of a wavefront each); the kernel goes over its rows with row_stride<lanes>().
+inline unsigned grid_rows(int64_t n, int lanes) {
+  const int64_t most = (int64_t)(0xffffffffu / kBlock);
+  const int64_t g = ceil_div(n * lanes, kBlock);
+  return (unsigned)(g < 1 ? 1 : g < most ? g : most);
+}
+template <int LANES>
+__device__ __forceinline__ int64_t first_row() {
+  return ((int64_t)blockIdx.x * kBlock + threadIdx.x) / LANES;
+}
+template <int LANES>
+__device__ __forceinline__ int64_t row_stride() {
+  return (int64_t)gridDim.x * (kBlock / LANES);
+}
+
 // Stream-ordered device allocation from the library's caching allocator (alloc.hip): a
 // block released on stream s is reused only for later work on s.
 void *dev_alloc(size_t bytes, hipStream_t s);

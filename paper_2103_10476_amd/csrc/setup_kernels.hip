@@ -243,28 +243,28 @@ template <int D, int P>
 __global__ __launch_bounds__(kBlock) void k_distance_weights(
     int32_t n, const int32_t *__restrict__ rp, const int32_t *__restrict__ col,
     const double *__restrict__ xyz, double *w, double *Ld, int32_t *err, int32_t ebit) {
-  const int64_t i64 = ((int64_t)blockIdx.x * kBlock + threadIdx.x) >> 3;
-  if (i64 >= n) return;  // uniform over the row's lanes
-  const int32_t i = (int32_t)i64;
   const int lane = threadIdx.x & 7;
-  const int32_t e = rp[i + 1];
-  double s = 0.0;
   bool bad = false;
-  for (int32_t k = rp[i]; k < e; k += 8) {
-    double wk = 0.0;  // the diagonal's, and past the row: leaves the sum as it is
-    if (k + lane < e) {
-      const int32_t j = col[k + lane];
-      if (j != i) {
-        const double d2 = dist2<D>(xyz, i, j);
-        bad |= !(d2 > 0.0);
-        wk = P == 1 ? 1.0 / sqrt(d2) : 1.0 / d2;
+  for (int64_t i64 = first_row<8>(); i64 < n; i64 += row_stride<8>()) {  // uniform over the lanes
+    const int32_t i = (int32_t)i64;
+    const int32_t e = rp[i + 1];
+    double s = 0.0;
+    for (int32_t k = rp[i]; k < e; k += 8) {
+      double wk = 0.0;  // the diagonal's, and past the row: leaves the sum as it is
+      if (k + lane < e) {
+        const int32_t j = col[k + lane];
+        if (j != i) {
+          const double d2 = dist2<D>(xyz, i, j);
+          bad |= !(d2 > 0.0);
+          wk = P == 1 ? 1.0 / sqrt(d2) : 1.0 / d2;
+        }
+        w[k + lane] = wk;
       }
-      w[k + lane] = wk;
-    }
 #pragma unroll
-    for (int o = 0; o < 8; ++o) s = s + __shfl(wk, o, 8);
+      for (int o = 0; o < 8; ++o) s = s + __shfl(wk, o, 8);
+    }
+    if (lane == 0) Ld[i] = s;
   }
-  if (lane == 0) Ld[i] = s;
   if (bad) atomicOr(err, ebit);
 }
 template <int D>
@@ -272,11 +272,11 @@ static void distance_weights_dim(int32_t n, const int32_t *rp, const int32_t *co
                                  const double *xyz, int32_t power, double *w, double *Ld,
                                  int32_t *err, int32_t ebit, hipStream_t s) {
   if (power == 1)
-    k_distance_weights<D, 1><<<grid_for((int64_t)n * 8), kBlock, 0, s>>>(n, rp, col, xyz, w, Ld,
-                                                                       err, ebit);
+    k_distance_weights<D, 1><<<grid_rows(n, 8), kBlock, 0, s>>>(n, rp, col, xyz, w, Ld, err,
+                                                              ebit);
   else
-    k_distance_weights<D, 2><<<grid_for((int64_t)n * 8), kBlock, 0, s>>>(n, rp, col, xyz, w, Ld,
-                                                                       err, ebit);
+    k_distance_weights<D, 2><<<grid_rows(n, 8), kBlock, 0, s>>>(n, rp, col, xyz, w, Ld, err,
+                                                              ebit);
 }
 void distance_weights(int32_t n, const int32_t *rp, const int32_t *col, const double *xyz,
                       int32_t dim, int32_t power, double *w, double *Ld, int32_t *err,
@@ -1101,35 +1101,35 @@ __global__ __launch_bounds__(kBlock) void k_agg_phase2_w(int32_t n,
                                                          const int32_t *__restrict__ gcol,
                                                          const int32_t *__restrict__ agg1,
                                                          int32_t *__restrict__ agg) {
-  const int64_t i = ((int64_t)blockIdx.x * kBlock + threadIdx.x) >> 6;
-  if (i >= n) return;  // wave-uniform
   const int lane = threadIdx.x & 63;
-  const int32_t b = grp[i], e = grp[i + 1];
-  if (e - b <= 32 || agg1[i] >= 0) return;
-  int32_t best = INT_MAX, bestc = 0;
-  for (int32_t k0 = b; k0 < e; k0 += 64) {
-    const int32_t c = k0 + lane < e ? agg1[gcol[k0 + lane]] : -1;
-    int32_t cnt = 0;
-    for (int32_t q0 = b; q0 < e; q0 += 64) {
-      const int32_t o = q0 + lane < e ? agg1[gcol[q0 + lane]] : -1;
-      const int32_t len = min(64, e - q0);
-      for (int32_t l = 0; l < len; ++l)
-        cnt += __builtin_amdgcn_readlane(o, l) == c ? 1 : 0;
+  for (int64_t i = first_row<64>(); i < n; i += row_stride<64>()) {  // wave-uniform
+    const int32_t b = grp[i], e = grp[i + 1];
+    if (e - b <= 32 || agg1[i] >= 0) continue;
+    int32_t best = INT_MAX, bestc = 0;
+    for (int32_t k0 = b; k0 < e; k0 += 64) {
+      const int32_t c = k0 + lane < e ? agg1[gcol[k0 + lane]] : -1;
+      int32_t cnt = 0;
+      for (int32_t q0 = b; q0 < e; q0 += 64) {
+        const int32_t o = q0 + lane < e ? agg1[gcol[q0 + lane]] : -1;
+        const int32_t len = min(64, e - q0);
+        for (int32_t l = 0; l < len; ++l)
+          cnt += __builtin_amdgcn_readlane(o, l) == c ? 1 : 0;
+      }
+      if (c >= 0 && (cnt > bestc || (cnt == bestc && c < best))) {
+        best = c;
+        bestc = cnt;
+      }
     }
-    if (c >= 0 && (cnt > bestc || (cnt == bestc && c < best))) {
-      best = c;
-      bestc = cnt;
-    }
-  }
 #pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) {
-    const int32_t oc = __shfl_xor(bestc, off, 64), ob = __shfl_xor(best, off, 64);
-    if (oc > bestc || (oc == bestc && ob < best)) {
-      best = ob;
-      bestc = oc;
+    for (int off = 32; off >= 1; off >>= 1) {
+      const int32_t oc = __shfl_xor(bestc, off, 64), ob = __shfl_xor(best, off, 64);
+      if (oc > bestc || (oc == bestc && ob < best)) {
+        best = ob;
+        bestc = oc;
+      }
     }
+    if (lane == 0) agg[i] = bestc > 0 ? best : -1;
   }
-  if (lane == 0) agg[i] = bestc > 0 ? best : -1;
 }
 
 template <class O>
@@ -1288,7 +1288,7 @@ static int32_t aggregate_impl(int32_t n, int64_t nnzG, const int32_t *grp, const
   SA_LAUNCH_CHECK();
   k_agg_phase2<<<grid_for(n), kBlock, 0, s>>>(n, grp, gcol, agg1, agg);
   if (maxdeg > 32 || maxdeg < 0)
-    k_agg_phase2_w<<<grid_for((int64_t)n * 64), kBlock, 0, s>>>(n, grp, gcol, agg1, agg);
+    k_agg_phase2_w<<<grid_rows(n, 64), kBlock, 0, s>>>(n, grp, gcol, agg1, agg);
   SA_LAUNCH_CHECK();
   *root_vertex = rv;
   return nc;

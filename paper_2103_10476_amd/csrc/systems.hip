@@ -37,12 +37,9 @@ constexpr int kMaxBs = 16;
 // (A thread per node walking its rows: 160 us per pass on 60,000 nodes of 3 rows of 76, 350 us
 // on 2,592 nodes of 6 rows of 136; now 45 and 14 us.)
 template <bool FILL>
-__global__ __launch_bounds__(kBlock) void k_node_graph(int32_t m, int32_t bs, const int32_t *rp,
-                                                       const int32_t *col, int32_t *cnt,
-                                                       const int32_t *grp, int32_t *gcol) {
-  const int64_t i64 = ((int64_t)blockIdx.x * kBlock + threadIdx.x) >> 6;
-  if (i64 >= m) return;  // wave-uniform
-  const int32_t I = (int32_t)i64;
+__device__ __forceinline__ void node_row(int32_t I, int32_t bs, const int32_t *rp,
+                                         const int32_t *col, int32_t *cnt, const int32_t *grp,
+                                         int32_t *gcol) {
   const int lane = threadIdx.x & 63;
   const int32_t *nrp = rp + (int64_t)I * bs;
   const int32_t b0 = nrp[0], len = nrp[1] - b0;
@@ -92,7 +89,13 @@ __global__ __launch_bounds__(kBlock) void k_node_graph(int32_t m, int32_t bs, co
   }
   if (!FILL) cnt[I] = c;
 }
-
+template <bool FILL>
+__global__ __launch_bounds__(kBlock) void k_node_graph(int32_t m, int32_t bs, const int32_t *rp,
+                                                       const int32_t *col, int32_t *cnt,
+                                                       const int32_t *grp, int32_t *gcol) {
+  for (int64_t i = first_row<64>(); i < m; i += row_stride<64>())  // wave-uniform
+    node_row<FILL>((int32_t)i, bs, rp, col, cnt, grp, gcol);
+}
 void node_graph(const Csr &A, int32_t bs, Arena &ar, Csr &G, hipStream_t s) {
   if (bs < 1 || bs > kMaxBs) throw Error(SA_ERR_INVALID_ARG, "block size not in 1..16");
   const int32_t m = A.n / bs;
@@ -100,7 +103,8 @@ void node_graph(const Csr &A, int32_t bs, Arena &ar, Csr &G, hipStream_t s) {
   G.n = G.ncols = m;
   G.rp = ar.alloc<int32_t>(m + 1);
   if (m > 0) {
-    k_node_graph<false><<<grid_for((int64_t)m * 64), kBlock, 0, s>>>(m, bs, A.rp, A.col, cnt, nullptr, nullptr);
+    k_node_graph<false><<<grid_rows(m, 64), kBlock, 0, s>>>(m, bs, A.rp, A.col, cnt, nullptr,
+                                                           nullptr);
     SA_LAUNCH_CHECK();
   }
   exclusive_scan_i32(cnt, G.rp, m, s);
@@ -109,7 +113,8 @@ void node_graph(const Csr &A, int32_t bs, Arena &ar, Csr &G, hipStream_t s) {
   G.col = ar.alloc<int32_t>(G.nnz > 0 ? G.nnz : 1);
   G.val = nullptr;
   if (m > 0) {
-    k_node_graph<true><<<grid_for((int64_t)m * 64), kBlock, 0, s>>>(m, bs, A.rp, A.col, nullptr, G.rp, G.col);
+    k_node_graph<true><<<grid_rows(m, 64), kBlock, 0, s>>>(m, bs, A.rp, A.col, nullptr, G.rp,
+                                                          G.col);
     SA_LAUNCH_CHECK();
   }
 }
@@ -127,40 +132,40 @@ __global__ __launch_bounds__(kBlock) void k_block_F(int32_t m, int32_t bs,
                                                     const int32_t *__restrict__ gcol,
                                                     double *__restrict__ F,
                                                     double *__restrict__ Fd) {
-  const int64_t i64 = ((int64_t)blockIdx.x * kBlock + threadIdx.x) >> 5;
-  if (i64 >= m) return;
-  const int32_t I = (int32_t)i64;
-  const int32_t g0 = grp[I], g1 = grp[I + 1];
-  const int32_t *nrp = rp + (int64_t)I * bs;
-  bool own = false;
-  for (int32_t q = g0 + (int32_t)(threadIdx.x & 31); q < g1; q += 32) {
-    const int32_t J = gcol[q];
-    double f = 0.0;
-    int32_t off = 0;
-    for (int r = 0; r < bs; ++r) {
-      const int32_t b = nrp[r], e = nrp[r + 1];
-      int32_t k = b + off;
-      const bool here = r > 0 && k < e && col[k] / bs == J && (off == 0 || col[k - 1] / bs < J);
-      if (!here) {  // first entry of the row with col / bs >= J
-        int32_t lo = b, hi = e;
-        while (lo < hi) {
-          const int32_t mid = (lo + hi) >> 1;
-          if (col[mid] / bs < J) lo = mid + 1;
-          else hi = mid;
+  for (int64_t i64 = first_row<32>(); i64 < m; i64 += row_stride<32>()) {  // uniform over the lanes
+    const int32_t I = (int32_t)i64;
+    const int32_t g0 = grp[I], g1 = grp[I + 1];
+    const int32_t *nrp = rp + (int64_t)I * bs;
+    bool own = false;
+    for (int32_t q = g0 + (int32_t)(threadIdx.x & 31); q < g1; q += 32) {
+      const int32_t J = gcol[q];
+      double f = 0.0;
+      int32_t off = 0;
+      for (int r = 0; r < bs; ++r) {
+        const int32_t b = nrp[r], e = nrp[r + 1];
+        int32_t k = b + off;
+        const bool here = r > 0 && k < e && col[k] / bs == J && (off == 0 || col[k - 1] / bs < J);
+        if (!here) {  // first entry of the row with col / bs >= J
+          int32_t lo = b, hi = e;
+          while (lo < hi) {
+            const int32_t mid = (lo + hi) >> 1;
+            if (col[mid] / bs < J) lo = mid + 1;
+            else hi = mid;
+          }
+          k = lo;
+          off = k - b;
         }
-        k = lo;
-        off = k - b;
+        for (; k < e && col[k] / bs == J; ++k) f = f + val[k] * val[k];
       }
-      for (; k < e && col[k] / bs == J; ++k) f = f + val[k] * val[k];
+      F[q] = f;
+      if (J == I) {
+        Fd[I] = f;
+        own = true;
+      }
     }
-    F[q] = f;
-    if (J == I) {
-      Fd[I] = f;
-      own = true;
-    }
+    const uint64_t any = __ballot(own) >> (threadIdx.x & 32);  // this node's half
+    if ((any & 0xffffffffull) == 0 && (threadIdx.x & 31) == 0) Fd[I] = 0.0;
   }
-  const uint64_t any = __ballot(own) >> (threadIdx.x & 32);  // this node's half
-  if ((any & 0xffffffffull) == 0 && (threadIdx.x & 31) == 0) Fd[I] = 0.0;
 }
 __global__ void k_block_label(int32_t m, const int32_t *grp, const int32_t *gcol,
                               const double *F, const double *Fd, double th4, uint8_t *nmask,
@@ -189,7 +194,7 @@ void block_strength(const Csr &A, int32_t bs, const Csr &G, double theta, uint8_
   tmp.stream = s;
   double *F = tmp.alloc<double>(G.nnz > 0 ? G.nnz : 1);
   double *Fd = tmp.alloc<double>(m);
-  k_block_F<<<grid_for((int64_t)m * 32), kBlock, 0, s>>>(m, bs, A.rp, A.col, A.val, G.rp, G.col, F, Fd);
+  k_block_F<<<grid_rows(m, 32), kBlock, 0, s>>>(m, bs, A.rp, A.col, A.val, G.rp, G.col, F, Fd);
   const double th4 = (theta * theta) * (theta * theta);
   k_block_label<<<grid_for(m), kBlock, 0, s>>>(m, G.rp, G.col, F, Fd, th4, nmask, scount);
   SA_LAUNCH_CHECK();
@@ -205,39 +210,40 @@ __global__ __launch_bounds__(kBlock) void k_dof_mask(int32_t n, int32_t bs,
                                                      const int32_t *__restrict__ gcol,
                                                      const uint8_t *__restrict__ nmask,
                                                      uint8_t *__restrict__ mask) {
-  const int64_t i64 = ((int64_t)blockIdx.x * kBlock + threadIdx.x) >> 6;
-  if (i64 >= n) return;
-  const int32_t i = (int32_t)i64, I = i / bs;
-  const int32_t g0 = grp[I], g1 = grp[I + 1];
-  const int32_t end = rp[i + 1];
-  for (int32_t e = rp[i] + (int32_t)(threadIdx.x & 63); e < end; e += 64) {
-    const int32_t j = col[e], J = j / bs;
-    uint8_t lab;
-    if (i == j) {
-      lab = 3;
-    } else if (I == J) {
-      lab = 1;
-    } else {
-      int32_t lo = g0, hi = g1 - 1;
-      lab = 0;
-      while (lo <= hi) {
-        const int32_t mid = (lo + hi) >> 1;
-        const int32_t c = gcol[mid];
-        if (c == J) {
-          lab = nmask[mid];
-          break;
+  for (int64_t i64 = first_row<64>(); i64 < n; i64 += row_stride<64>()) {
+    const int32_t i = (int32_t)i64, I = i / bs;
+    const int32_t g0 = grp[I], g1 = grp[I + 1];
+    const int32_t end = rp[i + 1];
+    for (int32_t e = rp[i] + (int32_t)(threadIdx.x & 63); e < end; e += 64) {
+      const int32_t j = col[e], J = j / bs;
+      uint8_t lab;
+      if (i == j) {
+        lab = 3;
+      } else if (I == J) {
+        lab = 1;
+      } else {
+        int32_t lo = g0, hi = g1 - 1;
+        lab = 0;
+        while (lo <= hi) {
+          const int32_t mid = (lo + hi) >> 1;
+          const int32_t c = gcol[mid];
+          if (c == J) {
+            lab = nmask[mid];
+            break;
+          }
+          if (c < J) lo = mid + 1;
+          else hi = mid - 1;
         }
-        if (c < J) lo = mid + 1;
-        else hi = mid - 1;
       }
+      mask[e] = lab;
     }
-    mask[e] = lab;
   }
 }
 void dof_mask(const Csr &A, int32_t bs, const Csr &G, const uint8_t *nmask, uint8_t *mask,
               hipStream_t s) {
   if (A.n <= 0) return;
-  k_dof_mask<<<grid_for((int64_t)A.n * 64), kBlock, 0, s>>>(A.n, bs, A.rp, A.col, G.rp, G.col, nmask, mask);
+  k_dof_mask<<<grid_rows(A.n, 64), kBlock, 0, s>>>(A.n, bs, A.rp, A.col, G.rp, G.col, nmask,
+                                                  mask);
   SA_LAUNCH_CHECK();
 }
 
@@ -487,24 +493,24 @@ __global__ __launch_bounds__(kBlock) void k_smooth_pt(
     const int32_t *__restrict__ ptrp, const int32_t *__restrict__ ptcol,
     const double *__restrict__ ptval, const double *__restrict__ invD,
     const double *__restrict__ omega) {
-  const int64_t i = ((int64_t)blockIdx.x * kBlock + threadIdx.x) >> 3;
-  if (i >= n) return;
-  const double t = (*omega) * invD[i];
-  const int32_t p0 = ptrp[i], np = ptrp[i + 1] - p0;
-  const int32_t c0 = np > 0 ? ptcol[p0] : 0;
-  const int32_t e1 = aprp[i + 1];
-  for (int32_t e = aprp[i] + (threadIdx.x & 7); e < e1; e += 8) {
-    const int32_t q = apcol[e] - c0;
-    const double pt = q >= 0 && q < np ? ptval[p0 + q] : 0.0;
-    apval[e] = pt - t * apval[e];
+  for (int64_t i = first_row<8>(); i < n; i += row_stride<8>()) {
+    const double t = (*omega) * invD[i];
+    const int32_t p0 = ptrp[i], np = ptrp[i + 1] - p0;
+    const int32_t c0 = np > 0 ? ptcol[p0] : 0;
+    const int32_t e1 = aprp[i + 1];
+    for (int32_t e = aprp[i] + (threadIdx.x & 7); e < e1; e += 8) {
+      const int32_t q = apcol[e] - c0;
+      const double pt = q >= 0 && q < np ? ptval[p0 + q] : 0.0;
+      apval[e] = pt - t * apval[e];
+    }
   }
 }
 void smooth_tentative(const Csr &abar, const Csr &Pt, const double *invD, const double *omega,
                       Arena &ar, Csr &P, hipStream_t s) {
   spgemm(abar, Pt, ar, P, s);
   if (P.n > 0) {
-    k_smooth_pt<<<grid_for((int64_t)P.n * 8), kBlock, 0, s>>>(P.n, P.rp, P.col, P.val, Pt.rp,
-                                                              Pt.col, Pt.val, invD, omega);
+    k_smooth_pt<<<grid_rows(P.n, 8), kBlock, 0, s>>>(P.n, P.rp, P.col, P.val, Pt.rp, Pt.col,
+                                                    Pt.val, invD, omega);
     SA_LAUNCH_CHECK();
   }
 }
