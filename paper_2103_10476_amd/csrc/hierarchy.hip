@@ -1153,7 +1153,8 @@ sa_status gmres_run(sa_hierarchy *h, const double *b, double *x, sa_location loc
                     int32_t restart, const GmresWork &wk, bool direct_reads,
                     int32_t *iterations, double *relres) {
   if (!h->valid) throw Error(SA_ERR_INVALID_ARG, "hierarchy left unusable by a failed re-setup");
-  if (restart < 1 || restart > kMaxRestart) throw Error(SA_ERR_INVALID_ARG, "restart not in 1..1024");
+  if (restart < 1 || restart > kMaxRestart)
+    throw Error(SA_ERR_INVALID_ARG, "restart not in 1..1024");
   const hipStream_t s = h->stream;
   const sa_options &o = h->opt;
   const int32_t n = h->n;
@@ -1238,7 +1239,7 @@ sa_status gmres_run(sa_hierarchy *h, const double *b, double *x, sa_location loc
     }
     if (kdim == 0) break;
     gmres_backsolve(H, m, kdim, g, y, S, s);
-    multi_axpy_f64(Z, n, kdim, y, xv, n, true, s);
+    multi_axpy_f64(Z, n, kdim, y, xv, n, s);
     read_scalars(&hs);
     if (hs.err) return SA_ERR_BREAKDOWN;
     if (converged || total >= o.max_iter) break;

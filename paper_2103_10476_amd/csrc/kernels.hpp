@@ -149,10 +149,11 @@ void cast_f32_to_f64(const float *a, double *b, int64_t n, hipStream_t s);
 template <class T>
 void gemv(int32_t n, const double *M, const T *x, T *y, hipStream_t s);
 
-// ---- GMRES (solve_kernels.hip) ----------------------------------------------------------
+// ---- GMRES (krylov.hip) -----------------------------------------------------------------
 // Device state of one GMRES cycle with restart length m: the Hessenberg matrix (row-major,
-// (m+1) x m), the rotations, the right-hand side g of the least-squares problem, its
-// solution y, Gram-Schmidt coefficients c and the scalars the host reads after each step.
+// (m+1) x m), whose columns hold the Gram-Schmidt coefficients, the rotations, the right-hand
+// side g of the least-squares problem, its solution y and the scalars the host reads after each
+// step.
 struct GmresScalars {
   double res;  // |g[j+1]| after the step's rotation
   double hn;   // norm of the new Arnoldi vector
@@ -164,10 +165,9 @@ struct GmresScalars {
 // res[0] = <x, y>, res[1] = <x, x>, each bitwise dot_f64's; ws of 2 dot_ws_size(n).
 void dot_xy_xx(const double *x, const double *y, int64_t n, double *res, double *ws,
                hipStream_t s);
-// w[k] = w[k] - c[0] V_0[k] - c[1] V_1[k] - ... (nv terms in ascending order); with add,
-// w[k] = w[k] + c[0] V_0[k] + ... instead.
+// w[k] = w[k] + c[0] V_0[k] + c[1] V_1[k] + ... (nv terms in ascending order).
 void multi_axpy_f64(const double *V, int64_t ldv, int32_t nv, const double *c, double *w,
-                    int64_t n, bool add, hipStream_t s);
+                    int64_t n, hipStream_t s);
 // y = H[0:k,0:k]^{-1} g (back substitution); err 1 on a zero diagonal entry.
 void gmres_backsolve(const double *H, int32_t m, int32_t k, const double *g, double *y,
                      GmresScalars *S, hipStream_t s);
@@ -284,8 +284,8 @@ int64_t strength_graph(int32_t n, int64_t nnz_a, const int32_t *rp, const int32_
 // a singleton aggregate when `singletons` is set (the covering reading).  Returns nc;
 // agg[n], is_root[n], root_vertex[nc].  maxdeg: the graph's longest row, or -1.
 int32_t aggregate(int32_t n, int64_t nnzG, const int32_t *grp, const int32_t *gcol,
-                  int32_t maxdeg, int32_t order, uint64_t seed, int32_t level, bool singletons, int32_t *agg,
-                  uint8_t *is_root, Arena &ar, int32_t **root_vertex, int32_t *rounds,
+                  int32_t maxdeg, int32_t order, uint64_t seed, int32_t level, bool singletons,
+                  int32_t *agg, uint8_t *is_root, Arena &ar, int32_t **root_vertex, int32_t *rounds,
                   hipStream_t s);
 // Sprsfy: marks dropped strong entries (mask 1 -> 2).
 void sprsfy(int32_t n, const int32_t *rp, const int32_t *col, uint8_t *mask,
@@ -294,7 +294,8 @@ void sprsfy(int32_t n, const int32_t *rp, const int32_t *col, uint8_t *mask,
 void lump_count(int32_t n, const int32_t *rp, const int32_t *col, const uint8_t *mask, bool wave,
                 Arena &ar, Csr &abar, hipStream_t s);
 // Filtered matrix (plain or OffLmp) and the smoothing diagonal inverse of the n-row CSR with
-// nnz_a entries, from abar's row pointers and nnz; returns nnz(Abar).  err bit 8: zero filtered diagonal with the plain diagonal.
+// nnz_a entries, from abar's row pointers and nnz; returns nnz(Abar).  err bit 8: zero filtered
+// diagonal with the plain diagonal.
 int64_t lump(int32_t n, int64_t nnz_a, const int32_t *rp, const int32_t *col, const double *val,
              const uint8_t *mask, bool offlmp, double tau, bool one_norm, double mult,
              bool wave, Arena &ar, Csr &abar, double *invD, int32_t *err, hipStream_t s);

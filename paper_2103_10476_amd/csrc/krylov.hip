@@ -117,21 +117,17 @@ DotParts gmres_project(const double *V, int64_t ldv, int32_t nv, double *ws, dou
   return wpart ? reduce_parts(wpart, nb, wpart + nb, s, 2048) : DotParts{};
 }
 __global__ void k_multi_axpy(const double *__restrict__ V, int64_t ldv, int32_t nv,
-                             const double *__restrict__ c, double *__restrict__ w, int64_t n,
-                             bool add) {
+                             const double *__restrict__ c, double *__restrict__ w, int64_t n) {
   const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (k >= n) return;
   double t = w[k];
-  if (add)
-    for (int32_t i = 0; i < nv; ++i) t = t + c[i] * V[i * ldv + k];
-  else
-    for (int32_t i = 0; i < nv; ++i) t = t - c[i] * V[i * ldv + k];
+  for (int32_t i = 0; i < nv; ++i) t = t + c[i] * V[i * ldv + k];
   w[k] = t;
 }
 void multi_axpy_f64(const double *V, int64_t ldv, int32_t nv, const double *c, double *w,
-                    int64_t n, bool add, hipStream_t s) {
+                    int64_t n, hipStream_t s) {
   if (n <= 0 || nv <= 0) return;
-  k_multi_axpy<<<grid_for(n), kBlock, 0, s>>>(V, ldv, nv, c, w, n, add);
+  k_multi_axpy<<<grid_for(n), kBlock, 0, s>>>(V, ldv, nv, c, w, n);
   SA_LAUNCH_CHECK();
 }
 __global__ void k_div_scalar(const double *w, double *v, int64_t n, const double *den) {

@@ -5,8 +5,10 @@
 // Every floating-point reduction runs in the order the method's definition fixes (row sums
 // sequential in ascending column order from 0), with FMA contraction disabled at compile
 // time, so the setup is deterministic and equal to the sequential definition bit for bit.
-// Setup kernels are one thread per row (rows hold 5-30 entries on the fine levels); they
-// run once per level and are bound by HBM traffic or by the level's size.
+// Most setup kernels work per entry, or with a few lanes or a wavefront per row; where a row's
+// sums are a chain anyway and rows are short (5-30 entries on the fine levels) one thread has the
+// row, its entries staged by the block where that pays.  They run once per level and are bound by
+// HBM traffic, by chains of dependent loads or by the level's size.
 #include <chrono>
 #include <climits>
 #include <cstdlib>
@@ -1295,14 +1297,14 @@ static int32_t aggregate_impl(int32_t n, int64_t nnzG, const int32_t *grp, const
 }
 
 int32_t aggregate(int32_t n, int64_t nnzG, const int32_t *grp, const int32_t *gcol,
-                  int32_t maxdeg, int32_t order, uint64_t seed, int32_t level, bool singletons, int32_t *agg,
-                  uint8_t *is_root, Arena &ar, int32_t **root_vertex, int32_t *rounds,
+                  int32_t maxdeg, int32_t order, uint64_t seed, int32_t level, bool singletons,
+                  int32_t *agg, uint8_t *is_root, Arena &ar, int32_t **root_vertex, int32_t *rounds,
                   hipStream_t s) {
   if (order == 0)
     return aggregate_impl(n, nnzG, grp, gcol, maxdeg, NaturalOrder{}, singletons, agg, is_root, ar,
                           root_vertex, rounds, s);
-  return aggregate_impl(n, nnzG, grp, gcol, maxdeg, HashedOrder{seed, level}, singletons, agg, is_root,
-                        ar, root_vertex, rounds, s);
+  return aggregate_impl(n, nnzG, grp, gcol, maxdeg, HashedOrder{seed, level}, singletons, agg,
+                        is_root, ar, root_vertex, rounds, s);
 }
 
 // ---- Sprsfy (Sec. 2.5) --------------------------------------------------------------------
@@ -2411,8 +2413,8 @@ void scale_sym(int32_t n, const int32_t *rp, const int32_t *col, const double *v
 // Up to kSortMid: a wavefront per row does the same with 4 keys per lane read against the
 // row's keys in LDS.  Up to kSortBlock: a block per row in the same way; its comparisons grow
 // with the square of the length, by their count of instructions they reach the bitonic sort's
-// time at about 1,400.  Longer rows: one block per row, bitonic sort in LDS (kSortLds entries) or, beyond that, in a global
-// scratch region sized for the row.  (A sorting network in one thread's registers for the short
+// time at about 1,400.  Longer rows: one block per row, bitonic sort in LDS (kSortLds entries)
+// or, beyond that, in a global scratch region sized for the row.  (A sorting network in one thread's registers for the short
 // rows: 131 us for the 600K rows of the 128^3 cube's first R; a block's bitonic sort for the
 // middle ones: 690 us for 54K rows of about 40, now 57; and for 9,114 rows of 257 and more,
 // about 400: 395 us, now 112; 582 longer ones: 89, now 42.)

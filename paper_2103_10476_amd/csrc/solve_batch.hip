@@ -61,7 +61,7 @@ __global__ __launch_bounds__(kBlock) void k_gspmv(const GSpmv<T, Epi> *segs,
 }
 
 enum GVecOp : int32_t {
-  G_CHEB_FIRST_D, G_CHEB_FIRST_F, G_VEC_ADD_D, G_VEC_ADD_F, G_JAC_FIRST_D, G_JAC_FIRST_F,
+  G_CHEB_FIRST_D, G_VEC_ADD_D, G_VEC_ADD_F, G_JAC_FIRST_D, G_JAC_FIRST_F,
   G_COPY_D, G_COPY_F, G_CAST_DF, G_CAST_FD, G_CAST_CHEB_F
 };
 
@@ -83,10 +83,6 @@ __global__ __launch_bounds__(kBlock) void k_gvec(const GVec *segs, const int32_t
     case G_CHEB_FIRST_D:
       cheb_first_at<double>(i, (const double *)v.a, (const double *)v.b, v.sc, (double *)v.c,
                             (double *)v.d, v.flag != 0);
-      break;
-    case G_CHEB_FIRST_F:
-      cheb_first_at<float>(i, (const float *)v.a, (const float *)v.b, (float)v.sc,
-                           (float *)v.c, (float *)v.d, v.flag != 0);
       break;
     case G_VEC_ADD_D: vec_add_at<double>(i, (double *)v.c, (const double *)v.a); break;
     case G_VEC_ADD_F: vec_add_at<float>(i, (float *)v.c, (const float *)v.a); break;
@@ -403,12 +399,12 @@ void rec_smooth(Recorder &rc, const std::vector<Item> &its, bool uzero, bool fir
     int sweep = 0;
     if (uzero) {
       std::vector<GVec> g;
-      for (size_t k = 0; k < its.size(); ++k) {
+      for (size_t k = 0; k < its.size() && !first_done; ++k) {
         const Level &L = its[k].h->lv[its[k].level];
         g.push_back(gv(f32 ? G_JAC_FIRST_F : G_JAC_FIRST_D, L.A.n, its[k].f, v[k].invD,
                        its[k].u, nullptr, (double)(T)L.jac_w));
       }
-      if (!first_done) rec_vec(rc, g);
+      rec_vec(rc, g);
       sweep = 1;
     }
     for (; sweep < o.degree; ++sweep) {
@@ -440,11 +436,12 @@ void rec_smooth(Recorder &rc, const std::vector<Item> &its, bool uzero, bool fir
     std::vector<GVec> g;
     for (size_t k = 0; k < its.size(); ++k) {
       const Level &L = its[k].h->lv[its[k].level];
-      g.push_back(gv(f32 ? G_CHEB_FIRST_F : G_CHEB_FIRST_D, L.A.n, its[k].f, v[k].invD, dc[k],
-                     its[k].u, (double)(T)L.cheb_theta, o.degree == 1 ? 1 : 0));
       rin.push_back((const T *)its[k].f);
+      if (first_done) continue;  // (in FP32 always: the fine level's rides along with the cast)
+      g.push_back(gv(G_CHEB_FIRST_D, L.A.n, its[k].f, v[k].invD, dc[k], its[k].u, L.cheb_theta,
+                     o.degree == 1 ? 1 : 0));
     }
-    if (!first_done) rec_vec(rc, g);
+    rec_vec(rc, g);
   } else {
     std::vector<GSpmv<T, EpChebStart<T>>> sp;
     std::vector<int32_t> nb;

@@ -296,10 +296,9 @@ struct EpScale {
 // non-negative double (monotone for non-negative values): each row block adds its maximum
 // with one atomic maximum to slot (block mod kMaxSlots).  x' = x / 2^ilogb(m) with m the largest
 // of prev, the slots that the launch before filled (none: x' = x): every wavefront reduces
-// them, which is cheaper than a pass over the vector between two products and a launch less (101x97x89
-// re-setup + solve 9.54 -> 9.37 ms).  A
-// zero or non-finite m marks the iteration dead.  The first block clears next, which the next
-// launch fills.
+// them, which is cheaper than a pass over the vector between two products and a launch less
+// (101x97x89 re-setup + solve 9.54 -> 9.37 ms).  A zero or non-finite m marks the iteration dead.
+// The first block clears next, which the next launch fills.
 template <class T>
 struct EpScaleMax {
   const T *d;

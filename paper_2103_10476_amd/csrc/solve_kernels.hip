@@ -565,8 +565,8 @@ void pcg_update_p(int64_t n, double *p, const double *z, const DotParts &rz, con
   SA_LAUNCH_CHECK();
 }
 // r.r from its partials into S, then S to the host's words and their tag.
-__global__ __launch_bounds__(kDotBlock) void k_pcg_post(const double *part, int32_t m, PcgScalars *S,
-                                                     HostWords host) {
+__global__ __launch_bounds__(kDotBlock) void k_pcg_post(const double *part, int32_t m,
+                                                     PcgScalars *S, HostWords host) {
   __shared__ DotShared sh;
   const double rr = dot_final(part, m, sh);
   if (threadIdx.x == 0) S->rr = rr;

@@ -153,7 +153,7 @@ __global__ __launch_bounds__(kWave) void k_row_prefix(const int32_t *rows, const
   }
 }
 
-// ---- block-level rows (T > 64) -------------------------------------------------------------
+// ---- rows in a dense accumulator (the last resort) -------------------------------------------
 __device__ inline int32_t find_entry(const int32_t *xpref, int32_t xb, int32_t xe, int32_t p) {
   // last e in [xb, xe) with xpref[e] <= p (entries with no products share a prefix value;
   // the last one holding p is the one whose Y row contains it).
@@ -442,8 +442,8 @@ template <int J>
 __device__ __forceinline__ uint32_t upper_of(int lane) {
   return (lane & J) ? ~0u : 0u;
 }
-// Value of lane (lane ^ M), M = 2^m - 1, the partner in a merge's first step (1, 3: quad permutations; 7, 15: the mirrors within 8 and 16 lanes; 31, 63: the
-// mirror and row swaps).
+// Value of lane (lane ^ M), M = 2^m - 1, the partner in a merge's first step (1, 3: quad
+// permutations; 7, 15: the mirrors within 8 and 16 lanes; 31, 63: the mirror and row swaps).
 template <int M>
 __device__ __forceinline__ uint32_t flip_lane(uint32_t v, int lane) {
   if constexpr (M == 1)
