@@ -135,7 +135,7 @@ __device__ __forceinline__ double rsqrt_newton(double d) {
 // each.  The inverse turns the panel solve below into a product and is what the triangular
 // inverse starts from.  (Column by column over the whole block in LDS, three barriers each,
 // took 73 us, and the inverse, a column per thread, 50 us in a launch of its own; both now
-// 23.5 us.)
+// 26.0 us, of which the corners' corrections are 2.3.)
 __global__ __launch_bounds__(256) void k_potrf_inv(int32_t ld, int32_t k0, double *D, double *Li,
                                                    int32_t *err) {
   __shared__ double a[kNB][kNB + 1], x[kNB][kNB + 1];
@@ -192,12 +192,26 @@ __global__ __launch_bounds__(256) void k_potrf_inv(int32_t ld, int32_t k0, doubl
   }
 }
 
+// A 16 x 64 strip times the transpose of a lower-triangular 64 x 64 block, out[ct] = a b^T for
+// the column tiles ct, each as deep as the triangle (leading dimensions kNB + 1).
+__device__ __forceinline__ void strip_times_lower_t(const double *a, const double (*b)[kNB + 1],
+                                                    v4d (&out)[4]) {
+  constexpr int LD = kNB + 1;
+  const v4d zero = {0.0, 0.0, 0.0, 0.0};
+  out[0] = mfma_16<16>(a, LD, &b[0][0], 1, LD, zero);
+  out[1] = mfma_16<32>(a, LD, &b[16][0], 1, LD, zero);
+  out[2] = mfma_16<48>(a, LD, &b[32][0], 1, LD, zero);
+  out[3] = mfma_16<64>(a, LD, &b[48][0], 1, LD, zero);
+}
+
 // Panel below the diagonal block: L_ik = A_ik L_kk^{-T}, a 64 x 64 block per workgroup on the
 // matrix cores, in place.  The product with the explicit inverse alone leaves a residual that
 // grows with the condition of L_kk (the factor's backward error 1e-15 to 3e-12 on Gaussian
 // kernels, and pivots lost from a condition of about 1e12 on), so one correction follows:
 // Q = A X^T with X = L_kk^{-1}, then Q += (A - Q L_kk^T) X^T, which brings the backward error
-// to forward substitution's (2e-16).  A wavefront works on its own 16 rows throughout.
+// to forward substitution's (2e-16).  A wavefront works on its own 16 rows throughout.  The step's
+// launch takes 15.1 us (9 blocks), 9.2 without the correction; substitution, a row per thread,
+// took 31.
 __device__ __forceinline__ void panel_tile(int32_t blk, int32_t ld, int32_t k0, const double *Li,
                                            double *D, double (*As)[kNB + 1],
                                            double (*Xs)[kNB + 1], double (*Ls)[kNB + 1]) {
@@ -212,32 +226,28 @@ __device__ __forceinline__ void panel_tile(int32_t blk, int32_t ld, int32_t k0, 
   }
   __syncthreads();
   const int lr = tid & 15, lk = (tid & 63) >> 4;
-  const v4d zero = {0.0, 0.0, 0.0, 0.0};
-  v4d a[4], l[4];
-#pragma unroll
-  for (int ct = 0; ct < 4; ++ct) {
-    l[ct] = mfma_16<64>(&As[16 * w][0], LD, &Xs[16 * ct][0], 1, LD, zero);
-#pragma unroll
-    for (int v = 0; v < 4; ++v) a[ct][v] = As[16 * w + 4 * v + lk][16 * ct + lr];
-  }
-  __syncthreads();
-#pragma unroll
-  for (int ct = 0; ct < 4; ++ct) put_16(&As[16 * w][16 * ct], LD, l[ct], 1.0, false);
-  __syncthreads();
+  double *strip = &As[16 * w][0];
+  v4d a[4], l[4], d[4];
 #pragma unroll
   for (int ct = 0; ct < 4; ++ct)
-    a[ct] = a[ct] - mfma_16<64>(&As[16 * w][0], LD, &Ls[16 * ct][0], 1, LD, zero);
+#pragma unroll
+    for (int v = 0; v < 4; ++v) a[ct][v] = strip[(4 * v + lk) * LD + 16 * ct + lr];
+  strip_times_lower_t(strip, Xs, l);
   __syncthreads();
 #pragma unroll
-  for (int ct = 0; ct < 4; ++ct) put_16(&As[16 * w][16 * ct], LD, a[ct], 1.0, false);
+  for (int ct = 0; ct < 4; ++ct) put_16(strip + 16 * ct, LD, l[ct], 1.0, false);
+  __syncthreads();
+  strip_times_lower_t(strip, Ls, d);
   __syncthreads();
 #pragma unroll
-  for (int ct = 0; ct < 4; ++ct) {
-    const v4d d = mfma_16<64>(&As[16 * w][0], LD, &Xs[16 * ct][0], 1, LD, zero);
+  for (int ct = 0; ct < 4; ++ct) put_16(strip + 16 * ct, LD, a[ct] - d[ct], 1.0, false);
+  __syncthreads();
+  strip_times_lower_t(strip, Xs, d);
+#pragma unroll
+  for (int ct = 0; ct < 4; ++ct)
 #pragma unroll
     for (int v = 0; v < 4; ++v)
-      D[(r0 + 16 * w + 4 * v + lk) * ld + k0 + 16 * ct + lr] = l[ct][v] + d[v];
-  }
+      D[(r0 + 16 * w + 4 * v + lk) * ld + k0 + 16 * ct + lr] = l[ct][v] + d[ct][v];
 }
 
 // Trailing update after step kb: D[ib][jb] -= L[ib][kb] L[jb][kb]^T for every block pair
@@ -412,7 +422,7 @@ static void trinv_blocks(int32_t ld, int32_t nbk, const double *L, double *Li, h
 // beyond step kb of the factorisation, so each step is three launches, the diagonal block
 // (k_potrf_inv), then the panel tiles L[i][kb] with the inverse's tiles X[kb][j] (j < kb), then
 // the trailing updates with the updates B[i][j] -= L[i][kb] X[kb][j] of the rows below.  The
-// launches are a few microseconds of work each (8-13 us for nbk = 9), so fewer of them is what
+// launches are a few microseconds of work each (13-26 us for nbk = 9), so fewer of them is what
 // counts.
 __global__ __launch_bounds__(256) void k_step_panels(int32_t ld, int32_t kb, int32_t nbk,
                                                      double *D, double *Li) {
