@@ -246,7 +246,7 @@ void batcher_main(sa_server *s) {
       q.res.rel_residual = b->relres;
       q.res.solve_seconds = now_s() - q.t_solve;
       if (b->status < 0) q.err = solve_message(b->status);
-      sa::hierarchy_release_nosync(q.h);  // the batcher's stream is idle after a tick
+      sa::hierarchy_release_nosync(q.h);  // no work that uses it is pending after a tick
       q.h = nullptr;
       finalize(s, q);
       inflight.erase(std::find_if(inflight.begin(), inflight.end(),
